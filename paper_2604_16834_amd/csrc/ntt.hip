@@ -1148,6 +1148,18 @@ static void launch_hi_any(u32 log_hi, bool inverse, dim3 grid, hipStream_t st, c
     }
 }
 
+// Batch items a lo-pass workgroup takes one after the other: as many as leave LO_FILL workgroups, at most `most`.  Sharing a
+// slice's twiddles saves cache traffic only once the chip is full; below that the items of a workgroup are a serial chain of
+// tiles next to idle CUs.  The line is the number of workgroups the chip holds at once (three waves per SIMD, 256 CUs); 512,
+// 1024 and 2048 measure the same.  A small launch's time is its longest workgroup: five polynomials of 13 limbs at N = 2^14
+// (520 slices of work), forward and inverse, 52 -> 41 us; six key switches of 10 limbs at N = 2^13, 101 -> 83 us; launches of
+// 768 slices and more are unchanged.
+#define LO_FILL 768
+static u32 lo_items(u32 slices, u32 batch, u32 most) {
+    const u32 n = (u32)((u64)slices * batch / LO_FILL);
+    return n < 1 ? 1 : (n < most ? n : most);
+}
+
 template <class A, int IT>
 static void launch_inv_lo_it(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul = false) {
     if constexpr (std::is_same<A, ArithF64>::value && IT == 1) {  // the product-forming variant takes one item
@@ -1158,13 +1170,13 @@ static void launch_inv_lo_it(dim3 grid, hipStream_t st, const NttArgs& args, con
     }
     hipLaunchKernelGGL((ntt_inv_lo_kernel<A, IT>), grid, dim3(NTT_THREADS), 0, st, args, pl);
 }
-// The plain forward lo pass: workgroups that loop over their items, up to eight each (measured at N = 2^16: 2, 4, 8 and 16
+// The plain forward lo pass: workgroups that loop over their items, up to eight each where the launch is large (measured at N = 2^16: 2, 4, 8 and 16
 // items give 2.04, 2.06, 2.08 and 2.10e6 limb transforms per second against 1.97e6 with one fetch of the twiddles per two
 // items; eight still leaves the layer's batches of eight a grid of one workgroup per slice).  `grid` is a lo pass' grid,
 // whose extent over items is set here.
 template <class A>
 static void launch_fwd_lo_loop(u32 batch, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl) {
-    constexpr u32 per_wg = 8;
+    const u32 per_wg = lo_items(pl.n << args.log_hi, batch, 8);
     const u32 ext = (batch + per_wg - 1) / per_wg;
     if (args.lo_group) grid.y = ext;
     else grid.x = ext;
@@ -1279,14 +1291,14 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
     }
     const dim3 grid(c->N >> CKKS_TILE_LOG, polys);  // hi pass: one workgroup per 2^11 points
     const u32 slices = pl.n << c->log_hi;
-    // batch items per lo-pass workgroup: in the inverse pass two share one fetch of the twiddles (an unrolled four cost too many
+    // batch items per lo-pass workgroup: in the inverse pass of a large launch two share one fetch of the twiddles (an unrolled four cost too many
     // registers, and a loop over the items as in the plain forward pass spills in the variant that forms a product as it
     // loads, 4.7 -> 6.3 ms per step of the block slice; that variant takes one item: with two it holds two operands' points a
     // tile ahead and spills at three waves per SIMD, 4.7 against 4.2 ms per step for the class); the pass that ends a division takes one (with its epilogue's operands
     // two items leave only two waves per SIMD, which costs more than the second fetch of the twiddles); the plain forward
     // pass sets its own extent (launch_fwd_lo_loop)
-    const u32 lo_items = (batch >= 2 && !epilogue) ? 2 : 1;
-    const u32 lo_wgs = (batch + lo_items - 1) / lo_items;
+    const u32 per_wg = epilogue ? 1 : lo_items(slices, batch, 2);
+    const u32 lo_wgs = (batch + per_wg - 1) / per_wg;
     const dim3 grid_lo = args.lo_group ? dim3(args.lo_group, lo_wgs, slices / args.lo_group) : dim3(lo_wgs, slices);  // see lo_tile()
     const double lo_ops = 0.5 * polys * c->N * c->log_lo, hi_ops = 0.5 * polys * c->N * c->log_hi;
     // the second pass of either direction continues in place on dst
@@ -1303,8 +1315,8 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             if (f64) launch_fwd_lo_loop<ArithF64>(batch, grid_lo, st, a, l);
             else launch_fwd_lo_loop<ArithU64>(batch, grid_lo, st, a, l);
         } else {
-            if (f64) launch_inv_lo<ArithF64>(lo_items, grid_lo, st, a, l);
-            else launch_inv_lo<ArithU64>(lo_items, grid_lo, st, a, l);
+            if (f64) launch_inv_lo<ArithF64>(per_wg, grid_lo, st, a, l);
+            else launch_inv_lo<ArithU64>(per_wg, grid_lo, st, a, l);
         }
     };
     if (!inverse) {
@@ -1441,8 +1453,9 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     const double n_tr = (double)beta * E - (level + 1.0);
     // the grid's extent over the batch: two, i.e. four items per workgroup in a batch of eight (measured: 16.5 ms per step for
     // the lo-pass class with one item per workgroup, 16.35 with all eight, 16.15 with four, which still leave the chip's 256
-    // CUs, two workgroups each, four rounds of workgroups)
-    const u32 b_ext = n < 2 ? n : 2;
+    // CUs, two workgroups each, four rounds of workgroups); more of them where the launch is small (see lo_items)
+    const u32 items = lo_items(slices, n, 4), b_least = n < 2 ? n : 2;
+    const u32 b_ext = (n + items - 1) / items < b_least ? b_least : (n + items - 1) / items;
     const dim3 grid = args.lo_group ? dim3(args.lo_group, b_ext, slices / args.lo_group) : dim3(b_ext, slices);
     // in: the transformed rows, the own limbs, the addends, the keys (once per distinct key); out: two components
     if (ep.lin) n_add = 4.0 * n;  // two components of two ciphertexts
