@@ -312,6 +312,7 @@ hipError_t launch_weighted_sum(const ckks_ctx* c, u32 level, bool extended, cons
                                u32 c_out, u64* acc, u64* scratch, u32 weight_bits, hipStream_t st);
 // wsum_mfma.hip
 bool wsum_mfma_applies(const ckks_ctx* c, u32 n_terms);
+u32 wsum_weight_digits(u32 weight_bits);
 size_t wsum_mfma_scratch_elems(u32 n_limbs, u32 n_terms, u32 c_out);
 hipError_t launch_wsum_mfma(const ckks_ctx* c, u32 level, u32 nl, const u64* xs, XLayout xl, u32 n_terms, const u64* w_res, u32 c_out,
                             u64* acc, u64* scratch, u32 weight_bits, hipStream_t st);

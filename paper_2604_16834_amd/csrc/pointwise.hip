@@ -328,6 +328,66 @@ __global__ __launch_bounds__(PW_THREADS) void weighted_sum_kernel(const u64* __r
         if (o0 + t < c_out) acc[(o0 + t) * ct_stride + off] = barrett_reduce(s[t], m);
 }
 
+// The same sum for moduli below 2^50 and few output channels, in exact double-precision sums.  The matrix-core kernel always
+// multiplies 64 terms by 64 outputs and runs a stream of blocks that takes thousands of cycles to start; with a handful of
+// outputs nearly all of that is padding.  Here a thread owns one column of one (component, limb): it takes the terms eight
+// at a time (requested a chunk ahead, 512 contiguous bytes per wave and term), centres them, and adds to each of OT outputs a
+// chain of fused multiply-adds (f64m_dot_w: about six operations per term and output with its share of the joins).  The
+// weights' centred representatives are staged in LDS, where every lane reads the same word.  Entries beyond the last term
+// repeat it against a zero weight.
+#define WF_TERMS 256  // terms whose weights are in LDS at a time (16 KiB for eight outputs)
+template <int OT>
+__global__ __launch_bounds__(PW_THREADS) void weighted_sum_f64_kernel(const u64* __restrict__ xs, XLayout xl, const u64* __restrict__ w_res,
+                                                                      u64* __restrict__ acc, const ModConstF* __restrict__ mcf, u32 N,
+                                                                      u32 level, u32 nl, u32 num_q, u32 n_terms, u32 c_out) {
+    __shared__ double lw[WF_TERMS * OT];  // [term][output]
+    const u32 tid = threadIdx.x, x = blockIdx.x * PW_THREADS + tid;
+    const u32 e = blockIdx.y % nl, comp = blockIdx.y / nl, o0 = blockIdx.z * OT;
+    const ModConstF m = mcf[e <= level ? e : num_q + (e - level - 1)];
+    const double halfq = 0.5 * m.q;
+    auto centred = [&](u64 v) {
+        const double d = f64m_from_u64(v);
+        return d > halfq ? d - m.q : d;
+    };
+    const u64* xp = xs + xl.at(0, comp, e, x < N ? x : N - 1);
+    double s[OT];
+#pragma unroll
+    for (int o = 0; o < OT; o++) s[o] = 0.0;
+    for (u32 k0 = 0; k0 < n_terms; k0 += WF_TERMS) {
+        const u32 kn = n_terms - k0 < WF_TERMS ? n_terms - k0 : WF_TERMS, k8 = (kn + 7) & ~7u;
+        u64 raw[8];
+#pragma unroll
+        for (u32 a = 0; a < 8; a++) raw[a] = xp[(size_t)(k0 + (a < kn ? a : kn - 1)) * xl.s_k];
+        if (k0) __syncthreads();
+        for (u32 i = tid; i < k8 * OT; i += PW_THREADS) {
+            const u32 k = i / OT, o = o0 + i % OT;
+            lw[i] = (k < kn && o < c_out) ? centred(w_res[((size_t)o * n_terms + k0 + k) * nl + e]) : 0.0;
+        }
+        __syncthreads();
+        for (u32 k = 0; k < k8; k += 8) {
+            double y[8];
+#pragma unroll
+            for (u32 a = 0; a < 8; a++) y[a] = centred(raw[a]);
+            if (k + 8 < k8) {
+#pragma unroll
+                for (u32 a = 0; a < 8; a++) raw[a] = xp[(size_t)(k0 + (k + 8 + a < kn ? k + 8 + a : kn - 1)) * xl.s_k];
+            }
+#pragma unroll
+            for (int o = 0; o < OT; o++) {
+                double w[8];
+#pragma unroll
+                for (u32 a = 0; a < 8; a++) w[a] = lw[(k + a) * OT + o];
+                s[o] = f64m_reduce(s[o] + f64m_dot_w<8>(y, w, m.q, m.qinv), m.q, m.qinv);
+            }
+        }
+    }
+    if (x >= N) return;
+    const size_t off = ((size_t)comp * nl + e) * N + x;
+#pragma unroll
+    for (int o = 0; o < OT; o++)
+        if (o0 + o < c_out) acc[(size_t)(o0 + o) * 2 * nl * N + off] = f64m_canonical(s[o], m.q);
+}
+
 size_t weighted_sum_scratch_elems(const ckks_ctx* c, u32 n_limbs, u32 n_terms, u32 c_out) {
     if (wsum_mfma_applies(c, n_terms)) return wsum_mfma_scratch_elems(n_limbs, n_terms, c_out);
     return 0;
@@ -340,6 +400,28 @@ hipError_t launch_weighted_sum(const ckks_ctx* c, u32 level, bool extended, cons
                                u32 c_out, u64* acc, u64* scratch, u32 weight_bits, hipStream_t st) {
     const u32 L1 = extended ? c->ext_limbs(level) : level + 1;
     const double bytes = 16.0 * c->N * L1 * ((double)n_terms + c_out), ops = 2.0 * c->N * L1 * n_terms * c_out;
+    // Few terms times few outputs: the double-precision kernel.  Its time goes with terms x outputs (rounded up to eights), the
+    // matrix-core kernel's with the 64-term blocks (more for seven weight digits than for four) and a start that is worth 512
+    // products.  Measured at N = 2^16, 16 limbs (us, double precision / matrix cores with seven, four digits): 27 terms x 2
+    // outputs 109 / 790, x 32 733 / 1242; 144 terms x 8 750 / 1740, 1340, x 16 1500 / 1870, 1490, x 32 2890 / 2050, 1640; 288
+    // terms x 8 1450 / 2940, 2240, x 16 2890 / 3000, 2330.  At N = 2^12, 6 limbs: 9 terms x 1 output 6.5 / 94, 71 (with 16 tiles
+    // per workgroup), 576 terms x 4 73 / 397, 224.
+    const u32 wd = wsum_weight_digits(weight_bits), kb = (n_terms + 63) / 64, out8 = c_out <= 4 ? c_out : (c_out + 7) / 8 * 8;
+    if (c->small_q && (u64)n_terms * out8 <= (u64)kb * (wd > 4 ? 832 : 640) + 512) {
+        const u32 x_wgs = (c->N + PW_THREADS - 1) / PW_THREADS;
+        u32 ot = c_out == 1 ? 1 : (c_out == 2 ? 2 : (c_out <= 4 ? 4 : 8));
+        // outputs per thread: fewer, and more workgroups that read the same terms, where the columns alone do not fill the chip
+        while (ot > 1 && x_wgs * 2 * L1 * ((c_out + ot - 1) / ot) < 768) ot >>= 1;
+        dim3 grid(x_wgs, 2 * L1, (c_out + ot - 1) / ot);
+        ProfScope ps__(c, K_WEIGHTED_SUM, st, bytes, ops);
+#define WSUM_F64(OT_) hipLaunchKernelGGL((weighted_sum_f64_kernel<OT_>), grid, dim3(PW_THREADS), 0, st, xs, xl, w_res, acc, c->d_mcf, c->N, level, L1, c->num_q, n_terms, c_out)
+        if (ot == 1) WSUM_F64(1);
+        else if (ot == 2) WSUM_F64(2);
+        else if (ot == 4) WSUM_F64(4);
+        else WSUM_F64(8);
+#undef WSUM_F64
+        return hipGetLastError();
+    }
     if (wsum_mfma_applies(c, n_terms)) {  // moduli below 2^50: exact 8-bit digit products on the matrix cores
         ProfScope ps__(c, K_WEIGHTED_SUM, st, bytes, ops);
         return launch_wsum_mfma(c, level, L1, xs, xl, n_terms, w_res, c_out, acc, scratch, weight_bits, st);

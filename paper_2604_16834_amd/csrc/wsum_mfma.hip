@@ -32,7 +32,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 #define WM_THREADS 256
 #define WM_DIGITS 7                                     // digits of an X value
 #define WM_BIAS 0x0080808080808080ull
-#define WM_TILES_PER_WG 16                              // 64-column tiles a workgroup streams one after the other
+#define WM_TILES_PER_WG 16                              // most 64-column tiles a workgroup streams one after the other
 #define WM_OT_PER_WG 2                                  // output tiles of 32 channels per workgroup
 #define WM_B_STAGE (WM_OT_PER_WG * WM_DIGITS * 2 * 64)  // uint4 words of one 64-term block of X digits (28 KiB)
 
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(WM_THREADS) void wsum_mfma_kernel(const u64* __rest
 bool wsum_mfma_applies(const ckks_ctx* c, u32 n_terms) { return c->small_q && n_terms <= c->lazy_terms && n_terms <= 4096; }
 
 // digits the weights are written in, from the caller's bound |w| < 2^(weight_bits - 1) (0 = none: any residue)
-static u32 weight_digits(u32 weight_bits) { return weight_bits == 0 || weight_bits > 32 ? WM_DIGITS : (weight_bits <= 24 ? 3 : 4); }
+u32 wsum_weight_digits(u32 weight_bits) { return weight_bits == 0 || weight_bits > 32 ? WM_DIGITS : (weight_bits <= 24 ? 3 : 4); }
 
 // scratch words (u64) for the weight digit planes (sized for the widest weights)
 size_t wsum_mfma_scratch_elems(u32 n_limbs, u32 n_terms, u32 c_out) {
@@ -376,15 +376,26 @@ static void launch_wsum_dw(bool ragged, dim3 grid, hipStream_t st, const u64* xs
                            c->num_q, n_terms, c_out, KB, OT, tiles_per_wg);
 }
 
+// 64-column tiles a workgroup streams one after the other: 16 where that leaves four workgroups per CU, fewer in smaller
+// launches, but at least the six blocks the stream is padded to (27 terms, 14 rows of 128 tiles: 106 us with 16 tiles, 84 with
+// six; 144 terms: 178 and 116 with two)
+static u32 wsum_tiles(u32 n_tiles, u32 rows, u32 KB) {
+    u32 t = (u32)((u64)n_tiles * rows / 1024);
+    const u32 least = (5 + KB) / KB;
+    if (t < least) t = least;
+    if (t > WM_TILES_PER_WG) t = WM_TILES_PER_WG;
+    return t < n_tiles ? t : n_tiles;
+}
+
 hipError_t launch_wsum_mfma(const ckks_ctx* c, u32 level, u32 nl, const u64* xs, XLayout xl, u32 n_terms, const u64* w_res, u32 c_out,
                             u64* acc, u64* scratch, u32 weight_bits, hipStream_t st) {
-    const u32 KB = (n_terms + 63) / 64, OT = (c_out + 63) / 64 * WM_OT_PER_WG, DW = weight_digits(weight_bits);
+    const u32 KB = (n_terms + 63) / 64, OT = (c_out + 63) / 64 * WM_OT_PER_WG, DW = wsum_weight_digits(weight_bits);
     const size_t prep = (size_t)nl * KB * OT * DW * 2 * 64;
     hipLaunchKernelGGL(wsum_prep_kernel, dim3((u32)((prep + WM_THREADS - 1) / WM_THREADS)), dim3(WM_THREADS), 0, st, w_res,
                        (uint4*)scratch, c->d_mc, level, c->num_q, c_out, n_terms, nl, KB, OT, DW);
     // tiles of one workgroup: enough that the start and the end of its stream are a small part of it, few enough that the
-    // chip's 256 CUs still get many workgroups each (16 tiles: 4096 workgroups at N = 2^16 and 32 limbs)
-    const u32 n_tiles = (c->N + 63) / 64, tiles_per_wg = n_tiles < WM_TILES_PER_WG ? n_tiles : WM_TILES_PER_WG;
+    // chip's 256 CUs still get many workgroups each (16 tiles: 4096 workgroups at N = 2^16 and 32 limbs; see wsum_tiles)
+    const u32 n_tiles = (c->N + 63) / 64, tiles_per_wg = wsum_tiles(n_tiles, 2 * nl * (OT / WM_OT_PER_WG), KB);
     dim3 grid((n_tiles + tiles_per_wg - 1) / tiles_per_wg, 2 * nl, OT / WM_OT_PER_WG);
     // the 32-bit lane offset of the regular kernel spans 16 terms: 16 * (2 * nl * N) words must fit
     const bool ragged = (n_terms & 63) || (c->N & 63) || 16 * xl.s_k + (size_t)(c->N >> 6) * xl.s_xt + 64 > 0xffffffffull;

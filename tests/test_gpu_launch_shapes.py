@@ -1,4 +1,5 @@
-"""GPU parity at the sizes where the launch rules change: how many batch items a lo-pass workgroup takes."""
+"""GPU parity at the sizes where the launch rules change: how many batch items a lo-pass workgroup takes, which kernel takes the
+layer's multiply-accumulate."""
 import numpy as np
 import pytest
 
@@ -10,8 +11,8 @@ if not torch.cuda.is_available():
 
 import paper_2604_16834_amd as hx  # noqa: E402
 from oracle import Oracle  # noqa: E402
-from workloads import make_params  # noqa: E402
-from gpu_common import rand_poly  # noqa: E402
+from workloads import conv_tap_offsets, make_params  # noqa: E402
+from gpu_common import rand_ct, rand_poly, w_residues  # noqa: E402
 
 
 @pytest.mark.parametrize("batch,bits", [(191, 50), (383, 50), (384, 50), (385, 57), (577, 50), (1537, 50)])
@@ -28,3 +29,34 @@ def test_ntt_items_per_workgroup(batch, bits):
     assert np.array_equal(hx.to_host(d), orc.ntt_many(polys, idx))
     hx.ckks_ntt_inv(ctx, d, idx)
     assert np.array_equal(hx.to_host(d), polys)
+
+
+def random_conv(log_n, c_in, c_out, bits_of_weights=31, seed=1):
+    """A convolution of uniform residues: (oracle's outputs, the device's outputs) in the default schedule."""
+    p = make_params(log_n, 3, 2, 2)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(3000 + seed)
+    level = p.num_q - 1
+    q = p.moduli
+    cts = [rand_ct(rng, q, level, orc.N) for _ in range(c_in)]
+    offs = conv_tap_offsets(4)
+    keys = {o: np.stack([np.stack([rand_poly(rng, q, orc.N) for _ in range(2)]) for _ in range(p.dnum)]) for o in offs if o}
+    masks = np.stack([rand_poly(rng, q[:level + 1], orc.N) for _ in range(9)])
+    w = rng.integers(-2 ** bits_of_weights, 2 ** bits_of_weights, size=(c_out, c_in, 9))
+    w[0, 0, :2] = (2 ** bits_of_weights - 1, -2 ** bits_of_weights + 1)
+    want = orc.he_conv(cts, level, 4, keys, masks, w)
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(keys[o]), hx.ckks_galois_element(ctx, o)) if o else None for o in offs]
+    outs = hx.he_conv_batched(ctx, 4, 4, 2, level, [hx.from_host(c) for c in cts], dkeys, hx.from_host(masks),
+                              hx.from_host(w_residues(w, q, level)), c_out, weight_bits=hx.conv_weight_bits(w))
+    return want, [hx.to_host(o) for o in outs]
+
+
+@pytest.mark.parametrize("log_n,c_in,c_out,bits", [(6, 2, 3, 48), (12, 1, 1, 31), (12, 3, 5, 48), (12, 29, 2, 31), (12, 15, 8, 22),
+                                                   (12, 3, 33, 48), (12, 3, 64, 48), (14, 1, 9, 31)])
+def test_weighted_sum_kernels(log_n, c_in, c_out, bits):
+    """Both sides of the rule: the double-precision kernel with one to eight outputs per thread, a ragged chunk of eight terms,
+    more terms than one stage of weights (261), a column block beyond the ring (N = 2^6) and several groups of outputs; the
+    matrix-core kernel with a ragged block of terms (27 x 64 outputs).  Exact, for weights up to the modulus' size."""
+    want, got = random_conv(log_n, c_in, c_out, bits, seed=c_in * 100 + c_out)
+    for o in range(c_out):
+        assert np.array_equal(got[o], want[o]), f"output {o}"
