@@ -125,11 +125,15 @@ int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const
     if (hi_only && !fused) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: fused inner product without fused ModUp");
     HIP_TRY(launch_ntt(c, true, nullptr, 0, ws.y, L1, range_list(0, L1, 0), n, st, srcs, nullptr,
                        fused ? c->d_modup_prep_f + (size_t)level * c->num_q : nullptr, muls));  // (positions 0..level are moduli 0..level)
+    if (fused) {
+        HIP_TRY(launch_ntt_modup(c, level, (const double*)ws.y, ws.y_b, ws.digits, n, st, hi_only));
+        return CKKS_OK;
+    }
     const PtrList8 cl = ptr_list(srcs, n);
     for (u32 j = 0; j < beta; j++) {
         const u32 lo = c->digit_lo(j), hi = c->digit_hi(j, level);
         u64* digit = ws.digits + (size_t)j * E * N;
-        if (!fused) HIP_TRY(launch_modup_conv(c, level, j, ws.y + (size_t)lo * N, ws.y_b, cl, digit, ws.dig_b, n, st));
+        HIP_TRY(launch_modup_conv(c, level, j, ws.y + (size_t)lo * N, ws.y_b, cl, digit, ws.dig_b, n, st));
         PolyList pl;
         pl.n = 0;
         for (u32 e = 0; e < E; e++) {
@@ -140,8 +144,7 @@ int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const
             pl.n++;
         }
         for (u32 a = pl.n; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = 0;
-        if (fused) HIP_TRY(launch_ntt_modup(c, level, j, (const double*)ws.y, ws.y_b, digit, (size_t)beta * E, pl, n, st, hi_only));
-        else HIP_TRY(launch_ntt(c, false, digit, (size_t)beta * E, digit, (size_t)beta * E, pl, n, st));
+        HIP_TRY(launch_ntt(c, false, digit, (size_t)beta * E, digit, (size_t)beta * E, pl, n, st));
     }
     return CKKS_OK;
 }

@@ -227,8 +227,8 @@ hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t sr
 // with lin_k = {ka, kb} (one limb only) it is ka * src_ptrs[b] + kb * mul_ptrs[b] instead.
 // ModUp fused into transforms (contexts with ntt_f64 and the two-pass transform): the inverse transform of the polynomial
 // scales the limb with modulus index m by inv_scale[m] instead of 1/N and stores the CENTRED residue as a double (launch_ntt with inv_scale);
-// launch_ntt_modup then evaluates the basis conversion of digit j, y [batch][level+1][N] doubles -> the pl.n target limbs
-// pl.dpos[] of dst (batch stride dst_bstride limb-polys), inside the first pass of their forward transforms.
+// launch_ntt_modup then evaluates the basis conversions of all digits, y [n][level+1][N] doubles -> digits [n][beta][E][N]
+// (but the digits' own limbs), inside the first pass of their forward transforms.
 inline bool ntt_has_modup(const ckks_ctx* c) { return c->ntt_f64 && c->log_n > CKKS_TILE_LOG && c->d_modup_prep_f != nullptr; }
 // The same for ModDown's conversion: y are the 2*batch extended polynomials ([E][N] each, the dropped limbs left as scaled
 // centred doubles by launch_ntt with the moddown prep table), dst the converted dropped part ([n_out][N] per polynomial,
@@ -242,8 +242,8 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 // hi_only: stop after the converting hi pass; launch_ntt_lo_mac then runs the lo passes of all digits and multiplies the
 // results by the switching keys (keys[b]: [dnum][2][M][N], one per batch item) as they come out, adding P * add0s[b] /
 // add1s[b] (optional, [level+1][N]) on the q-limbs: outs[b] [2][E][N] is the finished inner product on the extended basis.
-hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, u32 j, const double* y, size_t y_bstride, u64* dst, size_t dst_bstride,
-                            const PolyList& pl, u32 batch, hipStream_t st, bool hi_only = false);
+hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st,
+                            bool hi_only = false);
 // prod: the decomposed polynomial is the d2 = a1 (.) b1 of n ciphertext products and was never stored (the inverse
 // transform took it as a product, launch_ntt with mul_ptrs): the term of the digits' own limbs and the addends
 // d0 = a0 (.) b0, d1 = a0 (.) b1 + a1 (.) b0 are formed from the operands (host arrays of n device pointers,

@@ -236,6 +236,9 @@ struct NttArgs {
     PtrList8 mul_list;     // inverse, first pass, product variant: batch item b is src_list.p[b] (.) mul_list.p[b]
     u64 lin_ka, lin_kb;    // use_lin: ... is lin_ka * src_list.p[b] + lin_kb * mul_list.p[b] instead (one limb per item)
     u32 use_lin, pad2;
+    // loop variant of the forward lo pass, ModUp: the items are (polynomial, digit) pairs, digits fastest, `beta` of them per
+    // polynomial; limb e <= level is transformed for every digit but the one it belongs to, e / alpha (0: plain items)
+    u32 beta, alpha, level, pad3;
     const TwF* inv_scale;  // inverse, last pass (double-precision arithmetic): the limb of modulus m is scaled by inv_scale[m]
                            // instead of 1/N and stored as the centred residue in a double (the form ModUp's conversion reads)
 };
@@ -505,7 +508,17 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
     const LoTile tile = lo_tile(args.log_hi, args.lo_group);
     const u32 b_step = args.lo_group ? gridDim.y : gridDim.x;
     const u32 blk = tile.blk;
-    const PolyRef<A> P = poly_ref<A>(args, pl, tile.b, tile.a);
+    const bool digits = args.beta != 0;
+    const u32 own = digits && tile.a <= args.level ? tile.a / args.alpha : 0xffffffffu;
+    const u32 per = digits ? args.beta - (own < args.beta ? 1 : 0) : 1;  // items per polynomial of this limb
+    const u32 n_items = digits ? args.batch / args.beta * per : args.batch;
+    if (tile.b >= n_items) return;  // whole workgroup
+    auto row_of = [&](u32 i) {  // batch row of this limb's item i
+        if (!digits) return i;
+        const u32 p = i / per, j = i - p * per;
+        return p * args.beta + j + (j >= own ? 1 : 0);
+    };
+    const PolyRef<A> P = poly_ref<A>(args, pl, row_of(tile.b), tile.a);
     const size_t off = (size_t)blk << 11;
     const u32 TA = (1u << args.log_hi) + blk;
     const u32 d3 = tid >> 5, x5 = tid & 31, d2 = (tid >> 2) & 7, d0 = tid & 3;
@@ -522,7 +535,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
     load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
     load_lo_tw<A, 2>(P, 512 * TA + 2 * tid, wd);
     load_lo_tw<A, 2>(P, 512 * TA + 2 * tid + 1, wd + 3);
-    for (u32 b = tile.b; b < args.batch; b += b_step) {
+    for (u32 b = tile.b; b < n_items; b += b_step) {
         if (args.first) {
 #pragma unroll
             for (int j = 0; j < 8; j++) v[j] = A::load_first(raw[j], P.mc, false);
@@ -530,8 +543,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
 #pragma unroll
             for (int j = 0; j < 8; j++) v[j] = A::load_mid(raw[j]);
         }
-        if (b + b_step < args.batch) {  // the next item's points, a tile ahead
-            const u64* src = item_src<A>(args, pl, b + b_step, tile.a) + off;
+        if (b + b_step < n_items) {  // the next item's points, a tile ahead
+            const u64* src = item_src<A>(args, pl, row_of(b + b_step), tile.a) + off;
 #pragma unroll
             for (int j = 0; j < 8; j++) raw[j] = src[tid + 256 * j];
         }
@@ -563,7 +576,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
 #pragma unroll
         for (int j = 0; j < 8; j++) lds1[LDS_PAD(8 * tid + j)] = v[j];
         __syncthreads();
-        u64* dst = item_dst(args, pl, b, tile.a) + off;
+        u64* dst = item_dst(args, pl, row_of(b), tile.a) + off;
 #pragma unroll
         for (int j = 0; j < 8; j++) dst[tid + 256 * j] = A::store_fwd_final(lds1[LDS_PAD(tid + 256 * j)], P.mc);
         // (no barrier between items: the next item's first exchange writes lds0, whose last read is behind the barrier above,
@@ -945,12 +958,17 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_kernel(NttArgs args, P
 // evaluated from the source basis' centred residues yhat (doubles, nd limbs from position lo of each batch item of y)
 // as the tile is loaded: the converted polynomial is never written in coefficient form.
 // convf: [position][ap] (constant, constant / q_e), rows padded with zeros to ap = 4, 8, 12 or 16 entries.
+// alpha != 0 (ModUp): the digits of a polynomial in one launch, blockIdx.z = digit j.  Digit j has the source limbs
+// [j alpha, (j + 1) alpha) of the n_src there are, its table at convf + j * convf_dstride, its results at dst + j * dst_dstride,
+// and every entry of the list but its own limbs as targets.
 struct ConvPrologue {
     const double* y;
     size_t y_bstride;  // elements
     const TwF* convf;
     u32 lo, nd;
-    u32 ap, pad;
+    u32 ap, groups;    // groups: workgroups per tile and polynomial (T targets each)
+    u32 alpha, n_src, digit0, pad;  // digit0: the launch's first digit
+    size_t convf_dstride, dst_dstride;
 };
 
 // the source residues of one point: no branch around the loads (entries beyond the nd source limbs re-read the last
@@ -974,17 +992,23 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
     typedef ArithF64 A;
     typedef double E;
     constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R;
-    const u32 groups = (pl.n + T - 1) / T;
-    const u32 tid = threadIdx.x, tile = blockIdx.x, b = blockIdx.y / groups, a0 = (blockIdx.y % groups) * T;
+    const u32 tid = threadIdx.x, tile = blockIdx.x, b = blockIdx.y / cp.groups, a0 = (blockIdx.y % cp.groups) * T;
     const size_t N = (size_t)1 << args.log_n;
-    const double* y = cp.y + b * cp.y_bstride + (size_t)cp.lo * N + (size_t)tile * CC;
+    const u32 dig = cp.digit0 + blockIdx.z, lo = cp.lo + dig * cp.alpha;
+    const u32 nd = cp.alpha ? min(cp.alpha, cp.n_src - lo) : cp.nd;
+    const u32 n_targets = cp.alpha ? pl.n - nd : pl.n;
+    if (a0 >= n_targets) return;  // whole workgroup: a digit with more limbs has fewer targets
+    const TwF* convf = cp.convf + dig * cp.convf_dstride;
+    const double* y = cp.y + b * cp.y_bstride + (size_t)lo * N + (size_t)tile * CC;
     PolyRef<A> P[T];
     double cw[T][ND];  // the centred constants (the tables' quotients by the modulus are not read)
 #pragma unroll
     for (int t = 0; t < T; t++) {
-        const u32 a_idx = a0 + t < pl.n ? a0 + t : pl.n - 1;  // a ragged last group repeats its last limb and skips the store
+        u32 a_idx = a0 + t < n_targets ? a0 + t : n_targets - 1;  // a ragged last group repeats its last limb and skips the store
+        if (cp.alpha && a_idx >= lo) a_idx += nd;
         P[t] = poly_ref<A, true>(args, pl, b, a_idx);
-        const TwF* ce = cp.convf + (size_t)pl.dpos[a_idx] * AP;
+        P[t].dst += dig * cp.dst_dstride;
+        const TwF* ce = convf + (size_t)pl.dpos[a_idx] * AP;
 #pragma unroll
         for (int a = 0; a < ND; a++) cw[t][a] = ce[a].w;
     }
@@ -996,13 +1020,13 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
 #pragma unroll
             for (int kc = 0; kc < KC; kc++) {
                 double yv[AP];
-                conv_load<AP, ND>(yv, y + ((size_t)rr << 11) + kc * 256 + tid, N, cp.nd);
+                conv_load<AP, ND>(yv, y + ((size_t)rr << 11) + kc * 256 + tid, N, nd);
 #pragma unroll
                 for (int t = 0; t < T; t++) v[t][rr * KC + kc] = conv_sum<AP, ND>(yv, cw[t], P[t].mc.q, P[t].mc.qinv);
             }
 #pragma unroll
         for (int t = 0; t < T; t++) {
-            if (a0 + t >= pl.n) break;
+            if (a0 + t >= n_targets) break;
             u64* dst = P[t].dst + (size_t)tile * CC;
             fwd_rows<A, LOG_HI, KC>(v[t], P[t].tw, 1, P[t].mc);
             A::fwd_round_end(v[t], P[t].mc);
@@ -1018,14 +1042,14 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             double yv[AP];
-            conv_load<AP, ND>(yv, y + ((size_t)(r0 + R8 * j) << 11) + col, N, cp.nd);
+            conv_load<AP, ND>(yv, y + ((size_t)(r0 + R8 * j) << 11) + col, N, nd);
 #pragma unroll
             for (int t = 0; t < T; t++) v[t][j] = conv_sum<AP, ND>(yv, cw[t], P[t].mc.q, P[t].mc.qinv);
         }
         const u32 G = tid >> 5, cg = tid & 31;
 #pragma unroll
         for (int t = 0; t < T; t++) {
-            if (a0 + t >= pl.n) break;  // uniform over the workgroup
+            if (a0 + t >= n_targets) break;  // uniform over the workgroup
             u64* dst = P[t].dst + (size_t)tile * CC;
             if (t) __syncthreads();  // the previous limb's exchange has been read
             fwd_rows<A, 3, 1>(v[t], P[t].tw, 1, P[t].mc);
@@ -1044,6 +1068,106 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
 #pragma unroll
                 for (int kc = 0; kc < KC2; kc++) dst[((size_t)(G * R8 + rr) << 11) + cg * KC2 + kc] = A::store_mid(v[t][rr * KC2 + kc]);
         }
+    }
+}
+
+// The converting hi pass of the larger rings (LOG_HI >= 4) as two phases through LDS.  Its time is arithmetic, about 70
+// double-precision operations per point and target: 40 for a sum of eight terms, the rest butterflies.  With a thread holding
+// its eight points of several targets through both (the kernel above), most of 210 registers are points that wait and
+// the targets' constants overflow the scalar registers (two waves per SIMD, 50 scalar spills).  Here a workgroup of
+// 512 threads first converts its tile for four targets, one target at a time (a thread's points: tid + 512 i; the target's
+// constants are wide scalar loads), into 64 KB of LDS, then each half of the workgroup transforms two of the targets in
+// place.  Nothing but the source residues lives across targets: at most 128 registers, four waves per SIMD from two workgroups
+// whose phases interleave, and a small launch's workgroup is done sooner.  8 -> 13 and 5 -> 16 limbs of one polynomial at
+// N = 2^16 (a digit each): 17.5 us a launch and digit with the kernel above, 13 us for both; launches that fill the chip several
+// times gain little (8 polynomials, 8 -> 19 limbs: 47.8 and 45.2 us; vector units 68 % busy while a CU has work, which it
+// has 72 % of the time).  A workgroup that goes on with more sets of its tile is slower (52 us).
+// The tables are read through the constant address space: behind the stores to LDS the compiler would otherwise fetch
+// wave-uniform constants with vector loads.
+#define HC_THREADS 512
+#define HC_T 4
+template <class V>
+using ConstPtr = const __attribute__((address_space(4))) V*;
+template <class V>
+__device__ __forceinline__ ConstPtr<V> const_ptr(const V* p) { return (ConstPtr<V>)p; }
+template <int LOG_HI, int AP, int ND>
+__global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ntt_fwd_hi_conv_lds_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
+    typedef ArithF64 A;
+    constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R, PTS = NTT_TILE / HC_THREADS, PP = ND <= 9 ? PTS : 2;
+    constexpr int R8 = R / 8, S2 = LOG_HI - 3, KC2 = 8 / R8;
+    __shared__ __attribute__((aligned(16))) double lds[HC_T][NTT_TILE];
+    const u32 tid = threadIdx.x, tile = blockIdx.x, b = blockIdx.y / cp.groups, a0 = (blockIdx.y % cp.groups) * HC_T;
+    const size_t N = (size_t)1 << args.log_n;
+    const u32 dig = cp.digit0 + blockIdx.z, lo = cp.lo + dig * cp.alpha;
+    const u32 nd = cp.alpha ? min(cp.alpha, cp.n_src - lo) : cp.nd;
+    const u32 n_targets = cp.alpha ? pl.n - nd : pl.n;
+    if (a0 >= n_targets) return;  // whole workgroup: a digit with more limbs has fewer targets
+    const u32 cnt = min((u32)HC_T, n_targets - a0);
+    const TwF* convf = cp.convf + dig * cp.convf_dstride;
+    const double* y = cp.y + b * cp.y_bstride + (size_t)lo * N + (size_t)tile * CC;
+    u64* dst0 = args.dst + (((size_t)b * args.dst_bstride) << args.log_n) + dig * cp.dst_dstride + (size_t)tile * CC;
+    auto entry = [&](u32 a) { return cp.alpha && a >= lo ? a + nd : a; };  // list entry of target a: past the digit's own limbs
+    const u32 half = __builtin_amdgcn_readfirstlane(tid >> 8), lt = tid & 255;
+    const u32 r0 = lt / CC, col = lt % CC, G = lt >> 5, cg = lt & 31;
+#pragma unroll
+    for (int h = 0; h < PTS; h += PP) {
+        double yv[PP][AP];
+#pragma unroll
+        for (int i = 0; i < PP; i++) {
+            const u32 p = tid + HC_THREADS * (h + i), off = ((p / CC) << 11) + p % CC;
+#pragma unroll
+            for (int k = 0; k < ND; k++) yv[i][k] = (y + (size_t)((u32)k < nd ? k : nd - 1) * N)[off];  // see conv_load
+        }
+#pragma unroll 1
+        for (u32 t = 0; t < cnt; t++) {
+            const u32 a = entry(a0 + t), m_idx = pl_at(pl.mod, a);
+            ConstPtr<TwF> ce = const_ptr(convf + (size_t)pl_at(pl.dpos, a) * AP);
+            ConstPtr<ModConstF> mc = const_ptr((const ModConstF*)args.mc + m_idx);
+            const double q = mc->q, qinv = mc->qinv;
+            double cw[ND];
+#pragma unroll
+            for (int k = 0; k < ND; k++) cw[k] = ce[k].w;
+#pragma unroll
+            for (int i = 0; i < PP; i++) lds[t][tid + HC_THREADS * (h + i)] = conv_sum<AP, ND>(yv[i], cw, q, qinv);
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (u32 t = half; t < cnt; t += 2) {
+        const u32 m_idx = pl_at(pl.mod, entry(a0 + t));
+        const TwF* tw = (const TwF*)args.tw + ((size_t)m_idx << args.log_n);
+        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = lds[t][(r0 + R8 * j) * CC + col];
+        TwF w1[7];
+#pragma unroll
+        for (int i = 0; i < 7; i++) w1[i] = TwF{const_ptr(tw + 1 + i)->w, const_ptr(tw + 1 + i)->wq};
+        fwd_rows_pre<A, 3>(v, w1, mc);
+        A::fwd_round_end(v, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds[t][(r0 + R8 * j) * CC + col] = v[j];
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (u32 t = half; t < cnt; t += 2) {
+        const u32 a = entry(a0 + t), m_idx = pl_at(pl.mod, a);
+        const TwF* tw = (const TwF*)args.tw + ((size_t)m_idx << args.log_n);
+        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+        u64* dst = dst0 + ((size_t)pl_at(pl.dpos, a) << args.log_n);
+        double v[8];
+#pragma unroll
+        for (int rr = 0; rr < R8; rr++)
+#pragma unroll
+            for (int kc = 0; kc < KC2; kc++) v[rr * KC2 + kc] = lds[t][(G * R8 + rr) * CC + cg * KC2 + kc];
+        fwd_rows<A, S2, KC2>(v, tw, 8 + G, mc);
+        A::fwd_round_end(v, mc);
+#pragma unroll
+        for (int rr = 0; rr < R8; rr++)
+#pragma unroll
+            for (int kc = 0; kc < KC2; kc++) dst[((size_t)(G * R8 + rr) << 11) + cg * KC2 + kc] = A::store_mid(v[rr * KC2 + kc]);
     }
 }
 
@@ -1206,44 +1330,54 @@ static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& a
     else launch_inv_lo_it<A, 1>(grid, st, args, pl, mul);
 }
 
-// Target limbs per workgroup of the converting hi pass: four, or six where there are many of them and the ring is large (the
-// source residues are fetched by four workgroups instead of six for 24 targets; the pass takes as long by itself and leaves
-// more of the chip to the other stream's kernels: 0.5 ms per step of the block slice; with few targets or small launches the
-// larger groups cost parallelism)
-// (not for the one-term "conversion" of the rescale, which has no arithmetic to share: 36 us with four, 41 with six)
-static u32 conv_targets(u32 log_hi, u32 n_targets, u32 nd) { return (log_hi >= 4 && n_targets >= 12 && nd > 1) ? 6 : 4; }
-template <int LOG_HI, int T>
-static void launch_hi_conv_ap(u32 ap, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
-    if (ap == 4 && cp.nd == 1)  // the rescale: one dropped limb
-        hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 4, T, 1>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
-    else if (ap == 4) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 4, T>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
-    else if (ap == 8) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 8, T>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
-    else if (ap == 12 && cp.nd == 9)  // eight special primes and the dropped limb: three of the twelve entries are padding
-        hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 12, T, 9>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
-    else if (ap == 12) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 12, T>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
-    else hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, 16, T>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp);
+#define HI_CONV_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(threads), 0, st, args, pl, cp)
+template <int LOG_HI>
+static void launch_hi_conv_ap(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
+    const u32 ap = cp.ap;
+    if (ap == 4 && cp.nd == 1) {  // the rescale: one dropped limb
+        constexpr u32 threads = NTT_THREADS;
+        HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 4, 4, 1>);
+        return;
+    }
+    if constexpr (LOG_HI >= 4) {
+        constexpr u32 threads = HC_THREADS;
+        if (ap == 4) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 4, 4>);
+        else if (ap == 8) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 8, 8>);
+        else if (ap == 12 && cp.nd == 9) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 12, 9>);  // eight special primes and the dropped limb: three of the twelve entries are padding
+        else if (ap == 12) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 12, 12>);
+        else HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 16, 16>);
+    } else {
+        constexpr u32 threads = NTT_THREADS;
+        if (ap == 4) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 4, 4>);
+        else if (ap == 8) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 8, 4>);
+        else if (ap == 12 && cp.nd == 9) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 12, 4, 9>);
+        else if (ap == 12) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 12, 4>);
+        else HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 16, 4>);
+    }
 }
-static void launch_hi_conv(u32 log_hi, u32 ap, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
-    const bool six = conv_targets(log_hi, pl.n, cp.nd) == 6;
+#undef HI_CONV_LAUNCH
+// n_targets: the most targets a digit of the launch has
+static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
+    cp.groups = (n_targets + 3) / 4;  // workgroups of four targets
+    const dim3 grid(1u << log_hi, cp.groups * batch, digits);
     switch (log_hi) {
-        case 1: launch_hi_conv_ap<1, 4>(ap, grid, st, args, pl, cp); break;
-        case 2: launch_hi_conv_ap<2, 4>(ap, grid, st, args, pl, cp); break;
-        case 3: launch_hi_conv_ap<3, 4>(ap, grid, st, args, pl, cp); break;
-        case 4: six ? launch_hi_conv_ap<4, 6>(ap, grid, st, args, pl, cp) : launch_hi_conv_ap<4, 4>(ap, grid, st, args, pl, cp); break;
-        case 5: six ? launch_hi_conv_ap<5, 6>(ap, grid, st, args, pl, cp) : launch_hi_conv_ap<5, 4>(ap, grid, st, args, pl, cp); break;
-        default: six ? launch_hi_conv_ap<6, 6>(ap, grid, st, args, pl, cp) : launch_hi_conv_ap<6, 4>(ap, grid, st, args, pl, cp); break;
+        case 1: launch_hi_conv_ap<1>(grid, st, args, pl, cp); break;
+        case 2: launch_hi_conv_ap<2>(grid, st, args, pl, cp); break;
+        case 3: launch_hi_conv_ap<3>(grid, st, args, pl, cp); break;
+        case 4: launch_hi_conv_ap<4>(grid, st, args, pl, cp); break;
+        case 5: launch_hi_conv_ap<5>(grid, st, args, pl, cp); break;
+        default: launch_hi_conv_ap<6>(grid, st, args, pl, cp); break;
     }
 }
 
 static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                                  size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs,
-                                 const FwdEpilogue* epilogue, const TwF* inv_scale, const ConvPrologue* conv, bool hi_only = false,
+                                 const FwdEpilogue* epilogue, const TwF* inv_scale, const ConvPrologue* conv,
                                  const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
-    if (hi_only && (!conv || epilogue)) return hipErrorInvalidValue;
     if (src_ptrs && batch > KS_MAX_BATCH) return hipErrorInvalidValue;
     if (epilogue && (inverse || !ntt_has_epilogue(c) || batch > 2 * KS_MAX_BATCH)) return hipErrorInvalidValue;
     if ((inv_scale && !inverse) || (conv && inverse) || ((inv_scale || conv) && !ntt_has_modup(c))) return hipErrorInvalidValue;
@@ -1280,6 +1414,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
     args.lin_ka = lin_k ? lin_k[0] : 0;
     args.lin_kb = lin_k ? lin_k[1] : 0;
     args.pad2 = 0;
+    args.beta = args.alpha = args.level = args.pad3 = 0;
     const u32 polys = pl.n * batch;
     const dim3 block(NTT_THREADS);
     const double pass_bytes = 16.0 * polys * c->N;
@@ -1324,13 +1459,11 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             args.last = 0;
             if (conv) {  // reads the digit's nd limbs for every target limb (from cache after the first), writes the target limbs
                 ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * batch * ((double)conv->nd + pl.n), hi_ops);
-                const u32 ct = conv_targets(c->log_hi, pl.n, conv->nd);
-                launch_hi_conv(c->log_hi, conv->ap, dim3(grid.x, (pl.n + ct - 1) / ct * batch), st, args, pl, *conv);
+                launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv);
             } else {
                 ProfScope ps__(c, K_NTT_FWD_HI, st, pass_bytes, hi_ops);
                 hi(args, pl);
             }
-            if (hi_only) return hipGetLastError();  // the caller's own lo pass follows (launch_ntt_lo_mac)
             if (epilogue) {  // reads w and v, writes the quotients (plus the addends it reads)
                 ProfScope ps__(c, K_NTT_FWD_LO, st, (epilogue->use_vl == 2 ? 2.0 : 1.5) * pass_bytes, lo_ops);
                 if (f64) launch_lo_div<ArithF64>(grid_lo, st, second, pd, *epilogue);
@@ -1363,21 +1496,96 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst, size_t dst_bstride,
                       const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs, const FwdEpilogue* epilogue,
                       const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k) {
-    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, false,
-                          mul_ptrs, lin_k);
+    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k);
 }
 
-hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, u32 j, const double* y, size_t y_bstride, u64* dst, size_t dst_bstride,
-                            const PolyList& pl, u32 batch, hipStream_t st, bool hi_only) {
+// Small launches take all digits at once: one converting hi pass and (unless the inner product takes it from there) one lo pass,
+// instead of a launch per digit that leaves most of the chip idle (one polynomial of 13 limbs in digits of 8 and 5 at N = 2^16:
+// 17.5 us per digit; a product with its rescale 167 -> 153 us, six unhoisted rotations at N = 2^13 83 -> 70 us).  From 768
+// workgroups per digit on, a digit fills the chip by itself and goes through its two passes alone: what the second reads is
+// then still in the last-level cache, and the other stream's kernels get their turn between the launches (all digits at once:
+// 1 % slower for 64 channels, 2 % for the sixteen-channel activation).
+hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st, bool hi_only) {
+    if (!ntt_has_modup(c) || n == 0) return hipErrorInvalidValue;
+    const u32 E = c->ext_limbs(level), beta = c->live_digits(level), L1 = level + 1;
     ConvPrologue cp;
     cp.y = y;
     cp.y_bstride = y_bstride;
-    cp.convf = c->modup_table_f(level, j);
-    cp.lo = c->digit_lo(j);
-    cp.nd = c->digit_hi(j, level) - cp.lo;
+    cp.convf = c->modup_table_f(level, 0);
+    cp.lo = 0;
+    cp.nd = c->alpha < L1 ? c->alpha : L1;
     cp.ap = c->alpha_pad;
-    cp.pad = 0;
-    return launch_ntt_any(c, false, dst, dst_bstride, dst, dst_bstride, pl, batch, st, nullptr, nullptr, nullptr, &cp, hi_only);
+    cp.groups = 0;
+    cp.alpha = c->alpha;
+    cp.n_src = L1;
+    cp.digit0 = cp.pad = 0;
+    cp.convf_dstride = (size_t)c->M * c->alpha_pad;
+    cp.dst_dstride = (size_t)E * c->N;
+    PolyList all;
+    all.n = E;
+    for (u32 e = 0; e < CKKS_MAX_MODULI; e++) {
+        all.spos[e] = all.dpos[e] = (unsigned char)(e < E ? e : 0);
+        all.mod[e] = (unsigned char)(e < E ? c->ext_modulus(level, e) : 0);
+    }
+    NttArgs args = {};
+    args.mc = c->d_mcf;
+    args.tw = c->d_twf;
+    args.tw_val = c->d_twf_val;
+    args.log_n = c->log_n;
+    args.log_lo = c->log_lo;
+    args.log_hi = c->log_hi;
+    const bool together = ((E - cp.nd + 3) / 4 * n << c->log_hi) < 768;
+    for (u32 j0 = 0; j0 < beta; j0 += together ? beta : 1) {
+        const u32 nj = together ? beta : 1;
+        double rows = 0.0;  // transformed limb-polys
+        u32 most = 0;       // targets of one digit
+        for (u32 j = j0; j < j0 + nj; j++) {
+            const u32 t = E - (c->digit_hi(j, level) - c->digit_lo(j));
+            rows += (double)n * t;
+            most = t > most ? t : most;
+        }
+        cp.digit0 = j0;
+        args.src = nullptr;
+        args.dst = digits;
+        args.src_bstride = args.dst_bstride = (size_t)beta * E;
+        args.first = 1;
+        args.last = 0;
+        args.batch = n;
+        args.beta = 0;
+        {
+            ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * (n * (together ? (double)L1 : (double)(E - most)) + rows), 0.5 * rows * c->N * c->log_hi);
+            launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp);
+        }
+        if (hi_only) continue;  // the caller's own lo pass follows (launch_ntt_lo_mac)
+        PolyList pl = all;
+        args.dst = digits + (size_t)j0 * E * c->N;
+        if (together) {  // rows (polynomial, digit) at a stride of E limb-polys
+            args.dst_bstride = E;
+            args.batch = n * beta;
+            args.beta = beta;
+            args.alpha = c->alpha;
+            args.level = level;
+        } else {  // the digit's own limbs are not in the list
+            const u32 lo = c->digit_lo(j0), nd = E - most;
+            for (u32 a = lo; a + nd < E; a++) {
+                pl.spos[a] = pl.dpos[a] = all.dpos[a + nd];
+                pl.mod[a] = all.mod[a + nd];
+            }
+            pl.n = most;
+        }
+        args.src = args.dst;
+        args.src_bstride = args.dst_bstride;
+        args.first = 0;
+        args.last = 1;
+        const u32 slices = pl.n << c->log_hi;
+        args.lo_group = 0;
+        for (u32 g = 64; g >= 8; g >>= 1)
+            if (slices % g == 0) { args.lo_group = g; break; }
+        const dim3 grid = args.lo_group ? dim3(args.lo_group, 1, slices / args.lo_group) : dim3(1, slices);
+        ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_lo);
+        launch_fwd_lo_loop<ArithF64>(args.batch, grid, st, args, pl);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64* dst, u32 batch, hipStream_t st,
@@ -1390,7 +1598,8 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
     cp.lo = 0;
     cp.nd = 1;
     cp.ap = 4;
-    cp.pad = 0;
+    cp.alpha = cp.n_src = cp.digit0 = cp.pad = 0;
+    cp.convf_dstride = cp.dst_dstride = 0;
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < level ? a : 0);
     pl.n = level;
@@ -1481,7 +1690,8 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
     cp.lo = merged ? level : level + 1;  // the dropped limbs sit at consecutive positions of the extended polynomial
     cp.nd = merged ? c->num_p + 1 : c->num_p;
     cp.ap = merged ? c->k2_pad : c->k_pad;
-    cp.pad = 0;
+    cp.alpha = cp.n_src = cp.digit0 = cp.pad = 0;
+    cp.convf_dstride = cp.dst_dstride = 0;
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < n_out ? a : 0);
     pl.n = n_out;

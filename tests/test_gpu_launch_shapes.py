@@ -1,5 +1,5 @@
 """GPU parity at the sizes where the launch rules change: how many batch items a lo-pass workgroup takes, which kernel takes the
-layer's multiply-accumulate."""
+layer's multiply-accumulate, how many digits a decomposition launches at once."""
 import numpy as np
 import pytest
 
@@ -60,3 +60,23 @@ def test_weighted_sum_kernels(log_n, c_in, c_out, bits):
     want, got = random_conv(log_n, c_in, c_out, bits, seed=c_in * 100 + c_out)
     for o in range(c_out):
         assert np.array_equal(got[o], want[o]), f"output {o}"
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(15, 5, 2, 3, 4), (15, 13, 8, 2, 12), (15, 12, 9, 2, 7), (15, 11, 11, 1, 10),
+                                                          (15, 14, 14, 1, 13), (16, 7, 3, 4, 5), (13, 7, 12, 3, 6)])
+def test_digits_together(log_n, num_q, num_p, dnum, level):
+    """All digits of a small decomposition in one launch: ragged last digits (1 of 2, 6 of 7, 2 of 6 limbs) and a single digit, rows of
+    4, 8, 12 and 16 conversion constants on both sides (9 and 12 real ones of twelve), target counts that are not multiples of
+    four, with the inner product inside the second pass (key switch) and behind it (hoisted rotations)."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(4000 + num_q)
+    ct = rand_ct(rng, p.moduli, level, orc.N)
+    offs = [3, -1]
+    keys = [np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)]) for _ in offs]
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, r)) for k, r in zip(keys, offs)]
+    out = hx.ckks_keyswitch(ctx, hx.from_host(ct[1]), level, dkeys[0])
+    assert np.array_equal(hx.to_host(out), orc.keyswitch(ct[1], keys[0], level))
+    outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, dkeys, True)
+    for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, True)):
+        assert np.array_equal(hx.to_host(got), want)
