@@ -1263,21 +1263,48 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
     hipStream_t st = (hipStream_t)stream;
 
     // input alignment: nine aligned copies of every input channel, each times its tap mask.  Channels
-    // go in batches: one shared pass of the decomposition kernels, then per tap one inner product that
-    // streams the tap's key once for the whole batch and one batched ModDown.
+    // go in batches: one shared pass of the decomposition kernels, then inner products that stream each
+    // tap's key once for the whole batch and batched ModDowns (a single channel: one of each for its eight taps).
     auto mask_of = [&](u32 t) { return (const u64*)d_tap_masks + (size_t)t * L1 * N; };
     auto slot = [&](u32 ch, u32 t) { return xs + ((size_t)ch * 9 + t) * ct_elems; };
-    // rotate the batch `base` (digits already in ws) by the offset of tap `kt`; outs[b] gets mask `m`
-    auto rotate_batch = [&](const u64* const* base, u32 n, u32 kt, u64* const* outs, const u64* m) -> int {
-        HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, 0), rot_keys[kt]->d_key, gs[kt], ws.v, ws.v_b, n, st));
-        FinalItem items[CT_BATCH];
-        for (u32 b = 0; b < n; b++) items[b] = FinalItem{base[b], nullptr, m, outs[b], gs[kt], 0};
-        return run_moddown(c, level, ws, n, items, st);
+    // One rotation of every ciphertext of a batch: by the offset of tap kt, times masks[b] (or unmasked), to outs[b].
+    struct TapJob {
+        u32 kt;
+        u64* outs[CT_BATCH];
+        const u64* masks[CT_BATCH];
+    };
+    // The rotations `jobs` of the n ciphertexts `base`, whose digits are in ws: as many taps per launch as fill a batch of
+    // CT_BATCH key switches (eight for a single channel, one for eight channels).
+    auto rotate_jobs = [&](const u64* const* base, u32 n, const TapJob* jobs, u32 n_jobs) -> int {
+        const u32 per = CT_BATCH / n;
+        const bool fused = c->live_digits(level) <= 4;
+        for (u32 j0 = 0; j0 < n_jobs; j0 += per) {
+            const u32 m = n_jobs - j0 < per ? n_jobs - j0 : per;
+            FinalItem items[CT_BATCH];
+            const u64* keys[CT_BATCH];
+            u32 g[CT_BATCH], pos[CT_BATCH];
+            for (u32 j = 0; j < m; j++) {
+                const TapJob& job = jobs[j0 + j];
+                keys[j] = rot_keys[job.kt]->d_key;
+                g[j] = gs[job.kt];
+                pos[j] = j * n;
+                if (!fused) HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, 0), keys[j], g[j], ws.v + (size_t)pos[j] * ws.v_b, ws.v_b, n, st));
+                for (u32 b = 0; b < n; b++)
+                    items[pos[j] + b] = fused ? FinalItem{nullptr, nullptr, job.masks[b], job.outs[b], 1, 0} : FinalItem{base[b], nullptr, job.masks[b], job.outs[b], g[j], 0};
+            }
+            // one launch that reads the digits once for its taps and leaves P sigma_g(c0) + inner product: dividing it by P is the rotation
+            if (fused)
+                HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys, g, nullptr, pos, m, base, ws.v, XLayout::classic(c->ext_limbs(level), N),
+                                              0, 1, n, nullptr, false, st, nullptr, 0, true));
+            if (int rc = run_moddown(c, level, ws, m * n, items, st)) return rc;
+        }
+        return CKKS_OK;
     };
     for (u32 c0 = 0; c0 < d->c_in; c0 += CT_BATCH) {
         const u32 n = d->c_in - c0 < CT_BATCH ? d->c_in - c0 : CT_BATCH;
         const u64 *in[CT_BATCH], *c1s[CT_BATCH];
-        u64* outs[CT_BATCH];
+        TapJob jobs[8];
+        u32 nj = 0;
         for (u32 b = 0; b < n; b++) {
             in[b] = (const u64*)h_d_in[c0 + b];
             c1s[b] = in[b] + L1 * N;
@@ -1290,46 +1317,61 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
                     for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(t), in[b], slot(c0 + b, t), st));
                     continue;
                 }
-                for (u32 b = 0; b < n; b++) outs[b] = slot(c0 + b, t);
-                if ((rc = rotate_batch(in, n, t, outs, mask_of(t)))) return rc;
+                TapJob& job = jobs[nj++];
+                job.kt = t;
+                for (u32 b = 0; b < n; b++) job.outs[b] = slot(c0 + b, t), job.masks[b] = mask_of(t);
             }
+            if ((rc = rotate_jobs(in, n, jobs, nj))) return rc;
             continue;
         }
         // four-key alignment, first stage: the input rotated by -1, +1 (kept unmasked for the second
         // stage) and by -W, +W (final), all from the one decomposition of the input
+        const u64* base[2 * CT_BATCH];  // C^-1 of the batch, then C^+1
         for (u32 sd = 0; sd < 2; sd++) {
             const u32 kt = sd == 0 ? 3 : 5;
-            for (u32 b = 0; b < n; b++) outs[b] = side[sd] + (size_t)b * ct_elems;
+            u64* outs[CT_BATCH];
+            for (u32 b = 0; b < n; b++) base[sd * n + b] = outs[b] = side[sd] + (size_t)b * ct_elems;
             if (gs[kt] == 1) {
                 for (u32 b = 0; b < n; b++) HIP_TRY(launch_copy(in[b], outs[b], ct_elems, st));
-            } else if ((rc = rotate_batch(in, n, kt, outs, nullptr))) return rc;
+                continue;
+            }
+            TapJob& job = jobs[nj++];
+            job.kt = kt;
+            for (u32 b = 0; b < n; b++) job.outs[b] = outs[b], job.masks[b] = nullptr;
         }
         for (u32 kt = 1; kt <= 7; kt += 6) {
-            for (u32 b = 0; b < n; b++) outs[b] = slot(c0 + b, kt);
             if (gs[kt] == 1) {
-                for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(kt), in[b], outs[b], st));
-            } else if ((rc = rotate_batch(in, n, kt, outs, mask_of(kt)))) return rc;
+                for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(kt), in[b], slot(c0 + b, kt), st));
+                continue;
+            }
+            TapJob& job = jobs[nj++];
+            job.kt = kt;
+            for (u32 b = 0; b < n; b++) job.outs[b] = slot(c0 + b, kt), job.masks[b] = mask_of(kt);
         }
+        if ((rc = rotate_jobs(in, n, jobs, nj))) return rc;
         for (u32 b = 0; b < n; b++) {
             HIP_TRY(launch_mask_mul(c, level, mask_of(4), in[b], slot(c0 + b, 4), st));
             HIP_TRY(launch_mask_mul(c, level, mask_of(3), side[0] + (size_t)b * ct_elems, slot(c0 + b, 3), st));
             HIP_TRY(launch_mask_mul(c, level, mask_of(5), side[1] + (size_t)b * ct_elems, slot(c0 + b, 5), st));
         }
-        // second stage: C^-1 and C^+1 rotated by -W and +W (their own decompositions)
-        for (u32 sd = 0; sd < 2; sd++) {
-            const u64* base[CT_BATCH];
-            for (u32 b = 0; b < n; b++) {
-                base[b] = side[sd] + (size_t)b * ct_elems;
-                c1s[b] = base[b] + L1 * N;
-            }
-            if ((rc = run_modup(c, level, c1s, n, ws, st))) return rc;
+        // second stage: C^-1 and C^+1 rotated by -W and +W (their own decompositions; both in one batch where they fit)
+        const u32 n2 = 2 * n <= CT_BATCH ? 2 * n : n;
+        for (u32 b0 = 0; b0 < 2 * n; b0 += n2) {
+            for (u32 b = 0; b < n2; b++) c1s[b] = base[b0 + b] + L1 * N;
+            if ((rc = run_modup(c, level, c1s, n2, ws, st))) return rc;
+            nj = 0;
             for (u32 kt = 1; kt <= 7; kt += 6) {
-                const u32 t = (kt == 1 ? 0 : 6) + 2 * sd;  // corner taps 0, 2 (row -1) and 6, 8 (row +1)
-                for (u32 b = 0; b < n; b++) outs[b] = slot(c0 + b, t);
-                if (gs[kt] == 1) {
-                    for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(t), base[b], outs[b], st));
-                } else if ((rc = rotate_batch(base, n, kt, outs, mask_of(t)))) return rc;
+                TapJob job;
+                job.kt = kt;
+                for (u32 b = 0; b < n2; b++) {
+                    const u32 sd = (b0 + b) / n, t = (kt == 1 ? 0 : 6) + 2 * sd;  // corner taps 0, 2 (row -1) and 6, 8 (row +1)
+                    job.outs[b] = slot(c0 + (b0 + b) % n, t);
+                    job.masks[b] = mask_of(t);
+                    if (gs[kt] == 1) HIP_TRY(launch_mask_mul(c, level, job.masks[b], base[b0 + b], job.outs[b], st));
+                }
+                if (gs[kt] != 1) jobs[nj++] = job;
             }
+            if ((rc = rotate_jobs(base + b0, n2, jobs, nj))) return rc;
         }
     }
     // convolution evaluation: integer-weighted sum over (input channel, tap) for every output channel
