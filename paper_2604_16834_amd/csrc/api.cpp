@@ -323,7 +323,10 @@ int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride
         }
         HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st));
     } else {
-        HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, 0), d_rlk, 1, ws.v, ws.v_b, n, st));
+        const u64* keys[CT_BATCH];
+        u32 gs[CT_BATCH];
+        for (u32 i = 0; i < n; i++) keys[i] = d_rlk, gs[i] = 1;
+        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), keys, gs, nullptr, ws.v, ws.v_b, n, st));
     }
     return run_moddown(c, level, ws, n, items, st);
 }
@@ -534,9 +537,26 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     return join(CKKS_OK);
 }
 
+// Inner products of n_taps rotations of the same n ciphertexts, whose digits are in ws: P sigma_g(c0) + <sigma_g(digits), key> of
+// tap i and ciphertext b at ws.v + (pos[i] + b) * ws.v_b.  One launch that reads the digits once for its taps where their count
+// allows it, else one per tap.
+hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64* const* cts, u32 n, const u64* const* keys, const u32* gs,
+                         const u32* pos, u32 n_taps, hipStream_t st) {
+    if (c->live_digits(level) <= 4)
+        return launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys, gs, nullptr, pos, n_taps, cts, ws.v, XLayout::classic(c->ext_limbs(level), c->N),
+                                     0, 1, n, nullptr, false, st, nullptr, 0, true);
+    for (u32 i = 0; i < n_taps; i++) {
+        const u64* k[CT_BATCH];
+        u32 g[CT_BATCH];
+        for (u32 b = 0; b < n; b++) k[b] = keys[i], g[b] = gs[i];
+        if (hipError_t e = launch_key_inner_items(c, level, dsrc(c, ws, 0), k, g, cts, ws.v + (size_t)pos[i] * ws.v_b, ws.v_b, n, st); e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // n <= CT_BATCH different ciphertexts srcs[b] ([2][level+1][N]) rotated, outs[b] = Rot(srcs[b]) with keys[b] / gal[b]
-// ([2][level+1][N], no overlap).  Neighbouring items with the same key go through one inner-product launch (the key
-// streams once for all of them).
+// ([2][level+1][N], no overlap).  One inner-product launch for all of them (a key streams once for neighbouring items that
+// share it); it adds P sigma(c0), so that the division by P is the rotation.
 // accs (optional): outs[b] = Rot(srcs[b]) + accs[b], the sum formed by the division's last step.
 int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, const u32* gal,
                      u64* const* outs, const KsWs& ws, hipStream_t st, const u64* const* accs = nullptr) {
@@ -546,17 +566,10 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
     for (u32 b = 0; b < n; b++) c1s[b] = srcs[b] + L1 * N;
     int rc = run_modup(c, level, c1s, n, ws, st);
     if (rc) return rc;
-    for (u32 b0 = 0; b0 < n;) {
-        u32 b1 = b0 + 1;
-        while (b1 < n && keys[b1] == keys[b0]) b1++;
-        if (b1 - b0 == 1)
-            HIP_TRY(launch_key_inner(c, level, dsrc(c, ws, b0), keys[b0]->d_key, gal[b0], ws.v + b0 * ws.v_b, st));
-        else
-            HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, b0), keys[b0]->d_key, gal[b0], ws.v + b0 * ws.v_b,
-                                           ws.v_b, b1 - b0, st));
-        b0 = b1;
-    }
-    for (u32 b = 0; b < n; b++) items[b] = FinalItem{srcs[b], nullptr, nullptr, outs[b], gal[b], 0, accs ? accs[b] : nullptr};
+    const u64* kd[CT_BATCH];
+    for (u32 b = 0; b < n; b++) kd[b] = keys[b]->d_key;
+    HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), kd, gal, srcs, ws.v, ws.v_b, n, st));
+    for (u32 b = 0; b < n; b++) items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
     return run_moddown(c, level, ws, n, items, st);
 }
 
@@ -578,7 +591,10 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
     u64* total = ar.take(ct_elems);
     if (!ok || !ar.ok() || ar.used + ws_rescale(c, level, 1) > ar.cap)
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the merge");
-    for (u32 i = 0; i < g; i++) HIP_TRY(launch_mask_mul(c, level, mask, cts[i], masked + i * ct_elems, st));
+    const u64* masks[KS_MAX_BATCH];
+    u64* mouts[KS_MAX_BATCH];
+    for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems;
+    HIP_TRY(launch_mask_mul(c, level, masks, cts, mouts, g, st));
     // blocks 1..g-1: every block has its own key; a batch shares the decomposition and ModDown launches
     for (u32 i0 = 1; i0 < g; i0 += nb) {
         const u32 n = g - i0 < nb ? g - i0 : nb;
@@ -641,18 +657,19 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
         const u32 per = CT_BATCH / n;  // offsets per ModDown batch
         for (u32 la = 0; la < n_lo; la += per) {
             FinalItem items[CT_BATCH];
-            u32 nk = 0;
+            const u64* tkeys[CT_BATCH];
+            u32 tg[CT_BATCH], pos[CT_BATCH], nt = 0, nk = 0;
             for (u32 l = la; l < n_lo && l < la + per; l++) {
                 if (g_lo[l] == 1) {
                     for (u32 b = 0; b < n; b++) HIP_TRY(launch_copy(cts[c0 + b], r_at(b, l), ctl, st));
                     continue;
                 }
-                if (n == 1)
-                    HIP_TRY(launch_key_inner(c, level, dsrc(c, ws, 0), lo_keys[l]->d_key, g_lo[l], ws.v + nk * ws.v_b, st));
-                else
-                    HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, 0), lo_keys[l]->d_key, g_lo[l], ws.v + nk * ws.v_b, ws.v_b, n, st));
-                for (u32 b = 0; b < n; b++) items[nk++] = FinalItem{cts[c0 + b], nullptr, nullptr, r_at(b, l), g_lo[l], 0};
+                tkeys[nt] = lo_keys[l]->d_key;
+                tg[nt] = g_lo[l];
+                pos[nt++] = nk;
+                for (u32 b = 0; b < n; b++) items[nk++] = FinalItem{nullptr, nullptr, nullptr, r_at(b, l), 1, 0};
             }
+            HIP_TRY(rotated_inner(c, level, ws, cts + c0, n, tkeys, tg, pos, nt, st));
             if (nk && (rc = run_moddown(c, level, ws, nk, items, st))) return rc;
         }
         // masked sums, one per (ciphertext, h), and their rescale
@@ -986,7 +1003,9 @@ int ckks_keyswitch(const ckks_ctx* c, const uint64_t* d_c, uint32_t level, const
         const u64* k = key->d_key;
         HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), &k, &ws.v, 1, st));
     } else {
-        HIP_TRY(launch_key_inner(c, level, dsrc(c, ws, 0), key->d_key, 1, ws.v, st));
+        const u64* k = key->d_key;
+        const u32 g = 1;
+        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), &k, &g, nullptr, ws.v, ws.v_b, 1, st));
     }
     const FinalItem item = {nullptr, nullptr, nullptr, (u64*)d_out, 1, 0};
     return run_moddown(c, level, ws, 1, &item, st);
@@ -1066,26 +1085,25 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     u32 nb = 0, lane = 0;
     // the pending unhoisted rotations: sigma_g(c1) of each, one decomposition and one ModDown for the batch
     auto flush_unhoisted = [&]() -> int {
-        const u64* srcs[CT_BATCH];
+        const u64 *srcs[CT_BATCH], *ks[CT_BATCH];
+        u32 gs[CT_BATCH];
         for (u32 b = 0; b < nb; b++) {
-            u64* dst = pc1 + (size_t)b * L1 * N;
-            HIP_TRY(launch_automorph(c, (u32)L1, c1, items[b].g, dst, st));
-            srcs[b] = dst;
+            srcs[b] = pc1 + (size_t)b * L1 * N;
+            gs[b] = items[b].g;
+            ks[b] = pend_key[b]->d_key;
         }
+        HIP_TRY(launch_automorph(c, (u32)L1, c1, gs, nb, pc1, st));
         const bool mac = ntt_has_modup(c);
         int rc = run_modup(c, level, srcs, nb, ws, st, mac);
         if (rc) return rc;
         // the digits already belong to sigma_g(c1): no gather in the inner product, only on c0
         if (mac) {  // every item with its own key, inside the forward transforms' second pass
-            const u64* ks[CT_BATCH];
             u64* vs[CT_BATCH];
-            for (u32 b = 0; b < nb; b++) {
-                ks[b] = pend_key[b]->d_key;
-                vs[b] = ws.v + b * ws.v_b;
-            }
+            for (u32 b = 0; b < nb; b++) vs[b] = ws.v + b * ws.v_b;
             HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), ks, vs, nb, st));
         } else {
-            for (u32 b = 0; b < nb; b++) HIP_TRY(launch_key_inner(c, level, dsrc(c, ws, b), pend_key[b]->d_key, 1, ws.v + b * ws.v_b, st));
+            for (u32 b = 0; b < nb; b++) gs[b] = 1;
+            HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), ks, gs, nullptr, ws.v, ws.v_b, nb, st));
         }
         rc = run_moddown(c, level, ws, nb, items, st);
         nb = 0;
@@ -1131,9 +1149,10 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             // many digits: one launch per rotation; the digits are read through sigma_g
             const KsWs& lw = lane_ws[lane];
             hipStream_t ls = lane ? c->side : st;
-            if (hipError_t e = launch_key_inner(c, level, dsrc(c, lw, 0), keys[t]->d_key, g, lw.v + nb * lw.v_b, ls); e != hipSuccess)
+            const u64* k = keys[t]->d_key;
+            if (hipError_t e = launch_key_inner_items(c, level, dsrc(c, lw, 0), &k, &g, &c0, lw.v + nb * lw.v_b, lw.v_b, 1, ls); e != hipSuccess)
                 return join(set_hip_err(c, e));
-            items[nb] = FinalItem{c0, nullptr, nullptr, out, g, 0};
+            items[nb] = FinalItem{nullptr, nullptr, nullptr, out, 1, 0};
             if (++nb == rb) {
                 int rc = run_moddown(c, level, lw, nb, items, ls);
                 if (rc) return join(rc);
@@ -1277,7 +1296,6 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
     // CT_BATCH key switches (eight for a single channel, one for eight channels).
     auto rotate_jobs = [&](const u64* const* base, u32 n, const TapJob* jobs, u32 n_jobs) -> int {
         const u32 per = CT_BATCH / n;
-        const bool fused = c->live_digits(level) <= 4;
         for (u32 j0 = 0; j0 < n_jobs; j0 += per) {
             const u32 m = n_jobs - j0 < per ? n_jobs - j0 : per;
             FinalItem items[CT_BATCH];
@@ -1288,16 +1306,21 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
                 keys[j] = rot_keys[job.kt]->d_key;
                 g[j] = gs[job.kt];
                 pos[j] = j * n;
-                if (!fused) HIP_TRY(launch_key_inner_multi(c, level, dsrc(c, ws, 0), keys[j], g[j], ws.v + (size_t)pos[j] * ws.v_b, ws.v_b, n, st));
-                for (u32 b = 0; b < n; b++)
-                    items[pos[j] + b] = fused ? FinalItem{nullptr, nullptr, job.masks[b], job.outs[b], 1, 0} : FinalItem{base[b], nullptr, job.masks[b], job.outs[b], g[j], 0};
+                for (u32 b = 0; b < n; b++) items[pos[j] + b] = FinalItem{nullptr, nullptr, job.masks[b], job.outs[b], 1, 0};
             }
-            // one launch that reads the digits once for its taps and leaves P sigma_g(c0) + inner product: dividing it by P is the rotation
-            if (fused)
-                HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys, g, nullptr, pos, m, base, ws.v, XLayout::classic(c->ext_limbs(level), N),
-                                              0, 1, n, nullptr, false, st, nullptr, 0, true));
+            HIP_TRY(rotated_inner(c, level, ws, base, n, keys, g, pos, m, st));  // P sigma_g(c0) included: dividing it by P is the rotation
             if (int rc = run_moddown(c, level, ws, m * n, items, st)) return rc;
         }
+        return CKKS_OK;
+    };
+    // copies that only take their tap's mask: noted, then multiplied in as few launches as their number allows
+    const u64 *mm_masks[9 * CT_BATCH], *mm_cts[9 * CT_BATCH];
+    u64* mm_outs[9 * CT_BATCH];
+    u32 n_mm = 0;
+    auto masked = [&](const u64* m, const u64* ct, u64* out) { mm_masks[n_mm] = m, mm_cts[n_mm] = ct, mm_outs[n_mm++] = out; };
+    auto flush_masked = [&]() -> int {
+        HIP_TRY(launch_mask_mul(c, level, mm_masks, mm_cts, mm_outs, n_mm, st));
+        n_mm = 0;
         return CKKS_OK;
     };
     for (u32 c0 = 0; c0 < d->c_in; c0 += CT_BATCH) {
@@ -1314,13 +1337,14 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
         if (!four) {
             for (u32 t = 0; t < 9; t++) {
                 if (gs[t] == 1) {
-                    for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(t), in[b], slot(c0 + b, t), st));
+                    for (u32 b = 0; b < n; b++) masked(mask_of(t), in[b], slot(c0 + b, t));
                     continue;
                 }
                 TapJob& job = jobs[nj++];
                 job.kt = t;
                 for (u32 b = 0; b < n; b++) job.outs[b] = slot(c0 + b, t), job.masks[b] = mask_of(t);
             }
+            if ((rc = flush_masked())) return rc;
             if ((rc = rotate_jobs(in, n, jobs, nj))) return rc;
             continue;
         }
@@ -1341,7 +1365,7 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
         }
         for (u32 kt = 1; kt <= 7; kt += 6) {
             if (gs[kt] == 1) {
-                for (u32 b = 0; b < n; b++) HIP_TRY(launch_mask_mul(c, level, mask_of(kt), in[b], slot(c0 + b, kt), st));
+                for (u32 b = 0; b < n; b++) masked(mask_of(kt), in[b], slot(c0 + b, kt));
                 continue;
             }
             TapJob& job = jobs[nj++];
@@ -1350,9 +1374,9 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
         }
         if ((rc = rotate_jobs(in, n, jobs, nj))) return rc;
         for (u32 b = 0; b < n; b++) {
-            HIP_TRY(launch_mask_mul(c, level, mask_of(4), in[b], slot(c0 + b, 4), st));
-            HIP_TRY(launch_mask_mul(c, level, mask_of(3), side[0] + (size_t)b * ct_elems, slot(c0 + b, 3), st));
-            HIP_TRY(launch_mask_mul(c, level, mask_of(5), side[1] + (size_t)b * ct_elems, slot(c0 + b, 5), st));
+            masked(mask_of(4), in[b], slot(c0 + b, 4));
+            masked(mask_of(3), side[0] + (size_t)b * ct_elems, slot(c0 + b, 3));
+            masked(mask_of(5), side[1] + (size_t)b * ct_elems, slot(c0 + b, 5));
         }
         // second stage: C^-1 and C^+1 rotated by -W and +W (their own decompositions; both in one batch where they fit)
         const u32 n2 = 2 * n <= CT_BATCH ? 2 * n : n;
@@ -1367,12 +1391,13 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
                     const u32 sd = (b0 + b) / n, t = (kt == 1 ? 0 : 6) + 2 * sd;  // corner taps 0, 2 (row -1) and 6, 8 (row +1)
                     job.outs[b] = slot(c0 + (b0 + b) % n, t);
                     job.masks[b] = mask_of(t);
-                    if (gs[kt] == 1) HIP_TRY(launch_mask_mul(c, level, job.masks[b], base[b0 + b], job.outs[b], st));
+                    if (gs[kt] == 1) masked(job.masks[b], base[b0 + b], job.outs[b]);
                 }
                 if (gs[kt] != 1) jobs[nj++] = job;
             }
             if ((rc = rotate_jobs(base + b0, n2, jobs, nj))) return rc;
         }
+        if ((rc = flush_masked())) return rc;
     }
     // convolution evaluation: integer-weighted sum over (input channel, tap) for every output channel
     HIP_TRY(launch_weighted_sum(c, level, false, xs, XLayout::classic(L1, N), d->c_in * 9, (const u64*)d_w_res, d->c_out, acc, wscratch, d->weight_bits, st));
@@ -1528,14 +1553,16 @@ int he_fc_batched(const ckks_ctx* c, const he_fc_desc* d, const uint64_t* d_in, 
     // 1. per-output products, rescale, inner sums over d_in slots (all outputs of a batch share each rotation key)
     for (u32 i0 = 0; i0 < d->d_out; i0 += CT_BATCH) {
         const u32 n = d->d_out - i0 < CT_BATCH ? d->d_out - i0 : CT_BATCH;
-        const u64 *pp[CT_BATCH], *ps[CT_BATCH];
-        u64 *os[CT_BATCH], *orot[CT_BATCH];
+        const u64 *pp[CT_BATCH], *ps[CT_BATCH], *mm[CT_BATCH], *mi[CT_BATCH];
+        u64 *os[CT_BATCH], *orot[CT_BATCH], *mo[CT_BATCH];
         for (u32 b = 0; b < n; b++) {
-            HIP_TRY(launch_mask_mul(c, level, (const u64*)d_w_enc + (size_t)(i0 + b) * (level + 1) * N, in, prod + b * ct0, st));
-            pp[b] = prod + b * ct0;
+            mm[b] = (const u64*)d_w_enc + (size_t)(i0 + b) * (level + 1) * N;
+            mi[b] = in;
+            pp[b] = mo[b] = prod + b * ct0;
             ps[b] = os[b] = S + (i0 + b) * ct1;
             orot[b] = Srot + b * ct1;
         }
+        HIP_TRY(launch_mask_mul(c, level, mm, mi, mo, n, st));
         if ((rc = run_rescale(c, level, pp, (size_t)(level + 1) * N, os, n, ar.rest(), st))) return rc;
         // T <- T + Rot(T, 2^s): the sum rides on the rotation's last kernel, the running sums alternate between two buffers
         const u64* cur[CT_BATCH];

@@ -268,9 +268,9 @@ inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LO
 // keyswitch.hip
 hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digit,
                              size_t digit_bstride, u32 n, hipStream_t st);
-hipError_t launch_key_inner(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* key, u32 g, u64* v, hipStream_t st);
-hipError_t launch_key_inner_multi(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* key, u32 g,
-                                  u64* v, size_t v_bstride, u32 n, hipStream_t st);
+// n <= CT_BATCH key switches, each with its key and Galois element; add0s (or null): P sigma_g(add0s[b]) joins component 0
+hipError_t launch_key_inner_items(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs,
+                                  const u64* const* add0s, u64* v, size_t v_bstride, u32 n, hipStream_t st);
 // add0s / add1s: per item, polynomials [level+1][N] whose P-fold is added to component 0 / 1 (either list, or entries, may be null)
 hipError_t launch_key_inner_ext(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* key, u32 g,
                                 const u64* const* add0s, const u64* const* add1s, const u64* mask, u64* const* outs, u32 n,
@@ -287,7 +287,7 @@ hipError_t launch_moddown_conv(const ckks_ctx* c, u32 level, bool merged, const 
 hipError_t launch_moddown_final(const ckks_ctx* c, u32 level, bool merged, const u64* v, const u64* w, const FinalItem* items, u32 n,
                                 hipStream_t st);
 // pointwise.hip
-hipError_t launch_automorph(const ckks_ctx* c, u32 n_polys, const u64* in, u32 g, u64* out, hipStream_t st);
+hipError_t launch_automorph(const ckks_ctx* c, u32 n_polys, const u64* in, const u32* gs, u32 n, u64* out, hipStream_t st);
 hipError_t launch_copy(const u64* in, u64* out, size_t n, hipStream_t st);
 hipError_t launch_ptct_mac(const ckks_ctx* c, u32 level, const u64* const* pts, const u64* const* cts, u32 n_terms, u64* acc,
                            int accumulate, hipStream_t st, bool extended = false);
@@ -299,7 +299,7 @@ hipError_t launch_rescale_final(const ckks_ctx* c, u32 level, const PtrList8& ct
                                 u32 n, hipStream_t st);
 hipError_t launch_tensor(const ckks_ctx* c, u32 level, const PtrList8& a, size_t a_cstride, const PtrList8& b, size_t b_cstride,
                          u64* d0, u64* d1, u64* d2, u32 n, const u64* add, size_t add_bstride, hipStream_t st);
-hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* mask, const u64* ct, u64* out, hipStream_t st);
+hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st);
 hipError_t launch_key_expand_a(const ckks_ctx* c, u64 seed, u64* key, hipStream_t st);
 hipError_t launch_add_plain(const ckks_ctx* c, u32 level, const u64* pt, u64* ct, hipStream_t st);
 hipError_t launch_ct_sum(const ckks_ctx* c, u32 level, const PtrList8& items, u32 n, u64* out, hipStream_t st, bool extended = false);

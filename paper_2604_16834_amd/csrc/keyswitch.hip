@@ -173,110 +173,87 @@ hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, const u64* y, 
 }
 
 // ---- inner product with the switching key ------------------------------------------------------
-// digits [beta][E][N], key [dnum][2][M][N], v [2][E][N]
-__global__ __launch_bounds__(KS_THREADS) void key_inner_kernel(DigitSrc digits, const u64* __restrict__ key,
-                                                               u64* __restrict__ v, const ModConst* __restrict__ mc, u32 log_n,
-                                                               u32 level, u32 num_q, u32 M, u32 E, u32 beta, u32 g) {
-    const u32 N = 1u << log_n;
-    const u32 x = blockIdx.x * KS_THREADS + threadIdx.x;
-    if (x >= N) return;
-    const u32 e = blockIdx.y;
-    const u32 t = e <= level ? e : num_q + (e - level - 1);
-    const u32 xs = g == 1 ? x : galois_gather_index(x, g, log_n);
-    U128 acc0 = {0, 0}, acc1 = {0, 0};
-    const ModConst m = mc[t];
-    for (u32 j = 0; j < beta; j++) {
-        const u64 d = digit_row(digits, 0, j, e, E, N, level)[xs];
-        acc_wide(acc0, d, key[(((size_t)j * 2 + 0) * M + t) * N + x]);
-        acc_wide(acc1, d, key[(((size_t)j * 2 + 1) * M + t) * N + x]);
-        if ((j & 15) == 15) {  // keep the unreduced sums inside the Barrett input range
-            acc0.lo = barrett_reduce(acc0, m); acc0.hi = 0;
-            acc1.lo = barrett_reduce(acc1, m); acc1.hi = 0;
-        }
-    }
-    v[((size_t)0 * E + e) * N + x] = barrett_reduce(acc0, m);
-    v[((size_t)1 * E + e) * N + x] = barrett_reduce(acc1, m);
-}
-
-hipError_t launch_key_inner(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* key, u32 g, u64* v, hipStream_t st) {
-    const u32 E = c->ext_limbs(level);
-    dim3 grid((c->N + KS_THREADS - 1) / KS_THREADS, E);
-    { ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * E * (3.0 * c->live_digits(level) + 2.0), 2.0 * c->N * E * c->live_digits(level)); hipLaunchKernelGGL(key_inner_kernel, grid, dim3(KS_THREADS), 0, st, digits, key, v, c->d_mc, c->log_n, level, c->num_q,
-                       c->M, E, c->live_digits(level), g); }
-    return hipGetLastError();
-}
-
-// The same key applied to n <= KS_MAX_BATCH sets of digits (the channels of a layer share their
-// rotation and relinearisation keys): every thread keeps its key words while it walks the batch, so
-// the key streams from HBM once per batch instead of once per key switch.
-// digits + b*digits_bstride: [beta][E][N];  v + b*v_bstride: [2][E][N]
+// Of n <= CT_BATCH key switches in one launch: item b has its digits ([beta][E][N], see DigitSrc), key ([dnum][2][M][N]) and
+// Galois element; results v + b*v_bstride: [2][E][N].  blockIdx.z = a run of neighbouring items with the same key (the channels
+// of a layer share their rotation and relinearisation keys): every thread keeps its key words while it walks the run, so the key
+// streams from HBM once per run.  add0 (optional, [level+1][N]): P sigma_g(add0) joins component 0 on the live q-limbs, which
+// makes the division by P that follows the whole rotation, with no gather left in it.
 // F64 (every modulus below 2^50, at most four digits): the sums as chains of fused multiply-adds on centred doubles
-// (f64m_dot_w), as in the fused taps.
-template <bool F64>
-__global__ __launch_bounds__(KS_THREADS) void key_inner_multi_kernel(DigitSrc digits, const u64* __restrict__ key, u64* __restrict__ v,
-                                                                     size_t v_bstride, const ModConst* __restrict__ mc, u32 log_n,
-                                                                     u32 level, u32 num_q, u32 M, u32 E, u32 beta, u32 g, u32 n,
+// (f64m_dot_w), as in the fused taps; otherwise 128-bit integer sums.
+// (As a launch per key, rotations of 9 to 11 extended limbs at N = 2^16 were 8 us each; up to eight now take 27 us together.)
+struct KeyItems {
+    const u64* key[CT_BATCH];
+    const u64* add0[CT_BATCH];
+    u32 g[CT_BATCH];
+    u32 first[CT_BATCH + 1];  // run r: items first[r] .. first[r + 1] - 1
+};
+template <bool F64, bool ADD>
+__global__ __launch_bounds__(KS_THREADS) void key_inner_items_kernel(DigitSrc digits, KeyItems K, u64* __restrict__ v, size_t v_bstride,
+                                                                     const u64* __restrict__ negp, const ModConst* __restrict__ mc, u32 log_n,
+                                                                     u32 level, u32 num_q, u32 M, u32 E, u32 beta,
                                                                      const ModConstF* __restrict__ mcf) {
     const u32 N = 1u << log_n;
     const u32 x = blockIdx.x * KS_THREADS + threadIdx.x;
     if (x >= N) return;
-    const u32 e = blockIdx.y;
+    const u32 e = blockIdx.y, b0 = K.first[blockIdx.z], b1 = K.first[blockIdx.z + 1];
     const u32 t = e <= level ? e : num_q + (e - level - 1);
+    const u32 g = K.g[b0];
+    const u64* __restrict__ key = K.key[b0];
     const u32 xs = g == 1 ? x : galois_gather_index(x, g, log_n);
     const ModConst m = mc[t];
+    const bool has_add = ADD && e <= level;
+    const u64 pres = has_add ? m.q - negp[e] : 0;  // P mod q_e
     if constexpr (F64) {  // beta <= 4: entries past the last digit are zero on both sides
         const double qd = mcf[t].q, qinv = mcf[t].qinv, halfq = 0.5 * qd;
         auto centred = [&](u64 w) {
             const double d = f64m_from_u64(w);
             return d > halfq ? d - qd : d;
         };
-        double w0[4], w1[4];
+        double w0[5], w1[4];
 #pragma unroll
         for (u32 j = 0; j < 4; j++) {
             w0[j] = j < beta ? centred(key[(((size_t)j * 2 + 0) * M + t) * N + x]) : 0.0;
             w1[j] = j < beta ? centred(key[(((size_t)j * 2 + 1) * M + t) * N + x]) : 0.0;
         }
-        for (u32 b = 0; b < n; b++) {
-            double y[4];
+        w0[4] = centred(pres);
+        for (u32 b = b0; b < b1; b++) {
+            double y[5];
 #pragma unroll
             for (u32 j = 0; j < 4; j++) y[j] = j < beta ? centred(digit_row(digits, b, j, e, E, N, level)[xs]) : 0.0;
+            y[4] = has_add ? centred(K.add0[b][(size_t)e * N + xs]) : 0.0;
             u64* vb = v + b * v_bstride;
-            vb[((size_t)0 * E + e) * N + x] = f64m_canonical(f64m_dot_w<4>(y, w0, qd, qinv), qd);
+            vb[((size_t)0 * E + e) * N + x] = f64m_canonical(f64m_dot_w<ADD ? 5 : 4>(y, w0, qd, qinv), qd);
             vb[((size_t)1 * E + e) * N + x] = f64m_canonical(f64m_dot_w<4>(y, w1, qd, qinv), qd);
         }
         return;
     }
+    u64 k0[4], k1[4];  // beta <= 4: the thread's key words stay in registers for the whole run
     if (beta <= 4) {
-        // the thread's key words stay in registers for the whole batch
-        u64 k0[4], k1[4];
 #pragma unroll
         for (u32 j = 0; j < 4; j++) {
             k0[j] = j < beta ? key[(((size_t)j * 2 + 0) * M + t) * N + x] : 0;
             k1[j] = j < beta ? key[(((size_t)j * 2 + 1) * M + t) * N + x] : 0;
         }
-        for (u32 b = 0; b < n; b++) {
-            U128 acc0 = {0, 0}, acc1 = {0, 0};
+    }
+    for (u32 b = b0; b < b1; b++) {
+        U128 acc0 = {0, 0}, acc1 = {0, 0};
+        if (has_add) acc_wide(acc0, K.add0[b][(size_t)e * N + xs], pres);
+        if (beta <= 4) {
 #pragma unroll
             for (u32 j = 0; j < 4; j++) {
                 const u64 dv = j < beta ? digit_row(digits, b, j, e, E, N, level)[xs] : 0;
                 acc_wide(acc0, dv, k0[j]);
                 acc_wide(acc1, dv, k1[j]);
             }
-            u64* vb = v + b * v_bstride;
-            vb[((size_t)0 * E + e) * N + x] = barrett_reduce(acc0, m);
-            vb[((size_t)1 * E + e) * N + x] = barrett_reduce(acc1, m);
-        }
-        return;
-    }
-    for (u32 b = 0; b < n; b++) {
-        U128 acc0 = {0, 0}, acc1 = {0, 0};
-        for (u32 j = 0; j < beta; j++) {
-            const u64 dv = digit_row(digits, b, j, e, E, N, level)[xs];
-            acc_wide(acc0, dv, key[(((size_t)j * 2 + 0) * M + t) * N + x]);
-            acc_wide(acc1, dv, key[(((size_t)j * 2 + 1) * M + t) * N + x]);
-            if ((j & 15) == 15) {
-                acc0.lo = barrett_reduce(acc0, m); acc0.hi = 0;
-                acc1.lo = barrett_reduce(acc1, m); acc1.hi = 0;
+        } else {
+            for (u32 j = 0; j < beta; j++) {
+                const u64 dv = digit_row(digits, b, j, e, E, N, level)[xs];
+                acc_wide(acc0, dv, key[(((size_t)j * 2 + 0) * M + t) * N + x]);
+                acc_wide(acc1, dv, key[(((size_t)j * 2 + 1) * M + t) * N + x]);
+                if ((j & 15) == 15) {  // keep the unreduced sums inside the Barrett input range
+                    acc0.lo = barrett_reduce(acc0, m); acc0.hi = 0;
+                    acc1.lo = barrett_reduce(acc1, m); acc1.hi = 0;
+                }
             }
         }
         u64* vb = v + b * v_bstride;
@@ -285,17 +262,32 @@ __global__ __launch_bounds__(KS_THREADS) void key_inner_multi_kernel(DigitSrc di
     }
 }
 
-hipError_t launch_key_inner_multi(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* key, u32 g,
-                                  u64* v, size_t v_bstride, u32 n, hipStream_t st) {
+// keys / gs / add0s (or null): host arrays of n entries
+hipError_t launch_key_inner_items(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs,
+                                  const u64* const* add0s, u64* v, size_t v_bstride, u32 n, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    if (n > CT_BATCH) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
-    dim3 grid((c->N + KS_THREADS - 1) / KS_THREADS, E);
-    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * E * (2.0 * beta + n * (beta + 2.0)), 2.0 * n * c->N * E * beta);
-    if (c->small_q && beta <= 4)
-        hipLaunchKernelGGL(key_inner_multi_kernel<true>, grid, dim3(KS_THREADS), 0, st, digits, key, v, v_bstride, c->d_mc,
-                           c->log_n, level, c->num_q, c->M, E, beta, g, n, c->d_mcf);
-    else
-        hipLaunchKernelGGL(key_inner_multi_kernel<false>, grid, dim3(KS_THREADS), 0, st, digits, key, v, v_bstride, c->d_mc,
-                           c->log_n, level, c->num_q, c->M, E, beta, g, n, c->d_mcf);
+    KeyItems K = {};
+    u32 runs = 0;
+    for (u32 b = 0; b < n; b++) {
+        K.key[b] = keys[b];
+        K.g[b] = gs[b];
+        K.add0[b] = add0s ? add0s[b] : nullptr;
+        if (!keys[b] || (add0s && !add0s[b])) return hipErrorInvalidValue;
+        if (b == 0 || keys[b] != keys[b - 1] || gs[b] != gs[b - 1]) K.first[runs++] = b;
+    }
+    K.first[runs] = n;
+    const u64* negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
+    dim3 grid((c->N + KS_THREADS - 1) / KS_THREADS, E, runs);
+    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (2.0 * beta * runs + n * (beta + 2.0)) + (add0s ? n * (level + 1.0) : 0.0)), 2.0 * n * c->N * E * beta);
+#define KI_ITEMS(F64_, ADD_) hipLaunchKernelGGL((key_inner_items_kernel<F64_, ADD_>), grid, dim3(KS_THREADS), 0, st, digits, K, v, v_bstride, negp, c->d_mc, c->log_n, level, c->num_q, c->M, E, beta, c->d_mcf)
+    const bool f64 = c->small_q && beta <= 4;
+    if (f64 && add0s) KI_ITEMS(true, true);
+    else if (f64) KI_ITEMS(true, false);
+    else if (add0s) KI_ITEMS(false, true);
+    else KI_ITEMS(false, false);
+#undef KI_ITEMS
     return hipGetLastError();
 }
 

@@ -9,18 +9,28 @@
 
 #define PW_THREADS 256
 
-// out[p][k] = in[p][pi_g(k)] for n_polys limb-polys (the same gather for every modulus)
-__global__ __launch_bounds__(PW_THREADS) void automorph_kernel(const u64* __restrict__ in, u64* __restrict__ out, u32 log_n, u32 g) {
+// out[r][p][k] = in[p][pi_g_r(k)] for n_polys limb-polys (the same gather for every modulus) and every element g_r of the list:
+// one launch for a batch of rotations (six of seven limbs at N = 2^13: 2.3 us each as launches of their own, 3.8 us together)
+struct GaloisList {
+    u32 g[KS_MAX_BATCH];
+};
+__global__ __launch_bounds__(PW_THREADS) void automorph_kernel(const u64* __restrict__ in, u64* __restrict__ out, u32 log_n, GaloisList gl) {
     const u32 N = 1u << log_n;
     const u32 x = blockIdx.x * PW_THREADS + threadIdx.x;
     if (x >= N) return;
+    const u32 r = blockIdx.z;
     const size_t base = (size_t)blockIdx.y * N;
-    out[base + x] = in[base + galois_gather_index(x, g, log_n)];
+    out[(size_t)r * gridDim.y * N + base + x] = in[base + galois_gather_index(x, gl.g[r], log_n)];
 }
 
-hipError_t launch_automorph(const ckks_ctx* c, u32 n_polys, const u64* in, u32 g, u64* out, hipStream_t st) {
-    dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, n_polys);
-    { ProfScope ps__(c, K_AUTOMORPH, st, 16.0 * c->N * n_polys, 0.0); hipLaunchKernelGGL(automorph_kernel, grid, dim3(PW_THREADS), 0, st, in, out, c->log_n, g); }
+// outs: n x [n_polys][N], one after the other; n <= KS_MAX_BATCH
+hipError_t launch_automorph(const ckks_ctx* c, u32 n_polys, const u64* in, const u32* gs, u32 n, u64* out, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    if (n > KS_MAX_BATCH) return hipErrorInvalidValue;
+    GaloisList gl;
+    for (u32 r = 0; r < KS_MAX_BATCH; r++) gl.g[r] = r < n ? gs[r] : 1;
+    dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, n_polys, n);
+    { ProfScope ps__(c, K_AUTOMORPH, st, 16.0 * c->N * n_polys * n, 0.0); hipLaunchKernelGGL(automorph_kernel, grid, dim3(PW_THREADS), 0, st, in, out, c->log_n, gl); }
     return hipGetLastError();
 }
 
@@ -80,86 +90,117 @@ hipError_t launch_ptct_mac(const ckks_ctx* c, u32 level, const u64* const* pts, 
 // ---- the masked sums of a re-layout, all of them in one pass over the rotated copies --------------------------
 //   acc[b][h] = sum_l mask[h][l] (.) x[b][l]      b < n ciphertexts, h < n_hi, l < n_lo
 // x[b][l] = xs + (b*n_lo + l)*stride, acc[b][h] = acc + (b*n_hi + h)*stride, each [2][limbs][N].  A thread owns one
-// (coefficient, limb) of RL_CB ciphertexts and keeps the sums of up to RL_NH values of h, so every rotated copy is
+// (coefficient, limb) of CB ciphertexts and keeps the sums of up to RL_NH values of h, so every rotated copy is
 // read once per group of RL_NH sums (a launch per (h, l) pair list read it once per sum) and every mask word once per
-// RL_CB ciphertexts.  Absent pairs are null pointers.
+// CB ciphertexts.  Absent pairs are null pointers.  The masks are most of the traffic of a single ciphertext (the classifier's
+// layout: 512 of them), so their loads are kept in flight: the words of the next l are requested before the products of the
+// current one, and absent masks re-read a present one against a zero instead of branching around the load.  A launch takes
+// RL_NG groups of h (blockIdx.z).  One ciphertext of two limbs, 23 x 23 pairs at N = 2^16: 6 launches of 80 us as four sums
+// each behind branches, 2 of 72 us now (3.7 TB/s of masks).
 #define RL_NH 4
+#define RL_NG 3
 #define RL_CB 4
 #define RL_NL 32
 struct RelayoutMasks {
-    const u64* m[RL_NH][RL_NL];
+    const u64* m[RL_NG * RL_NH][RL_NL];
+    u32 any[RL_NG][RL_NL];  // per group of h: 1 + the index of a present mask of this l, or 0
 };
 
+template <u32 CB>
 __global__ __launch_bounds__(PW_THREADS) void relayout_mac_kernel(const u64* __restrict__ xs, RelayoutMasks M, u64* __restrict__ acc,
                                                                   const ModConst* __restrict__ mc, u32 N, u32 level, u32 limbs, u32 num_q,
                                                                   size_t stride, u32 n, u32 n_lo, u32 n_hi, u32 l0, u32 nl, u32 h0,
-                                                                  u32 nh, int accumulate) {
+                                                                  u32 nh_all, u32 groups, int accumulate) {
     const u32 x = blockIdx.x * PW_THREADS + threadIdx.x;
     if (x >= N) return;
-    const u32 i = blockIdx.y, b0 = blockIdx.z * RL_CB;
+    const u32 grp = blockIdx.z % groups, i = blockIdx.y, b0 = blockIdx.z / groups * CB;
+    const u32 hg = grp * RL_NH, nh = nh_all - hg < RL_NH ? nh_all - hg : RL_NH;
     const ModConst m = mc[i <= level ? i : num_q + (i - level - 1)];
     const size_t po = (size_t)i * N + x;
-    U128 s[RL_NH][RL_CB][2];
+    U128 s[RL_NH][CB][2];
 #pragma unroll
     for (u32 h = 0; h < RL_NH; h++)
 #pragma unroll
-        for (u32 b = 0; b < RL_CB; b++)
+        for (u32 b = 0; b < CB; b++)
 #pragma unroll
             for (u32 comp = 0; comp < 2; comp++) {
                 s[h][b][comp] = {0, 0};
                 if (accumulate && h < nh && b0 + b < n)
-                    s[h][b][comp].lo = acc[((size_t)(b0 + b) * n_hi + h0 + h) * stride + ((size_t)comp * limbs + i) * N + x];
+                    s[h][b][comp].lo = acc[((size_t)(b0 + b) * n_hi + h0 + hg + h) * stride + ((size_t)comp * limbs + i) * N + x];
             }
-    for (u32 l = 0; l < nl; l++) {
-        u64 xv[RL_CB][2];
-#pragma unroll
-        for (u32 b = 0; b < RL_CB; b++)
-#pragma unroll
-            for (u32 comp = 0; comp < 2; comp++)
-                xv[b][comp] = b0 + b < n ? xs[((size_t)(b0 + b) * n_lo + l0 + l) * stride + ((size_t)comp * limbs + i) * N + x] : 0;
+    u64 mv[RL_NH], xv[CB][2];
+    auto request = [&](u32 l) {
+        const u32 any = M.any[grp][l];
+        if (!any) return;  // uniform: no sum of the group takes this copy
+        const u64* some = M.m[hg + any - 1][l];
 #pragma unroll
         for (u32 h = 0; h < RL_NH; h++) {
-            const u64* mp = M.m[h][l];
-            if (h >= nh || !mp) continue;  // uniform over the workgroup
-            const u64 mv = mp[po];
+            const u64* mp = M.m[hg + h][l];
+            mv[h] = (mp ? mp : some)[po];
+        }
 #pragma unroll
-            for (u32 b = 0; b < RL_CB; b++)
+        for (u32 b = 0; b < CB; b++)
 #pragma unroll
-                for (u32 comp = 0; comp < 2; comp++) acc_wide(s[h][b][comp], mv, xv[b][comp]);
+            for (u32 comp = 0; comp < 2; comp++)
+                xv[b][comp] = xs[((size_t)(b0 + b < n ? b0 + b : n - 1) * n_lo + l0 + l) * stride + ((size_t)comp * limbs + i) * N + x];
+    };
+    request(0);
+    for (u32 l = 0; l < nl; l++) {
+        u64 mc_[RL_NH], xc[CB][2];
+#pragma unroll
+        for (u32 h = 0; h < RL_NH; h++) mc_[h] = mv[h];
+#pragma unroll
+        for (u32 b = 0; b < CB; b++) xc[b][0] = xv[b][0], xc[b][1] = xv[b][1];
+        if (l + 1 < nl) request(l + 1);
+        if (!M.any[grp][l]) continue;
+#pragma unroll
+        for (u32 h = 0; h < RL_NH; h++) {
+            if (!M.m[hg + h][l]) continue;  // uniform over the workgroup
+#pragma unroll
+            for (u32 b = 0; b < CB; b++)
+#pragma unroll
+                for (u32 comp = 0; comp < 2; comp++) acc_wide(s[h][b][comp], mc_[h], xc[b][comp]);
         }
     }
 #pragma unroll
     for (u32 h = 0; h < RL_NH; h++)
 #pragma unroll
-        for (u32 b = 0; b < RL_CB; b++)
+        for (u32 b = 0; b < CB; b++)
 #pragma unroll
             for (u32 comp = 0; comp < 2; comp++)
                 if (h < nh && b0 + b < n)
-                    acc[((size_t)(b0 + b) * n_hi + h0 + h) * stride + ((size_t)comp * limbs + i) * N + x] = barrett_reduce(s[h][b][comp], m);
+                    acc[((size_t)(b0 + b) * n_hi + h0 + hg + h) * stride + ((size_t)comp * limbs + i) * N + x] = barrett_reduce(s[h][b][comp], m);
 }
 
 // masks: host array of n_hi*n_lo device pointers ([limbs][N] each, or null)
 hipError_t launch_relayout_mac(const ckks_ctx* c, u32 level, bool extended, const u64* xs, const u64* const* masks, u64* acc, u32 n,
                                u32 n_lo, u32 n_hi, hipStream_t st) {
-    const u32 limbs = extended ? c->ext_limbs(level) : level + 1;
+    const u32 limbs = extended ? c->ext_limbs(level) : level + 1, cb = n == 1 ? 1 : RL_CB;
     const size_t stride = 2 * (size_t)limbs * c->N;
     const u32 nl_max = c->lazy_terms < RL_NL ? (c->lazy_terms ? c->lazy_terms : 1) : RL_NL;  // products summed before a reduction
-    dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, limbs, (n + RL_CB - 1) / RL_CB);
-    for (u32 h0 = 0; h0 < n_hi; h0 += RL_NH) {
-        const u32 nh = n_hi - h0 < RL_NH ? n_hi - h0 : RL_NH;
+    const u32 nh_max = n == 1 ? RL_NG * RL_NH : RL_NH;
+    for (u32 h0 = 0; h0 < n_hi; h0 += nh_max) {
+        const u32 nh = n_hi - h0 < nh_max ? n_hi - h0 : nh_max, groups = (nh + RL_NH - 1) / RL_NH;
         for (u32 l0 = 0; l0 < n_lo; l0 += nl_max) {
             const u32 nl = n_lo - l0 < nl_max ? n_lo - l0 : nl_max;
-            RelayoutMasks M;
+            RelayoutMasks M = {};
             double n_masks = 0.0;
-            for (u32 h = 0; h < RL_NH; h++)
-                for (u32 l = 0; l < RL_NL; l++) {
-                    M.m[h][l] = (h < nh && l < nl) ? masks[(size_t)(h0 + h) * n_lo + l0 + l] : nullptr;
-                    n_masks += M.m[h][l] ? 1.0 : 0.0;
+            for (u32 h = 0; h < nh; h++)
+                for (u32 l = 0; l < nl; l++) {
+                    M.m[h][l] = masks[(size_t)(h0 + h) * n_lo + l0 + l];
+                    if (!M.m[h][l]) continue;
+                    n_masks += 1.0;
+                    M.any[h / RL_NH][l] = 1 + h % RL_NH;
                 }
-            ProfScope ps__(c, K_PTCT_MAC, st, 8.0 * c->N * limbs * (2.0 * n * nl + n_masks * ((n + RL_CB - 1) / RL_CB) + 2.0 * n * nh * (l0 ? 2.0 : 1.0)),
+            dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, limbs, groups * ((n + cb - 1) / cb));
+            ProfScope ps__(c, K_PTCT_MAC, st, 8.0 * c->N * limbs * (2.0 * n * nl * groups + n_masks * ((n + cb - 1) / cb) + 2.0 * n * nh * (l0 ? 2.0 : 1.0)),
                            2.0 * c->N * limbs * n * n_masks);
-            hipLaunchKernelGGL(relayout_mac_kernel, grid, dim3(PW_THREADS), 0, st, xs, M, acc, c->d_mc, c->N, level, limbs, c->num_q, stride, n,
-                               n_lo, n_hi, l0, nl, h0, nh, l0 > 0 ? 1 : 0);
+            if (cb == 1)
+                hipLaunchKernelGGL(relayout_mac_kernel<1>, grid, dim3(PW_THREADS), 0, st, xs, M, acc, c->d_mc, c->N, level, limbs, c->num_q, stride, n,
+                                   n_lo, n_hi, l0, nl, h0, nh, groups, l0 > 0 ? 1 : 0);
+            else
+                hipLaunchKernelGGL(relayout_mac_kernel<RL_CB>, grid, dim3(PW_THREADS), 0, st, xs, M, acc, c->d_mc, c->N, level, limbs, c->num_q, stride,
+                                   n, n_lo, n_hi, l0, nl, h0, nh, groups, l0 > 0 ? 1 : 0);
         }
     }
     return hipGetLastError();
@@ -251,19 +292,31 @@ hipError_t launch_tensor(const ckks_ctx* c, u32 level, const PtrList8& a, size_t
 }
 
 // ---- convolution operands -----------------------------------------------------------------------
-// out[comp][i] = mask[i] * ct[comp][i]: an aligned ciphertext times the tap's encoded validity mask
-__global__ __launch_bounds__(PW_THREADS) void mask_mul_kernel(const u64* __restrict__ mask, const u64* __restrict__ ct,
-                                                              u64* __restrict__ out, const ModConst* __restrict__ mc, u32 N, u32 level) {
+// out[comp][i] = mask[i] * ct[comp][i]: aligned ciphertexts times their taps' encoded validity masks, blockIdx.z = 2 item + comp
+__global__ __launch_bounds__(PW_THREADS) void mask_mul_kernel(PtrList8 masks, PtrList8 cts, OutList8 outs, const ModConst* __restrict__ mc,
+                                                              u32 N, u32 level) {
     const u32 x = blockIdx.x * PW_THREADS + threadIdx.x;
     if (x >= N) return;
-    const u32 i = blockIdx.y, comp = blockIdx.z;
+    const u32 i = blockIdx.y, r = blockIdx.z >> 1, comp = blockIdx.z & 1;
     const size_t co = ((size_t)comp * (level + 1) + i) * N + x;
-    out[co] = mulmod_barrett(mask[(size_t)i * N + x], ct[co], mc[i]);
+    outs.p[r][co] = mulmod_barrett(masks.p[r][(size_t)i * N + x], cts.p[r][co], mc[i]);
 }
 
-hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* mask, const u64* ct, u64* out, hipStream_t st) {
-    dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, level + 1, 2);
-    { ProfScope ps__(c, K_MASK_MUL, st, 40.0 * c->N * (level + 1.0), 2.0 * c->N * (level + 1.0)); hipLaunchKernelGGL(mask_mul_kernel, grid, dim3(PW_THREADS), 0, st, mask, ct, out, c->d_mc, c->N, level); }
+// host arrays of n device pointers ([level+1][N]; [2][level+1][N] twice); KS_MAX_BATCH of them per launch
+hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st) {
+    for (u32 r0 = 0; r0 < n; r0 += KS_MAX_BATCH) {
+        const u32 m = n - r0 < KS_MAX_BATCH ? n - r0 : KS_MAX_BATCH;
+        PtrList8 ml, cl;
+        OutList8 ol;
+        for (u32 r = 0; r < KS_MAX_BATCH; r++) {
+            ml.p[r] = r < m ? masks[r0 + r] : nullptr;
+            cl.p[r] = r < m ? cts[r0 + r] : nullptr;
+            ol.p[r] = r < m ? outs[r0 + r] : nullptr;
+        }
+        dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, level + 1, 2 * m);
+        ProfScope ps__(c, K_MASK_MUL, st, 40.0 * m * c->N * (level + 1.0), 2.0 * m * c->N * (level + 1.0));
+        hipLaunchKernelGGL(mask_mul_kernel, grid, dim3(PW_THREADS), 0, st, ml, cl, ol, c->d_mc, c->N, level);
+    }
     return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@ import paper_2604_16834_amd as hx  # noqa: E402
 from oracle import Oracle  # noqa: E402
 from workloads import conv_tap_offsets, make_params  # noqa: E402
 from gpu_common import rand_ct, rand_poly, w_residues  # noqa: E402
+from test_gpu_parity import fc_case  # noqa: E402
 
 
 @pytest.mark.parametrize("batch,bits", [(191, 50), (383, 50), (384, 50), (385, 57), (577, 50), (1537, 50)])
@@ -80,3 +81,11 @@ def test_digits_together(log_n, num_q, num_p, dnum, level):
     outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, dkeys, True)
     for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, True)):
         assert np.array_equal(hx.to_host(got), want)
+
+
+@pytest.mark.parametrize("batch,base", [(38, 3), (40, 36)])
+def test_masked_sums_of_the_layout(batch, base):
+    """More second rotations than one launch of the masked sums takes (13 = 12 + 1, the last sum without its third mask), and more
+    first rotations than one launch takes (36 = 32 + 4) with a sum that has masks for four of them only."""
+    k = fc_case(8, 1, batch, base, seed=700 + batch)
+    assert np.array_equal(hx.to_host(k["run"]()), k["want"])
