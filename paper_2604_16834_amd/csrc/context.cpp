@@ -20,6 +20,12 @@ static u64 h_powmod(u64 a, u64 e, u64 q) {
 }
 static u64 h_invmod(u64 a, u64 q) { return h_powmod(a, q - 2, q); }
 static u64 h_shoup(u64 w, u64 q) { return (u64)(((u128)w << 64) / q); }
+// a constant multiplier of the double-precision routines: the centred representative (f64m_dot takes centred operands, the
+// butterflies count on |w| < q/2, see f64mod.h) and its quotient by the modulus
+static TwF centred_twf(u64 w, u64 q) {
+    const double v = w > (q >> 1) ? -(double)(q - w) : (double)w;
+    return TwF{v, v / (double)q};
+}
 static u32 h_bits(u64 v) { u32 b = 0; while (v) { b++; v >>= 1; } return b; }
 static u32 h_bitrev(u32 x, u32 bits) {
     u32 r = 0;
@@ -153,8 +159,8 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
         if (c->small_q) {  // every value below is an integer below 2^50: exact as a double; the quotients are correctly rounded
             mcf[t].q = (double)q;
             mcf[t].qinv = 1.0 / (double)q;
-            mcf[t].ninv = (double)m.n_inv;
-            mcf[t].ninv_q = (double)m.n_inv / (double)q;
+            mcf[t].ninv = centred_twf(m.n_inv, q).w;
+            mcf[t].ninv_q = centred_twf(m.n_inv, q).wq;
         }
         std::vector<u64> pw(N);
         pw[0] = 1;
@@ -167,8 +173,8 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
             const u32 r = h_bitrev(i, p->log_n);
             const size_t o = (size_t)t * N + i;
             if (c->ntt_f64) {
-                twf[o].w = (double)pw[r]; twf[o].wq = (double)pw[r] / (double)q;
-                itwf[o].w = (double)ipw[r]; itwf[o].wq = (double)ipw[r] / (double)q;
+                twf[o] = centred_twf(pw[r], q);
+                itwf[o] = centred_twf(ipw[r], q);
             } else {
                 tw[o].w = pw[r]; tw[o].s = h_shoup(pw[r], q);
                 itw[o].w = ipw[r]; itw[o].s = h_shoup(ipw[r], q);
@@ -288,12 +294,7 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
             }
         }
     }
-    // the conversion constants as doubles for the double-precision conversions: the centred representative (f64m_dot takes
-    // centred operands) and its quotient by the target modulus
-    auto centred = [](u64 w, u64 q) {
-        const double v = w > (q >> 1) ? -(double)(q - w) : (double)w;
-        return TwF{v, v / (double)q};
-    };
+    // the conversion constants as doubles for the double-precision conversions
     std::vector<TwF> modup_f, modup_prep_f, moddown_f, moddown_rs_f, moddown_prep_f, moddown_rs_prep_f, rescale_prep_f, rescale_conv_f;
     if (c->dnum && c->ntt_f64) {
         const u32 nq = c->num_q;
@@ -305,7 +306,7 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
                 for (u32 e = 0; e < c->ext_limbs(level); e++) {
                     const u64 qt = c->mod[c->ext_modulus(level, e)];
                     for (u32 a = 0; a < c->alpha_pad; a++)
-                        tf[(size_t)e * c->alpha_pad + a] = centred(tab[2 * c->alpha_pad + (size_t)e * c->alpha_pad + a], qt);
+                        tf[(size_t)e * c->alpha_pad + a] = centred_twf(tab[2 * c->alpha_pad + (size_t)e * c->alpha_pad + a], qt);
                 }
             }
         modup_prep_f.assign((size_t)nq * nq, TwF{0.0, 0.0});
@@ -314,22 +315,19 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
                 const u64* tab = modup.data() + level * c->modup_level_stride() + j * c->modup_digit_stride();
                 for (u32 i = c->digit_lo(j); i < c->digit_hi(j, level); i++) {
                     const u64 qi = c->mod[i];
-                    const double w = (double)h_mulmod(tab[i - c->digit_lo(j)], c->mc[i].n_inv, qi);
-                    modup_prep_f[(size_t)level * nq + i] = TwF{w, w / (double)qi};
+                    modup_prep_f[(size_t)level * nq + i] = centred_twf(h_mulmod(tab[i - c->digit_lo(j)], c->mc[i].n_inv, qi), qi);
                 }
             }
         moddown_f.assign((size_t)nq * c->k_pad, TwF{0.0, 0.0});
         for (u32 i = 0; i < nq; i++)
-            for (u32 a = 0; a < c->k_pad; a++) moddown_f[(size_t)i * c->k_pad + a] = centred(moddown[2 * c->k_pad + (size_t)i * c->k_pad + a], c->mod[i]);
+            for (u32 a = 0; a < c->k_pad; a++) moddown_f[(size_t)i * c->k_pad + a] = centred_twf(moddown[2 * c->k_pad + (size_t)i * c->k_pad + a], c->mod[i]);
         // what the inverse transform in front of ModDown scales a dropped limb by: 1/N times the limb's conversion constant
         auto prep = [&](u64 inv, u32 m) {
-            const u64 q = c->mod[m];
-            const double w = (double)h_mulmod(inv, c->mc[m].n_inv, q);
-            return TwF{w, w / (double)q};
+            return centred_twf(h_mulmod(inv, c->mc[m].n_inv, c->mod[m]), c->mod[m]);
         };
         // the rescale as a one-limb conversion: the inverse transform scales by 1/N only, the conversion constant is 1
         rescale_prep_f.assign(M, TwF{0.0, 0.0});
-        for (u32 m = 0; m < M; m++) rescale_prep_f[m] = TwF{(double)c->mc[m].n_inv, (double)c->mc[m].n_inv / (double)c->mod[m]};
+        for (u32 m = 0; m < M; m++) rescale_prep_f[m] = centred_twf(c->mc[m].n_inv, c->mod[m]);
         rescale_conv_f.assign((size_t)nq * 4, TwF{0.0, 0.0});
         for (u32 i = 0; i < nq; i++) rescale_conv_f[(size_t)i * 4] = TwF{1.0, 1.0 / (double)c->mod[i]};
         moddown_prep_f.assign(M, TwF{0.0, 0.0});
@@ -345,7 +343,7 @@ extern "C" int ckks_ctx_create(const ckks_params* p, ckks_ctx** out) {
             const u64* tab = moddown_rs.data() + l * c->moddown_rs_stride();
             for (u32 i = 0; i < l; i++)
                 for (u32 a = 0; a < c->k2_pad; a++)
-                    moddown_rs_f[((size_t)l * nq + i) * c->k2_pad + a] = centred(tab[2 * c->k2_pad + (size_t)i * c->k2_pad + a], c->mod[i]);
+                    moddown_rs_f[((size_t)l * nq + i) * c->k2_pad + a] = centred_twf(tab[2 * c->k2_pad + (size_t)i * c->k2_pad + a], c->mod[i]);
         }
     }
     // rescale table [l][i] = (q_l^-1 mod q_i, Shoup companion, q_l mod q_i)

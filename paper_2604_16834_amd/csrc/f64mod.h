@@ -16,8 +16,22 @@
 //   mulmod_any  |y| < q,    0 <= w < q, qinv = 1 / q rounded to nearest ->  |result| <= (1/2 + |y| / 2^52) q  < 3/4 q
 //   reduce      |v| < 2^53                                              ->  |result| <= q/2 + 1
 // (for reduced multiplicands, |y| <= q/2 + 1: below 0.57 q and 0.63 q).  h - c q is an integer below 2^51 and l one below
-// 2^48, so the last two operations are exact.  A sum of up to eight products stays below 2^53 and is exact, and three
-// forward butterfly stages after a reduce keep every multiplicand below 2q + 1 < 2^51.
+// 2^48, so the last two operations are exact.  A sum of up to eight products stays below 2^53 and is exact.
+//
+// The butterflies' multipliers are CENTRED, |w| <= (q - 1) / 2.  The quotient of |y| <= Y q is then at most Y q / 2, below
+// 2^51 up to Y = 4, and half as far off:
+//   mulmod      |y| <= Y q, Y <= 4, |w| < q/2   ->  |result| <= (1/2 + Y/16) q
+//   mulmod_any  |y| <= Y q, Y <= 4, |w| < q/2   ->  |result| <= (1/2 + Y/8) q
+// and h - c q stays below 2^51, so a transform needs far fewer reductions than one per output and round.  In units of q, with
+// t the product of a stage:
+//   forward round of three stages, x +- t on the left half after a reduce of the four left values (f64m_fwd_begin), inputs
+//     up to B <= 3.9:  1 + B/8, then 1.63 + 0.15 B, then 2.33 + 0.16 B  (2.8 from 2.8: rounds follow each other with no other
+//     reduction); without the first reduce, from 1 (canonical residues): 1.63, 2.33, 3.13.  Two more stages from 2.8: 3.7, 4.6.
+//   inverse round of three stages, sums and differences: the sums of the first stage are reduced (f64m_inv_mid); from inputs
+//     up to 1.72 the differences that are multiplied stay below 3.8 and the results below 3.8; v[0] and v[1] are the only ones
+//     above 1.46 and are reduced where another round follows (f64m_inv_end).  The first round has two stages on canonical
+//     residues: one value of four reaches 4 and is reduced, the others stay below 1.4.
+// Every sum stays below 8 q < 2^53: exact.
 #pragma once
 #include <stdint.h>
 
@@ -69,6 +83,22 @@ F64M_FN double f64m_mulmod_any(double y, double w, double q, double qinv) {
     const double l = __builtin_fma(y, w, -h);
     const double c = f64m_round_mul(h, qinv);
     return __builtin_fma(-c, q, h) + l;
+}
+
+// The reductions of a round (see above) on eight values: v[row * KC + column], 2^S rows of KC columns.
+F64M_FN void f64m_fwd_begin(double* v, double q, double qinv) {  // the values that the first stage does not multiply
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[j] = f64m_reduce(v[j], q, qinv);
+}
+template <int KC>
+F64M_FN void f64m_inv_mid(double* v, double q, double qinv) {  // after the first stage (rows 2r, 2r + 1 paired): its sums
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+        if (((j / KC) & 1) == 0) v[j] = f64m_reduce(v[j], q, qinv);
+}
+F64M_FN void f64m_inv_end(double* v, double q, double qinv) {  // after three stages (KC = 1)
+    v[0] = f64m_reduce(v[0], q, qinv);
+    v[1] = f64m_reduce(v[1], q, qinv);
 }
 
 // canonical residues below 2^52 <-> doubles through the mantissa of 2^52 + v

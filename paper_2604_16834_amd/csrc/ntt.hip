@@ -22,12 +22,15 @@
 //   ArithF64  every modulus below 2^50: residues are integers held in doubles and the twiddle product is
 //             reduced with fused multiply-adds: for |y| < 2^51, h = y*w rounded, l = fma(y, w, -h) its
 //             exact error, c = the integer nearest to y*(w/q) (one fma against 1.5*2^52), and
-//             fma(-c, q, h) + l = y*w - c*q exactly, of magnitude below 0.75 q: six double-precision
+//             fma(-c, q, h) + l = y*w - c*q exactly: six double-precision
 //             operations where the integer path spends more than twenty 32-bit ones, which moves the
-//             lo pass from instruction issue to the HBM roof.  Values are brought back to |v| <= q/2 + 1
-//             (three operations) after every round of at most three forward stages and after every sum of
-//             an inverse butterfly, so every multiplicand stays below 2q < 2^51 and every sum below 2^53:
-//             all arithmetic is exact.  Between the two passes the data sit in HBM as doubles.
+//             lo pass from instruction issue to the HBM roof.  Twiddles are centred, |w| < q/2, so a multiplicand
+//             may reach 4q and its product stays below q: values are brought back to |v| <= q/2 + 1 (three
+//             operations) only where the bounds in f64mod.h ask for it, four of eight per forward round
+//             and six of eight per inverse round; every sum stays below 2^53: all arithmetic is
+//             exact.  Between the two passes the data sit in HBM as doubles below 4q.  (With every output of a
+//             forward round and every sum of an inverse butterfly re-centred, 1920 limb-polys at N = 2^16: inverse lo
+//             pass 486 us, now 444, forward 459 and 453; converting hi pass, 8 x 8 -> 19 limbs, 45.2 and 41.0.)
 // Rings below 2^11 use a plain one-tile integer kernel.
 #include <type_traits>
 
@@ -72,7 +75,12 @@ struct ArithU64 {
         x = s;
         y = mul_shoup_lazy(d, w.w, w.s, m.q);
     }
-    static __device__ __forceinline__ void fwd_round_end(E*, const MC&) {}
+    static __device__ __forceinline__ void fwd_begin(E*, const MC&) {}
+    static __device__ __forceinline__ void fwd_end(E*, const MC&) {}
+    template <int KC>
+    static __device__ __forceinline__ void inv_mid(E*, const MC&) {}
+    static __device__ __forceinline__ void inv_end(E*, const MC&) {}
+    static __device__ __forceinline__ void inv_end2(E*, const MC&) {}
 };
 
 // ---- double-precision arithmetic for moduli below 2^50 (the routines themselves: f64mod.h) -----------------------
@@ -91,10 +99,10 @@ struct ArithF64 {
     static __device__ __forceinline__ double from_u64(u64 raw) { return f64m_from_u64(raw); }
     static __device__ __forceinline__ u64 to_u64(double v) { return f64m_to_u64(v); }
     static __device__ __forceinline__ u64 canonical(double v, const MC& m) { return f64m_canonical(v, m.q); }  // |v| <= q/2 + 1 -> [0, q)
-    static __device__ __forceinline__ E load_first(u64 raw, const MC& m, bool) { return reduce(from_u64(raw), m); }
+    static __device__ __forceinline__ E load_first(u64 raw, const MC&, bool) { return from_u64(raw); }  // canonical: in [0, q)
     static __device__ __forceinline__ E load_mid(u64 raw) { return __longlong_as_double((long long)raw); }
     static __device__ __forceinline__ u64 store_mid(E v) { return (u64)__double_as_longlong(v); }
-    static __device__ __forceinline__ u64 store_fwd_final(E v, const MC& m) { return canonical(v, m); }  // after fwd_round_end
+    static __device__ __forceinline__ u64 store_fwd_final(E v, const MC& m) { return canonical(v, m); }  // after fwd_end
     static __device__ __forceinline__ u64 store_inv_final(E v, const MC& m) { return canonical(mulmod(v, m.ninv, m.ninv_q, m.q), m); }
     static __device__ __forceinline__ void fwd_bf(E& x, E& y, const TW w, const MC& m) {
         const double t = mulmod(y, w.w, w.wq, m.q);
@@ -103,12 +111,22 @@ struct ArithF64 {
     }
     static __device__ __forceinline__ void inv_bf(E& x, E& y, const TW w, const MC& m) {
         const double s = x + y, d = x - y;
-        x = reduce(s, m);
+        x = s;
         y = mulmod(d, w.w, w.wq, m.q);
     }
-    static __device__ __forceinline__ void fwd_round_end(E* v, const MC& m) {
+    // the reductions (bounds: f64mod.h): before a forward round, after a transform's last one; after the first stage of an
+    // inverse round, after its third, after the two-stage round that starts the inverse transform
+    static __device__ __forceinline__ void fwd_begin(E* v, const MC& m) { f64m_fwd_begin(v, m.q, m.qinv); }
+    static __device__ __forceinline__ void fwd_end(E* v, const MC& m) {
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = reduce(v[j], m);
+    }
+    template <int KC>
+    static __device__ __forceinline__ void inv_mid(E* v, const MC& m) { f64m_inv_mid<KC>(v, m.q, m.qinv); }
+    static __device__ __forceinline__ void inv_end(E* v, const MC& m) { f64m_inv_end(v, m.q, m.qinv); }
+    static __device__ __forceinline__ void inv_end2(E* v, const MC& m) {
+        v[0] = reduce(v[0], m);
+        v[4] = reduce(v[4], m);
     }
 };
 
@@ -141,12 +159,12 @@ __device__ __forceinline__ void inv_rows(typename A::E* v, const typename A::TW*
 #pragma unroll
             for (int kc = 0; kc < KC; kc++) A::inv_bf(v[rr * KC + kc], v[(rr + half) * KC + kc], w, m);
         }
+        if (a == S - 1) A::template inv_mid<KC>(v, m);
     }
 }
 
 // Butterflies whose twiddle is the value alone (no twiddle / q): the quotient comes from the rounded product.  Half the
-// registers and half the bytes per twiddle; from inputs reduced to q/2 + 1 the three stages of a round add at most 0.63 q,
-// 0.79 q and 0.98 q, so multiplicands stay below 2q and sums below 2^53 as with the precomputed quotient.
+// registers and half the bytes per twiddle; the bounds in f64mod.h are for these.
 struct ArithF64W : ArithF64 {
     typedef double TW;
     static __device__ __forceinline__ void fwd_bf(E& x, E& y, const double w, const MC& m) {
@@ -154,10 +172,9 @@ struct ArithF64W : ArithF64 {
         y = x - t;
         x = x + t;
     }
-    // the inverse butterfly: the sum is re-centred, the difference (below 2q) times the twiddle is at most q
     static __device__ __forceinline__ void inv_bf(E& x, E& y, const double w, const MC& m) {
         const double s = x + y, d = x - y;
-        x = reduce(s, m);
+        x = s;
         y = mulmod_any(d, w, m.q, m.qinv);
     }
 };
@@ -215,6 +232,7 @@ __device__ __forceinline__ void inv_rows_pre(typename A::E* v, const typename A:
             if (rr & half) continue;
             A::inv_bf(v[rr], v[rr + half], tv[(1 << a) - 1 + (rr >> (S - a))], m);
         }
+        if (S == 3 && a == S - 1) A::template inv_mid<1>(v, m);
     }
 }
 
@@ -368,16 +386,16 @@ __device__ __forceinline__ void fwd_lo_body(const NttArgs& args, const PolyList&
 #pragma unroll
             for (int j = 0; j < 8; j++) raw[j] = src[tid + 256 * j];
         }
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wa, P.mc);
-        A::fwd_round_end(v, P.mc);
         if (it == 0) load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
 #pragma unroll
         for (int j = 0; j < 8; j++) buf0[LDS_PAD(tid + 256 * j)] = v[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + 32 * j + x5)];
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wb, P.mc);
-        A::fwd_round_end(v, P.mc);
         if (it == 0) {
             load_lo_tw<A, 2>(P, 512 * TA + 2 * tid, wd);
             load_lo_tw<A, 2>(P, 512 * TA + 2 * tid + 1, wd + 3);
@@ -387,8 +405,8 @@ __device__ __forceinline__ void fwd_lo_body(const NttArgs& args, const PolyList&
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wc, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
         __syncthreads();
@@ -432,7 +450,7 @@ __device__ __forceinline__ void fwd_lo_body(const NttArgs& args, const PolyList&
         }
         fwd_rows_pre<AR, 2>(v, wd, P.mc);
         fwd_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
-        A::fwd_round_end(v, P.mc);
+        A::fwd_end(v, P.mc);
         // back through LDS so that a wave stores 512 contiguous bytes per instruction
 #pragma unroll
         for (int j = 0; j < 8; j++) buf1[LDS_PAD(8 * tid + j)] = v[j];
@@ -565,22 +583,22 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
 #pragma unroll
             for (int j = 0; j < 8; j++) raw[j] = src[tid + 256 * j];
         }
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wa, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) lds0[LDS_PAD(tid + 256 * j)] = v[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(d3 * 256 + 32 * j + x5)];
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wb, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) lds1[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = lds1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+        A::fwd_begin(v, P.mc);
         fwd_rows_pre<AR, 3>(v, wc, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) lds0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
         __syncthreads();
@@ -588,7 +606,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
         for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(8 * tid + j)];
         fwd_rows_pre<AR, 2>(v, wd, P.mc);
         fwd_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
-        A::fwd_round_end(v, P.mc);
+        A::fwd_end(v, P.mc);
         // back through LDS so that a wave stores 512 contiguous bytes per instruction
 #pragma unroll
         for (int j = 0; j < 8; j++) lds1[LDS_PAD(8 * tid + j)] = v[j];
@@ -686,22 +704,22 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
 #pragma unroll
             for (int i = 0; i < 8; i++) raw[i] = hi[(size_t)jn * dstride + tid + 256 * i];
         }
+        A::fwd_begin(v, mc);
         fwd_rows_pre<AW, 3>(v, wa, mc);
-        A::fwd_round_end(v, mc);
 #pragma unroll
         for (int i = 0; i < 8; i++) lds0[LDS_PAD(tid + 256 * i)] = v[i];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 8; i++) v[i] = lds0[LDS_PAD(d3 * 256 + 32 * i + x5)];
+        A::fwd_begin(v, mc);
         fwd_rows_pre<AW, 3>(v, wb, mc);
-        A::fwd_round_end(v, mc);
 #pragma unroll
         for (int i = 0; i < 8; i++) lds1[LDS_PAD(d3 * 256 + 32 * i + x5)] = v[i];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 8; i++) v[i] = lds1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * i + d0)];
+        A::fwd_begin(v, mc);
         fwd_rows_pre<AW, 3>(v, wc, mc);
-        A::fwd_round_end(v, mc);
 #pragma unroll
         for (int i = 0; i < 8; i++) lds0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * i + d0)] = v[i];
         __syncthreads();
@@ -719,7 +737,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
         }
         fwd_rows_pre<AW, 2>(v, wd, mc);
         fwd_rows_pre<AW, 2>(v + 4, wd + 3, mc);
-        A::fwd_round_end(v, mc);
+        A::fwd_end(v, mc);
         // back through LDS: point tid + 256 i of the slice, where the key words were fetched
 #pragma unroll
         for (int i = 0; i < 8; i++) lds1[LDS_PAD(8 * tid + i)] = v[i];
@@ -885,6 +903,7 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
         }
         inv_rows_pre<AR, 2>(v, wd, P.mc);
         inv_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
+        A::inv_end2(v, P.mc);
         if (it == 0) load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
 #pragma unroll
         for (int j = 0; j < 8; j++) buf0[LDS_PAD(8 * tid + j)] = v[j];
@@ -892,6 +911,7 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
         inv_rows_pre<AR, 3>(v, wc, P.mc);
+        A::inv_end(v, P.mc);
         if (it == 0) load_lo_tw<A, 3>(P, TA, wa);
 #pragma unroll
         for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
@@ -899,12 +919,14 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + 32 * j + x5)];
         inv_rows_pre<AR, 3>(v, wb, P.mc);
+        A::inv_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(tid + 256 * j)];
         inv_rows_pre<AR, 3>(v, wa, P.mc);
+        A::inv_end(v, P.mc);
         u64* dst = item_dst(args, pl, b0 + it, tile.a) + off;
         if (args.last) {
 #pragma unroll
@@ -939,7 +961,6 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_kernel(NttArgs args, P
 #pragma unroll
             for (int kc = 0; kc < KC; kc++) v[rr * KC + kc] = A::load_first(src[((size_t)rr << 11) + kc * 256 + tid], P.mc, false);
         fwd_rows<A, LOG_HI, KC>(v, P.tw, 1, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int rr = 0; rr < R; rr++)
 #pragma unroll
@@ -951,7 +972,6 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_kernel(NttArgs args, P
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = A::load_first(src[((size_t)(r0 + R8 * j) << 11) + col], P.mc, false);
         fwd_rows<A, 3, 1>(v, P.tw, 1, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) lds[(r0 + R8 * j) * CC + col] = v[j];
         __syncthreads();
@@ -960,8 +980,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_kernel(NttArgs args, P
         for (int rr = 0; rr < R8; rr++)
 #pragma unroll
             for (int kc = 0; kc < KC2; kc++) v[rr * KC2 + kc] = lds[(G * R8 + rr) * CC + cg * KC2 + kc];
+        A::fwd_begin(v, P.mc);
         fwd_rows<A, S2, KC2>(v, P.tw, 8 + G, P.mc);
-        A::fwd_round_end(v, P.mc);
 #pragma unroll
         for (int rr = 0; rr < R8; rr++)
 #pragma unroll
@@ -1046,7 +1066,6 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
             if (a0 + t >= n_targets) break;
             u64* dst = P[t].dst + (size_t)tile * CC;
             fwd_rows<A, LOG_HI, KC>(v[t], P[t].tw, 1, P[t].mc);
-            A::fwd_round_end(v[t], P[t].mc);
 #pragma unroll
             for (int rr = 0; rr < R; rr++)
 #pragma unroll
@@ -1070,7 +1089,6 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
             u64* dst = P[t].dst + (size_t)tile * CC;
             if (t) __syncthreads();  // the previous limb's exchange has been read
             fwd_rows<A, 3, 1>(v[t], P[t].tw, 1, P[t].mc);
-            A::fwd_round_end(v[t], P[t].mc);
 #pragma unroll
             for (int j = 0; j < 8; j++) lds[(r0 + R8 * j) * CC + col] = v[t][j];
             __syncthreads();
@@ -1078,8 +1096,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
             for (int rr = 0; rr < R8; rr++)
 #pragma unroll
                 for (int kc = 0; kc < KC2; kc++) v[t][rr * KC2 + kc] = lds[(G * R8 + rr) * CC + cg * KC2 + kc];
+            A::fwd_begin(v[t], P[t].mc);
             fwd_rows<A, S2, KC2>(v[t], P[t].tw, 8 + G, P[t].mc);
-            A::fwd_round_end(v[t], P[t].mc);
 #pragma unroll
             for (int rr = 0; rr < R8; rr++)
 #pragma unroll
@@ -1162,7 +1180,6 @@ __global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
         for (int i = 0; i < 7; i++) w1[i] = TwF{const_ptr(tw + 1 + i)->w, const_ptr(tw + 1 + i)->wq};
         fwd_rows_pre<A, 3>(v, w1, mc);
-        A::fwd_round_end(v, mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) lds[t][(r0 + R8 * j) * CC + col] = v[j];
     }
@@ -1179,8 +1196,8 @@ __global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4
         for (int rr = 0; rr < R8; rr++)
 #pragma unroll
             for (int kc = 0; kc < KC2; kc++) v[rr * KC2 + kc] = lds[t][(G * R8 + rr) * CC + cg * KC2 + kc];
+        A::fwd_begin(v, mc);
         fwd_rows<A, S2, KC2>(v, tw, 8 + G, mc);
-        A::fwd_round_end(v, mc);
 #pragma unroll
         for (int rr = 0; rr < R8; rr++)
 #pragma unroll
@@ -1231,6 +1248,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_inv_hi_kernel(NttArgs args, P
 #pragma unroll
             for (int kc = 0; kc < KC2; kc++) v[rr * KC2 + kc] = A::load_mid(dst[((size_t)(G * R8 + rr) << 11) + cg * KC2 + kc]);
         inv_rows<A, S2, KC2>(v, P.tw, 8 + G, P.mc);
+        if (S2 == 3) A::inv_end(v, P.mc);
 #pragma unroll
         for (int rr = 0; rr < R8; rr++)
 #pragma unroll

@@ -67,7 +67,7 @@ def test_weighted_sum_kernels(log_n, c_in, c_out, bits):
                                                           (15, 14, 14, 1, 13), (16, 7, 3, 4, 5), (13, 7, 12, 3, 6)])
 def test_digits_together(log_n, num_q, num_p, dnum, level):
     """All digits of a small decomposition in one launch: ragged last digits (1 of 2, 6 of 7, 2 of 6 limbs) and a single digit, rows of
-    4, 8, 12 and 16 conversion constants on both sides (9 and 12 real ones of twelve), target counts that are not multiples of
+    4, 8 and 16 conversion constants on both sides (9 to 14 real ones of sixteen), target counts that are not multiples of
     four, with the inner product inside the second pass (key switch) and behind it (hoisted rotations)."""
     p = make_params(log_n, num_q, num_p, dnum)
     orc, ctx = Oracle(p), hx.Context(p)
