@@ -311,7 +311,7 @@ int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride
         d2s[i] = d2 + i * L1 * N;
         items[i] = FinalItem{d0 + i * L1 * N, d1 + i * L1 * N, nullptr, outs[i], 1, 0};
     }
-    const bool mac = ntt_has_modup(c);  // the inner product inside the forward transforms' second pass
+    const bool mac = ntt_has_mac(c);  // the inner product inside the forward transforms' second pass
     int rc = run_modup(c, level, d2s, n, ws, st, mac);
     if (rc) return rc;
     if (mac) {
@@ -996,7 +996,7 @@ int ckks_keyswitch(const ckks_ctx* c, const uint64_t* d_c, uint32_t level, const
     if (!carve_ks(c, level, 1, 1, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for key switch");
     hipStream_t st = (hipStream_t)stream;
     const u64* src = (const u64*)d_c;
-    const bool mac = ntt_has_modup(c);
+    const bool mac = ntt_has_mac(c);
     int rc = run_modup(c, level, &src, 1, ws, st, mac);
     if (rc) return rc;
     if (mac) {
@@ -1093,7 +1093,7 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             ks[b] = pend_key[b]->d_key;
         }
         HIP_TRY(launch_automorph(c, (u32)L1, c1, gs, nb, pc1, st));
-        const bool mac = ntt_has_modup(c);
+        const bool mac = ntt_has_mac(c);
         int rc = run_modup(c, level, srcs, nb, ws, st, mac);
         if (rc) return rc;
         // the digits already belong to sigma_g(c1): no gather in the inner product, only on c0

@@ -263,6 +263,11 @@ struct MacProduct {
 };
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
                              hipStream_t st, const MacProduct* prod = nullptr);
+// rings whose transforms run as one kernel (the whole limb-poly in one workgroup)
+inline bool ntt_one_pass(const ckks_ctx* c) { return c->log_hi == 1; }
+// whether a key switch takes its inner product inside the forward transforms' second pass (launch_ntt_lo_mac) rather than behind
+// whole transforms
+inline bool ntt_has_mac(const ckks_ctx* c) { return ntt_has_modup(c) && !ntt_one_pass(c); }
 // whether launch_ntt can apply an epilogue in this ring (it needs the two-pass transform)
 inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LOG; }
 // keyswitch.hip

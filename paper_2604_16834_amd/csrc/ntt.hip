@@ -339,190 +339,115 @@ __device__ __forceinline__ u64* item_dst(const NttArgs& args, const PolyList& pl
     return args.dst + (((size_t)b * args.dst_bstride + pl_at(pl.dpos, a)) << args.log_n);
 }
 
-// EM (with EPI): which of the optional operands of the division's last step the launch has: 0 = look at each item's pointers,
+// The last step of a division by dropped moduli on a slice of 2^11 results w that sit in LDS (buf, point p at LDS_PAD(p)) and
+// are not stored: out = ((v - w) * cinv + addend) * mask + acc.  div_request asks for its operands, a round of butterflies
+// ahead of div_store.
+// EM: which of the optional operands the launch has: 0 = look at each item's pointers,
 // 1 = every item has its addend (of component 0 at least) and nothing else, 2 = none has any, 3 = every item has the ciphertext
 // `acc` and nothing else, 4 = every item has its mask and nothing else.  In all but case 0 the operand is requested with v, a
 // round ahead of its use; behind a condition the compiler keeps each request next to its use, one round trip to memory per
-// point (eight rotations of two limbs each at N = 2^16, sums added: 17.7 us in case 0, 14.2 us in case 3 with the rotated addend inside the inner product).
-template <class A, int IT, bool EPI, int EM = 0>
-__device__ __forceinline__ void fwd_lo_body(const NttArgs& args, const PolyList& pl, const FwdEpilogue& ep) {
-    typedef typename A::E E;
-    __shared__ E lds0[LDS_PADDED_WORDS];
-    __shared__ E lds1[LDS_PADDED_WORDS];
-    const u32 tid = threadIdx.x;
-    const LoTile tile = lo_tile(args.log_hi, args.lo_group);
-    const u32 blk = tile.blk, b0 = tile.b * IT;
-    const u32 cnt = args.batch - b0 < (u32)IT ? args.batch - b0 : (u32)IT;
-    const PolyRef<A> P = poly_ref<A>(args, pl, b0, tile.a);
-    const size_t off = (size_t)blk << 11;
-    const u32 TA = (1u << args.log_hi) + blk;
-    const u32 d3 = tid >> 5, x5 = tid & 31, d2 = (tid >> 2) & 7, d0 = tid & 3;
-    typedef typename LoTw<A>::TW TW;
-    typedef typename LoTw<A>::AR AR;
-    E v[8];
-    u64 raw[8];
-    TW wa[7], wb[7], wc[7], wd[6];
-    load_lo_tw<A, 3>(P, TA, wa);
-    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
-    {
-        const u64* src = P.src + off;
+// point (eight rotations of two limbs each at N = 2^16, sums added: 17.7 us in case 0, 14.2 us in case 3 with the rotated addend
+// inside the inner product).
+// i: limb (the list's dpos entry), bb: batch item (2 ciphertext + component), off: the slice's first point, t = 0..255
+struct DivOperands {
+    u64 v[8], v2[8], op[8];
+};
+template <class A, int EM>
+__device__ __forceinline__ void div_request(const NttArgs& args, const FwdEpilogue& ep, u32 i, u32 bb, size_t off, u32 t, DivOperands& O) {
+    const FinalItem& fi = ep.B.it[bb >> 1];
+    if (EM == 1) {  // the addend, gathered through the item's automorphism; component 1 may have none
+        const u64* add = (bb & 1) ? fi.add1 : fi.add0;
+        if (add) {
+            add += (size_t)i << args.log_n;
 #pragma unroll
-        for (int j = 0; j < 8; j++) raw[j] = src[tid + 256 * j];
+            for (int j = 0; j < 8; j++) {
+                const u32 x = (u32)off + t + 256 * j;
+                O.op[j] = add[fi.g == 1 ? x : galois_gather_index(x, fi.g, args.log_n)];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++) O.op[j] = 0;
+        }
+    } else if (EM == 3 || EM == 4) {
+        const u64* op = (EM == 3 ? fi.acc + ((size_t)((bb & 1) * ep.n_out + i) << args.log_n) : fi.mask + ((size_t)i << args.log_n)) + off;
+#pragma unroll
+        for (int j = 0; j < 8; j++) O.op[j] = op[t + 256 * j];
     }
+    const u64* vrow = (ep.use_vl ? ep.vl.p[bb >> 1] + (bb & 1) * ep.v_cstride + ((size_t)i << args.log_n)
+                                 : ep.v + (((size_t)bb * ep.E + i) << args.log_n)) + off;
 #pragma unroll
-    for (int it = 0; it < IT; it++) {
-        if ((u32)it >= cnt) break;
-        E* buf0 = lds0;
-        E* buf1 = lds1;
-        if (args.first) {
+    for (int j = 0; j < 8; j++) O.v[j] = vrow[t + 256 * j];
+    if constexpr (std::is_same<A, ArithF64>::value) {
+        if (ep.use_vl == 2) {
+            const u64* vrow2 = ep.vl2.p[bb >> 1] + (bb & 1) * ep.v2_cstride + ((size_t)i << args.log_n) + off;
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = A::load_first(raw[j], P.mc, false);
+            for (int j = 0; j < 8; j++) O.v2[j] = vrow2[t + 256 * j];
+        }
+    }
+}
+template <class A, int EM>
+__device__ __forceinline__ void div_store(const NttArgs& args, const FwdEpilogue& ep, u32 i, u32 m_idx, u32 bb, size_t off, u32 t,
+                                          const typename A::E* buf, const typename A::MC& mc, const DivOperands& O) {
+    const u32 comp = bb & 1;
+    const FinalItem fi = ep.B.it[bb >> 1];
+    const u64 cv = ep.cinv[i];
+    const u64* add = comp ? fi.add1 : fi.add0;
+    u64* orow = fi.out + (((size_t)comp * ep.n_out + i) << args.log_n) + off;
+    if constexpr (std::is_same<A, ArithF64>::value) {
+        // in the transform's own arithmetic: v - w is an integer below 2q in magnitude, its product with the constant is
+        // below 0.75 q, one more reduction after the addend; every value below is exact
+        const double q = mc.q, cvd = A::from_u64(cv), cvq = cvd / q;
+        double vd[8];
+        if (ep.use_vl == 2) {  // v = ka * x + kb * y
+            const double ka = A::from_u64(ep.ka[i]), kb = A::from_u64(ep.kb[i]);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                vd[j] = A::reduce(A::mulmod_any(A::from_u64(O.v[j]), ka, q, mc.qinv) + A::mulmod_any(A::from_u64(O.v2[j]), kb, q, mc.qinv), mc);
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = A::load_mid(raw[j]);
-        }
-        if (it + 1 < IT && (u32)(it + 1) < cnt) {  // the next item's points, a tile ahead
-            const u64* src = item_src<A>(args, pl, b0 + it + 1, tile.a) + off;
-#pragma unroll
-            for (int j = 0; j < 8; j++) raw[j] = src[tid + 256 * j];
-        }
-        A::fwd_begin(v, P.mc);
-        fwd_rows_pre<AR, 3>(v, wa, P.mc);
-        if (it == 0) load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
-#pragma unroll
-        for (int j = 0; j < 8; j++) buf0[LDS_PAD(tid + 256 * j)] = v[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + 32 * j + x5)];
-        A::fwd_begin(v, P.mc);
-        fwd_rows_pre<AR, 3>(v, wb, P.mc);
-        if (it == 0) {
-            load_lo_tw<A, 2>(P, 512 * TA + 2 * tid, wd);
-            load_lo_tw<A, 2>(P, 512 * TA + 2 * tid + 1, wd + 3);
+            for (int j = 0; j < 8; j++) vd[j] = A::from_u64(O.v[j]);
         }
 #pragma unroll
-        for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
-        A::fwd_begin(v, P.mc);
-        fwd_rows_pre<AR, 3>(v, wc, P.mc);
-#pragma unroll
-        for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(8 * tid + j)];
-        u64 vv[8], vv2[8], av[8];
-        if (EPI) {  // what the results are subtracted from: requested now, needed after the last round
-            const u32 bv = b0 + it;
-            if (EM == 1) {  // and the addend (gathered through the item's automorphism); component 1 may have none
-                const FinalItem& fa = ep.B.it[bv >> 1];
-                const u64* add = (bv & 1) ? fa.add1 : fa.add0;
+        for (int j = 0; j < 8; j++) {
+            const u32 p = t + 256 * j;
+            double r = A::mulmod(vd[j] - buf[LDS_PAD(p)], cvd, cvq, q);
+            if (EM == 1 || EM == 3) {
+                r = A::reduce(r + A::from_u64(O.op[j]), mc);
+            } else if (EM == 4) {
+                r = A::mulmod_any(r, A::from_u64(O.op[j]), q, mc.qinv);
+            } else if (EM == 0) {
                 if (add) {
-                    add += (size_t)pl_at(pl.dpos, tile.a) << args.log_n;
-#pragma unroll
-                    for (int j = 0; j < 8; j++) {
-                        const u32 x = (u32)off + tid + 256 * j;
-                        av[j] = add[fa.g == 1 ? x : galois_gather_index(x, fa.g, args.log_n)];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; j++) av[j] = 0;
+                    const u32 x = (u32)off + p;
+                    const u32 xs = fi.g == 1 ? x : galois_gather_index(x, fi.g, args.log_n);
+                    r = A::reduce(r + A::from_u64(add[((size_t)i << args.log_n) + xs]), mc);
                 }
-            } else if (EM == 3 || EM == 4) {
-                const FinalItem& fa = ep.B.it[bv >> 1];
-                const u32 row = pl_at(pl.dpos, tile.a);
-                const u64* op = (EM == 3 ? fa.acc + ((size_t)((bv & 1) * ep.n_out + row) << args.log_n) : fa.mask + ((size_t)row << args.log_n)) + off;
-#pragma unroll
-                for (int j = 0; j < 8; j++) av[j] = op[tid + 256 * j];
+                if (fi.mask) r = A::mulmod_any(r, A::from_u64(fi.mask[((size_t)i << args.log_n) + off + p]), q, mc.qinv);
+                if (fi.acc) r = A::reduce(r + A::from_u64(fi.acc[(((size_t)comp * ep.n_out + i) << args.log_n) + off + p]), mc);
             }
-            const u64* vrow = (ep.use_vl ? ep.vl.p[bv >> 1] + (bv & 1) * ep.v_cstride + ((size_t)pl_at(pl.dpos, tile.a) << args.log_n)
-                                         : ep.v + (((size_t)bv * ep.E + pl_at(pl.dpos, tile.a)) << args.log_n)) + off;
-#pragma unroll
-            for (int j = 0; j < 8; j++) vv[j] = vrow[tid + 256 * j];
-            if constexpr (std::is_same<A, ArithF64>::value) {
-                if (ep.use_vl == 2) {
-                    const u64* vrow2 = ep.vl2.p[bv >> 1] + (bv & 1) * ep.v2_cstride + ((size_t)pl_at(pl.dpos, tile.a) << args.log_n) + off;
-#pragma unroll
-                    for (int j = 0; j < 8; j++) vv2[j] = vrow2[tid + 256 * j];
-                }
-            }
+            orow[p] = A::canonical(r, mc);
         }
-        fwd_rows_pre<AR, 2>(v, wd, P.mc);
-        fwd_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
-        A::fwd_end(v, P.mc);
-        // back through LDS so that a wave stores 512 contiguous bytes per instruction
+    } else {
+        const ModConst mi = ep.mci[m_idx];
+        const u64 cvs = ep.cinv[ep.num_q + i];
 #pragma unroll
-        for (int j = 0; j < 8; j++) buf1[LDS_PAD(8 * tid + j)] = v[j];
-        __syncthreads();
-        if (!EPI) {
-            u64* dst = item_dst(args, pl, b0 + it, tile.a) + off;
-#pragma unroll
-            for (int j = 0; j < 8; j++) dst[tid + 256 * j] = A::store_fwd_final(buf1[LDS_PAD(tid + 256 * j)], P.mc);
-        } else {
-            // the division's last step on the results w, which are not stored: out = ((v - w) * cinv + addend) * mask
-            const u32 i = pl_at(pl.dpos, tile.a), bb = b0 + it, comp = bb & 1;
-            const FinalItem fi = ep.B.it[bb >> 1];
-            const u64 cv = ep.cinv[i];
-            const u64* add = comp ? fi.add1 : fi.add0;
-            u64* orow = fi.out + (((size_t)comp * ep.n_out + i) << args.log_n) + off;
-            if constexpr (std::is_same<A, ArithF64>::value) {
-                // in the transform's own arithmetic: v - w is an integer below 2q in magnitude, its product with the constant is
-                // below 0.75 q, one more reduction after the addend; every value below is exact
-                const double q = P.mc.q, cvd = A::from_u64(cv), cvq = cvd / q;
-                double vd[8];
-                if (ep.use_vl == 2) {  // v = ka * x + kb * y
-                    const double ka = A::from_u64(ep.ka[i]), kb = A::from_u64(ep.kb[i]);
-#pragma unroll
-                    for (int j = 0; j < 8; j++)
-                        vd[j] = A::reduce(A::mulmod_any(A::from_u64(vv[j]), ka, q, P.mc.qinv) + A::mulmod_any(A::from_u64(vv2[j]), kb, q, P.mc.qinv), P.mc);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; j++) vd[j] = A::from_u64(vv[j]);
+        for (int j = 0; j < 8; j++) {
+            const u32 p = t + 256 * j;
+            const u64 w = A::store_fwd_final(buf[LDS_PAD(p)], mc);
+            u64 r = mul_shoup(sub_mod(O.v[j], w, mi.q), cv, cvs, mi.q);
+            if (EM == 1 || EM == 3) {
+                r = add_mod(r, O.op[j], mi.q);
+            } else if (EM == 4) {
+                r = mulmod_barrett(r, O.op[j], mi);
+            } else if (EM == 0) {
+                if (add) {
+                    const u32 x = (u32)off + p;
+                    const u32 xs = fi.g == 1 ? x : galois_gather_index(x, fi.g, args.log_n);
+                    r = add_mod(r, add[((size_t)i << args.log_n) + xs], mi.q);
                 }
-#pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    const u32 p = tid + 256 * j;
-                    double r = A::mulmod(vd[j] - buf1[LDS_PAD(p)], cvd, cvq, q);
-                    if (EM == 1 || EM == 3) {
-                        r = A::reduce(r + A::from_u64(av[j]), P.mc);
-                    } else if (EM == 4) {
-                        r = A::mulmod_any(r, A::from_u64(av[j]), q, P.mc.qinv);
-                    } else if (EM == 0) {
-                        if (add) {
-                            const u32 x = (u32)off + p;
-                            const u32 xs = fi.g == 1 ? x : galois_gather_index(x, fi.g, args.log_n);
-                            r = A::reduce(r + A::from_u64(add[((size_t)i << args.log_n) + xs]), P.mc);
-                        }
-                        if (fi.mask) r = A::mulmod_any(r, A::from_u64(fi.mask[((size_t)i << args.log_n) + off + p]), q, P.mc.qinv);
-                        if (fi.acc) r = A::reduce(r + A::from_u64(fi.acc[(((size_t)comp * ep.n_out + i) << args.log_n) + off + p]), P.mc);
-                    }
-                    orow[p] = A::canonical(r, P.mc);
-                }
-            } else {
-                const ModConst mi = ep.mci[pl_at(pl.mod, tile.a)];
-                const u64 cvs = ep.cinv[ep.num_q + i];
-#pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    const u32 p = tid + 256 * j;
-                    const u64 w = A::store_fwd_final(buf1[LDS_PAD(p)], P.mc);
-                    u64 r = mul_shoup(sub_mod(vv[j], w, mi.q), cv, cvs, mi.q);
-                    if (EM == 1 || EM == 3) {
-                        r = add_mod(r, av[j], mi.q);
-                    } else if (EM == 4) {
-                        r = mulmod_barrett(r, av[j], mi);
-                    } else if (EM == 0) {
-                        if (add) {
-                            const u32 x = (u32)off + p;
-                            const u32 xs = fi.g == 1 ? x : galois_gather_index(x, fi.g, args.log_n);
-                            r = add_mod(r, add[((size_t)i << args.log_n) + xs], mi.q);
-                        }
-                        if (fi.mask) r = mulmod_barrett(r, fi.mask[((size_t)i << args.log_n) + off + p], mi);
-                        if (fi.acc) r = add_mod(r, fi.acc[(((size_t)comp * ep.n_out + i) << args.log_n) + off + p], mi.q);
-                    }
-                    orow[p] = r;
-                }
+                if (fi.mask) r = mulmod_barrett(r, fi.mask[((size_t)i << args.log_n) + off + p], mi);
+                if (fi.acc) r = add_mod(r, fi.acc[(((size_t)comp * ep.n_out + i) << args.log_n) + off + p], mi.q);
             }
+            orow[p] = r;
         }
     }
 }
@@ -619,10 +544,65 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
     }
 }
 
-// the lo pass as the last kernel of a division by dropped moduli
-template <class A, int IT, int EM>
+// the lo pass as the last kernel of a division by dropped moduli: one batch item per workgroup
+template <class A, int EM>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_div_kernel(NttArgs args, PolyList pl, FwdEpilogue ep) {
-    fwd_lo_body<A, IT, true, EM>(args, pl, ep);
+    typedef typename A::E E;
+    typedef typename LoTw<A>::TW TW;
+    typedef typename LoTw<A>::AR AR;
+    __shared__ E lds0[LDS_PADDED_WORDS];
+    __shared__ E lds1[LDS_PADDED_WORDS];
+    const u32 tid = threadIdx.x;
+    const LoTile tile = lo_tile(args.log_hi, args.lo_group);
+    const u32 blk = tile.blk, b = tile.b;
+    const PolyRef<A> P = poly_ref<A>(args, pl, b, tile.a);
+    const size_t off = (size_t)blk << 11;
+    const u32 TA = (1u << args.log_hi) + blk;
+    const u32 d3 = tid >> 5, x5 = tid & 31, d2 = (tid >> 2) & 7, d0 = tid & 3;
+    E v[8];
+    u64 raw[8];
+    TW wa[7], wb[7], wc[7], wd[6];
+    load_lo_tw<A, 3>(P, TA, wa);
+    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
+#pragma unroll
+    for (int j = 0; j < 8; j++) raw[j] = P.src[off + tid + 256 * j];
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = A::load_mid(raw[j]);
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wa, P.mc);
+    load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) lds0[LDS_PAD(tid + 256 * j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(d3 * 256 + 32 * j + x5)];
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wb, P.mc);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * tid, wd);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * tid + 1, wd + 3);
+#pragma unroll
+    for (int j = 0; j < 8; j++) lds1[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = lds1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wc, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) lds0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(8 * tid + j)];
+    DivOperands O;
+    const u32 i = pl_at(pl.dpos, tile.a);
+    div_request<A, EM>(args, ep, i, b, off, tid, O);
+    fwd_rows_pre<AR, 2>(v, wd, P.mc);
+    fwd_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
+    A::fwd_end(v, P.mc);
+    // back through LDS so that a wave stores 512 contiguous bytes per instruction
+#pragma unroll
+    for (int j = 0; j < 8; j++) lds1[LDS_PAD(8 * tid + j)] = v[j];
+    __syncthreads();
+    div_store<A, EM>(args, ep, i, pl_at(pl.mod, tile.a), b, off, tid, lds1, P.mc, O);
 }
 
 // The lo pass of ModUp's forward transforms with the inner product with the switching key in place of its stores.
@@ -828,6 +808,33 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     }
 }
 
+// the first points of an inverse transform: canonical residues, or (MUL) the product or linear combination of two operands
+template <class A, bool MUL>
+__device__ __forceinline__ void inv_first_points(const NttArgs& args, const typename A::MC& mc, const ulonglong2* raw, const ulonglong2* raw2, typename A::E* v) {
+    if constexpr (MUL) {
+        if (args.use_lin) {  // uniform
+            const double ka = A::from_u64(args.lin_ka), kb = A::from_u64(args.lin_kb);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                v[2 * j] = A::reduce(A::mulmod_any(A::from_u64(raw[j].x), ka, mc.q, mc.qinv) + A::mulmod_any(A::from_u64(raw2[j].x), kb, mc.q, mc.qinv), mc);
+                v[2 * j + 1] = A::reduce(A::mulmod_any(A::from_u64(raw[j].y), ka, mc.q, mc.qinv) + A::mulmod_any(A::from_u64(raw2[j].y), kb, mc.q, mc.qinv), mc);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                v[2 * j] = A::mulmod_any(A::from_u64(raw[j].x), A::from_u64(raw2[j].x), mc.q, mc.qinv);
+                v[2 * j + 1] = A::mulmod_any(A::from_u64(raw[j].y), A::from_u64(raw2[j].y), mc.q, mc.qinv);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            v[2 * j] = A::load_first(raw[j].x, mc, true);
+            v[2 * j + 1] = A::load_first(raw[j].y, mc, true);
+        }
+    }
+}
+
 // MUL (double-precision arithmetic, first pass, source list): the transform's input is the pointwise product of two
 // polynomials (the d2 = a1 (.) b1 of a ciphertext product), formed as the points are loaded: d2 itself is never stored.
 template <class A, int IT, bool MUL = false>
@@ -867,30 +874,7 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
         if ((u32)it >= cnt) break;
         E* buf0 = (it & 1) ? lds1 : lds0;  // three exchanges per item: the buffers swap roles from item to item
         E* buf1 = (it & 1) ? lds0 : lds1;
-        if constexpr (MUL) {
-            if (args.use_lin) {  // uniform
-                const double ka = A::from_u64(args.lin_ka), kb = A::from_u64(args.lin_kb);
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    v[2 * j] = A::reduce(A::mulmod_any(A::from_u64(raw[j].x), ka, P.mc.q, P.mc.qinv) +
-                                         A::mulmod_any(A::from_u64(raw2[j].x), kb, P.mc.q, P.mc.qinv), P.mc);
-                    v[2 * j + 1] = A::reduce(A::mulmod_any(A::from_u64(raw[j].y), ka, P.mc.q, P.mc.qinv) +
-                                             A::mulmod_any(A::from_u64(raw2[j].y), kb, P.mc.q, P.mc.qinv), P.mc);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    v[2 * j] = A::mulmod_any(A::from_u64(raw[j].x), A::from_u64(raw2[j].x), P.mc.q, P.mc.qinv);
-                    v[2 * j + 1] = A::mulmod_any(A::from_u64(raw[j].y), A::from_u64(raw2[j].y), P.mc.q, P.mc.qinv);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                v[2 * j] = A::load_first(raw[j].x, P.mc, true);
-                v[2 * j + 1] = A::load_first(raw[j].y, P.mc, true);
-            }
-        }
+        inv_first_points<A, MUL>(args, P.mc, raw, raw2, v);
         if (it + 1 < IT && (u32)(it + 1) < cnt) {  // the next item's points, a tile ahead
             const ulonglong2* in = reinterpret_cast<const ulonglong2*>(item_src<A>(args, pl, b0 + it + 1, tile.a) + off + 8 * tid);
 #pragma unroll
@@ -1263,6 +1247,201 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_inv_hi_kernel(NttArgs args, P
     }
 }
 
+// ============================ rings of 2^12 points: the whole transform in one workgroup ============================
+// 256 R threads (R = 2 blocks of 2^11 points, eight points per thread) hold a whole limb-poly: the hi pass' stage acts
+// on the R points of a thread's columns, one more exchange through LDS takes the place of the trip through memory, and the lo
+// pass' rounds follow, 256 threads per block.  On this ring a call is a chain of launches that leave most of the chip idle;
+// each is worth a launch (about 2 us) and a chain of dependent loads (1 to 2 us) whatever it computes: a rescale in two
+// kernels instead of four takes 14.2 us instead of 20.7, five limbs forward and back 17.4 instead of 23.5, and a filled chip gains
+// the memory traffic (1536 limb-polys 58 us instead of 88).  With four blocks (2^13 points) the
+// compute units next door, which the two passes use, are missed more than the launches: key switches 58 -> 64 us.
+// AP: 0 = the source is a polynomial, else rows of conversion constants as in ntt_fwd_hi_conv_kernel, ND of them real.  DIV: the
+// results go through a division's last step (em as in div_request) instead of being stored.
+// grid = (entries of the list or most targets of a digit, batch, digits)
+#define RING_LOG_HI 1
+#define RING_THREADS (NTT_THREADS << RING_LOG_HI)
+template <class A, int AP, int ND, bool DIV>
+__device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const FwdEpilogue* ep, int em) {
+    typedef typename A::E E;
+    typedef typename LoTw<A>::TW TW;
+    typedef typename LoTw<A>::AR AR;
+    constexpr int R = 1 << RING_LOG_HI, KC = 8 / R, THREADS = RING_THREADS;
+    __shared__ E lds0[R * LDS_PADDED_WORDS];
+    __shared__ E lds1[R * LDS_PADDED_WORDS];
+    const u32 tid = threadIdx.x, b = blockIdx.y;
+    u32 a = blockIdx.x;
+    const u32 dig = cp.digit0 + blockIdx.z, lo = cp.lo + dig * cp.alpha;
+    u32 nd = cp.nd;
+    if (AP) {
+        if (cp.alpha) nd = min(cp.alpha, cp.n_src - lo);
+        if (a >= (cp.alpha ? pl.n - nd : pl.n)) return;  // whole workgroup: a digit with more limbs has fewer targets
+        if (cp.alpha && a >= lo) a += nd;
+    }
+    PolyRef<A> P = poly_ref<A>(args, pl, b, a);
+    if (AP) P.dst += dig * cp.dst_dstride;
+    const u32 blk = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
+    const size_t N = (size_t)1 << args.log_n, off = (size_t)blk << 11;
+    const u32 TA = R + blk;
+    const u32 d3 = t >> 5, x5 = t & 31, d2 = (t >> 2) & 7, d0 = t & 3;
+    TW wa[7], wb[7], wc[7], wd[6];
+    load_lo_tw<A, 3>(P, TA, wa);
+    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
+    E v[8];
+    if constexpr (AP > 0) {
+        const double* y = cp.y + b * cp.y_bstride + (size_t)lo * N;
+        const TwF* ce = cp.convf + dig * cp.convf_dstride + (size_t)pl_at(pl.dpos, a) * AP;
+        double cw[ND];
+#pragma unroll
+        for (int k = 0; k < ND; k++) cw[k] = ce[k].w;
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            double yv[AP];
+            conv_load<AP, ND>(yv, y + ((size_t)(j / KC) << 11) + (j % KC) * THREADS + tid, N, nd);
+            v[j] = conv_sum<AP, ND>(yv, cw, P.mc.q, P.mc.qinv);
+        }
+    } else {
+        u64 raw[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) raw[j] = P.src[((size_t)(j / KC) << 11) + (j % KC) * THREADS + tid];
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = A::load_first(raw[j], P.mc, false);
+    }
+    fwd_rows<A, RING_LOG_HI, KC>(v, P.tw, 1, P.mc);
+    E* buf0 = lds0 + blk * LDS_PADDED_WORDS;
+    E* buf1 = lds1 + blk * LDS_PADDED_WORDS;
+#pragma unroll
+    for (int j = 0; j < 8; j++) lds1[(j / KC) * LDS_PADDED_WORDS + LDS_PAD((j % KC) * THREADS + tid)] = v[j];
+    load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(t + 256 * j)];
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wa, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(t + 256 * j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + 32 * j + x5)];
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wb, P.mc);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t, wd);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t + 1, wd + 3);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+    A::fwd_begin(v, P.mc);
+    fwd_rows_pre<AR, 3>(v, wc, P.mc);
+    DivOperands O;
+    const u32 i = pl_at(pl.dpos, a);
+    if constexpr (DIV) {
+        if (em == 1) div_request<A, 1>(args, *ep, i, b, off, t, O);
+        else if (em == 3) div_request<A, 3>(args, *ep, i, b, off, t, O);
+        else if (em == 4) div_request<A, 4>(args, *ep, i, b, off, t, O);
+        else div_request<A, 2>(args, *ep, i, b, off, t, O);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(8 * t + j)];
+    fwd_rows_pre<AR, 2>(v, wd, P.mc);
+    fwd_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
+    A::fwd_end(v, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(8 * t + j)] = v[j];
+    __syncthreads();
+    if constexpr (DIV) {
+        const u32 m_idx = pl_at(pl.mod, a);
+        if (em == 1 || em == 3) div_store<A, 1>(args, *ep, i, m_idx, b, off, t, buf1, P.mc, O);
+        else if (em == 4) div_store<A, 4>(args, *ep, i, m_idx, b, off, t, buf1, P.mc, O);
+        else if (em == 2) div_store<A, 2>(args, *ep, i, m_idx, b, off, t, buf1, P.mc, O);
+        else div_store<A, 0>(args, *ep, i, m_idx, b, off, t, buf1, P.mc, O);
+    } else {
+        u64* dst = P.dst + off;
+#pragma unroll
+        for (int j = 0; j < 8; j++) dst[t + 256 * j] = A::store_fwd_final(buf1[LDS_PAD(t + 256 * j)], P.mc);
+    }
+}
+template <class A, int AP, int ND>
+__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
+    fwd_ring_body<A, AP, ND, false>(args, pl, cp, nullptr, 0);
+}
+template <class A, int AP, int ND>
+__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_div_kernel(NttArgs args, PolyList pl, ConvPrologue cp, FwdEpilogue ep, int em) {
+    fwd_ring_body<A, AP, ND, true>(args, pl, cp, &ep, em);
+}
+
+// the inverse transform likewise: the lo pass' rounds mirrored, an exchange, the hi pass' stages.  grid = (entries of the list, batch)
+template <class A, bool MUL>
+__global__ __launch_bounds__(RING_THREADS) void ntt_inv_ring_kernel(NttArgs args, PolyList pl) {
+    typedef typename A::E E;
+    typedef typename LoTw<A>::TW TW;
+    typedef typename LoTw<A>::AR AR;
+    constexpr int R = 1 << RING_LOG_HI, KC = 8 / R, THREADS = RING_THREADS;
+    __shared__ E lds0[R * LDS_PADDED_WORDS];
+    __shared__ E lds1[R * LDS_PADDED_WORDS];
+    const u32 tid = threadIdx.x, a = blockIdx.x, b = blockIdx.y;
+    const PolyRef<A> P = poly_ref<A>(args, pl, b, a);
+    const u32 blk = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
+    const size_t off = (size_t)blk << 11;
+    const u32 TA = R + blk;
+    const u32 d3 = t >> 5, x5 = t & 31, d2 = (t >> 2) & 7, d0 = t & 3;
+    E* buf0 = lds0 + blk * LDS_PADDED_WORDS;
+    E* buf1 = lds1 + blk * LDS_PADDED_WORDS;
+    TW wa[7], wb[7], wc[7], wd[6];
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t, wd);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t + 1, wd + 3);
+    load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
+    ulonglong2 raw[4], raw2[MUL ? 4 : 1];
+    const ulonglong2* in = reinterpret_cast<const ulonglong2*>(P.src + off + 8 * t);
+#pragma unroll
+    for (int j = 0; j < 4; j++) raw[j] = in[j];
+    if constexpr (MUL) {
+        const ulonglong2* in2 = reinterpret_cast<const ulonglong2*>(args.mul_list.p[b] + ((size_t)pl_at(pl.spos, a) << args.log_n) + off + 8 * t);
+#pragma unroll
+        for (int j = 0; j < 4; j++) raw2[j] = in2[j];
+    }
+    const TwF* scale = args.inv_scale ? args.inv_scale + pl_at(pl.mod, a) : nullptr;
+    E v[8];
+    inv_first_points<A, MUL>(args, P.mc, raw, raw2, v);
+    inv_rows_pre<AR, 2>(v, wd, P.mc);
+    inv_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
+    A::inv_end2(v, P.mc);
+    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(8 * t + j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+    inv_rows_pre<AR, 3>(v, wc, P.mc);
+    A::inv_end(v, P.mc);
+    load_lo_tw<A, 3>(P, TA, wa);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + 32 * j + x5)];
+    inv_rows_pre<AR, 3>(v, wb, P.mc);
+    A::inv_end(v, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(t + 256 * j)];
+    inv_rows_pre<AR, 3>(v, wa, P.mc);
+    A::inv_end(v, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(t + 256 * j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = lds1[(j / KC) * LDS_PADDED_WORDS + LDS_PAD((j % KC) * THREADS + tid)];
+    inv_rows<A, RING_LOG_HI, KC>(v, P.tw, 1, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) P.dst[((size_t)(j / KC) << 11) + (j % KC) * THREADS + tid] = inv_last_store<A>(v[j], P.mc, scale);
+}
+
 // ================================= rings below 2^11: one tile per poly (integer arithmetic) ==============
 template <bool INVERSE>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_small_kernel(NttArgs args, PolyList pl) {
@@ -1298,7 +1477,6 @@ static void launch_hi(bool inverse, dim3 grid, hipStream_t st, const NttArgs& ar
 template <class A>
 static void launch_hi_any(u32 log_hi, bool inverse, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl) {
     switch (log_hi) {
-        case 1: launch_hi<A, 1>(inverse, grid, st, args, pl); break;
         case 2: launch_hi<A, 2>(inverse, grid, st, args, pl); break;
         case 3: launch_hi<A, 3>(inverse, grid, st, args, pl); break;
         case 4: launch_hi<A, 4>(inverse, grid, st, args, pl); break;
@@ -1341,9 +1519,8 @@ static void launch_fwd_lo_loop(u32 batch, dim3 grid, hipStream_t st, const NttAr
     else grid.x = ext;
     hipLaunchKernelGGL((ntt_fwd_lo_loop_kernel<A>), grid, dim3(NTT_THREADS), 0, st, args, pl);
 }
-template <class A>
-static void launch_lo_div(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const FwdEpilogue& ep) {
-    // which optional operands the division's last step has is the same for the whole launch: one instantiation per case
+// which optional operands the division's last step has: the same for the whole launch (see div_request)
+static int div_operands(const NttArgs& args, const FwdEpilogue& ep) {
     u32 n_add0 = 0, n_add1 = 0, n_mask = 0, n_acc = 0;
     const u32 n_ct = (args.batch + 1) / 2;
     for (u32 r = 0; r < n_ct; r++) {
@@ -1353,11 +1530,15 @@ static void launch_lo_div(dim3 grid, hipStream_t st, const NttArgs& args, const 
         n_mask += fi.mask ? 1 : 0;
         n_acc += fi.acc ? 1 : 0;
     }
-    int em = 0;
-    if (n_mask + n_acc == 0) em = n_add0 == n_ct ? 1 : (n_add0 + n_add1 == 0 ? 2 : 0);
-    else if (n_add0 + n_add1 == 0) em = n_acc == n_ct && !n_mask ? 3 : (n_mask == n_ct && !n_acc ? 4 : 0);
-    // one batch item per workgroup (see lo_items in launch_ntt_any)
-#define LO_DIV_LAUNCH(EM) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<A, 1, EM>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
+    if (n_mask + n_acc == 0) return n_add0 == n_ct ? 1 : (n_add0 + n_add1 == 0 ? 2 : 0);
+    if (n_add0 + n_add1 == 0) return n_acc == n_ct && !n_mask ? 3 : (n_mask == n_ct && !n_acc ? 4 : 0);
+    return 0;
+}
+template <class A>
+static void launch_lo_div(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const FwdEpilogue& ep) {
+    const int em = div_operands(args, ep);
+    // one instantiation per case; one batch item per workgroup (see per_wg in launch_ntt_any)
+#define LO_DIV_LAUNCH(EM) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<A, EM>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
     if (em == 1) LO_DIV_LAUNCH(1);
     else if (em == 2) LO_DIV_LAUNCH(2);
     else if (em == 3) LO_DIV_LAUNCH(3);
@@ -1371,44 +1552,92 @@ static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& a
     else launch_inv_lo_it<A, 1>(grid, st, args, pl, mul);
 }
 
-#define HI_CONV_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(threads), 0, st, args, pl, cp)
+// four target limbs per workgroup share one fetch of the source residues
+template <int LOG_HI, int AP, int ND>
+static void launch_hi_conv_regs(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
+    cp.groups = (n_targets + 3) / 4;
+    hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 4, ND>), dim3(1u << LOG_HI, cp.groups * batch, digits), dim3(NTT_THREADS), 0, st, args, pl, cp);
+}
+template <int LOG_HI, int AP, int ND>
+static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
+    cp.groups = (n_targets + HC_T - 1) / HC_T;
+    hipLaunchKernelGGL((ntt_fwd_hi_conv_lds_kernel<LOG_HI, AP, ND>), dim3(1u << LOG_HI, cp.groups * batch, digits), dim3(HC_THREADS), 0, st, args, pl, cp);
+}
+// n_targets: the most targets a digit of the launch has
 template <int LOG_HI>
-static void launch_hi_conv_ap(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
-    const u32 ap = cp.ap;
-    if (ap == 4 && cp.nd == 1) {  // the rescale: one dropped limb
-        constexpr u32 threads = NTT_THREADS;
-        HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 4, 4, 1>);
+static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
+#define HI_CONV(HOW, AP, ND) launch_hi_conv_##HOW<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp)
+    if (cp.ap == 4 && cp.nd == 1) {  // the rescale: one dropped limb
+        HI_CONV(regs, 4, 1);
         return;
     }
     if constexpr (LOG_HI >= 4) {
-        constexpr u32 threads = HC_THREADS;
-        if (ap == 4) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 4, 4>);
-        else if (ap == 8) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 8, 8>);
-        else if (ap == 12 && cp.nd == 9) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 12, 9>);  // eight special primes and the dropped limb: three of the twelve entries are padding
-        else if (ap == 12) HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 12, 12>);
-        else HI_CONV_LAUNCH(ntt_fwd_hi_conv_lds_kernel<LOG_HI, 16, 16>);
+        if (cp.ap == 4) HI_CONV(lds, 4, 4);
+        else if (cp.ap == 8) HI_CONV(lds, 8, 8);
+        else if (cp.ap == 12 && cp.nd == 9) HI_CONV(lds, 12, 9);  // eight special primes and the dropped limb: three of the twelve entries are padding
+        else if (cp.ap == 12) HI_CONV(lds, 12, 12);
+        else HI_CONV(lds, 16, 16);
     } else {
-        constexpr u32 threads = NTT_THREADS;
-        if (ap == 4) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 4, 4>);
-        else if (ap == 8) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 8, 4>);
-        else if (ap == 12 && cp.nd == 9) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 12, 4, 9>);
-        else if (ap == 12) HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 12, 4>);
-        else HI_CONV_LAUNCH(ntt_fwd_hi_conv_kernel<LOG_HI, 16, 4>);
+        if (cp.ap == 4) HI_CONV(regs, 4, 4);
+        else if (cp.ap == 8) HI_CONV(regs, 8, 8);
+        else if (cp.ap == 12 && cp.nd == 9) HI_CONV(regs, 12, 9);
+        else if (cp.ap == 12) HI_CONV(regs, 12, 12);
+        else HI_CONV(regs, 16, 16);
+    }
+#undef HI_CONV
+}
+static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
+    switch (log_hi) {
+        case 1: launch_hi_conv_ap<1>(n_targets, digits, batch, st, args, pl, cp); break;
+        case 2: launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp); break;
+        case 3: launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp); break;
+        case 4: launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp); break;
+        case 5: launch_hi_conv_ap<5>(n_targets, digits, batch, st, args, pl, cp); break;
+        default: launch_hi_conv_ap<6>(n_targets, digits, batch, st, args, pl, cp); break;
     }
 }
-#undef HI_CONV_LAUNCH
-// n_targets: the most targets a digit of the launch has
-static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
-    cp.groups = (n_targets + 3) / 4;  // workgroups of four targets
-    const dim3 grid(1u << log_hi, cp.groups * batch, digits);
-    switch (log_hi) {
-        case 1: launch_hi_conv_ap<1>(grid, st, args, pl, cp); break;
-        case 2: launch_hi_conv_ap<2>(grid, st, args, pl, cp); break;
-        case 3: launch_hi_conv_ap<3>(grid, st, args, pl, cp); break;
-        case 4: launch_hi_conv_ap<4>(grid, st, args, pl, cp); break;
-        case 5: launch_hi_conv_ap<5>(grid, st, args, pl, cp); break;
-        default: launch_hi_conv_ap<6>(grid, st, args, pl, cp); break;
+
+// The whole-ring kernels: `entries` list entries (a conversion: the most targets of a digit), all digits at once.
+template <class A>
+static void launch_ring_as(bool inverse, bool mul, u32 entries, u32 digits, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue* conv,
+                           const FwdEpilogue* ep) {
+    const dim3 grid(entries, args.batch, digits), block(RING_THREADS);
+    if (inverse) {
+        if constexpr (std::is_same<A, ArithF64>::value) {
+            if (mul) {
+                hipLaunchKernelGGL((ntt_inv_ring_kernel<A, true>), grid, block, 0, st, args, pl);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((ntt_inv_ring_kernel<A, false>), grid, block, 0, st, args, pl);
+        return;
     }
+    ConvPrologue cp = {};
+    if (conv) cp = *conv;
+    const int em = ep ? div_operands(args, *ep) : 0;
+#define RING_LAUNCH(AP, ND)                                                                                                          \
+    do {                                                                                                                             \
+        if (ep) hipLaunchKernelGGL((ntt_fwd_ring_div_kernel<A, AP, ND>), grid, block, 0, st, args, pl, cp, *ep, em);         \
+        else hipLaunchKernelGGL((ntt_fwd_ring_kernel<A, AP, ND>), grid, block, 0, st, args, pl, cp);                         \
+    } while (0)
+    if constexpr (std::is_same<A, ArithF64>::value) {
+        if (conv) {
+            if (cp.ap == 4 && cp.nd == 1) RING_LAUNCH(4, 1);
+            else if (cp.ap == 4) RING_LAUNCH(4, 4);
+            else if (cp.ap == 8) RING_LAUNCH(8, 8);
+            else if (cp.ap == 12 && cp.nd == 9) RING_LAUNCH(12, 9);
+            else if (cp.ap == 12) RING_LAUNCH(12, 12);
+            else RING_LAUNCH(16, 16);
+            return;
+        }
+    }
+    RING_LAUNCH(0, 1);
+#undef RING_LAUNCH
+}
+static void launch_ring(const ckks_ctx* c, bool inverse, bool mul, u32 entries, u32 digits, hipStream_t st, const NttArgs& args, const PolyList& pl,
+                        const ConvPrologue* conv, const FwdEpilogue* ep) {
+    if (c->ntt_f64) launch_ring_as<ArithF64>(inverse, mul, entries, digits, st, args, pl, conv, ep);
+    else launch_ring_as<ArithU64>(inverse, mul, entries, digits, st, args, pl, conv, ep);
 }
 
 static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
@@ -1463,6 +1692,12 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
         ProfScope ps__(c, inverse ? K_NTT_INV_LO : K_NTT_FWD_LO, st, pass_bytes, 0.5 * polys * c->N * c->log_n);
         if (inverse) hipLaunchKernelGGL(ntt_small_kernel<true>, dim3(1, polys), block, 0, st, args, pl);
         else hipLaunchKernelGGL(ntt_small_kernel<false>, dim3(1, polys), block, 0, st, args, pl);
+        return hipGetLastError();
+    }
+    if (ntt_one_pass(c)) {
+        const double ring_bytes = conv ? 8.0 * c->N * batch * ((double)conv->nd + (epilogue ? 2.0 : 1.0) * pl.n) : (mul_ptrs || epilogue ? 1.5 : 1.0) * pass_bytes;
+        ProfScope ps__(c, inverse ? K_NTT_INV_LO : K_NTT_FWD_LO, st, ring_bytes, 0.5 * polys * c->N * c->log_n);
+        launch_ring(c, inverse, mul_ptrs != nullptr, pl.n, 1, st, args, pl, conv, epilogue);
         return hipGetLastError();
     }
     const dim3 grid(c->N >> CKKS_TILE_LOG, polys);  // hi pass: one workgroup per 2^11 points
@@ -1593,6 +1828,11 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
         args.last = 0;
         args.batch = n;
         args.beta = 0;
+        if (!hi_only && ntt_one_pass(c)) {  // (a launch of these rings is always small: all digits)
+            ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (double)L1 + rows), 0.5 * rows * c->N * c->log_n);
+            launch_ring(c, false, false, most, nj, st, args, all, &cp, nullptr);
+            continue;
+        }
         {
             ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * (n * (together ? (double)L1 : (double)(E - most)) + rows), 0.5 * rows * c->N * c->log_hi);
             launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp);

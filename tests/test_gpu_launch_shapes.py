@@ -89,3 +89,32 @@ def test_masked_sums_of_the_layout(batch, base):
     first rotations than one launch takes (36 = 32 + 4) with a sum that has masks for four of them only."""
     k = fc_case(8, 1, batch, base, seed=700 + batch)
     assert np.array_equal(hx.to_host(k["run"]()), k["want"])
+
+
+@pytest.mark.parametrize("bits,dnum,level", [(50, 3, 6), (50, 1, 6), (50, 7, 3), (57, 3, 5)])
+def test_whole_ring_kernels(bits, dnum, level):
+    """The one-workgroup transforms of N = 2^12, both arithmetics: in place and from a list, batches and any order of moduli,
+    conversions of digits of three (ragged), seven and one limbs, divisions without operands (key switch, rescale), with an addend
+    (unhoisted rotation) and with a mask (the single-channel convolution is compared in the other tests)."""
+    p = make_params(12, 7, 7 if dnum == 1 else 3, dnum, bits=bits)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(5000 + bits + dnum)
+    idx = [p.num_q, 0, 6, 3, 1]
+    polys = np.stack([rand_poly(rng, [p.moduli[t] for t in idx], orc.N) for _ in range(3)])
+    polys[0, :, :2] = [[0, p.moduli[t] - 1] for t in idx]
+    d = hx.from_host(polys)
+    hx.ckks_ntt_fwd(ctx, d, idx)
+    assert np.array_equal(hx.to_host(d), orc.ntt_many(polys, idx))
+    hx.ckks_ntt_inv(ctx, d, idx)
+    assert np.array_equal(hx.to_host(d), polys)
+    ct = rand_ct(rng, p.moduli, level, orc.N)
+    offs = [5, -2]
+    keys = [np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)]) for _ in offs]
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, r)) for k, r in zip(keys, offs)]
+    d_ct = hx.from_host(ct)
+    assert np.array_equal(hx.to_host(hx.ckks_keyswitch(ctx, hx.from_host(ct[1]), level, dkeys[0])), orc.keyswitch(ct[1], keys[0], level))
+    assert np.array_equal(hx.to_host(hx.ckks_rescale(ctx, d_ct, level)), orc.rescale(ct, level))
+    for hoisted in (True, False):
+        outs = hx.ckks_rotate_hoisted(ctx, d_ct, level, offs, dkeys, hoisted)
+        for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, hoisted)):
+            assert np.array_equal(hx.to_host(got), want)
