@@ -1552,11 +1552,18 @@ static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& a
     else launch_inv_lo_it<A, 1>(grid, st, args, pl, mul);
 }
 
-// four target limbs per workgroup share one fetch of the source residues
+// Target limbs per workgroup: four share one fetch of the source residues; in a launch that would not give every CU two
+// workgroups, two or one, each done sooner (one polynomial pair's rescale at N = 2^16, 12 limbs: 13.1 us with four, 8.9 with one; six
+// decompositions of digits of three limbs at N = 2^13: 9.3 and 6.6).
 template <int LOG_HI, int AP, int ND>
 static void launch_hi_conv_regs(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
-    cp.groups = (n_targets + 3) / 4;
-    hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 4, ND>), dim3(1u << LOG_HI, cp.groups * batch, digits), dim3(NTT_THREADS), 0, st, args, pl, cp);
+    u32 t = 4;
+    while (t > 1 && ((n_targets + t - 1) / t * batch * digits << LOG_HI) < 512) t >>= 1;
+    cp.groups = (n_targets + t - 1) / t;
+    const dim3 grid(1u << LOG_HI, cp.groups * batch, digits), block(NTT_THREADS);
+    if (t == 4) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 4, ND>), grid, block, 0, st, args, pl, cp);
+    else if (t == 2) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 2, ND>), grid, block, 0, st, args, pl, cp);
+    else hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 1, ND>), grid, block, 0, st, args, pl, cp);
 }
 template <int LOG_HI, int AP, int ND>
 static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
