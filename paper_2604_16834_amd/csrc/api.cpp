@@ -294,6 +294,46 @@ int run_rescale_lin(const ckks_ctx* c, u32 level, const u64* const* xs, size_t x
     return CKKS_OK;
 }
 
+// lin (optional): an addend ka * x + kb * y of a ciphertext product, formed on the fly.
+struct LinAddend {
+    const u64* const* x;
+    size_t x_cstride;
+    const u64* ka;
+    const u64* const* y;
+    size_t y_cstride;
+    const u64* kb;
+};
+
+// n <= CT_BATCH ciphertext products with relinearisation in contexts with the fused inner product: no tensor-product kernel, d2 =
+// a1 (.) b1 is formed as the inverse transform loads it, P d0, P d1 and the own-limb term as the inner product's last terms, all
+// from the operands themselves; dividing the sums by P (merged: by P*q_level) is then the whole product.
+int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride, const u64* d_rlk,
+                u64* const* outs, u32 n, const KsWs& ws, hipStream_t st, bool merged, const LinAddend* lin = nullptr) {
+    const u64 *a1[CT_BATCH], *b1[CT_BATCH], *keys[CT_BATCH];
+    u64* vs[CT_BATCH];
+    FinalItem items[CT_BATCH];
+    for (u32 i = 0; i < n; i++) {
+        a1[i] = a[i] + a_cstride;
+        b1[i] = b[i] + b_cstride;
+        vs[i] = ws.v + i * ws.v_b;
+        keys[i] = d_rlk;
+        items[i] = FinalItem{nullptr, nullptr, nullptr, outs[i], 1, 0};
+    }
+    int rc = run_modup(c, level, a1, n, ws, st, true, b1);
+    if (rc) return rc;
+    MacProduct prod = {a, a1, b, b1};
+    if (lin) {
+        prod.lin_x = lin->x;
+        prod.x_cstride = lin->x_cstride;
+        prod.ka = lin->ka;
+        prod.lin_y = lin->y;
+        prod.y_cstride = lin->y_cstride;
+        prod.kb = lin->kb;
+    }
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, &prod));
+    return run_moddown(c, level, ws, n, items, st, merged);
+}
+
 // n <= CT_BATCH products a[b]*b[b] with relinearisation (operands possibly at a higher level:
 // component strides given); outs[b] = [2][level+1][N]
 int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride,
@@ -304,46 +344,27 @@ int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride
     u64* d2 = ar.take(n * L1 * N);
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
+    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);
     HIP_TRY(launch_tensor(c, level, ptr_list(a, n), a_cstride, ptr_list(b, n), b_cstride, d0, d1, d2, n, nullptr, 0, st));
-    const u64* d2s[CT_BATCH];
+    const u64 *d2s[CT_BATCH], *keys[CT_BATCH];
+    u32 gs[CT_BATCH];
     FinalItem items[CT_BATCH];
     for (u32 i = 0; i < n; i++) {
         d2s[i] = d2 + i * L1 * N;
+        keys[i] = d_rlk;
+        gs[i] = 1;
         items[i] = FinalItem{d0 + i * L1 * N, d1 + i * L1 * N, nullptr, outs[i], 1, 0};
     }
-    const bool mac = ntt_has_mac(c);  // the inner product inside the forward transforms' second pass
-    int rc = run_modup(c, level, d2s, n, ws, st, mac);
+    int rc = run_modup(c, level, d2s, n, ws, st);
     if (rc) return rc;
-    if (mac) {
-        const u64* keys[CT_BATCH];
-        u64* vs[CT_BATCH];
-        for (u32 i = 0; i < n; i++) {
-            keys[i] = d_rlk;
-            vs[i] = ws.v + i * ws.v_b;
-        }
-        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st));
-    } else {
-        const u64* keys[CT_BATCH];
-        u32 gs[CT_BATCH];
-        for (u32 i = 0; i < n; i++) keys[i] = d_rlk, gs[i] = 1;
-        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), keys, gs, nullptr, ws.v, ws.v_b, n, st));
-    }
+    HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), keys, gs, nullptr, ws.v, ws.v_b, n, st));
     return run_moddown(c, level, ws, n, items, st);
 }
 
 // n <= CT_BATCH products Rescale(a[b]*b[b] + addend[b]) with the relinearisation's ModDown and the rescale merged into
 // one division by P*q_level: the tensor product's d0, d1 (plus the addend) enter the extended basis as P times
 // themselves inside the inner-product kernel.  addend (optional): n ciphertexts [2][level+1][N], item stride
-// add_bstride.  outs[b] = [2][level][N].
-// lin (optional, contexts with the fused inner product only, instead of addend): the addend is ka * x + kb * y, formed on the fly.
-struct LinAddend {
-    const u64* const* x;
-    size_t x_cstride;
-    const u64* ka;
-    const u64* const* y;
-    size_t y_cstride;
-    const u64* kb;
-};
+// add_bstride; in contexts with the fused inner product it is given as lin instead.  outs[b] = [2][level][N].
 int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride,
                     const u64* addend, size_t add_bstride, const u64* d_rlk, u64* const* outs, u32 n, Arena ar, hipStream_t st,
                     const LinAddend* lin = nullptr) {
@@ -356,34 +377,10 @@ int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_
     const bool mac = ntt_has_modup(c);  // the inner product inside the forward transforms' second pass
     if (lin && (!mac || addend)) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: linear addend without the fused inner product");
     if (mac && addend) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: with the fused inner product the addend is given as a linear combination");
+    if (mac) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, true, lin);
     const u64 *d2s[CT_BATCH], *add0[CT_BATCH], *add1[CT_BATCH];
     u64* vs[CT_BATCH];
     FinalItem items[CT_BATCH];
-    if (mac) {
-        // no tensor-product kernel either: d2 = a1 (.) b1 is formed as the inverse transform loads it, d0, d1 and the own-limb
-        // term as the inner product's last terms, all from the operands themselves
-        const u64 *a1[CT_BATCH], *b1[CT_BATCH], *keys[CT_BATCH];
-        for (u32 i = 0; i < n; i++) {
-            a1[i] = a[i] + a_cstride;
-            b1[i] = b[i] + b_cstride;
-            vs[i] = ws.v + i * ws.v_b;
-            keys[i] = d_rlk;
-            items[i] = FinalItem{nullptr, nullptr, nullptr, outs[i], 1, 0};
-        }
-        int rc = run_modup(c, level, a1, n, ws, st, true, b1);
-        if (rc) return rc;
-        MacProduct prod = {a, a1, b, b1};
-        if (lin) {
-            prod.lin_x = lin->x;
-            prod.x_cstride = lin->x_cstride;
-            prod.ka = lin->ka;
-            prod.lin_y = lin->y;
-            prod.y_cstride = lin->y_cstride;
-            prod.kb = lin->kb;
-        }
-        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, &prod));
-        return run_moddown(c, level, ws, n, items, st, true);
-    }
     HIP_TRY(launch_tensor(c, level, ptr_list(a, n), a_cstride, ptr_list(b, n), b_cstride, d0, d1, d2, n, addend, add_bstride, st));
     for (u32 i = 0; i < n; i++) {
         d2s[i] = d2 + i * L1 * N;
