@@ -423,7 +423,6 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     u64* xs = ar.take((size_t)d->c_in * 9 * x_elems);
     u64* acc = ar.take((size_t)d->c_out * x_elems);
     u64* wscratch = ar.take(weighted_sum_scratch_elems(c, E, d->c_in * 9, d->c_out));
-    u64* kscratch = ar.take(key_inner_taps_scratch_elems(c, level, 8));
     // Batches of input channels (alignment) and of output channels (division) are independent: with room for two sets of
     // scratch every other batch runs on the library's side stream, between a fork and a join on the caller's stream.
     const size_t lane_bytes = ws_conv_lane(c, level);
@@ -494,8 +493,8 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
             ttap[n_taps++] = t;
         }
         if (fused_taps) {
-            HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), tkeys, tg, tmasks, ttap, n_taps, in, xs, xl, c0 * 9, 9, n, kscratch,
-                                          c0 == 0, st, centre_mask, centre_tap));  // the masked keys are made once, by the first batch
+            HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), tkeys, tg, tmasks, ttap, n_taps, in, xs, xl, c0 * 9, 9, n, st, centre_mask,
+                                          centre_tap));
         } else {  // many digits: one launch per tap (classic layout: every term is a [2][E][N] array)
             for (u32 i = 0; i < n_taps; i++) {
                 u64* outs[CT_BATCH];
@@ -506,11 +505,9 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
         return CKKS_OK;
     };
     int rc;
-    for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += CT_BATCH, k++) {
-        // the first batch also prepares the masked keys on the caller's stream; the fork comes after it
-        if ((rc = align_batch(c0, lanes[k == 0 ? 0 : (n_lanes == 2 ? k & 1 : 0)]))) return join(rc);
-        if (k == 0 && c0 + CT_BATCH < d->c_in && (rc = fork())) return rc;
-    }
+    if (d->c_in > CT_BATCH && (rc = fork())) return rc;
+    for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += CT_BATCH, k++)
+        if ((rc = align_batch(c0, lanes[forked ? k & 1 : 0]))) return join(rc);
     if ((rc = join(CKKS_OK))) return rc;
     HIP_TRY(launch_weighted_sum(c, level, true, xs, xl, d->c_in * 9, w_res, d->c_out, acc, wscratch, d->weight_bits, st0));
     if (d->c_out > CT_BATCH && (rc = fork())) return rc;
@@ -541,7 +538,7 @@ hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64
                          const u32* pos, u32 n_taps, hipStream_t st) {
     if (c->live_digits(level) <= 4)
         return launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys, gs, nullptr, pos, n_taps, cts, ws.v, XLayout::classic(c->ext_limbs(level), c->N),
-                                     0, 1, n, nullptr, false, st, nullptr, 0, true);
+                                     0, 1, n, st);
     for (u32 i = 0; i < n_taps; i++) {
         const u64* k[CT_BATCH];
         u32 g[CT_BATCH];
@@ -781,7 +778,7 @@ int run_relayout_deferred(const ckks_ctx* c, u32 level, u32 n_ct, const u64* con
                 ttap[nt++] = l;
             }
             HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), tkeys, tg, nullptr, ttap, nt, in, X, XLayout::classic(c->ext_limbs(level), N), 0,
-                                          n_lo, n, nullptr, false, st, nullptr, 0, true));
+                                          n_lo, n, st));
         }
         HIP_TRY(launch_relayout_mac(c, level, true, X, masks, Vacc, n, n_lo, n_hi, st));
         const u32 n_v = n * n_hi;
@@ -886,7 +883,7 @@ size_t he_conv_workspace_bytes(const ckks_ctx* c, const he_conv_desc* d) {
         const size_t E = c->ext_limbs(d->level);
         const u32 lanes = (c->side && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;  // sized for overlap on
         return lanes * ws_conv_lane(c, d->level) + blk((size_t)d->c_in * 9 * 2 * E * N) + blk((size_t)d->c_out * 2 * E * N) +
-               blk(weighted_sum_scratch_elems(c, (u32)E, d->c_in * 9, d->c_out)) + blk(key_inner_taps_scratch_elems(c, d->level, 8));
+               blk(weighted_sum_scratch_elems(c, (u32)E, d->c_in * 9, d->c_out));
     }
     return ws_ks(c, d->level, CT_BATCH, CT_BATCH) + blk((size_t)d->c_in * 9 * 2 * L1 * N) + blk((size_t)d->c_out * 2 * L1 * N) +
            blk(weighted_sum_scratch_elems(c, (u32)L1, d->c_in * 9, d->c_out)) + ws_rescale(c, d->level, CT_BATCH) +
@@ -1119,7 +1116,7 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             items[b].g = 1;  // the division's last step adds nothing: c0 is inside the sum already
         }
         if (hipError_t e = launch_key_inner_taps(c, level, dsrc(c, lw, 0), tkeys, tg, nullptr, ttap, nb, &ct, lw.v,
-                                                 XLayout::classic(c->ext_limbs(level), N), 0, 0, 1, nullptr, false, ls, nullptr, 0, true);
+                                                 XLayout::classic(c->ext_limbs(level), N), 0, 0, 1, ls);
             e != hipSuccess)
             return set_hip_err(c, e);
         int rc = run_moddown(c, level, lw, nb, items, ls);

@@ -402,42 +402,20 @@ struct TapSet {
     u32 centre_tap;
 };
 
-// The tap's mask is folded into the key before the batch runs: mk[i][j][comp][e][x] = mask_i[e][x] * key_i[j][comp][t(e)][x]
-// on the live digits and limbs, mp[i][e][x] = mask_i[e][x] * [P]_{q_e} for e <= level.  Then
-//   mask * (sum_j d_j key_j + P c0) = sum_j d_j mk_j + c0 mp
-// is one unreduced sum with one reduction per result: the per-result mask product (half of the arithmetic)
-// is gone.  Costs one pass over the eight keys per call.
-__global__ __launch_bounds__(KS_THREADS) void mask_keys_kernel(TapSet T, u64* __restrict__ mk, u64* __restrict__ mp,
-                                                               const u64* __restrict__ negp, const ModConst* __restrict__ mc, u32 N,
-                                                               u32 level, u32 num_q, u32 M, u32 E, u32 beta) {
-    const u32 x = blockIdx.x * KS_THREADS + threadIdx.x;
-    if (x >= N) return;
-    const u32 e = blockIdx.y, i = blockIdx.z;
-    const u32 t = e <= level ? e : num_q + (e - level - 1);
-    const ModConst m = mc[t];
-    if (i == T.n_taps) {  // the centre tap has no key: only mask * P
-        if (e <= level) mp[((size_t)i * (level + 1) + e) * N + x] = mulmod_barrett(T.centre_mask[(size_t)e * N + x], m.q - negp[e], m);
-        return;
-    }
-    const u64 mv = T.mask[i] ? T.mask[i][(size_t)e * N + x] : 1;  // no mask: the key as it is, and P
-    for (u32 j = 0; j < beta; j++)
-        for (u32 comp = 0; comp < 2; comp++)
-            mk[((((size_t)i * beta + j) * 2 + comp) * E + e) * N + x] = mulmod_barrett(mv, T.key[i][(((size_t)j * 2 + comp) * M + t) * N + x], m);
-    if (e <= level) mp[((size_t)i * (level + 1) + e) * N + x] = mulmod_barrett(mv, m.q - negp[e], m);
-}
-
 // F64: every modulus below 2^50: the sums of BETA + 1 products as chains of fused multiply-adds on centred doubles (f64m_dot_w:
 // four full-rate operations per term where a split integer sum takes three quarter-rate 64-bit multiply-adds and the splits:
 // 117 registers instead of 232, 776 us instead of 904 for eight ciphertexts and nine taps at N = 2^16); the digits and the
 // ciphertext's words are centred once per thread, a tap's key words once per tap.  Otherwise 128-bit integer sums.
-template <int BETA, bool F64>
-__global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc digits, TapSet T,
-                                                                    const u64* __restrict__ mk, const u64* __restrict__ mp,
-                                                                    PtrList8 c0s, u64* __restrict__ xs, XLayout xl, u32 k0base,
-                                                                    u32 k_bstride, const ModConst* __restrict__ mc, u32 log_n,
+// NB: most ciphertexts of the launch (their digits are held in registers).
+// MASKED: every result is multiplied by its tap's mask word (one product per result; folding the masks into copies of the keys
+// beforehand, as this kernel did while its sums were integers, writes and reads the eight keys once more per call, 329 of 16600 us for 64
+// channels at N = 2^16 and 10.8 of 73 us for three at 2^13; the eight-channel launch takes 780 us instead of 770).
+template <int BETA, bool F64, int NB, bool MASKED>
+__global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc digits, TapSet T, PtrList8 c0s, u64* __restrict__ xs, XLayout xl,
+                                                                    u32 k0base, u32 k_bstride, const ModConst* __restrict__ mc, u32 log_n,
                                                                     u32 level, u32 num_q, u32 E, u32 n, u32 M, const u64* __restrict__ negp,
-                                                                    const ModConstF* __restrict__ mcf) {
-    // negp != nullptr: no masks; the keys are read where they are (T.key[i]: [dnum][2][M][N]) and mask * P is P itself
+                                                                    const ModConstF* __restrict__ mcf, u32 taps_per_wg) {
+    // blockIdx.z: which taps_per_wg of the taps
     const u32 N = 1u << log_n;
     const u32 xsrc = blockIdx.x * KS_THREADS + threadIdx.x;
     if (xsrc >= N) return;
@@ -445,11 +423,10 @@ __global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc dig
     const u32 t = e <= level ? e : num_q + (e - level - 1);
     const ModConst m = mc[t];
     const bool has_add = e <= level;
-    const bool direct = negp != nullptr;
-    const u64 pres = (direct && has_add) ? m.q - negp[e] : 0;  // P mod q_e
-    u64 dv[CT_BATCH][BETA], cv[CT_BATCH];
+    const u64 pres = has_add ? m.q - negp[e] : 0;  // P mod q_e
+    u64 dv[NB][BETA], cv[NB];
 #pragma unroll
-    for (u32 b = 0; b < CT_BATCH; b++) {
+    for (u32 b = 0; b < NB; b++) {
         const bool on = b < n;
         cv[b] = (on && has_add) ? c0s.p[b][(size_t)e * N + xsrc] : 0;
 #pragma unroll
@@ -461,42 +438,46 @@ __global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc dig
         const double d = f64m_from_u64(v);
         return d > halfq ? d - qd : d;
     };
-    double yd[CT_BATCH][BETA + 1];  // F64: digits and the ciphertext's word of every batch item
+    double yd[NB][BETA + 1];  // F64: digits and the ciphertext's word of every batch item
     if (F64) {
 #pragma unroll
-        for (u32 b = 0; b < CT_BATCH; b++) {
+        for (u32 b = 0; b < NB; b++) {
 #pragma unroll
             for (u32 j = 0; j < BETA; j++) yd[b][j] = centred(dv[b][j]);
             yd[b][BETA] = centred(cv[b]);
         }
     }
-    for (u32 i = 0; i < T.n_taps; i++) {
+    const u32 i0 = blockIdx.z * taps_per_wg, i1 = min(T.n_taps, i0 + taps_per_wg);
+    for (u32 i = i0; i < i1; i++) {
         const u32 x = galois_gather_index(xsrc, T.ginv[i], log_n);  // destination point
         u64 k0[BETA], k1[BETA];
 #pragma unroll
         for (u32 j = 0; j < BETA; j++) {
-            const u64* kb = direct ? T.key[i] + (((size_t)j * 2) * M + t) * N + x : mk + ((((size_t)i * BETA + j) * 2) * E + e) * N + x;
+            const u64* kb = T.key[i] + (((size_t)j * 2) * M + t) * N + x;
             k0[j] = kb[0];
-            k1[j] = kb[(size_t)(direct ? M : E) * N];
+            k1[j] = kb[(size_t)M * N];
         }
-        const u64 kp = direct ? pres : (has_add ? mp[((size_t)i * (level + 1) + e) * N + x] : 0);
+        const u64 mk = MASKED ? T.mask[i][(size_t)e * N + x] : 0;
         u64* ot = xs + xl.at(k0base + T.tap[i], 0, e, x);
         if (F64) {
             double w0[BETA + 1], w1[BETA];
 #pragma unroll
             for (u32 j = 0; j < BETA; j++) { w0[j] = centred(k0[j]); w1[j] = centred(k1[j]); }
-            w0[BETA] = centred(kp);  // zero on the special primes
+            w0[BETA] = centred(pres);  // zero on the special primes
+            const double md = f64m_from_u64(mk);
 #pragma unroll
-            for (u32 b = 0; b < CT_BATCH; b++) {
+            for (u32 b = 0; b < NB; b++) {
                 if (b < n) {
                     u64* ob = ot + (size_t)b * k_bstride * xl.s_k;
-                    ob[0] = f64m_canonical(f64m_dot_w<BETA + 1>(yd[b], w0, qd, qinv), qd);
-                    ob[xl.s_comp] = f64m_canonical(f64m_dot_w<BETA>(yd[b], w1, qd, qinv), qd);
+                    double r0 = f64m_dot_w<BETA + 1>(yd[b], w0, qd, qinv), r1 = f64m_dot_w<BETA>(yd[b], w1, qd, qinv);
+                    if (MASKED) r0 = f64m_mulmod_any(r0, md, qd, qinv), r1 = f64m_mulmod_any(r1, md, qd, qinv);
+                    ob[0] = f64m_canonical(r0, qd);
+                    ob[xl.s_comp] = f64m_canonical(r1, qd);
                 }
             }
         } else {
 #pragma unroll
-            for (u32 b = 0; b < CT_BATCH; b++) {
+            for (u32 b = 0; b < NB; b++) {
                 if (b < n) {
                     U128 acc0 = {0, 0}, acc1 = {0, 0};
 #pragma unroll
@@ -504,19 +485,21 @@ __global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc dig
                         acc_wide(acc0, dv[b][j], k0[j]);
                         acc_wide(acc1, dv[b][j], k1[j]);
                     }
-                    acc_wide(acc0, cv[b], kp);
+                    acc_wide(acc0, cv[b], pres);
                     u64* ob = ot + (size_t)b * k_bstride * xl.s_k;
-                    ob[0] = barrett_reduce(acc0, m);
-                    ob[xl.s_comp] = barrett_reduce(acc1, m);
+                    u64 r0 = barrett_reduce(acc0, m), r1 = barrett_reduce(acc1, m);
+                    if (MASKED) r0 = mulmod_barrett(r0, mk, m), r1 = mulmod_barrett(r1, mk, m);
+                    ob[0] = r0;
+                    ob[xl.s_comp] = r1;
                 }
             }
         }
     }
-    if (T.centre_mask) {  // no rotation: mask * P * ct on the live limbs, zero on the special primes
-        const u64 kp = has_add ? mp[((size_t)T.n_taps * (level + 1) + e) * N + xsrc] : 0;
+    if (T.centre_mask && blockIdx.z == 0) {  // no rotation: mask * P * ct on the live limbs, zero on the special primes
+        const u64 kp = has_add ? mulmod_barrett(T.centre_mask[(size_t)e * N + xsrc], pres, m) : 0;
         u64* ot = xs + xl.at(k0base + T.centre_tap, 0, e, xsrc);
 #pragma unroll
-        for (u32 b = 0; b < CT_BATCH; b++) {
+        for (u32 b = 0; b < NB; b++) {
             if (b < n) {
                 const u64 c1 = has_add ? c0s.p[b][((size_t)(level + 1) + e) * N + xsrc] : 0;
                 u64* ob = ot + (size_t)b * k_bstride * xl.s_k;
@@ -527,28 +510,16 @@ __global__ __launch_bounds__(KS_THREADS) void key_inner_taps_kernel(DigitSrc dig
     }
 }
 
-// words of scratch launch_key_inner_taps needs (the masked keys)
-size_t key_inner_taps_scratch_elems(const ckks_ctx* c, u32 level, u32 n_taps) {
-    return (size_t)n_taps * c->N * ((size_t)c->live_digits(level) * 2 * c->ext_limbs(level) + level + 1) + (size_t)c->N * (level + 1);
-}
-
-// keys / gs / masks / taps: n_taps <= 8 entries (taps[i] = position of tap i in the output's tap stride);
-// c0s: n <= CT_BATCH device pointers [level+1][N]; scratch: key_inner_taps_scratch_elems() words, filled by
-// prepare (once per set of taps) and read by every later call with prepare = false.
+// keys / gs / masks / taps: n_taps <= 8 entries (taps[i] = position of tap i in the output's tap stride); masks: null, or one
+// [E][N] plaintext per tap; c0s: n <= CT_BATCH device pointers [2][level+1][N].
 // Needs beta <= 4 (returns hipErrorNotSupported otherwise: the caller then falls back to one launch per tap).
 hipError_t launch_key_inner_taps(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys,
                                  const u32* gs, const u64* const* masks, const u32* taps, u32 n_taps, const u64* const* c0s,
-                                 u64* xs, XLayout xl, u32 k0, u32 k_bstride, u32 n, u64* scratch, bool prepare, hipStream_t st,
-                                 const u64* centre_mask, u32 centre_tap, bool direct_keys) {
-    if (n_taps == 0 || n == 0) return hipSuccess;
+                                 u64* xs, XLayout xl, u32 k0, u32 k_bstride, u32 n, hipStream_t st, const u64* centre_mask, u32 centre_tap) {
+    if ((n_taps == 0 && !centre_mask) || n == 0) return hipSuccess;
     if (n_taps > 8 || n > CT_BATCH) return hipErrorInvalidValue;
-    if (direct_keys) {  // no masks, no prepared copies: the keys are read where they are
-        if (centre_mask) return hipErrorInvalidValue;
-        for (u32 i = 0; i < n_taps; i++)
-            if (masks && masks[i]) return hipErrorInvalidValue;
-    } else if (!scratch || !masks) {
-        return hipErrorInvalidValue;
-    }
+    for (u32 i = 0; i < n_taps; i++)
+        if (!keys[i] || (masks && !masks[i])) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     if (beta > 4) return hipErrorNotSupported;
     TapSet T;
@@ -572,34 +543,40 @@ hipError_t launch_key_inner_taps(const ckks_ctx* c, u32 level, const DigitSrc& d
     T.centre_tap = centre_tap;
     PtrList8 cl;
     for (u32 b = 0; b < KS_MAX_BATCH; b++) cl.p[b] = b < n ? c0s[b] : nullptr;
-    u64* mk = scratch;
-    u64* mp = direct_keys ? nullptr : scratch + (size_t)n_taps * beta * 2 * E * c->N;
     const u32 nxb = (c->N + KS_THREADS - 1) / KS_THREADS;
     const u64* negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
-    const u64* negp_direct = direct_keys ? negp : nullptr;
-    if (prepare && !direct_keys) {
-        ProfScope ps__(c, K_MASK_MUL, st, 8.0 * c->N * n_taps * (E * (4.0 * beta + 1.0) + level + 1.0), 2.0 * c->N * n_taps * E * beta);
-        hipLaunchKernelGGL(mask_keys_kernel, dim3(nxb, E, n_taps + (centre_mask ? 1 : 0)), dim3(KS_THREADS), 0, st, T, mk, mp, negp, c->d_mc, c->N, level, c->num_q,
-                           c->M, E, beta);
-    }
-    dim3 grid(nxb, E);
-    // digits and c0 once per batch, per tap one masked key and the outputs
-    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (n * (double)beta + n_taps * (2.0 * beta + 2.0 * n)) + (n + n_taps) * (level + 1.0)),
-                   2.0 * n_taps * n * c->N * E * (beta + 1.0));
+    // Taps per workgroup: all, so that the digits are read once for them; in a launch that does not give every CU four workgroups
+    // the taps one after the other are a serial chain next to idle CUs, and what is read again comes from cache: fewer per
+    // workgroup (one channel, eight taps, 6 limbs at N = 2^12: 10.2 us with eight, 7.1 with one)
+    u32 taps_per_wg = 8;
+    while (taps_per_wg > 1 && nxb * E * ((n_taps + taps_per_wg - 1) / taps_per_wg) < 1024) taps_per_wg >>= 1;
+    const u32 groups = (n_taps + taps_per_wg - 1) / taps_per_wg;
+    dim3 grid(nxb, E, groups ? groups : 1);
+    // digits and c0 once per batch, per tap one key, one mask and the outputs
+    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (n * (double)beta + n_taps * (2.0 * beta + (masks ? 1.0 : 0.0) + 2.0 * n)) + n * (level + 1.0)),
+                   2.0 * n_taps * n * c->N * E * (beta + 1.0 + (masks ? 1.0 : 0.0)));
+#define KI_TAPS_LAUNCH(B_, F_, NB_, M_)                                                                                              \
+    hipLaunchKernelGGL((key_inner_taps_kernel<B_, F_, NB_, M_>), grid, dim3(KS_THREADS), 0, st, digits, T, cl, xs, xl, k0, k_bstride, \
+                       c->d_mc, c->log_n, level, c->num_q, E, n, c->M, negp, c->d_mcf, taps_per_wg)
+#define KI_TAPS_NB(B_, M_)                                                                                                           \
+    do {                                                                                                                             \
+        if (!c->small_q) KI_TAPS_LAUNCH(B_, false, CT_BATCH, M_);                                                                    \
+        else if (n == 1) KI_TAPS_LAUNCH(B_, true, 1, M_);                                                                            \
+        else if (n <= 4) KI_TAPS_LAUNCH(B_, true, 4, M_);                                                                            \
+        else KI_TAPS_LAUNCH(B_, true, CT_BATCH, M_);                                                                                 \
+    } while (0)
 #define KI_TAPS(B_)                                                                                                                  \
     do {                                                                                                                             \
-        if (c->small_q)                                                                                                              \
-            hipLaunchKernelGGL((key_inner_taps_kernel<B_, true>), grid, dim3(KS_THREADS), 0, st, digits, T, mk, mp, cl, xs, xl, \
-                               k0, k_bstride, c->d_mc, c->log_n, level, c->num_q, E, n, c->M, negp_direct, c->d_mcf);                \
-        else                                                                                                                         \
-            hipLaunchKernelGGL((key_inner_taps_kernel<B_, false>), grid, dim3(KS_THREADS), 0, st, digits, T, mk, mp, cl, xs, xl, \
-                               k0, k_bstride, c->d_mc, c->log_n, level, c->num_q, E, n, c->M, negp_direct, c->d_mcf);                \
+        if (masks) KI_TAPS_NB(B_, true);                                                                                             \
+        else KI_TAPS_NB(B_, false);                                                                                                  \
     } while (0)
     if (beta == 1) KI_TAPS(1);
     else if (beta == 2) KI_TAPS(2);
     else if (beta == 3) KI_TAPS(3);
     else KI_TAPS(4);
 #undef KI_TAPS
+#undef KI_TAPS_NB
+#undef KI_TAPS_LAUNCH
     return hipGetLastError();
 }
 
