@@ -567,6 +567,25 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
     return run_moddown(c, level, ws, n, items, st);
 }
 
+// The same for ciphertexts that are given permuted, sigma_gal(src), in contexts with the fused inner product (the digits of a
+// permuted polynomial are the permuted digits): the extended digits are never written in evaluation form.
+int run_rotate_permuted(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, u64* const* outs, const KsWs& ws,
+                        hipStream_t st) {
+    const u64 *c1s[CT_BATCH], *kd[CT_BATCH];
+    u64* vs[CT_BATCH];
+    FinalItem items[CT_BATCH];
+    for (u32 b = 0; b < n; b++) {
+        c1s[b] = srcs[b] + (size_t)(level + 1) * c->N;
+        kd[b] = keys[b]->d_key;
+        vs[b] = ws.v + b * ws.v_b;
+        items[b] = FinalItem{srcs[b], nullptr, nullptr, outs[b], 1, 0};
+    }
+    int rc = run_modup(c, level, c1s, n, ws, st, true);
+    if (rc) return rc;
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st));
+    return run_moddown(c, level, ws, n, items, st);
+}
+
 size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) {
     const size_t N = c->N, L1 = level + 1;
     const u32 nb = g - 1 < CT_BATCH ? (g > 1 ? g - 1 : 1) : CT_BATCH;
@@ -587,8 +606,10 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the merge");
     const u64* masks[KS_MAX_BATCH];
     u64* mouts[KS_MAX_BATCH];
-    for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems;
-    HIP_TRY(launch_mask_mul(c, level, masks, cts, mouts, g, st));
+    u32 mg[KS_MAX_BATCH];
+    const bool permuted = ntt_has_mac(c);  // the blocks take their automorphism as they are masked
+    for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems, mg[i] = permuted && i ? gal[i] : 1;
+    HIP_TRY(launch_mask_mul(c, level, masks, cts, mouts, g, st, mg));
     // blocks 1..g-1: every block has its own key; a batch shares the decomposition and ModDown launches
     for (u32 i0 = 1; i0 < g; i0 += nb) {
         const u32 n = g - i0 < nb ? g - i0 : nb;
@@ -598,7 +619,7 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
             srcs[b] = masked + (i0 + b) * ct_elems;
             outs[b] = rotated + (i0 + b) * ct_elems;
         }
-        int rc = run_rotate_batch(c, level, n, srcs, keys + i0, gal + i0, outs, ws, st);
+        int rc = permuted ? run_rotate_permuted(c, level, n, srcs, keys + i0, outs, ws, st) : run_rotate_batch(c, level, n, srcs, keys + i0, gal + i0, outs, ws, st);
         if (rc) return rc;
     }
     const u64* terms[KS_MAX_BATCH];

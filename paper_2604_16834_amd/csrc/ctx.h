@@ -303,7 +303,8 @@ hipError_t launch_rescale_final(const ckks_ctx* c, u32 level, const PtrList8& ct
                                 u32 n, hipStream_t st);
 hipError_t launch_tensor(const ckks_ctx* c, u32 level, const PtrList8& a, size_t a_cstride, const PtrList8& b, size_t b_cstride,
                          u64* d0, u64* d1, u64* d2, u32 n, const u64* add, size_t add_bstride, hipStream_t st);
-hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st);
+hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st,
+                           const u32* gs = nullptr);
 hipError_t launch_key_expand_a(const ckks_ctx* c, u64 seed, u64* key, hipStream_t st);
 hipError_t launch_add_plain(const ckks_ctx* c, u32 level, const u64* pt, u64* ct, hipStream_t st);
 hipError_t launch_ct_sum(const ckks_ctx* c, u32 level, const PtrList8& items, u32 n, u64* out, hipStream_t st, bool extended = false);
