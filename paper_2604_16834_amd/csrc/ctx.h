@@ -244,6 +244,9 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 // add1s[b] (optional, [level+1][N]) on the q-limbs: outs[b] [2][E][N] is the finished inner product on the extended basis.
 hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st,
                             bool hi_only = false);
+// contexts with a modulus of 2^50 or more, two-pass transforms: digits [n][beta][E][N], coefficient form (but each digit's own
+// limbs, which are not touched) -> evaluation form
+hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, hipStream_t st);
 // prod: the decomposed polynomial is the d2 = a1 (.) b1 of n ciphertext products and was never stored (the inverse
 // transform took it as a product, launch_ntt with mul_ptrs): the term of the digits' own limbs and the addends
 // d0 = a0 (.) b0, d1 = a0 (.) b1 + a1 (.) b0 are formed from the operands (host arrays of n device pointers,
@@ -271,7 +274,7 @@ inline bool ntt_has_mac(const ckks_ctx* c) { return ntt_has_modup(c) && !ntt_one
 // whether launch_ntt can apply an epilogue in this ring (it needs the two-pass transform)
 inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LOG; }
 // keyswitch.hip
-hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digit,
+hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digits,
                              size_t digit_bstride, u32 n, hipStream_t st);
 // n <= CT_BATCH key switches, each with its key and Galois element; add0s (or null): P sigma_g(add0s[b]) joins component 0
 hipError_t launch_key_inner_items(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs,

@@ -29,15 +29,18 @@ __device__ __forceinline__ const u64* digit_row(const DigitSrc& D, u32 b, u32 j,
 // y     [nd][N]      digit limbs in coefficient form (canonical)
 // c_in  [level+1][N] the polynomial being switched, NTT form (source of the digit's own limbs)
 // digit [E][N]       out: own limbs copied (NTT form), other limbs in coefficient form
-__global__ __launch_bounds__(KS_THREADS) void modup_conv_kernel(const u64* __restrict__ y, size_t y_bstride, PtrList8 c_list,
+// This one takes digits j0 .. j0 + nj - 1 of every polynomial: y [level+1][N], digits [beta][E][N], tab the table of digit j0,
+// the next digit's tab_stride on; size: limbs per digit (the last may have fewer).
+__global__ __launch_bounds__(KS_THREADS) void modup_conv_kernel(const u64* __restrict__ y, size_t y_bstride,
                                                                 u64* __restrict__ digit, size_t digit_bstride,
-                                                                const u64* __restrict__ tab, const ModConst* __restrict__ mc, u32 N,
-                                                                u32 level, u32 num_q, u32 lo, u32 nd, u32 alpha, u32 M, u32 E, u32 lpb) {
+                                                                const u64* __restrict__ tab, size_t tab_stride, const ModConst* __restrict__ mc, u32 N,
+                                                                u32 level, u32 num_q, u32 size, u32 j0, u32 nj, u32 alpha, u32 M, u32 E, u32 lpb) {
     const u32 x = blockIdx.x * KS_THREADS + threadIdx.x;
     if (x >= N) return;
-    y += blockIdx.z * y_bstride;
-    digit += blockIdx.z * digit_bstride;
-    const u64* __restrict__ c_in = c_list.p[blockIdx.z];
+    const u32 b = blockIdx.z / nj, dj = blockIdx.z - b * nj, lo = (j0 + dj) * size, nd = min(size, level + 1 - lo);
+    y += b * y_bstride + (size_t)lo * N;
+    digit += b * digit_bstride + (size_t)(j0 + dj) * E * N;
+    tab += dj * tab_stride;
     u64 yv[KS_MAX_DIGIT];
     u64 n_neg = 0;
 #pragma unroll
@@ -139,17 +142,22 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* _
     }
 }
 
-// n <= KS_MAX_BATCH polynomials at once: item b reads y + b*y_bstride and c_in.p[b], writes digit + b*digit_bstride
-hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digit,
+// Digits j .. j + nj - 1 of n <= KS_MAX_BATCH polynomials at once (nj > 1 only with moduli of 2^50 and above): item b reads
+// y + b*y_bstride ([level+1][N]) and c_in.p[b], writes digits + b*digit_bstride ([beta][E][N])
+hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digits,
                              size_t digit_bstride, u32 n, hipStream_t st) {
     const u32 E = c->ext_limbs(level), lo = c->digit_lo(j), nd = c->digit_hi(j, level) - lo;
+    if (nj == 0 || j + nj > c->live_digits(level) || (nj > 1 && c->small_q)) return hipErrorInvalidValue;
+    u64* digit = digits + (size_t)j * E * c->N;
+    const u64* y_all = y;
+    y += (size_t)lo * c->N;
     // target limbs per thread: the digit's prepared residues are reused for all of them, but a small batch needs the
     // limbs spread over more workgroups to fill the chip
     const u32 x_wgs = (c->N + KS_THREADS - 1) / KS_THREADS;
-    const u32 lpb = x_wgs * n >= 1024 ? 32 : (x_wgs * n >= 512 ? 8 : 4);
-    dim3 grid(x_wgs, (E + lpb - 1) / lpb, n);
+    const u32 lpb = x_wgs * n * nj >= 1024 ? 32 : (x_wgs * n * nj >= 512 ? 8 : 4);
+    dim3 grid(x_wgs, (E + lpb - 1) / lpb, n * nj);
     const u64* tab = c->modup_table(level, j);
-    ProfScope ps__(c, K_MODUP_CONV, st, 8.0 * n * c->N * (2.0 * nd + E), (double)n * c->N * nd * (1.0 + E - nd));
+    ProfScope ps__(c, K_MODUP_CONV, st, 8.0 * n * nj * c->N * (2.0 * nd + E), (double)n * nj * c->N * nd * (1.0 + E - nd));
     if (c->ntt_f64 && c->d_modup_f) {
         const TwF* tf = c->modup_table_f(level, j);
         if (c->alpha_pad == 4)
@@ -166,8 +174,8 @@ hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, const u64* y, 
         else
             hipLaunchKernelGGL(modup_conv50_kernel<16>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
     } else {
-        hipLaunchKernelGGL(modup_conv_kernel, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, c->d_mc,
-                           c->N, level, c->num_q, lo, nd, c->alpha_pad, c->M, E, lpb);
+        hipLaunchKernelGGL(modup_conv_kernel, grid, dim3(KS_THREADS), 0, st, y_all, y_bstride, digits, digit_bstride, tab, c->modup_digit_stride(),
+                           c->d_mc, c->N, level, c->num_q, c->alpha, j, nj, c->alpha_pad, c->M, E, lpb);
     }
     return hipGetLastError();
 }

@@ -287,6 +287,12 @@ __device__ __forceinline__ u32 pl_at(const unsigned char* arr, u32 i) {
     return (w >> (8 * (i & 3))) & 0xffu;
 }
 
+// ModUp, all digits in one launch (launch_ntt_digits): whether entry a of row (polynomial, digit) is one of the digit's own limbs, which
+// are not transformed
+__device__ __forceinline__ bool own_limb(const NttArgs& args, u32 row, u32 a) {
+    return args.beta && a <= args.level && a / args.alpha == row % args.beta;
+}
+
 template <class A>
 struct PolyRef {
     const u64* src;
@@ -933,8 +939,10 @@ template <class A, int LOG_HI>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_kernel(NttArgs args, PolyList pl) {
     typedef typename A::E E;
     constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R;
-    const u32 tid = threadIdx.x;
-    const PolyRef<A> P = poly_ref<A>(args, pl, blockIdx.y / pl.n, blockIdx.y % pl.n);
+    const u32 tid = threadIdx.x, row = blockIdx.y / pl.n, a = blockIdx.y % pl.n;
+    if constexpr (!std::is_same<A, ArithF64>::value)
+        if (own_limb(args, row, a)) return;  // whole workgroup
+    const PolyRef<A> P = poly_ref<A>(args, pl, row, a);
     const u64* src = P.src + (size_t)blockIdx.x * CC;
     u64* dst = P.dst + (size_t)blockIdx.x * CC;
     E v[8];
@@ -1276,6 +1284,8 @@ __device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyLis
         if (cp.alpha) nd = min(cp.alpha, cp.n_src - lo);
         if (a >= (cp.alpha ? pl.n - nd : pl.n)) return;  // whole workgroup: a digit with more limbs has fewer targets
         if (cp.alpha && a >= lo) a += nd;
+    } else if constexpr (!std::is_same<A, ArithF64>::value) {
+        if (own_limb(args, b, a)) return;  // whole workgroup
     }
     PolyRef<A> P = poly_ref<A>(args, pl, b, a);
     if (AP) P.dst += dig * cp.dst_dstride;
@@ -1891,6 +1901,56 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
         ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_lo);
         launch_fwd_lo_loop<ArithF64>(args.batch, grid, st, args, pl);
     }
+    return hipGetLastError();
+}
+
+// The forward transforms of all digits of a ModUp with 64-bit integer butterflies (the conversions have written their target
+// limbs in coefficient form): rows (polynomial, digit), a digit's own limbs skipped.  One launch per pass for all digits at every size: the
+// passes are bound by instruction issue, so nothing is lost by a first pass that ends before the second starts, and a digit
+// alone ends with a part of the chip idle.  56-bit moduli, a launch per digit and pass (conversion included) and now, in us: one
+// unhoisted rotation of 7 limbs at N = 2^12 89.5 and 65.6, at 2^13 107.8 and 75.8, of 24 limbs at 2^16 293 and 257, four of those
+// 784 and 724; a product of 24 limbs 365 and 329.
+hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, hipStream_t st) {
+    if (c->ntt_f64 || c->log_hi == 0 || n == 0) return hipErrorInvalidValue;
+    const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
+    PolyList all;
+    all.n = E;
+    for (u32 e = 0; e < CKKS_MAX_MODULI; e++) {
+        all.spos[e] = all.dpos[e] = (unsigned char)(e < E ? e : 0);
+        all.mod[e] = (unsigned char)(e < E ? c->ext_modulus(level, e) : 0);
+    }
+    NttArgs args = {};
+    args.mc = c->d_mc;
+    args.tw = c->d_tw;
+    args.log_n = c->log_n;
+    args.log_lo = c->log_lo;
+    args.log_hi = c->log_hi;
+    args.src = args.dst = digits;  // rows (polynomial, digit) at a stride of E limb-polys
+    args.src_bstride = args.dst_bstride = E;
+    args.batch = n * beta;
+    args.beta = beta;
+    args.alpha = c->alpha;
+    args.level = level;
+    args.first = 1;
+    const double rows = n * ((double)beta * E - (level + 1.0));
+    if (ntt_one_pass(c)) {
+        args.last = 1;
+        ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_n);
+        launch_ring(c, false, false, E, 1, st, args, all, nullptr, nullptr);
+        return hipGetLastError();
+    }
+    {
+        ProfScope ps__(c, K_NTT_FWD_HI, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_hi);
+        launch_hi_any<ArithU64>(c->log_hi, false, dim3(c->N >> CKKS_TILE_LOG, E * args.batch), st, args, all);
+    }
+    args.first = 0;
+    args.last = 1;
+    const u32 slices = E << c->log_hi;
+    for (u32 g = 64; g >= 8; g >>= 1)
+        if (slices % g == 0) { args.lo_group = g; break; }
+    const dim3 grid = args.lo_group ? dim3(args.lo_group, 1, slices / args.lo_group) : dim3(1, slices);
+    ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_lo);
+    launch_fwd_lo_loop<ArithU64>(args.batch, grid, st, args, all);
     return hipGetLastError();
 }
 

@@ -83,6 +83,26 @@ def test_digits_together(log_n, num_q, num_p, dnum, level):
         assert np.array_equal(hx.to_host(got), want)
 
 
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(12, 7, 3, 3, 6), (12, 5, 5, 1, 4), (13, 9, 2, 5, 7), (15, 11, 4, 3, 8), (16, 6, 2, 3, 3)])
+def test_integer_digits_together(log_n, num_q, num_p, dnum, level):
+    """All digits of a decomposition in one launch per pass with 57-bit moduli: ragged last digits (1 of 3, 1 of 4 limbs), a single digit,
+    five digits of two limbs, fewer live digits than the key has; one, two and eight polynomials (unhoisted rotations), and
+    hoisted ones."""
+    p = make_params(log_n, num_q, num_p, dnum, bits=57)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(5000 + num_q)
+    ct = rand_ct(rng, p.moduli, level, orc.N)
+    offs = [1, -2, 3, 4, -5, 6, 7, -8][: 8 if log_n <= 12 else 2]
+    keys = [np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)]) for _ in offs]
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, r)) for k, r in zip(keys, offs)]
+    out = hx.ckks_keyswitch(ctx, hx.from_host(ct[1]), level, dkeys[0])
+    assert np.array_equal(hx.to_host(out), orc.keyswitch(ct[1], keys[0], level))
+    for hoisted in (False, True):
+        outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, dkeys, hoisted)
+        for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, hoisted)):
+            assert np.array_equal(hx.to_host(got), want)
+
+
 @pytest.mark.parametrize("batch,base", [(38, 3), (40, 36)])
 def test_masked_sums_of_the_layout(batch, base):
     """More second rotations than one launch of the masked sums takes (13 = 12 + 1, the last sum without its third mask), and more
