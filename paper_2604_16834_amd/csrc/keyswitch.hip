@@ -414,7 +414,8 @@ struct TapSet {
 // four full-rate operations per term where a split integer sum takes three quarter-rate 64-bit multiply-adds and the splits:
 // 117 registers instead of 232, 776 us instead of 904 for eight ciphertexts and nine taps at N = 2^16); the digits and the
 // ciphertext's words are centred once per thread, a tap's key words once per tap.  Otherwise 128-bit integer sums.
-// NB: most ciphertexts of the launch (their digits are held in registers).
+// NB: most ciphertexts of the launch (their digits are held in registers; hoisted 56-bit rotations, one ciphertext: 10.9e3 per second
+// with eight, 11.5e3 with one).
 // MASKED: every result is multiplied by its tap's mask word (one product per result; folding the masks into copies of the keys
 // beforehand, as this kernel did while its sums were integers, writes and reads the eight keys once more per call, 329 of 16600 us for 64
 // channels at N = 2^16 and 10.8 of 73 us for three at 2^13; the eight-channel launch takes 780 us instead of 770).
@@ -568,7 +569,8 @@ hipError_t launch_key_inner_taps(const ckks_ctx* c, u32 level, const DigitSrc& d
                        c->d_mc, c->log_n, level, c->num_q, E, n, c->M, negp, c->d_mcf, taps_per_wg)
 #define KI_TAPS_NB(B_, M_)                                                                                                           \
     do {                                                                                                                             \
-        if (!c->small_q) KI_TAPS_LAUNCH(B_, false, CT_BATCH, M_);                                                                    \
+        if (!c->small_q && n == 1) KI_TAPS_LAUNCH(B_, false, 1, M_);                                                                 \
+        else if (!c->small_q) KI_TAPS_LAUNCH(B_, false, CT_BATCH, M_);                                                               \
         else if (n == 1) KI_TAPS_LAUNCH(B_, true, 1, M_);                                                                            \
         else if (n <= 4) KI_TAPS_LAUNCH(B_, true, 4, M_);                                                                            \
         else KI_TAPS_LAUNCH(B_, true, CT_BATCH, M_);                                                                                 \
