@@ -101,6 +101,11 @@ F64M_FN void f64m_inv_end(double* v, double q, double qinv) {  // after three st
     v[1] = f64m_reduce(v[1], q, qinv);
 }
 
+// A sum that takes one product (mulmod_any) of a reduced value and a residue per digit, j = 0, 1, ... in order, some left out: whether it is
+// to be reduced between digit j and the next one it takes, jn.  At most eight products of 0.625 q then follow a value of
+// q/2 + 1, 5.5 q in all, which leaves room for two more that need not be of reduced values (0.75 q each).
+F64M_FN bool f64m_sum_due(uint32_t j, uint32_t jn) { return (j >> 3) != (jn >> 3); }
+
 // canonical residues below 2^52 <-> doubles through the mantissa of 2^52 + v
 F64M_FN double f64m_from_u64(uint64_t v) { return f64m_bits_to_double(v | 0x4330000000000000ull) - F64M_2P52; }
 F64M_FN uint64_t f64m_to_u64(double v) { return f64m_double_to_bits(v + F64M_2P52) & 0x000fffffffffffffull; }

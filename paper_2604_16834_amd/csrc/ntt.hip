@@ -617,8 +617,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_div_kernel(NttArgs arg
 // slice's twiddles are fetched once for all of them), multiplies each result by the two key words of (digit, e) as it
 // comes out, adds the product of the digit that owns e (its limb is the decomposed polynomial's own, never transformed)
 // and stores the two components of the inner product: the extended
-// digits are never written in evaluation form nor read back.  All sums are exact integers in doubles (at most
-// beta + 1 terms below 0.75 q each).
+// digits are never written in evaluation form nor read back.  All sums are exact integers in doubles for any number of digits:
+// they are reduced at every eighth digit (f64m_sum_due).
 struct MacEpilogue {
     DigitSrc D;           // D.digits: rows (j*E + e) hold the hi pass' output (doubles); D.own: the decomposed polynomials
     PtrList8 key;         // per batch item: [dnum][2][M][N] (the same pointer for a shared key)
@@ -733,6 +733,10 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
             const double y = lds1[LDS_PAD(tid + 256 * i)];
             acc0[i] += A::mulmod_any(y, A::from_u64(k0[i]), mc.q, mc.qinv);
             acc1[i] += A::mulmod_any(y, A::from_u64(k1[i]), mc.q, mc.qinv);
+        }
+        if (f64m_sum_due(j, jn)) {  // uniform; never with seven digits or fewer
+#pragma unroll
+            for (int i = 0; i < 8; i++) acc0[i] = A::reduce(acc0[i], mc), acc1[i] = A::reduce(acc1[i], mc);
         }
         j = jn;
     }

@@ -80,4 +80,45 @@ long run_round(double* io, const int64_t* tw, uint64_t q, int stages, int invers
     return bad;
 }
 
+// The sum of a fused inner product over `digits` digits but `own` (none left out where own >= digits), then two products that
+// need not be of reduced values (the own limb's, a product's addend): io holds n rows of digits + 2 multiplicands, each
+// negated where its product is negative, so that the sum grows as far as it can; w the multipliers in [0, q).  worst: the largest
+// magnitude of a sum in units of q.  Returns the number of sums that are wrong.
+long run_key_sum(double* io, const uint64_t* w, uint64_t q, int digits, int own, double* worst, size_t n) {
+    const double qd = (double)q, qinv = 1.0 / qd;
+    long bad = 0;
+    *worst = 0.0;
+    for (size_t i = 0; i < n; i++) {
+        double* y = io + (digits + 2) * i;
+        const uint64_t* k = w + (digits + 2) * i;
+        double acc = 0.0;
+        i128 want = 0;
+        auto add = [&](int j) {
+            double t = f64m_mulmod_any(y[j], (double)k[j], qd, qinv);
+            if (t < 0.0) y[j] = -y[j], t = f64m_mulmod_any(y[j], (double)k[j], qd, qinv);
+            acc += t;
+            want = (want + (i128)y[j] * (i128)k[j]) % (i128)q;
+            if (acc / qd > *worst) *worst = acc / qd;
+        };
+        int j = own == 0 ? 1 : 0;
+        while (j < digits) {
+            int jn = j + 1;
+            if (jn == own) jn++;
+            add(j);
+            if (f64m_sum_due((uint32_t)j, (uint32_t)jn)) {
+                acc = f64m_reduce(acc, qd, qinv);
+                if (acc < 0.0) {  // the negated sum: as good a sum of negated terms, and the one that grows
+                    acc = -acc;
+                    want = -want;
+                }
+            }
+            j = jn;
+        }
+        add(digits);
+        add(digits + 1);
+        if (f64m_canonical(f64m_reduce(acc, qd, qinv), qd) != residue(want, q)) bad++;
+    }
+    return bad;
+}
+
 }  // extern "C"

@@ -22,6 +22,7 @@ def lib(tmp_path_factory):
                    check=True, capture_output=True, text=True)
     lib = ctypes.CDLL(so)
     lib.run_round.restype = ctypes.c_long
+    lib.run_key_sum.restype = ctypes.c_long
     return lib
 
 
@@ -68,3 +69,21 @@ def test_rounds_are_exact_within_their_bounds(lib, name, stages, inverse, begin,
         assert bad == 0
         assert worst[0] <= 3.9 + slack and worst[1] < 8.0
         assert np.abs(v).max() / q <= out + slack, np.abs(v).max() / q
+
+
+@pytest.mark.parametrize("digits,own", [(1, 1), (2, 0), (7, 3), (8, 8), (9, 7), (12, 12), (16, 8), (17, 15), (40, 0), (63, 31), (63, 63)])
+def test_key_sums_of_any_number_of_digits(lib, digits, own):
+    """The fused inner product's sum in a plain double, reduced where f64m_sum_due says: products of one sign whose residues lie around
+    half the modulus, where their representatives are largest (up to 0.625 q), behind the digits two of multiplicands up to q.
+    Unreduced, such a sum leaves 2^53 = 8q from about thirteen digits on."""
+    for k, q in enumerate(Q[:3]):
+        rng = np.random.default_rng(300 + k)
+        n = 3000
+        w = rng.integers(1, q, size=(n, digits + 2), dtype=np.uint64)
+        target = (q // 2 + rng.integers(-q // 8, q // 8, size=w.shape)).tolist()
+        y = np.array([[(t * pow(int(x), -1, q) + q // 2) % q - q // 2 for t, x in zip(tr, wr)] for tr, wr in zip(target, w)], dtype=np.float64)
+        y[:, digits:] += np.where(y[:, digits:] < 0, q, 0)  # residues in [0, q): not reduced
+        worst = np.zeros(1)
+        assert lib.run_key_sum(y.ctypes.data_as(ctypes.c_void_p), w.ctypes.data_as(ctypes.c_void_p), ctypes.c_uint64(q), digits, own,
+                               worst.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(n)) == 0
+        assert worst[0] < 7.05  # q/2, eight of 0.625 q, two of 0.75 q, and some units
