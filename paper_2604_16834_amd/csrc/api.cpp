@@ -105,7 +105,11 @@ bool carve_ks(const ckks_ctx* c, u32 level, u32 n_dig, u32 n_v, Arena& ar, KsWs&
     return ar.ok();
 }
 size_t ws_rescale(const ckks_ctx* c, u32 level, u32 n) { return blk(2 * (size_t)n * c->N) + blk(2 * (size_t)n * level * c->N); }
-size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) { return 3 * blk((size_t)n * (level + 1) * c->N) + ws_ks(c, level, n, n); }
+// a product's scratch: the key switch's, and the three polynomials of the tensor product where a kernel forms them (elsewhere they
+// are not stored: run_product)
+size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
+    return (ntt_has_modup(c) ? 0 : 3 * blk((size_t)n * (level + 1) * c->N)) + ws_ks(c, level, n, n);
+}
 
 // Decompose + ModUp of n <= CT_BATCH polynomials srcs[b] ([level+1][N], NTT form) into
 // ws.digits + b*ws.dig_b ([beta][E][N], NTT form).
@@ -344,12 +348,13 @@ int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstr
 int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride,
              const u64* d_rlk, u64* const* outs, u32 n, Arena ar, hipStream_t st) {
     const size_t N = c->N, L1 = level + 1;
-    u64* d0 = ar.take(n * L1 * N);
-    u64* d1 = ar.take(n * L1 * N);
-    u64* d2 = ar.take(n * L1 * N);
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
     if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);
+    u64* d0 = ar.take(n * L1 * N);
+    u64* d1 = ar.take(n * L1 * N);
+    u64* d2 = ar.take(n * L1 * N);
+    if (!ar.ok()) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
     HIP_TRY(launch_tensor(c, level, ptr_list(a, n), a_cstride, ptr_list(b, n), b_cstride, d0, d1, d2, n, nullptr, 0, st));
     const u64 *d2s[CT_BATCH], *keys[CT_BATCH];
     u32 gs[CT_BATCH];
@@ -374,15 +379,16 @@ int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_
                     const u64* addend, size_t add_bstride, const u64* d_rlk, u64* const* outs, u32 n, Arena ar, hipStream_t st,
                     const LinAddend* lin = nullptr) {
     const size_t N = c->N, L1 = level + 1;
-    u64* d0 = ar.take(n * L1 * N);
-    u64* d1 = ar.take(n * L1 * N);
-    u64* d2 = ar.take(n * L1 * N);
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
     const bool mac = ntt_has_modup(c);  // the inner product inside the forward transforms' second pass
     if (lin && (!mac || addend)) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: linear addend without the fused inner product");
     if (mac && addend) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: with the fused inner product the addend is given as a linear combination");
     if (mac) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, true, lin);
+    u64* d0 = ar.take(n * L1 * N);
+    u64* d1 = ar.take(n * L1 * N);
+    u64* d2 = ar.take(n * L1 * N);
+    if (!ar.ok()) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
     const u64 *d2s[CT_BATCH], *add0[CT_BATCH], *add1[CT_BATCH];
     u64* vs[CT_BATCH];
     FinalItem items[CT_BATCH];

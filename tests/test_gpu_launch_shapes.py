@@ -138,3 +138,37 @@ def test_whole_ring_kernels(bits, dnum, level):
         outs = hx.ckks_rotate_hoisted(ctx, d_ct, level, offs, dkeys, hoisted)
         for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, hoisted)):
             assert np.array_equal(hx.to_host(got), want)
+
+
+@pytest.mark.parametrize("log_n,bits,stored", [(13, 50, False), (12, 50, False), (11, 50, True), (13, 57, True)])
+def test_products_stay_within_their_workspace(log_n, bits, stored):
+    """The scratch of a product is a key switch's, plus the tensor product's three polynomials only where a kernel stores them; product
+    and activation (two batches in flight) with exactly the queried bytes give the oracle's residues and touch nothing around them."""
+    p = make_params(log_n, 6, 2, 3, bits=bits)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(7000 + log_n + bits)
+    level, n_ct = p.num_q - 1, 9
+    key = np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(p.dnum)])
+    rlk = hx.ckks_key_load(ctx, hx.from_host(key), 0)
+    product = hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_CTCT_MUL_RELIN, level)
+    assert product == hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_KEYSWITCH, level) + (3 * (level + 1) * orc.N * 8 if stored else 0)
+
+    def guarded(nbytes):
+        buf = torch.full((nbytes // 8 + 128,), 0x5A5A5A5A, dtype=torch.int64, device="cuda")
+        return buf, buf[64:-64]
+
+    def untouched(buf):
+        return bool((buf[:64] == 0x5A5A5A5A).all()) and bool((buf[-64:] == 0x5A5A5A5A).all())
+
+    cts = [rand_ct(rng, p.moduli, level, orc.N) for _ in range(2)]
+    d_cts = [hx.from_host(c) for c in cts]
+    buf, ws = guarded(product)
+    ok = np.array_equal(hx.to_host(hx.ckks_ctct_mul_relin(ctx, d_cts[0], d_cts[1], level, rlk, ws=ws)), orc.ctct_mul_relin(*cts, key, level))
+    assert ok and untouched(buf)
+    k = (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+    want = {True: [orc.poly_activation_merged(c, level, k, key) for c in cts], False: [orc.poly_activation(c, level, k, key) for c in cts]}
+    for merged in (True, False):
+        buf, ws = guarded(hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_POLY_ACT, level, n_ct))
+        outs = hx.he_poly_act_deg7(ctx, [d_cts[i % 2] for i in range(n_ct)], level, k, rlk, ws=ws, merged=merged)
+        ok = all(np.array_equal(hx.to_host(o), want[merged][i % 2]) for i, o in enumerate(outs))
+        assert ok and untouched(buf), f"merged = {merged}"
