@@ -133,16 +133,15 @@ int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const
         HIP_TRY(launch_ntt_modup(c, level, (const double*)ws.y, ws.y_b, ws.digits, n, st, hi_only));
         return CKKS_OK;
     }
-    const PtrList8 cl = ptr_list(srcs, n);
     if (!c->small_q && c->log_hi > 0) {  // all digits together (see launch_ntt_digits)
-        HIP_TRY(launch_modup_conv(c, level, 0, beta, ws.y, ws.y_b, cl, ws.digits, ws.dig_b, n, st));
+        HIP_TRY(launch_modup_conv(c, level, 0, beta, ws.y, ws.y_b, ws.digits, ws.dig_b, n, st));
         HIP_TRY(launch_ntt_digits(c, level, ws.digits, n, st));
         return CKKS_OK;
     }
     for (u32 j = 0; j < beta; j++) {
         const u32 lo = c->digit_lo(j), hi = c->digit_hi(j, level);
         u64* digit = ws.digits + (size_t)j * E * N;
-        HIP_TRY(launch_modup_conv(c, level, j, 1, ws.y, ws.y_b, cl, ws.digits, ws.dig_b, n, st));
+        HIP_TRY(launch_modup_conv(c, level, j, 1, ws.y, ws.y_b, ws.digits, ws.dig_b, n, st));
         PolyList pl;
         pl.n = 0;
         for (u32 e = 0; e < E; e++) {

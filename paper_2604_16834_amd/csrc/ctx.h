@@ -274,7 +274,7 @@ inline bool ntt_has_mac(const ckks_ctx* c) { return ntt_has_modup(c) && !ntt_one
 // whether launch_ntt can apply an epilogue in this ring (it needs the two-pass transform)
 inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LOG; }
 // keyswitch.hip
-hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digits,
+hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, u64* digits,
                              size_t digit_bstride, u32 n, hipStream_t st);
 // n <= CT_BATCH key switches, each with its key and Galois element; add0s (or null): P sigma_g(add0s[b]) joins component 0
 hipError_t launch_key_inner_items(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs,

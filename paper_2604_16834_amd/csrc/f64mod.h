@@ -76,8 +76,8 @@ F64M_FN double f64m_mulmod(double y, double w, double wq, double q) {
     return __builtin_fma(-c, q, h) + l;
 }
 
-// the same for a multiplier without a precomputed w / q: the quotient comes from the rounded product (|y| < 2q: the quotient
-// is at most 1/2 + |y| / 2^52 off, the result at most q in magnitude)
+// the same for a multiplier without a precomputed w / q: the quotient comes from the rounded product, and is at most 1/2 and
+// |y| / 2^52 (a centred multiplier: half of that) off, so results are at most q for |y| < 2q, for |y| < 4q with a centred multiplier
 F64M_FN double f64m_mulmod_any(double y, double w, double q, double qinv) {
     const double h = y * w;
     const double l = __builtin_fma(y, w, -h);

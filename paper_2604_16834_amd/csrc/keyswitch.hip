@@ -27,9 +27,8 @@ __device__ __forceinline__ const u64* digit_row(const DigitSrc& D, u32 b, u32 j,
 
 // ---- ModUp: basis extension of one digit --------------------------------------------------------
 // y     [nd][N]      digit limbs in coefficient form (canonical)
-// c_in  [level+1][N] the polynomial being switched, NTT form (source of the digit's own limbs)
-// digit [E][N]       out: own limbs copied (NTT form), other limbs in coefficient form
-// This one takes digits j0 .. j0 + nj - 1 of every polynomial: y [level+1][N], digits [beta][E][N], tab the table of digit j0,
+// digit [E][N]       out: every limb but the digit's own, in coefficient form (the own limbs stay where they are: DigitSrc)
+// This one takes digits j0 .. j0 + nj - 1 of every polynomial: y [level+1][N], digit [beta][E][N], tab the table of digit j0,
 // the next digit's tab_stride on; size: limbs per digit (the last may have fewer).
 __global__ __launch_bounds__(KS_THREADS) void modup_conv_kernel(const u64* __restrict__ y, size_t y_bstride,
                                                                 u64* __restrict__ digit, size_t digit_bstride,
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv_kernel(const u64* __res
 // ModUp for moduli below 2^50: carry-free 25-bit-split accumulation (three multiply-adds per term).
 // AP = padded digit size: the AP constants of a target limb are one aligned run (wide scalar load).
 template <int AP>
-__global__ __launch_bounds__(KS_THREADS) void modup_conv50_kernel(const u64* __restrict__ y, size_t y_bstride, PtrList8 c_list,
+__global__ __launch_bounds__(KS_THREADS) void modup_conv50_kernel(const u64* __restrict__ y, size_t y_bstride,
                                                                   u64* __restrict__ digit, size_t digit_bstride,
                                                                   const u64* __restrict__ tab, const ModConst* __restrict__ mc, u32 N,
                                                                   u32 level, u32 num_q, u32 lo, u32 nd, u32 M, u32 E, u32 lpb) {
@@ -75,7 +74,6 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv50_kernel(const u64* __r
     if (x >= N) return;
     y += blockIdx.z * y_bstride;
     digit += blockIdx.z * digit_bstride;
-    const u64* __restrict__ c_in = c_list.p[blockIdx.z];
     Split50 yv[AP];
     u32 n_neg = 0;
 #pragma unroll
@@ -112,7 +110,7 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv50_kernel(const u64* __r
 // full-rate instructions per target residue where the split integer sum takes about 90; no correction for the negative
 // terms is needed, their representatives are negative doubles.  convf: [E][AP] (constant, constant / target modulus).
 template <int AP>
-__global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* __restrict__ y, size_t y_bstride, PtrList8 c_list,
+__global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* __restrict__ y, size_t y_bstride,
                                                                     u64* __restrict__ digit, size_t digit_bstride,
                                                                     const u64* __restrict__ tab, const TwF* __restrict__ convf,
                                                                     const ModConst* __restrict__ mc, const ModConstF* __restrict__ mcf,
@@ -121,7 +119,6 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* _
     if (x >= N) return;
     y += blockIdx.z * y_bstride;
     digit += blockIdx.z * digit_bstride;
-    const u64* __restrict__ c_in = c_list.p[blockIdx.z];
     double yd[AP];
 #pragma unroll
     for (u32 a = 0; a < AP; a++) {
@@ -143,8 +140,8 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* _
 }
 
 // Digits j .. j + nj - 1 of n <= KS_MAX_BATCH polynomials at once (nj > 1 only with moduli of 2^50 and above): item b reads
-// y + b*y_bstride ([level+1][N]) and c_in.p[b], writes digits + b*digit_bstride ([beta][E][N])
-hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, const PtrList8& c_in, u64* digits,
+// y + b*y_bstride ([level+1][N]), writes digits + b*digit_bstride ([beta][E][N])
+hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const u64* y, size_t y_bstride, u64* digits,
                              size_t digit_bstride, u32 n, hipStream_t st) {
     const u32 E = c->ext_limbs(level), lo = c->digit_lo(j), nd = c->digit_hi(j, level) - lo;
     if (nj == 0 || j + nj > c->live_digits(level) || (nj > 1 && c->small_q)) return hipErrorInvalidValue;
@@ -161,18 +158,18 @@ hipError_t launch_modup_conv(const ckks_ctx* c, u32 level, u32 j, u32 nj, const 
     if (c->ntt_f64 && c->d_modup_f) {
         const TwF* tf = c->modup_table_f(level, j);
         if (c->alpha_pad == 4)
-            hipLaunchKernelGGL(modup_conv_f64_kernel<4>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
+            hipLaunchKernelGGL(modup_conv_f64_kernel<4>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
         else if (c->alpha_pad == 8)
-            hipLaunchKernelGGL(modup_conv_f64_kernel<8>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
+            hipLaunchKernelGGL(modup_conv_f64_kernel<8>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
         else
-            hipLaunchKernelGGL(modup_conv_f64_kernel<16>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
+            hipLaunchKernelGGL(modup_conv_f64_kernel<16>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, tf, c->d_mc, c->d_mcf, c->N, level, c->num_q, lo, nd, E, lpb);
     } else if (c->small_q) {
         if (c->alpha_pad == 4)
-            hipLaunchKernelGGL(modup_conv50_kernel<4>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
+            hipLaunchKernelGGL(modup_conv50_kernel<4>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
         else if (c->alpha_pad == 8)
-            hipLaunchKernelGGL(modup_conv50_kernel<8>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
+            hipLaunchKernelGGL(modup_conv50_kernel<8>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
         else
-            hipLaunchKernelGGL(modup_conv50_kernel<16>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, c_in, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
+            hipLaunchKernelGGL(modup_conv50_kernel<16>, grid, dim3(KS_THREADS), 0, st, y, y_bstride, digit, digit_bstride, tab, c->d_mc, c->N, level, c->num_q, lo, nd, c->M, E, lpb);
     } else {
         hipLaunchKernelGGL(modup_conv_kernel, grid, dim3(KS_THREADS), 0, st, y_all, y_bstride, digits, digit_bstride, tab, c->modup_digit_stride(),
                            c->d_mc, c->N, level, c->num_q, c->alpha, j, nj, c->alpha_pad, c->M, E, lpb);

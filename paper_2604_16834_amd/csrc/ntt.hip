@@ -625,18 +625,17 @@ struct MacEpilogue {
     OutList8 out;         // per batch item: [2][E][N]
     const u64* negp;      // [num_q]: -P mod q_i
     u32 level, M, E, beta;
-    // prod != 0: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
+    // PROD: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
     // addends are d0 = a0 (.) b0 and d1 = a0 (.) b1 + a1 (.) b0 (D.own is not read)
     PtrList8 a0, a1, b0, b1;
-    u32 prod, lin;
-    // lin != 0 (with prod): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
+    // LIN (with PROD): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
     PtrList8 lx, ly;
     size_t x_cstride, y_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
 };
 
-// PROD, LIN: ep.prod, ep.lin.  They are template arguments so that what follows the digits is straight-line code: with the
+// PROD, LIN (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
 // use, one round trip to memory per point.
 template <bool PROD, bool LIN>
@@ -2014,19 +2013,18 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     ep.M = c->M;
     ep.E = E;
     ep.beta = beta;
-    ep.prod = prod ? 1 : 0;
-    ep.lin = (prod && prod->lin_x) ? 1 : 0;
-    if (ep.lin && (!prod->lin_y || !prod->ka || !prod->kb)) return hipErrorInvalidValue;
-    ep.x_cstride = ep.lin ? prod->x_cstride : 0;
-    ep.y_cstride = ep.lin ? prod->y_cstride : 0;
+    const bool lin = prod && prod->lin_x;
+    if (lin && (!prod->lin_y || !prod->ka || !prod->kb)) return hipErrorInvalidValue;
+    ep.x_cstride = lin ? prod->x_cstride : 0;
+    ep.y_cstride = lin ? prod->y_cstride : 0;
     for (u32 b = 0; b < KS_MAX_BATCH; b++) {
-        ep.lx.p[b] = (ep.lin && b < n) ? prod->lin_x[b] : nullptr;
-        ep.ly.p[b] = (ep.lin && b < n) ? prod->lin_y[b] : nullptr;
-        if (ep.lin && b < n && (!ep.lx.p[b] || !ep.ly.p[b])) return hipErrorInvalidValue;
+        ep.lx.p[b] = (lin && b < n) ? prod->lin_x[b] : nullptr;
+        ep.ly.p[b] = (lin && b < n) ? prod->lin_y[b] : nullptr;
+        if (lin && b < n && (!ep.lx.p[b] || !ep.ly.p[b])) return hipErrorInvalidValue;
     }
     for (u32 i = 0; i < CKKS_MAX_MODULI; i++) {
-        ep.ka[i] = (ep.lin && i <= level) ? prod->ka[i] : 0;
-        ep.kb[i] = (ep.lin && i <= level) ? prod->kb[i] : 0;
+        ep.ka[i] = (lin && i <= level) ? prod->ka[i] : 0;
+        ep.kb[i] = (lin && i <= level) ? prod->kb[i] : 0;
     }
     // digits transformed per batch item: every (digit, position) pair but the digits' own limbs
     const double n_tr = (double)beta * E - (level + 1.0);
@@ -2037,13 +2035,13 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     const u32 b_ext = (n + items - 1) / items < b_least ? b_least : (n + items - 1) / items;
     const dim3 grid = args.lo_group ? dim3(args.lo_group, b_ext, slices / args.lo_group) : dim3(b_ext, slices);
     // in: the transformed rows, the own limbs, the addends, the keys (once per distinct key); out: two components
-    if (ep.lin) n_add = 4.0 * n;  // two components of two ciphertexts
+    if (lin) n_add = 4.0 * n;  // two components of two ciphertexts
     ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (n_tr + (prod ? 4.0 : 1.0) * (level + 1.0) + 2.0 * E) + n_add * (level + 1.0) + n_keys * 2.0 * beta * E),
                    0.5 * n * n_tr * c->N * c->log_lo);
     // which operands join after the digits is the same for the whole launch: one instantiation per case
 #define LO_MAC_LAUNCH(PROD, LIN) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<PROD, LIN>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
-    if (ep.lin) LO_MAC_LAUNCH(true, true);
-    else if (ep.prod) LO_MAC_LAUNCH(true, false);
+    if (lin) LO_MAC_LAUNCH(true, true);
+    else if (prod) LO_MAC_LAUNCH(true, false);
     else LO_MAC_LAUNCH(false, false);
 #undef LO_MAC_LAUNCH
     return hipGetLastError();
