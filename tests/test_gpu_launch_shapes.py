@@ -16,11 +16,12 @@ from gpu_common import rand_ct, rand_poly, w_residues  # noqa: E402
 from test_gpu_parity import fc_case  # noqa: E402
 
 
-@pytest.mark.parametrize("batch,bits", [(191, 50), (383, 50), (384, 50), (385, 57), (577, 50), (1537, 50)])
+@pytest.mark.parametrize("batch,bits", [(95, 50), (191, 50), (192, 57), (193, 50), (289, 50), (289, 57), (769, 50), (769, 57)])
 def test_ntt_items_per_workgroup(batch, bits):
-    """Four slices at N = 2^12: one item per workgroup below 384 polynomials, two from there (the inverse pass' most), three at
-    577 with a ragged last share, eight (the forward pass' most) with a workgroup of one at 1537."""
-    p = make_params(12, 2, 1, 1, bits=bits)
+    """Two limbs of four slices at N = 2^13: one item per workgroup below 192 polynomials, two from there (the inverse pass' most; a
+    workgroup of one at 193), three at 289 with a ragged last share, eight (the forward pass' most) at 769, where a few
+    workgroups get seven."""
+    p = make_params(13, 2, 1, 1, bits=bits)
     orc, ctx = Oracle(p), hx.Context(p)
     rng = np.random.default_rng(2000 + batch)
     idx = [2, 1]
@@ -64,10 +65,11 @@ def test_weighted_sum_kernels(log_n, c_in, c_out, bits):
 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(15, 5, 2, 3, 4), (15, 13, 8, 2, 12), (15, 12, 9, 2, 7), (15, 11, 11, 1, 10),
-                                                          (15, 14, 14, 1, 13), (16, 7, 3, 4, 5), (13, 7, 12, 3, 6)])
+                                                          (15, 14, 14, 1, 13), (15, 12, 12, 1, 6), (15, 12, 10, 1, 9),
+                                                          (16, 7, 3, 4, 5), (13, 7, 12, 3, 6)])
 def test_digits_together(log_n, num_q, num_p, dnum, level):
     """All digits of a small decomposition in one launch: ragged last digits (1 of 2, 6 of 7, 2 of 6 limbs) and a single digit, rows of
-    4, 8 and 16 conversion constants on both sides (9 to 14 real ones of sixteen), target counts that are not multiples of
+    4, 8 and 16 conversion constants on both sides (7 to 14 real ones of sixteen), target counts that are not multiples of
     four, with the inner product inside the second pass (key switch) and behind it (hoisted rotations)."""
     p = make_params(log_n, num_q, num_p, dnum)
     orc, ctx = Oracle(p), hx.Context(p)
@@ -83,11 +85,13 @@ def test_digits_together(log_n, num_q, num_p, dnum, level):
         assert np.array_equal(hx.to_host(got), want)
 
 
-@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(12, 7, 3, 3, 6), (12, 5, 5, 1, 4), (13, 9, 2, 5, 7), (15, 11, 4, 3, 8), (16, 6, 2, 3, 3)])
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(12, 7, 3, 3, 6), (12, 5, 5, 1, 4), (13, 9, 2, 5, 7), (13, 9, 2, 5, 8), (15, 11, 4, 3, 8),
+                                                          (16, 6, 2, 3, 3), (16, 10, 3, 4, 9)])
 def test_integer_digits_together(log_n, num_q, num_p, dnum, level):
-    """All digits of a decomposition in one launch per pass with 57-bit moduli: ragged last digits (1 of 3, 1 of 4 limbs), a single digit,
-    five digits of two limbs, fewer live digits than the key has; one, two and eight polynomials (unhoisted rotations), and
-    hoisted ones."""
+    """All digits of a decomposition in one launch per pass with 57-bit moduli: ragged last digits (1 of 3, 1 of 2, 1 of 4 limbs), a single
+    digit, five digits (more than the kernel that keeps its key words takes) and four of five, two of three; one, two and eight
+    polynomials (unhoisted rotations), and hoisted ones; at N = 2^16 with ten limbs a workgroup of the second pass takes two
+    rows (polynomial, digit) for one polynomial and four for two, stepping past each digit's own limbs."""
     p = make_params(log_n, num_q, num_p, dnum, bits=57)
     orc, ctx = Oracle(p), hx.Context(p)
     rng = np.random.default_rng(5000 + num_q)
@@ -101,6 +105,67 @@ def test_integer_digits_together(log_n, num_q, num_p, dnum, level):
         outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, dkeys, hoisted)
         for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, hoisted)):
             assert np.array_equal(hx.to_host(got), want)
+
+
+@pytest.mark.parametrize("num_p", [9, 10, 11])
+def test_merged_divisions_of_many_special_primes(num_p):
+    """Ten, eleven and twelve dropped limbs at N = 2^15 (rows of twelve conversion constants): the merged activation's divisions by
+    P q_level, down to two remaining limbs."""
+    p = make_params(15, 5, num_p, 1)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(4500 + num_p)
+    level, k = 4, (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+    ct = rand_ct(rng, p.moduli, level, orc.N)
+    key = np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)])])
+    (got,) = hx.he_poly_act_deg7(ctx, [hx.from_host(ct)], level, k, hx.ckks_key_load(ctx, hx.from_host(key), 0), merged=True)
+    assert np.array_equal(hx.to_host(got), orc.poly_activation_merged(ct, level, k, key))
+
+
+@pytest.mark.parametrize("log_n,num_p,dnum", [(11, 2, 3), (12, 2, 3), (13, 2, 3), (13, 1, 6)])
+def test_integer_merge_layer_and_layout(log_n, num_p, dnum):
+    """What adds P c0 to its inner products or sums in its divisions' last step, with 57-bit moduli: the merge of four blocks, the fully
+    connected layer (three outputs, a ragged block of second rotations) and the layout in both schedules; up to three digits,
+    whose key words a thread keeps, and six."""
+    p = make_params(log_n, 6, num_p, dnum, bits=57)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(5500 + log_n + dnum)
+    level, q, n = p.num_q - 1, p.moduli, orc.N
+    pt = lambda lv: rand_poly(rng, q[:lv + 1], n)
+    ext = lambda lv: rand_poly(rng, [q[t] for t in orc.ext_moduli_idx(lv)], n)
+    keys, dkeys = {}, {}
+
+    def key(r):
+        if r % orc.n == 0:
+            return None
+        if r not in keys:
+            keys[r] = np.stack([np.stack([rand_poly(rng, q, n) for _ in range(2)]) for _ in range(dnum)])
+            dkeys[r] = hx.ckks_key_load(ctx, hx.from_host(keys[r]), hx.ckks_galois_element(ctx, r))
+        return dkeys[r]
+
+    same = lambda got, want: bool(np.array_equal(hx.to_host(got), want))
+    cts = [rand_ct(rng, q, level, n) for _ in range(4)]
+    d_cts = [hx.from_host(c) for c in cts]
+    sts, mask = orc.n // 4, pt(level)
+    got = hx.he_accumulator_merge(ctx, d_cts, level, sts, hx.from_host(mask), [key(-i * sts) for i in range(4)])
+    ok = same(got, orc.accumulator_merge(cts, level, sts, mask, keys))
+    assert ok, "merge"
+    d_in, d_out, batch, base = 8, 3, 5, 2
+    _, lo, hi = orc.fc_shifts(d_in, d_out, batch, base)
+    ops = (np.stack([pt(level) for _ in range(d_out)]), pt(level - 1), np.stack([pt(level - 2) for _ in range(batch)]), pt(level - 3))
+    got = hx.he_fc_batched(ctx, d_cts[0], level, d_in, d_out, batch, base, *[hx.from_host(o) for o in ops], [key(1 << s) for s in range(3)],
+                           [key(-i) for i in range(d_out)], [key(r) for r in lo], [key(r) for r in hi])
+    ok = same(got, orc.fc_batched(cts[0], level, d_in, d_out, batch, base, *ops, keys))
+    assert ok, "fully connected layer"
+    lo, hi = [0, 3, 5], [7, 0]
+    for schedule in (hx.HE_RELAYOUT_DIRECT, hx.HE_RELAYOUT_DEFERRED):
+        deferred = schedule == hx.HE_RELAYOUT_DEFERRED
+        masks = [[(ext if deferred else pt)(level) for _ in lo] for _ in hi]
+        masks[1][2] = None
+        outs = hx.he_relayout_two_rotations(ctx, d_cts[:3], level, lo, [key(r) for r in lo], hi, [key(r) for r in hi],
+                                            [[None if m is None else hx.from_host(m) for m in row] for row in masks], schedule=schedule)
+        oracle = orc.relayout_two_rotations_deferred if deferred else orc.relayout_two_rotations
+        ok = [same(o, oracle(c, level, lo, hi, masks, keys)) for o, c in zip(outs, cts)]
+        assert all(ok), f"layout, schedule {schedule}"
 
 
 @pytest.mark.parametrize("batch,base", [(38, 3), (40, 36)])

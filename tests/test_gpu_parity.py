@@ -41,12 +41,14 @@ def test_ntt_matches_oracle(log_n, bits):
     assert np.array_equal(hx.to_host(d), orc.ntt_many(polys, idx, inverse=True))
 
 
-@pytest.mark.parametrize("batch,bits", [(1, 50), (8, 50), (9, 50), (19, 50), (19, 57), (64, 50)])
-def test_ntt_batches_span_the_item_loop(batch, bits):
-    """The forward lo pass gives a workgroup up to eight polynomials of a batch, taken with the stride of the grid's extent
-    over items: batches of one item, of exactly eight, of one more, and of 19 and 64 (three and eight workgroups per slice, the
-    first with a ragged share) in both arithmetics; every residue against the oracle, forward and back."""
-    p = make_params(12, 2, 1, 1, bits=bits)
+@pytest.mark.parametrize("log_n,batch,bits", [(12, 1, 50), (12, 8, 50), (12, 9, 50), (12, 19, 50), (12, 19, 57), (12, 64, 50),
+                                              (17, 19, 50), (17, 19, 57), (17, 64, 50)])
+def test_ntt_batches_span_the_item_loop(log_n, batch, bits):
+    """The forward lo pass of a large launch gives a workgroup up to eight polynomials of a batch, taken with the stride of the
+    grid's extent over items: at N = 2^17 three of 19 (seven workgroups per slice, the last ones with a share of two) and eight of
+    64, in both arithmetics; at N = 2^12, whose transforms are one workgroup each, batches of one to 64; every residue against
+    the oracle, forward and back."""
+    p = make_params(log_n, 2, 1, 1, bits=bits)
     orc, ctx = both(p)
     rng = np.random.default_rng(1000 + batch)
     idx = [2, 0]
