@@ -57,8 +57,9 @@ typedef struct ckks_ctx ckks_ctx; /* tables immutable after creation; see ckks_c
 typedef struct ckks_key ckks_key;
 
 /* Parameter set.  Supported: 4 <= log_n <= 17; num_q >= 1; num_q + num_p <= 64; every modulus a
- * prime below 2^58 with q = 1 mod 2N; psi[t]^N = -1 mod moduli[t]; dnum = 0 (no key switching,
- * then num_p = 0) or 1 <= dnum <= num_q with num_p >= 1. */
+ * prime above 2^10 with q = 1 mod 2N, twice the longest's bits less the shortest's at most 57 (so
+ * 57 bits where all are alike); psi[t]^N = -1 mod moduli[t]; dnum = 0 (no key switching, then
+ * num_p = 0) or 1 <= dnum <= num_q with 1 <= num_p <= 15 and at most 16 limbs per digit. */
 typedef struct ckks_params {
     uint32_t log_n;
     uint32_t num_q;

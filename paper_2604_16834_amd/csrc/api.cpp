@@ -349,7 +349,7 @@ int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride
     const size_t N = c->N, L1 = level + 1;
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
-    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);
+    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);  // at N = 2^12 too: see ntt_has_mac
     u64* d0 = ar.take(n * L1 * N);
     u64* d1 = ar.take(n * L1 * N);
     u64* d2 = ar.take(n * L1 * N);

@@ -269,7 +269,10 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
 // rings whose transforms run as one kernel (the whole limb-poly in one workgroup)
 inline bool ntt_one_pass(const ckks_ctx* c) { return c->log_hi == 1; }
 // whether a key switch takes its inner product inside the forward transforms' second pass (launch_ntt_lo_mac) rather than behind
-// whole transforms
+// whole transforms.  A product does so on the rings of 2^12 points too (ntt_has_modup decides there): with it goes the tensor product's
+// kernel and d0..d2 in memory.  Products at N = 2^12, 4 to 20 limbs, us: 50.5-56.7 in the second pass, 53.5-60.6 behind whole-ring
+// transforms (54.5 either way with four digits); activation of one, four, eight and sixteen ciphertexts at 7 + 3 limbs 165, 174,
+// 182, 213 and 173, 202, 235, 322.
 inline bool ntt_has_mac(const ckks_ctx* c) { return ntt_has_modup(c) && !ntt_one_pass(c); }
 // whether launch_ntt can apply an epilogue in this ring (it needs the two-pass transform)
 inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LOG; }

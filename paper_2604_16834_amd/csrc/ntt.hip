@@ -1593,7 +1593,10 @@ static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t 
     }
     if constexpr (LOG_HI >= 4) {
         // as many terms as the launch has source limbs: the rest of a row is padding (digits of 7, 7 and 4 or 5
-        // limbs in rows of eight: 41.0 us a launch with eight terms everywhere, 38.0 with their own)
+        // limbs in rows of eight: 41.0 us a launch with eight terms everywhere, 38.0 with their own).  Whole calls with two equal
+        // digits at N = 2^16 take this much longer with full rows (product / activation of eight / eight rotations low in the
+        // chain): digits of 2 limbs 1.02 / - / 1.04, of 3 1.02 / 1.00 / 1.02, of 5 1.03 / 1.02 / 1.03, of 6 1.04 / 1.00 / 1.03, of 7
+        // 1.03 / 1.00 / 1.01, of 9 1.06 / 1.04 / 1.06, of 10 1.02 / 1.02 / 1.06, of 11 1.02 / 1.02 / 1.03, of 12 1.03 / 1.02 / 1.04
         if (cp.ap == 4) {
             if (cp.nd == 2) HI_CONV(lds, 4, 2);
             else if (cp.nd == 3) HI_CONV(lds, 4, 3);
