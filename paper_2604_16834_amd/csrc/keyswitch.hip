@@ -105,10 +105,9 @@ __global__ __launch_bounds__(KS_THREADS) void modup_conv50_kernel(const u64* __r
     }
 }
 
-// ModUp for moduli below 2^50 in double precision: the centred residues of the digit as doubles, every term reduced by
-// an exact fused-multiply-add product (f64mod.h), the sum of at most 8 terms (below 2^53) reduced once.  About 60
-// full-rate instructions per target residue where the split integer sum takes about 90; no correction for the negative
-// terms is needed, their representatives are negative doubles.  convf: [E][AP] (constant, constant / target modulus).
+// ModUp for moduli below 2^50 in double precision (the ring of 2^11 points): the centred residues of the digit as doubles, summed
+// in chains of fused multiply-adds of up to eight terms, each chain reduced once (f64m_dot).  No correction for the negative
+// terms is needed, their representatives are negative doubles.  convf: [E][AP] (centred constant, its quotient, not read).
 template <int AP>
 __global__ __launch_bounds__(KS_THREADS) void modup_conv_f64_kernel(const u64* __restrict__ y, size_t y_bstride,
                                                                     u64* __restrict__ digit, size_t digit_bstride,
