@@ -175,18 +175,24 @@ FwdEpilogue moddown_epilogue(const ckks_ctx* c, u32 level, bool merged, const u6
     return ep;
 }
 
+// The first of the extended basis' positions that a division drops: the special primes', or (merged) limb `level` in front of them.
+u32 dropped_from(u32 level, bool merged) { return merged ? level : level + 1; }
+
 // ModDown of the n inner products sitting in ws.v: one pass of each kernel over the whole batch.
 // items[r] says what is added to / multiplied into the r-th result and where it goes ([2][level+1][N]).
 // merged: the division is by P*q_level (ModDown and rescale in one): the dropped limbs are position
 // level and the special primes, the results are [2][level][N].
-int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const FinalItem* items, hipStream_t st, bool merged = false) {
+// lo_done: the dropped limbs have been through the first pass of their inverse transform (launch_ntt_lo_mac with inv_from).
+int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const FinalItem* items, hipStream_t st, bool merged = false,
+                bool lo_done = false) {
     const u32 L1 = level + 1, E = c->ext_limbs(level), k = c->num_p;
     if (merged) {
         PolyList dl = range_list(level, k + 1, c->num_q - 1);  // positions level.. ; moduli fixed up below
         dl.mod[0] = (unsigned char)level;
         for (u32 a = 1; a <= k; a++) dl.mod[a] = (unsigned char)(c->num_q + a - 1);
         if (ntt_has_modup(c)) {  // conversion inside the forward transform's first pass, last step inside its second
-            HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st, nullptr, nullptr, c->d_moddown_rs_prep_f + (size_t)level * c->M));
+            HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st, nullptr, nullptr, c->d_moddown_rs_prep_f + (size_t)level * c->M,
+                               nullptr, nullptr, lo_done));
             const FwdEpilogue ep = moddown_epilogue(c, level, true, ws.v, items, n);
             HIP_TRY(launch_ntt_moddown(c, level, true, (const double*)ws.v, ws.w, 2 * n, st, &ep));
             return CKKS_OK;
@@ -203,7 +209,7 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
         return CKKS_OK;
     }
     if (ntt_has_modup(c)) {
-        HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st, nullptr, nullptr, c->d_moddown_prep_f));
+        HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st, nullptr, nullptr, c->d_moddown_prep_f, nullptr, nullptr, lo_done));
         const FwdEpilogue ep = moddown_epilogue(c, level, false, ws.v, items, n);
         HIP_TRY(launch_ntt_moddown(c, level, false, (const double*)ws.v, ws.w, 2 * n, st, &ep));
         return CKKS_OK;
@@ -338,8 +344,9 @@ int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstr
         prod.y_cstride = lin->y_cstride;
         prod.kb = lin->kb;
     }
-    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, &prod));
-    return run_moddown(c, level, ws, n, items, st, merged);
+    const bool inv = ntt_has_mac(c);
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, inv ? dropped_from(level, merged) : c->ext_limbs(level), &prod));
+    return run_moddown(c, level, ws, n, items, st, merged, inv);
 }
 
 // n <= CT_BATCH products a[b]*b[b] with relinearisation (operands possibly at a higher level:
@@ -592,8 +599,8 @@ int run_rotate_permuted(const ckks_ctx* c, u32 level, u32 n, const u64* const* s
     }
     int rc = run_modup(c, level, c1s, n, ws, st, true);
     if (rc) return rc;
-    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st));
-    return run_moddown(c, level, ws, n, items, st);
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st, dropped_from(level, false)));
+    return run_moddown(c, level, ws, n, items, st, false, true);
 }
 
 size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) {
@@ -1026,14 +1033,14 @@ int ckks_keyswitch(const ckks_ctx* c, const uint64_t* d_c, uint32_t level, const
     if (rc) return rc;
     if (mac) {
         const u64* k = key->d_key;
-        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), &k, &ws.v, 1, st));
+        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), &k, &ws.v, 1, st, dropped_from(level, false)));
     } else {
         const u64* k = key->d_key;
         const u32 g = 1;
         HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), &k, &g, nullptr, ws.v, ws.v_b, 1, st));
     }
     const FinalItem item = {nullptr, nullptr, nullptr, (u64*)d_out, 1, 0};
-    return run_moddown(c, level, ws, 1, &item, st);
+    return run_moddown(c, level, ws, 1, &item, st, false, mac);
 }
 
 int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level, const int32_t* h_offsets, uint32_t n_rot,
@@ -1125,12 +1132,12 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
         if (mac) {  // every item with its own key, inside the forward transforms' second pass
             u64* vs[CT_BATCH];
             for (u32 b = 0; b < nb; b++) vs[b] = ws.v + b * ws.v_b;
-            HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), ks, vs, nb, st));
+            HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), ks, vs, nb, st, dropped_from(level, false)));
         } else {
             for (u32 b = 0; b < nb; b++) gs[b] = 1;
             HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), ks, gs, nullptr, ws.v, ws.v_b, nb, st));
         }
-        rc = run_moddown(c, level, ws, nb, items, st);
+        rc = run_moddown(c, level, ws, nb, items, st, false, mac);
         nb = 0;
         return rc;
     };

@@ -222,7 +222,8 @@ hipError_t noalloc_scratch_current_device(int* device, void** ptr);
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                       size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs = nullptr,
                       const FwdEpilogue* epilogue = nullptr, const TwF* inv_scale = nullptr, const u64* const* mul_ptrs = nullptr,
-                      const u64* lin_k = nullptr);
+                      const u64* lin_k = nullptr, bool lo_done = false);
+// lo_done (inverse, in place, two-pass rings): the first pass has been done already (launch_ntt_lo_mac with inv_from)
 // mul_ptrs (inverse, with src_ptrs, double-precision arithmetic): batch item b is src_ptrs[b] (.) mul_ptrs[b], formed on load;
 // with lin_k = {ka, kb} (one limb only) it is ka * src_ptrs[b] + kb * mul_ptrs[b] instead.
 // ModUp fused into transforms (contexts with ntt_f64 and the two-pass transform): the inverse transform of the polynomial
@@ -253,6 +254,8 @@ hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, h
 // [level+1][N] each).
 // lin (optional): the product's addend is the linear combination ka * x + kb * y of two more ciphertexts (component
 // strides x_cstride, y_cstride; ka, kb: one residue per q-limb), formed on the fly as well.
+// inv_from: the positions of the extended basis from here on (the limbs that the division behind drops) leave with the first pass of
+// their inverse transform done, so that launch_ntt goes on with lo_done; E where that is not wanted.
 struct MacProduct {
     const u64* const* a0;
     const u64* const* a1;
@@ -265,7 +268,7 @@ struct MacProduct {
     const u64* kb = nullptr;
 };
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, const MacProduct* prod = nullptr);
+                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr);
 // rings whose transforms run as one kernel (the whole limb-poly in one workgroup)
 inline bool ntt_one_pass(const ckks_ctx* c) { return c->log_hi == 1; }
 // whether a key switch takes its inner product inside the forward transforms' second pass (launch_ntt_lo_mac) rather than behind

@@ -625,6 +625,10 @@ struct MacEpilogue {
     OutList8 out;         // per batch item: [2][E][N]
     const u64* negp;      // [num_q]: -P mod q_i
     u32 level, M, E, beta;
+    // the positions from inv_from on are what a division that follows drops: their sums leave in the form between the two passes of an
+    // inverse transform (E: none of them)
+    const double* itw_val;  // [M][N], NttArgs::tw_val of inverse transforms
+    u32 inv_from, pad;
     // PROD: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
     // addends are d0 = a0 (.) b0 and d1 = a0 (.) b1 + a1 (.) b0 (D.own is not read)
@@ -634,6 +638,63 @@ struct MacEpilogue {
     size_t x_cstride, y_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
 };
+
+// The inverse lo pass of a slice whose points tid + 256 i the workgroup's threads hold, |v| <= q / 2 + 1 (ntt_inv_lo_kernel's rounds
+// behind one more exchange), for both components of an inner product one after the other: the slice's inverse twiddles are fetched
+// once for the two.  The sums of the limbs that a division drops are read by nothing but the inverse transform, whose first pass
+// owns the same slices: kept here, they are neither written nor read in between, and a launch goes.  At N = 2^16, 13 + 8 limbs, a
+// product with its rescale 122 -> 113 us (117 with these limbs' workgroups, the longer ones, last in the launch instead of first);
+// three rotations of 19 + 8 limbs 363 -> 355, the activation of sixteen ciphertexts of 20 + 7 limbs 4646 -> 4585, six rotations of 7 + 3
+// limbs at N = 2^13 52.9 -> 51.1.  (Both components side by side in two buffers spill: activation 4914.)
+__device__ __forceinline__ void mac_inverse_lo(double (&r0)[8], double (&r1)[8], double* lds0, double* lds1, const double* __restrict__ itw, u32 TA, u32 tid,
+                                               const ModConstF& mc, u64* __restrict__ o0, u64* __restrict__ o1) {
+    typedef ArithF64 A;
+    typedef ArithF64W AW;
+    const u32 d3 = tid >> 5, x5 = tid & 31, d2 = (tid >> 2) & 7, d0 = tid & 3;
+    double wa[7], wb[7], wc[7], wd[6];
+    load_tw_w<2>(itw, 512 * TA + 2 * tid, wd);
+    load_tw_w<2>(itw, 512 * TA + 2 * tid + 1, wd + 3);
+    load_tw_w<3>(itw, 64 * TA + 8 * d3 + d2, wc);
+    load_tw_w<3>(itw, 8 * TA + d3, wb);
+    load_tw_w<3>(itw, TA, wa);
+#pragma unroll
+    for (int comp = 0; comp < 2; comp++) {
+        double v[8];
+        // (lds0: its last readers are behind a barrier, the last digit's or the other component's last one)
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds0[LDS_PAD(tid + 256 * j)] = comp ? r1[j] : r0[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(8 * tid + j)];
+        inv_rows_pre<AW, 2>(v, wd, mc);
+        inv_rows_pre<AW, 2>(v + 4, wd + 3, mc);
+        A::inv_end2(v, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds1[LDS_PAD(8 * tid + j)] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = lds1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+        inv_rows_pre<AW, 3>(v, wc, mc);
+        A::inv_end(v, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = lds0[LDS_PAD(d3 * 256 + 32 * j + x5)];
+        inv_rows_pre<AW, 3>(v, wb, mc);
+        A::inv_end(v, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds1[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = lds1[LDS_PAD(tid + 256 * j)];
+        inv_rows_pre<AW, 3>(v, wa, mc);
+        A::inv_end(v, mc);
+        u64* o = comp ? o1 : o0;
+#pragma unroll
+        for (int j = 0; j < 8; j++) o[tid + 256 * j] = A::store_mid(v[j]);
+    }
+}
 
 // PROD, LIN (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
@@ -646,7 +707,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     __shared__ E lds1[LDS_PADDED_WORDS];
     const u32 tid = threadIdx.x;
     const LoTile tile = lo_tile(args.log_hi, args.lo_group);
-    const u32 blk = tile.blk, e = tile.a, m_idx = pl_at(pl.mod, e);
+    const u32 e_at = tile.a + ep.inv_from, e = e_at < ep.E ? e_at : e_at - ep.E;  // the dropped limbs, the longer work, first
+    const u32 blk = tile.blk, m_idx = pl_at(pl.mod, e);
     // the batch items of this workgroup: tile.b, tile.b + (the grid's extent over items), ...: a workgroup that takes several
     // fetches the slice's twiddles (half as many bytes as an item's points) once for all of them and requests an item's first
     // points before it is done with the previous item
@@ -808,9 +870,15 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     u64* o0 = ep.out.p[b] + (size_t)e * N + off;
     u64* o1 = o0 + (size_t)ep.E * N;
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        o0[tid + 256 * i] = A::canonical(A::reduce(acc0[i], mc), mc);
-        o1[tid + 256 * i] = A::canonical(A::reduce(acc1[i], mc), mc);
+    for (int i = 0; i < 8; i++) acc0[i] = A::reduce(acc0[i], mc), acc1[i] = A::reduce(acc1[i], mc);
+    if (e >= ep.inv_from) {
+        mac_inverse_lo(acc0, acc1, lds0, lds1, ep.itw_val + ((size_t)m_idx << args.log_n), TA, tid, mc, o0, o1);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            o0[tid + 256 * i] = A::canonical(acc0[i], mc);
+            o1[tid + 256 * i] = A::canonical(acc1[i], mc);
+        }
     }
     // (no barrier between items: the next item's first exchange writes lds0, and its barrier stands between the last item's
     // reads of lds1 and the next writes to it)
@@ -1683,8 +1751,9 @@ static void launch_ring(const ckks_ctx* c, bool inverse, bool mul, u32 entries, 
 static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                                  size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs,
                                  const FwdEpilogue* epilogue, const TwF* inv_scale, const ConvPrologue* conv,
-                                 const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr) {
+                                 const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, bool lo_done = false) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
+    if (lo_done && (!inverse || c->log_hi < 2 || src != dst || src_ptrs)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
@@ -1794,7 +1863,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
         }
     } else {
         args.last = c->log_hi == 0;
-        {
+        if (!lo_done) {
             ProfScope ps__(c, K_NTT_INV_LO, st, mul_ptrs ? 1.5 * pass_bytes : pass_bytes, lo_ops);
             if (mul_ptrs) {  // one item per workgroup (see lo_items)
                 dim3 g1 = grid_lo;
@@ -1811,8 +1880,8 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
 
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst, size_t dst_bstride,
                       const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs, const FwdEpilogue* epilogue,
-                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k) {
-    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k);
+                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k, bool lo_done) {
+    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k, lo_done);
 }
 
 // Small launches take all digits at once: one converting hi pass and (unless the inner product takes it from there) one lo pass,
@@ -1979,7 +2048,7 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 }
 
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, const MacProduct* prod) {
+                             hipStream_t st, u32 inv_from, const MacProduct* prod) {
     if (!ntt_has_modup(c) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     NttArgs args = {};
@@ -2016,6 +2085,9 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     ep.M = c->M;
     ep.E = E;
     ep.beta = beta;
+    ep.itw_val = c->d_itwf_val;
+    ep.inv_from = inv_from;
+    ep.pad = 0;
     const bool lin = prod && prod->lin_x;
     if (lin && (!prod->lin_y || !prod->ka || !prod->kb)) return hipErrorInvalidValue;
     ep.x_cstride = lin ? prod->x_cstride : 0;

@@ -237,3 +237,30 @@ def test_products_stay_within_their_workspace(log_n, bits, stored):
         outs = hx.he_poly_act_deg7(ctx, [d_cts[i % 2] for i in range(n_ct)], level, k, rlk, ws=ws, merged=merged)
         ok = all(np.array_equal(hx.to_host(o), want[merged][i % 2]) for i, o in enumerate(outs))
         assert ok and untouched(buf), f"merged = {merged}"
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n_ct", [(13, 6, 2, 3, 5, 1), (13, 5, 5, 1, 4, 3), (14, 9, 3, 3, 6, 8), (13, 19, 2, 10, 18, 2),
+                                                               (15, 7, 3, 3, 5, 1)])
+def test_inner_products_go_on_into_the_inverse_pass(log_n, num_q, num_p, dnum, level, n_ct):
+    """The sums of the limbs that the division behind drops leave the fused inner product with the first pass of their inverse
+    transform done: special primes alone (product, unhoisted rotations) and with the level's own limb (merged activation),
+    whose sum has no transformed digit where there is one digit; one item per workgroup and several; ten digits."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(8000 + log_n * 10 + dnum)
+    cts = [rand_ct(rng, p.moduli, level, orc.N) for _ in range(2)]
+    d_cts = [hx.from_host(c) for c in cts]
+    offs = [3, -1, 7][:1 + n_ct % 3]
+    keys = [np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)]) for _ in range(1 + len(offs))]
+    rlk = hx.ckks_key_load(ctx, hx.from_host(keys[0]), 0)
+    got = hx.ckks_ctct_mul_relin(ctx, d_cts[0], d_cts[1], level, rlk)
+    assert np.array_equal(hx.to_host(got), orc.ctct_mul_relin(*cts, keys[0], level))
+    rot = [hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, r)) for k, r in zip(keys[1:], offs)]
+    outs = hx.ckks_rotate_hoisted(ctx, d_cts[0], level, offs, rot, False)
+    for out, want in zip(outs, orc.rotate_many(cts[0], level, offs, keys[1:], False)):
+        assert np.array_equal(hx.to_host(out), want)
+    k = (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+    want = [orc.poly_activation_merged(c, level, k, keys[0]) for c in cts]
+    outs = hx.he_poly_act_deg7(ctx, [d_cts[i % 2] for i in range(n_ct)], level, k, rlk, merged=True)
+    for i, out in enumerate(outs):
+        assert np.array_equal(hx.to_host(out), want[i % 2]), f"ciphertext {i}"
