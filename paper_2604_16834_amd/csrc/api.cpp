@@ -127,10 +127,11 @@ int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const
     // of the extended digit).
     const bool fused = ntt_has_modup(c);
     if (hi_only && !fused) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: fused inner product without fused ModUp");
+    const u32 mid = ntt_mid_modup(c, level, n);  // the inverse's second pass inside the converting one
     HIP_TRY(launch_ntt(c, true, nullptr, 0, ws.y, L1, range_list(0, L1, 0), n, st, srcs, nullptr,
-                       fused ? c->d_modup_prep_f + (size_t)level * c->num_q : nullptr, muls));  // (positions 0..level are moduli 0..level)
+                       fused ? c->d_modup_prep_f + (size_t)level * c->num_q : nullptr, muls, nullptr, mid ? NTT_LO : NTT_BOTH));  // (positions 0..level are moduli 0..level)
     if (fused) {
-        HIP_TRY(launch_ntt_modup(c, level, (const double*)ws.y, ws.y_b, ws.digits, n, st, hi_only));
+        HIP_TRY(launch_ntt_modup(c, level, (const double*)ws.y, ws.y_b, ws.digits, n, st, hi_only, mid));
         return CKKS_OK;
     }
     if (!c->small_q && c->log_hi > 0) {  // all digits together (see launch_ntt_digits)
@@ -186,15 +187,17 @@ u32 dropped_from(u32 level, bool merged) { return merged ? level : level + 1; }
 int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const FinalItem* items, hipStream_t st, bool merged = false,
                 bool lo_done = false) {
     const u32 L1 = level + 1, E = c->ext_limbs(level), k = c->num_p;
+    const u32 mid = ntt_mid_moddown(c, level, merged, 2 * n);
     if (merged) {
         PolyList dl = range_list(level, k + 1, c->num_q - 1);  // positions level.. ; moduli fixed up below
         dl.mod[0] = (unsigned char)level;
         for (u32 a = 1; a <= k; a++) dl.mod[a] = (unsigned char)(c->num_q + a - 1);
         if (ntt_has_modup(c)) {  // conversion inside the forward transform's first pass, last step inside its second
-            HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st, nullptr, nullptr, c->d_moddown_rs_prep_f + (size_t)level * c->M,
-                               nullptr, nullptr, lo_done));
+            if (!lo_done || !mid)
+                HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st, nullptr, nullptr, c->d_moddown_rs_prep_f + (size_t)level * c->M,
+                                   nullptr, nullptr, lo_done ? NTT_HI : (mid ? NTT_LO : NTT_BOTH)));
             const FwdEpilogue ep = moddown_epilogue(c, level, true, ws.v, items, n);
-            HIP_TRY(launch_ntt_moddown(c, level, true, (const double*)ws.v, ws.w, 2 * n, st, &ep));
+            HIP_TRY(launch_ntt_moddown(c, level, true, (const double*)ws.v, ws.w, 2 * n, st, &ep, mid));
             return CKKS_OK;
         }
         HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st));
@@ -209,9 +212,11 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
         return CKKS_OK;
     }
     if (ntt_has_modup(c)) {
-        HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st, nullptr, nullptr, c->d_moddown_prep_f, nullptr, nullptr, lo_done));
+        if (!lo_done || !mid)
+            HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st, nullptr, nullptr, c->d_moddown_prep_f, nullptr, nullptr,
+                               lo_done ? NTT_HI : (mid ? NTT_LO : NTT_BOTH)));
         const FwdEpilogue ep = moddown_epilogue(c, level, false, ws.v, items, n);
-        HIP_TRY(launch_ntt_moddown(c, level, false, (const double*)ws.v, ws.w, 2 * n, st, &ep));
+        HIP_TRY(launch_ntt_moddown(c, level, false, (const double*)ws.v, ws.w, 2 * n, st, &ep, mid));
         return CKKS_OK;
     }
     HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st));  // P-part -> coefficients
@@ -233,6 +238,7 @@ int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_c
     u64* r = ar.take(2 * (size_t)n * N);
     u64* w = ar.take(2 * (size_t)n * level * N);
     if (!ar.ok()) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rescale");
+    const u32 mid = ntt_mid_rescale(c, level, 2 * n);  // the inverse's second pass inside the converting one
     const u64* last[KS_MAX_BATCH];  // the dropped limb of every component
     for (u32 b = 0; b < n; b++) {
         last[2 * b] = cts[b] + (size_t)level * N;
@@ -241,7 +247,7 @@ int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_c
     if (ntt_has_modup(c)) {
         // the rescale as a division by one dropped limb through the fused passes: the inverse transform leaves centred doubles,
         // the forward transform reduces them modulo each remaining limb as it loads and applies (c_i - w_i) q_level^-1 as it stores
-        HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f));
+        HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f, nullptr, nullptr, mid ? NTT_LO : NTT_BOTH));
         FwdEpilogue ep;
         ep.v = nullptr;
         ep.cinv = c->d_rescale_ep + (size_t)level * 2 * c->num_q;
@@ -257,7 +263,7 @@ int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_c
             ep.vl.p[b] = b < n ? cts[b] : nullptr;
             ep.B.it[b] = b < n ? FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0} : FinalItem{nullptr, nullptr, nullptr, nullptr, 1, 0};
         }
-        HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep));
+        HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep, mid));
         return CKKS_OK;
     }
     HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last));
@@ -276,6 +282,7 @@ int run_rescale_lin(const ckks_ctx* c, u32 level, const u64* const* xs, size_t x
     u64* r = ar.take(2 * (size_t)n * N);
     u64* w = ar.take(2 * (size_t)n * level * N);
     if (!ar.ok()) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rescale");
+    const u32 mid = ntt_mid_rescale(c, level, 2 * n);
     const u64 *last[KS_MAX_BATCH], *last2[KS_MAX_BATCH];
     for (u32 b = 0; b < n; b++) {
         last[2 * b] = xs[b] + (size_t)level * N;
@@ -284,7 +291,7 @@ int run_rescale_lin(const ckks_ctx* c, u32 level, const u64* const* xs, size_t x
         last2[2 * b + 1] = ys[b] + y_cstride + (size_t)level * N;
     }
     const u64 lin_k[2] = {ka[level], kb[level]};
-    HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f, last2, lin_k));
+    HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f, last2, lin_k, mid ? NTT_LO : NTT_BOTH));
     FwdEpilogue ep;
     ep.v = nullptr;
     ep.cinv = c->d_rescale_ep + (size_t)level * 2 * c->num_q;
@@ -304,7 +311,7 @@ int run_rescale_lin(const ckks_ctx* c, u32 level, const u64* const* xs, size_t x
         ep.ka[i] = i < level ? ka[i] : 0;
         ep.kb[i] = i < level ? kb[i] : 0;
     }
-    HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep));
+    HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep, mid));
     return CKKS_OK;
 }
 

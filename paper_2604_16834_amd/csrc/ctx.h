@@ -217,13 +217,15 @@ struct ProfScope {
 hipError_t noalloc_scratch_current_device(int* device, void** ptr);
 
 // ---- kernel launchers (each enqueues on `st` and returns the launch status) -------------------
+enum NttPasses { NTT_BOTH = 0, NTT_LO, NTT_HI };
 // ntt.hip: batch x pl.n limb-polys; item b reads src + b*src_bstride*N (or src_ptrs[b] when given: host
 // array of `batch` <= KS_MAX_BATCH device pointers) and writes dst + b*dst_bstride*N
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                       size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs = nullptr,
                       const FwdEpilogue* epilogue = nullptr, const TwF* inv_scale = nullptr, const u64* const* mul_ptrs = nullptr,
-                      const u64* lin_k = nullptr, bool lo_done = false);
-// lo_done (inverse, in place, two-pass rings): the first pass has been done already (launch_ntt_lo_mac with inv_from)
+                      const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH);
+// passes (inverse, two-pass rings): the first pass alone (a kernel that goes on from there follows: ntt_mid_*), or the second alone, in place
+// (the first has been done: launch_ntt_lo_mac with inv_from)
 // mul_ptrs (inverse, with src_ptrs, double-precision arithmetic): batch item b is src_ptrs[b] (.) mul_ptrs[b], formed on load;
 // with lin_k = {ka, kb} (one limb only) it is ka * src_ptrs[b] + kb * mul_ptrs[b] instead.
 // ModUp fused into transforms (contexts with ntt_f64 and the two-pass transform): the inverse transform of the polynomial
@@ -235,16 +237,22 @@ inline bool ntt_has_modup(const ckks_ctx* c) { return c->ntt_f64 && c->log_n > C
 // centred doubles by launch_ntt with the moddown prep table), dst the converted dropped part ([n_out][N] per polynomial,
 // NTT form), epilogue what the second pass does with it.  merged: the dropped set is {q_level, p_0..p_{k-1}}.
 hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue);
+                              const FwdEpilogue* epilogue, u32 mid_per = 0);
 // The same for the rescale: y [batch][N] is the dropped limb `level` of every component (centred doubles, from launch_ntt
 // with d_rescale_prep_f), dst [batch][level][N] scratch, epilogue the subtraction and the multiplication by q_level^-1.
 hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue);
+                              const FwdEpilogue* epilogue, u32 mid_per = 0);
 // hi_only: stop after the converting hi pass; launch_ntt_lo_mac then runs the lo passes of all digits and multiplies the
 // results by the switching keys (keys[b]: [dnum][2][M][N], one per batch item) as they come out, adding P * add0s[b] /
 // add1s[b] (optional, [level+1][N]) on the q-limbs: outs[b] [2][E][N] is the finished inner product on the extended basis.
 hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st,
-                            bool hi_only = false);
+                            bool hi_only = false, u32 mid_per = 0);
+// Small launches: the inverse transform's second pass, the conversion and the forward transforms' first pass in one kernel.  Each gives the
+// targets per workgroup (mid_per of the call above, whose y then has been through the inverse transform's first pass only), or 0 where
+// the passes go one by one.  n, polys: polynomials converted.
+u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n);
+u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys);
+u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys);
 // contexts with a modulus of 2^50 or more, two-pass transforms: digits [n][beta][E][N], coefficient form (but each digit's own
 // limbs, which are not touched) -> evaluation form
 hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, hipStream_t st);

@@ -1067,7 +1067,7 @@ struct ConvPrologue {
     const TwF* convf;
     u32 lo, nd;
     u32 ap, groups;    // groups: workgroups per tile and polynomial (T targets each)
-    u32 alpha, n_src, digit0, pad;  // digit0: the launch's first digit
+    u32 alpha, n_src, digit0, per;  // digit0: the launch's first digit; per: targets per workgroup (ntt_mid_conv_kernel)
     size_t convf_dstride, dst_dstride;
 };
 
@@ -1085,10 +1085,20 @@ __device__ __forceinline__ double conv_sum(const double (&yv)[AP], const double*
     return f64m_dot_w<ND>(yv, cw, q, qinv);
 }
 
+// The source limbs of a conversion that are still to go through the last pass of their inverse transform.
+struct MidPrologue {
+    const TwF* itw;     // [M][N] inverse twiddles
+    const TwF* scale;   // by modulus: what the inverse transform's last step multiplies by
+    u32 first, next;    // source limb k has the modulus k ? next + k - 1 : first (a digit's first limb is added to both)
+};
+
 // One workgroup converts and transforms the same tile of T target limbs: the source residues are fetched once for all T
 // (the fetch, from L2 after the first, is what bounds a one-target-per-workgroup version).
-template <int LOG_HI, int AP, int T, int ND = AP>
-__global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
+// MID (one source limb, LOG_HI >= 4): the source is what the inverse transform's first pass left, and goes through its second here, on the
+// same tile.
+template <int LOG_HI, int AP, int T, int ND = AP, bool MID = false>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs args, PolyList pl, ConvPrologue cp, MidPrologue mp) {
+    static_assert(!MID || (ND == 1 && LOG_HI >= 4), "");
     typedef ArithF64 A;
     typedef double E;
     constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R;
@@ -1137,20 +1147,47 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_kernel(NttArgs ar
     } else {
         __shared__ __attribute__((aligned(16))) E lds[NTT_TILE];
         constexpr int R8 = R / 8, S2 = LOG_HI - 3, KC2 = 8 / R8;
-        const u32 r0 = tid / CC, col = tid % CC;
+        const u32 r0 = tid / CC, col = tid % CC, G = tid >> 5, cg = tid & 31;
+        if constexpr (MID) {  // ntt_inv_hi_kernel's two rounds
+            const u32 m_src = dig * cp.alpha + mp.first;
+            const ModConstF mc = ((const ModConstF*)args.mc)[m_src];
+            const TwF scale = mp.scale[m_src];
+            const TwF* tw = mp.itw + ((size_t)m_src << args.log_n);
+            E u[8];
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            double yv[AP];
-            conv_load<AP, ND>(yv, y + ((size_t)(r0 + R8 * j) << 11) + col, N, nd);
+            for (int rr = 0; rr < R8; rr++)
 #pragma unroll
-            for (int t = 0; t < T; t++) v[t][j] = conv_sum<AP, ND>(yv, cw[t], P[t].mc.q, P[t].mc.qinv);
+                for (int kc = 0; kc < KC2; kc++) u[rr * KC2 + kc] = y[((size_t)(G * R8 + rr) << 11) + cg * KC2 + kc];
+            inv_rows<A, S2, KC2>(u, tw, 8 + G, mc);
+            if (S2 == 3) A::inv_end(u, mc);
+#pragma unroll
+            for (int rr = 0; rr < R8; rr++)
+#pragma unroll
+                for (int kc = 0; kc < KC2; kc++) lds[(G * R8 + rr) * CC + cg * KC2 + kc] = u[rr * KC2 + kc];
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 8; j++) u[j] = lds[(r0 + R8 * j) * CC + col];
+            inv_rows<A, 3, 1>(u, tw, 1, mc);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const double yv[1] = {f64m_centre(A::mulmod(u[j], scale.w, scale.wq, mc.q), mc.q)};
+#pragma unroll
+                for (int t = 0; t < T; t++) v[t][j] = f64m_dot_w<1>(yv, cw[t], P[t].mc.q, P[t].mc.qinv);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                double yv[AP];
+                conv_load<AP, ND>(yv, y + ((size_t)(r0 + R8 * j) << 11) + col, N, nd);
+#pragma unroll
+                for (int t = 0; t < T; t++) v[t][j] = conv_sum<AP, ND>(yv, cw[t], P[t].mc.q, P[t].mc.qinv);
+            }
         }
-        const u32 G = tid >> 5, cg = tid & 31;
 #pragma unroll
         for (int t = 0; t < T; t++) {
             if (a0 + t >= n_targets) break;  // uniform over the workgroup
             u64* dst = P[t].dst + (size_t)tile * CC;
-            if (t) __syncthreads();  // the previous limb's exchange has been read
+            if (t || MID) __syncthreads();  // the previous exchange has been read
             fwd_rows<A, 3, 1>(v[t], P[t].tw, 1, P[t].mc);
 #pragma unroll
             for (int j = 0; j < 8; j++) lds[(r0 + R8 * j) * CC + col] = v[t][j];
@@ -1188,8 +1225,12 @@ template <class V>
 using ConstPtr = const __attribute__((address_space(4))) V*;
 template <class V>
 __device__ __forceinline__ ConstPtr<V> const_ptr(const V* p) { return (ConstPtr<V>)p; }
-template <int LOG_HI, int AP, int ND>
-__global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ntt_fwd_hi_conv_lds_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
+// MID: the source limbs are what the inverse transform's first pass left and go through its second here first, four at a time: each half of
+// the workgroup takes two through the two rounds of ntt_inv_hi_kernel in the buffers that the targets use afterwards.
+template <int LOG_HI, int AP, int ND, bool MID>
+__global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ntt_fwd_hi_conv_lds_kernel(NttArgs args, PolyList pl, ConvPrologue cp,
+                                                                                                                   MidPrologue mp) {
+    static_assert(!MID || ND <= 9, "");
     typedef ArithF64 A;
     constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R, PTS = NTT_TILE / HC_THREADS, PP = ND <= 9 ? PTS : 2;
     constexpr int R8 = R / 8, S2 = LOG_HI - 3, KC2 = 8 / R8;
@@ -1213,8 +1254,64 @@ __global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
         for (int i = 0; i < PP; i++) {
             const u32 p = tid + HC_THREADS * (h + i), off = ((p / CC) << 11) + p % CC;
+            if constexpr (!MID)
 #pragma unroll
-            for (int k = 0; k < ND; k++) yv[i][k] = (y + (size_t)((u32)k < nd ? k : nd - 1) * N)[off];  // see conv_load
+                for (int k = 0; k < ND; k++) yv[i][k] = (y + (size_t)((u32)k < nd ? k : nd - 1) * N)[off];  // see conv_load
+        }
+        if constexpr (MID) {
+#pragma unroll
+            for (int k0 = 0; k0 < ND; k0 += HC_T) {
+                double u[2][8];
+                auto source = [&](int s) { return min((u32)k0 + half + 2 * s, nd - 1); };  // see conv_load
+                auto modulus = [&](u32 k) { return dig * cp.alpha + (k ? mp.next + k - 1 : mp.first); };
+                if (k0) __syncthreads();  // the last four have been read
+#pragma unroll
+                for (int s = 0; s < 2; s++)
+                    if (k0 + 2 * s < ND) {
+                        const double* ys = y + (size_t)source(s) * N;
+#pragma unroll
+                        for (int rr = 0; rr < R8; rr++)
+#pragma unroll
+                            for (int kc = 0; kc < KC2; kc++) u[s][rr * KC2 + kc] = ys[((G * R8 + rr) << 11) + cg * KC2 + kc];
+                    }
+#pragma unroll
+                for (int s = 0; s < 2; s++)
+                    if (k0 + 2 * s < ND) {
+                        const u32 m_idx = modulus(source(s));
+                        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+                        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+                        inv_rows<A, S2, KC2>(u[s], mp.itw + ((size_t)m_idx << args.log_n), 8 + G, mc);
+                        if (S2 == 3) A::inv_end(u[s], mc);
+#pragma unroll
+                        for (int rr = 0; rr < R8; rr++)
+#pragma unroll
+                            for (int kc = 0; kc < KC2; kc++) lds[half + 2 * s][(G * R8 + rr) * CC + cg * KC2 + kc] = u[s][rr * KC2 + kc];
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int s = 0; s < 2; s++)
+                    if (k0 + 2 * s < ND) {
+                        const u32 m_idx = modulus(source(s));
+                        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+                        ConstPtr<TwF> ps = const_ptr(mp.scale + m_idx), tw = const_ptr(mp.itw + ((size_t)m_idx << args.log_n));
+                        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+                        const TwF scale = {ps->w, ps->wq};
+                        TwF w1[7];
+#pragma unroll
+                        for (int i = 0; i < 7; i++) w1[i] = TwF{tw[1 + i].w, tw[1 + i].wq};
+                        double* buf = lds[half + 2 * s];  // a thread writes back what it has read
+#pragma unroll
+                        for (int j = 0; j < 8; j++) u[s][j] = buf[(r0 + R8 * j) * CC + col];
+                        inv_rows_pre<A, 3>(u[s], w1, mc);
+#pragma unroll
+                        for (int j = 0; j < 8; j++) buf[(r0 + R8 * j) * CC + col] = f64m_centre(A::mulmod(u[s][j], scale.w, scale.wq, mc.q), mc.q);
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < PP; i++)
+#pragma unroll
+                    for (int k = k0; k < k0 + HC_T && k < ND; k++) yv[i][k] = lds[k - k0][tid + HC_THREADS * i];
+            }
         }
 #pragma unroll 1
         for (u32 t = 0; t < cnt; t++) {
@@ -1323,6 +1420,93 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_inv_hi_kernel(NttArgs args, P
         inv_rows<A, 3, 1>(v, P.tw, 1, P.mc);
 #pragma unroll
         for (int j = 0; j < 8; j++) dst[((size_t)(r0 + R8 * j) << 11) + col] = inv_last_store<A>(v[j], P.mc, scale);
+    }
+}
+
+// The last pass of an inverse transform, a basis conversion and the first pass of the forward transforms of its targets in one
+// kernel, for the rings of 2^13 and 2^14 points: a thread owns the R = 2^LOG_HI points of one column, which is all that the three act
+// on, so nothing goes through LDS.  It takes the column of every source limb through the inverse pass' LOG_HI stages (scaled and
+// centred as inv_last_store does), and per target the conversion sum and the forward pass' stages.  The inverse stages are repeated by
+// every group of cp.per targets (mid_conv_per: when, and figures).
+// grid = (2^11 columns / NTT_THREADS, groups x polynomials, digits)
+// A column's stages, twiddles tw[1..2^S - 1] through the scalar path; the inverse reduces the sums of its first stage (bounds: f64mod.h)
+template <int S>
+__device__ __forceinline__ void load_column_tw(ConstPtr<TwF> tw, TwF* w) {
+#pragma unroll
+    for (int i = 0; i < (1 << S) - 1; i++) w[i] = TwF{tw[1 + i].w, tw[1 + i].wq};
+}
+template <int S>
+__device__ __forceinline__ void inv_column(double* v, ConstPtr<TwF> tw, const ModConstF& m) {
+    typedef ArithF64 A;
+    TwF w[(1 << S) - 1];
+    load_column_tw<S>(tw, w);
+#pragma unroll
+    for (int a = S - 1; a >= 0; a--) {
+        const int half = (1 << S) >> (a + 1);
+#pragma unroll
+        for (int rr = 0; rr < (1 << S); rr++) {
+            if (rr & half) continue;
+            A::inv_bf(v[rr], v[rr + half], w[(1 << a) - 1 + (rr >> (S - a))], m);
+            if (a == S - 1) v[rr] = A::reduce(v[rr], m);
+        }
+    }
+}
+template <int S>
+__device__ __forceinline__ void fwd_column(double* v, ConstPtr<TwF> tw, const ModConstF& m) {
+    TwF w[(1 << S) - 1];
+    load_column_tw<S>(tw, w);
+    fwd_rows_pre<ArithF64, S>(v, w, m);
+}
+template <int LOG_HI, int ND>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_kernel(NttArgs args, PolyList pl, ConvPrologue cp, MidPrologue mp) {
+    typedef ArithF64 A;
+    constexpr int R = 1 << LOG_HI;
+    const u32 col = blockIdx.x * NTT_THREADS + threadIdx.x, b = blockIdx.y / cp.groups, a0 = (blockIdx.y % cp.groups) * cp.per;
+    const size_t N = (size_t)1 << args.log_n;
+    const u32 dig = cp.digit0 + blockIdx.z, lo = dig * cp.alpha;
+    const u32 nd = cp.alpha ? min(cp.alpha, cp.n_src - lo) : cp.nd;
+    const u32 n_targets = cp.alpha ? pl.n - nd : pl.n;
+    if (a0 >= n_targets) return;  // whole workgroup: a digit with more limbs has fewer targets
+    const u32 a1 = min(a0 + cp.per, n_targets);
+    const double* y = cp.y + b * cp.y_bstride + (size_t)(cp.lo + lo) * N + col;
+    u64* dst0 = args.dst + (((size_t)b * args.dst_bstride) << args.log_n) + dig * cp.dst_dstride + col;
+    const TwF* convf = cp.convf + dig * cp.convf_dstride;
+    double yv[R][ND];
+#pragma unroll
+    for (int k = 0; k < ND; k++) {
+        const size_t row = (size_t)((u32)k < nd ? k : nd - 1) * N;  // see conv_load
+#pragma unroll
+        for (int r = 0; r < R; r++) yv[r][k] = y[row + ((size_t)r << 11)];
+    }
+#pragma unroll
+    for (int k = 0; k < ND; k++) {
+        const u32 kk = (u32)k < nd ? k : nd - 1, m_idx = lo + (kk ? mp.next + kk - 1 : mp.first);
+        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+        ConstPtr<TwF> ps = const_ptr(mp.scale + m_idx), tw = const_ptr(mp.itw + ((size_t)m_idx << args.log_n));
+        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+        const TwF scale = {ps->w, ps->wq};
+        double v[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) v[r] = yv[r][k];
+        inv_column<LOG_HI>(v, tw, mc);
+#pragma unroll
+        for (int r = 0; r < R; r++) yv[r][k] = f64m_centre(A::mulmod(v[r], scale.w, scale.wq, mc.q), mc.q);
+    }
+#pragma unroll 1
+    for (u32 t = a0; t < a1; t++) {
+        const u32 a = cp.alpha && t >= lo ? t + nd : t, m_idx = pl_at(pl.mod, a), pos = pl_at(pl.dpos, a);  // past the digit's own limbs
+        ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+        ConstPtr<TwF> ce = const_ptr(convf + (size_t)pos * cp.ap), tw = const_ptr((const TwF*)args.tw + ((size_t)m_idx << args.log_n));
+        const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+        double cw[ND], v[R];
+#pragma unroll
+        for (int k = 0; k < ND; k++) cw[k] = ce[k].w;
+#pragma unroll
+        for (int r = 0; r < R; r++) v[r] = f64m_dot_w<ND>(yv[r], cw, mc.q, mc.qinv);
+        fwd_column<LOG_HI>(v, tw, mc);
+        u64* dst = dst0 + ((size_t)pos << args.log_n);
+#pragma unroll
+        for (int r = 0; r < R; r++) dst[(size_t)r << 11] = A::store_mid(v[r]);
     }
 }
 
@@ -1636,25 +1820,42 @@ static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& a
 // Target limbs per workgroup: four share one fetch of the source residues; in a launch that would not give every CU two
 // workgroups, two or one, each done sooner (one polynomial pair's rescale at N = 2^16, 12 limbs: 13.1 us with four, 8.9 with one; six
 // decompositions of digits of three limbs at N = 2^13: 9.3 and 6.6).
-template <int LOG_HI, int AP, int ND>
-static void launch_hi_conv_regs(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
+template <int LOG_HI, int AP, int ND, bool MID>
+static void launch_hi_conv_regs_as(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue& mp) {
     u32 t = 4;
     while (t > 1 && ((n_targets + t - 1) / t * batch * digits << LOG_HI) < 512) t >>= 1;
     cp.groups = (n_targets + t - 1) / t;
     const dim3 grid(1u << LOG_HI, cp.groups * batch, digits), block(NTT_THREADS);
-    if (t == 4) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 4, ND>), grid, block, 0, st, args, pl, cp);
-    else if (t == 2) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 2, ND>), grid, block, 0, st, args, pl, cp);
-    else hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 1, ND>), grid, block, 0, st, args, pl, cp);
+    if (t == 4) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 4, ND, MID>), grid, block, 0, st, args, pl, cp, mp);
+    else if (t == 2) hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 2, ND, MID>), grid, block, 0, st, args, pl, cp, mp);
+    else hipLaunchKernelGGL((ntt_fwd_hi_conv_kernel<LOG_HI, AP, 1, ND, MID>), grid, block, 0, st, args, pl, cp, mp);
 }
 template <int LOG_HI, int AP, int ND>
-static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp) {
+static void launch_hi_conv_regs(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue* mp) {
+    if constexpr (LOG_HI >= 4 && ND == 1) {
+        if (mp) {
+            launch_hi_conv_regs_as<LOG_HI, AP, ND, true>(n_targets, digits, batch, st, args, pl, cp, *mp);
+            return;
+        }
+    }
+    launch_hi_conv_regs_as<LOG_HI, AP, ND, false>(n_targets, digits, batch, st, args, pl, cp, MidPrologue{});
+}
+template <int LOG_HI, int AP, int ND>
+static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue* mp) {
     cp.groups = (n_targets + HC_T - 1) / HC_T;
-    hipLaunchKernelGGL((ntt_fwd_hi_conv_lds_kernel<LOG_HI, AP, ND>), dim3(1u << LOG_HI, cp.groups * batch, digits), dim3(HC_THREADS), 0, st, args, pl, cp);
+    const dim3 grid(1u << LOG_HI, cp.groups * batch, digits), block(HC_THREADS);
+    if constexpr (ND <= 9) {
+        if (mp) {
+            hipLaunchKernelGGL((ntt_fwd_hi_conv_lds_kernel<LOG_HI, AP, ND, true>), grid, block, 0, st, args, pl, cp, *mp);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((ntt_fwd_hi_conv_lds_kernel<LOG_HI, AP, ND, false>), grid, block, 0, st, args, pl, cp, MidPrologue{});
 }
 // n_targets: the most targets a digit of the launch has
 template <int LOG_HI>
-static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
-#define HI_CONV(HOW, AP, ND) launch_hi_conv_##HOW<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp)
+static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue* mp) {
+#define HI_CONV(HOW, AP, ND) launch_hi_conv_##HOW<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp, mp)
     if (cp.ap == 4 && cp.nd == 1) {  // the rescale: one dropped limb
         HI_CONV(regs, 4, 1);
         return;
@@ -1694,14 +1895,78 @@ static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t 
     }
 #undef HI_CONV
 }
-static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp) {
+// Whether the inverse transform's second pass goes inside the converting first pass, for a launch of `rows` (polynomial, digit) rows of nd
+// source limbs (rows of ap constants) and up to n_targets targets each: 0, or the targets per workgroup.  It saves a launch with its
+// round trip through memory and repeats the inverse stages per group of targets.  Measured in whole calls, one by one / together in us:
+//   rescale: at every size (N = 2^13, 4 limbs 18.5 / 14.5, 2^16, 13 limbs 27.9 / 24.2; eight ciphertexts of 24 limbs the same)
+//   rings up to 2^14 (ntt_mid_conv_kernel) while a thread's points of all source limbs are at most 40: one rotation at N = 2^13 of 4 + 2
+//     limbs 45.6 / 33.0, of 21 + 8 50.1 / 48.9, eight 112 / 107; at 2^14 of 7 + 3 45.8 / 41.1, but of 13 + 7 (56 points) 46.1 / 49.6, of
+//     21 + 8 (64) 59.9 / 66.6
+//   larger rings, up to four source limbs: up to 1200 workgroups or two groups of targets (2^15, 13 + 4 limbs, one rotation 67.3 / 62.0, eight
+//     276 / 275; activation of eight at 2^16 1628 / 1624, with no such line 1659); five and six: up to 300 or two groups (9 + 6 limbs
+//     60.6 / 58.1, two 69.2 / 66.9, four 95.5 / 95.1, with no line 99.1); more: a single group (nothing repeated: 2^16, 3 + 8 limbs, eight
+//     rotations 160 / 141), or two of four rows and more (7 + 8 limbs: one rotation 60.4 / 61.5, eight 233 / 222; with 13 + 8, four groups,
+//     eight 428 / 450)
+static u32 mid_conv_per(const ckks_ctx* c, u32 nd, u32 ap, u32 n_targets, u32 rows) {
+    if (!ntt_has_modup(c) || ntt_one_pass(c)) return 0;
+    if (c->log_hi > 3) {
+        const u32 groups = (n_targets + HC_T - 1) / HC_T, wgs = groups * rows << c->log_hi;
+        bool together;
+        if (nd == 1) together = true;
+        else if (nd <= 4) together = groups <= 2 || wgs <= 1200;
+        else if (nd <= 6) together = groups <= 2 || wgs <= 300;
+        else together = (nd <= 8 || (nd == 9 && ap == 12)) && (groups == 1 || (groups == 2 && rows >= 4));  // (ntt_fwd_hi_conv_lds_kernel: up to nine)
+        return together ? HC_T : 0;
+    }
+    if (nd > 1 && (nd << c->log_hi) > 40) return 0;
+    u32 per = 4;  // fewer, and more workgroups, until every CU has one
+    while (per > 1 && (1u << CKKS_TILE_LOG) / NTT_THREADS * rows * ((n_targets + per - 1) / per) < 256) per >>= 1;
+    return per;
+}
+u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n) {
+    const u32 nd = c->alpha < level + 1 ? c->alpha : level + 1;
+    return mid_conv_per(c, nd, c->alpha_pad, c->ext_limbs(level) - nd, n * c->live_digits(level));
+}
+u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys) { return mid_conv_per(c, c->num_p + (merged ? 1 : 0), merged ? c->k2_pad : c->k_pad, merged ? level : level + 1, polys); }
+u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys) { return mid_conv_per(c, 1, 4, level, polys); }
+
+template <int LOG_HI>
+static void launch_mid_conv_hi(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue& mp) {
+#define MID_CONV(ND) hipLaunchKernelGGL((ntt_mid_conv_kernel<LOG_HI, ND>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp, mp)
+    if (cp.nd == 1) MID_CONV(1);
+    else if (cp.nd == 2) MID_CONV(2);
+    else if (cp.nd == 3) MID_CONV(3);
+    else if (cp.nd == 4) MID_CONV(4);
+    else if (cp.nd == 5) MID_CONV(5);
+    else if constexpr (LOG_HI < 3) {
+        if (cp.nd == 6) MID_CONV(6);
+        else if (cp.nd == 7) MID_CONV(7);
+        else if (cp.nd == 8) MID_CONV(8);
+        else if (cp.nd == 9) MID_CONV(9);
+        else MID_CONV(10);
+    }
+#undef MID_CONV
+}
+static void launch_mid_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue& mp) {
+    cp.groups = (n_targets + cp.per - 1) / cp.per;
+    const dim3 grid((1u << CKKS_TILE_LOG) / NTT_THREADS, cp.groups * batch, digits);
+    if (log_hi == 2) launch_mid_conv_hi<2>(grid, st, args, pl, cp, mp);
+    else launch_mid_conv_hi<3>(grid, st, args, pl, cp, mp);
+}
+
+static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp,
+                           const MidPrologue* mp) {
+    if (mp && log_hi <= 3) {
+        launch_mid_conv(log_hi, n_targets, digits, batch, st, args, pl, cp, *mp);
+        return;
+    }
     switch (log_hi) {
-        case 1: launch_hi_conv_ap<1>(n_targets, digits, batch, st, args, pl, cp); break;
-        case 2: launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp); break;
-        case 3: launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp); break;
-        case 4: launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp); break;
-        case 5: launch_hi_conv_ap<5>(n_targets, digits, batch, st, args, pl, cp); break;
-        default: launch_hi_conv_ap<6>(n_targets, digits, batch, st, args, pl, cp); break;
+        case 1: launch_hi_conv_ap<1>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        case 2: launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        case 3: launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        case 4: launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        case 5: launch_hi_conv_ap<5>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        default: launch_hi_conv_ap<6>(n_targets, digits, batch, st, args, pl, cp, mp); break;
     }
 }
 
@@ -1751,9 +2016,12 @@ static void launch_ring(const ckks_ctx* c, bool inverse, bool mul, u32 entries, 
 static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                                  size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs,
                                  const FwdEpilogue* epilogue, const TwF* inv_scale, const ConvPrologue* conv,
-                                 const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, bool lo_done = false) {
+                                 const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH,
+                                 const MidPrologue* mid = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
-    if (lo_done && (!inverse || c->log_hi < 2 || src != dst || src_ptrs)) return hipErrorInvalidValue;
+    if (passes != NTT_BOTH && (!inverse || c->log_hi < 2)) return hipErrorInvalidValue;
+    if (passes == NTT_HI && (src != dst || src_ptrs)) return hipErrorInvalidValue;
+    if (mid && (!conv || !conv->per || c->log_hi < 2)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
@@ -1844,7 +2112,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             args.last = 0;
             if (conv) {  // reads the digit's nd limbs for every target limb (from cache after the first), writes the target limbs
                 ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * batch * ((double)conv->nd + pl.n), hi_ops);
-                launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv);
+                launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv, mid);
             } else {
                 ProfScope ps__(c, K_NTT_FWD_HI, st, pass_bytes, hi_ops);
                 hi(args, pl);
@@ -1863,7 +2131,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
         }
     } else {
         args.last = c->log_hi == 0;
-        if (!lo_done) {
+        if (passes != NTT_HI) {
             ProfScope ps__(c, K_NTT_INV_LO, st, mul_ptrs ? 1.5 * pass_bytes : pass_bytes, lo_ops);
             if (mul_ptrs) {  // one item per workgroup (see lo_items)
                 dim3 g1 = grid_lo;
@@ -1873,15 +2141,15 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             }
             else lo(args, pl);
         }
-        if (c->log_hi > 0) { ProfScope ps__(c, K_NTT_INV_HI, st, pass_bytes, hi_ops); hi(second, pd); }
+        if (c->log_hi > 0 && passes != NTT_LO) { ProfScope ps__(c, K_NTT_INV_HI, st, pass_bytes, hi_ops); hi(second, pd); }
     }
     return hipGetLastError();
 }
 
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst, size_t dst_bstride,
                       const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs, const FwdEpilogue* epilogue,
-                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k, bool lo_done) {
-    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k, lo_done);
+                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k, NttPasses passes) {
+    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k, passes);
 }
 
 // Small launches take all digits at once: one converting hi pass and (unless the inner product takes it from there) one lo pass,
@@ -1890,7 +2158,7 @@ hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t sr
 // workgroups per digit on, a digit fills the chip by itself and goes through its two passes alone: what the second reads is
 // then still in the last-level cache, and the other stream's kernels get their turn between the launches (all digits at once:
 // 1 % slower for 64 channels, 2 % for the sixteen-channel activation).
-hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st, bool hi_only) {
+hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_t y_bstride, u64* digits, u32 n, hipStream_t st, bool hi_only, u32 mid_per) {
     if (!ntt_has_modup(c) || n == 0) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level), L1 = level + 1;
     ConvPrologue cp;
@@ -1903,7 +2171,7 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
     cp.groups = 0;
     cp.alpha = c->alpha;
     cp.n_src = L1;
-    cp.digit0 = cp.pad = 0;
+    cp.digit0 = cp.per = 0;
     cp.convf_dstride = (size_t)c->M * c->alpha_pad;
     cp.dst_dstride = (size_t)E * c->N;
     PolyList all;
@@ -1919,7 +2187,9 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
     args.log_n = c->log_n;
     args.log_lo = c->log_lo;
     args.log_hi = c->log_hi;
-    const bool together = ((E - cp.nd + 3) / 4 * n << c->log_hi) < 768;
+    const MidPrologue mp = {c->d_itwf, c->d_modup_prep_f + (size_t)level * c->num_q, 0, 1};
+    cp.per = mid_per;
+    const bool together = (mid_per && c->log_hi <= 3) || ((E - cp.nd + 3) / 4 * n << c->log_hi) < 768;
     for (u32 j0 = 0; j0 < beta; j0 += together ? beta : 1) {
         const u32 nj = together ? beta : 1;
         double rows = 0.0;  // transformed limb-polys
@@ -1945,7 +2215,7 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
         }
         {
             ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * (n * (together ? (double)L1 : (double)(E - most)) + rows), 0.5 * rows * c->N * c->log_hi);
-            launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp);
+            launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp, mid_per ? &mp : nullptr);
         }
         if (hi_only) continue;  // the caller's own lo pass follows (launch_ntt_lo_mac)
         PolyList pl = all;
@@ -2030,7 +2300,7 @@ hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, h
 }
 
 hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue) {
+                              const FwdEpilogue* epilogue, u32 mid_per) {
     if (level == 0 || !c->d_rescale_conv_f) return hipErrorInvalidValue;
     ConvPrologue cp;
     cp.y = y;
@@ -2039,12 +2309,14 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
     cp.lo = 0;
     cp.nd = 1;
     cp.ap = 4;
-    cp.alpha = cp.n_src = cp.digit0 = cp.pad = 0;
+    cp.alpha = cp.n_src = cp.digit0 = cp.per = 0;
     cp.convf_dstride = cp.dst_dstride = 0;
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < level ? a : 0);
     pl.n = level;
-    return launch_ntt_any(c, false, dst, level, dst, level, pl, batch, st, nullptr, epilogue, nullptr, &cp);
+    const MidPrologue mp = {c->d_itwf, c->d_rescale_prep_f, level, level};
+    cp.per = mid_per;
+    return launch_ntt_any(c, false, dst, level, dst, level, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);
 }
 
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
@@ -2123,7 +2395,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
 }
 
 hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue) {
+                              const FwdEpilogue* epilogue, u32 mid_per) {
     if (merged && level == 0) return hipErrorInvalidValue;
     const u32 n_out = merged ? level : level + 1;
     ConvPrologue cp;
@@ -2133,10 +2405,13 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
     cp.lo = merged ? level : level + 1;  // the dropped limbs sit at consecutive positions of the extended polynomial
     cp.nd = merged ? c->num_p + 1 : c->num_p;
     cp.ap = merged ? c->k2_pad : c->k_pad;
-    cp.alpha = cp.n_src = cp.digit0 = cp.pad = 0;
+    cp.alpha = cp.n_src = cp.digit0 = cp.per = 0;
     cp.convf_dstride = cp.dst_dstride = 0;
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < n_out ? a : 0);
     pl.n = n_out;
-    return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp);
+    const MidPrologue mp = {c->d_itwf, merged ? c->d_moddown_rs_prep_f + (size_t)level * c->M : c->d_moddown_prep_f, merged ? level : c->num_q,
+                            merged ? c->num_q : c->num_q + 1};
+    cp.per = mid_per;
+    return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);
 }

@@ -264,3 +264,29 @@ def test_inner_products_go_on_into_the_inverse_pass(log_n, num_q, num_p, dnum, l
     outs = hx.he_poly_act_deg7(ctx, [d_cts[i % 2] for i in range(n_ct)], level, k, rlk, merged=True)
     for i, out in enumerate(outs):
         assert np.array_equal(hx.to_host(out), want[i % 2]), f"ciphertext {i}"
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(13, 10, 10, 1, 9), (13, 11, 9, 2, 10), (13, 5, 1, 5, 4), (14, 9, 4, 3, 8), (14, 6, 6, 1, 5),
+                                                          (15, 5, 1, 5, 4), (15, 5, 8, 2, 4), (15, 13, 5, 3, 12), (16, 5, 1, 5, 4), (17, 3, 2, 2, 2)])
+def test_inverse_pass_inside_the_conversion(log_n, num_q, num_p, dnum, level):
+    """The inverse transform's second pass inside the converting first pass and on its own: one source limb (rescales; digits of one limb,
+    each with a modulus of its own), ragged digits, the most points a thread takes on the small rings (ten limbs of four, five of
+    eight) and one more (six of eight: pass by pass), two to nine limbs through LDS with one group of targets (eight special primes and
+    the level's limb in a merged division) and more, N = 2^17."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(9000 + log_n * 10 + num_q)
+    ct = rand_ct(rng, p.moduli, level, orc.N)
+    d_ct = hx.from_host(ct)
+    key = np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)])
+    dkey = hx.ckks_key_load(ctx, hx.from_host(key), hx.ckks_galois_element(ctx, 3))
+    for lv in {level, 1, level // 2 + 1}:
+        c = np.ascontiguousarray(ct[:, :lv + 1])
+        assert np.array_equal(hx.to_host(hx.ckks_rescale(ctx, hx.from_host(c), lv)), orc.rescale(c, lv)), f"rescale from level {lv}"
+    for hoisted in (True, False):
+        (got,) = hx.ckks_rotate_hoisted(ctx, d_ct, level, [3], [dkey], hoisted)
+        assert np.array_equal(hx.to_host(got), orc.rotate_many(ct, level, [3], [key], hoisted)[0]), f"hoisted = {hoisted}"
+    if level >= 4:
+        k = (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+        (got,) = hx.he_poly_act_deg7(ctx, [d_ct], level, k, hx.ckks_key_load(ctx, hx.from_host(key), 0), merged=True)
+        assert np.array_equal(hx.to_host(got), orc.poly_activation_merged(ct, level, k, key)), "activation"
