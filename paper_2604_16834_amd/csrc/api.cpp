@@ -116,8 +116,9 @@ size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
 // hi_only (double-precision transforms only): the forward transforms stop after their first pass; the caller finishes them
 // inside the inner product (launch_ntt_lo_mac).
 // muls (with hi_only): the polynomial to decompose is srcs[b] (.) muls[b], formed as the inverse transform loads it.
+// gals (with hi_only, ntt_has_mac): it is sigma_gals[b](srcs[b]); the own limbs stay where they are, not permuted.
 int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const KsWs& ws, hipStream_t st, bool hi_only = false,
-              const u64* const* muls = nullptr) {
+              const u64* const* muls = nullptr, const u32* gals = nullptr) {
     const u32 N = c->N, L1 = level + 1, E = c->ext_limbs(level), beta = c->live_digits(level);
     for (u32 b = 0; b < CT_BATCH; b++) ws.own[b] = (b < n && !muls) ? srcs[b] : nullptr;  // a product has no stored own limbs
     if (muls && !hi_only) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: product source without the fused inner product");
@@ -129,7 +130,7 @@ int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const
     if (hi_only && !fused) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: fused inner product without fused ModUp");
     const u32 mid = ntt_mid_modup(c, level, n);  // the inverse's second pass inside the converting one
     HIP_TRY(launch_ntt(c, true, nullptr, 0, ws.y, L1, range_list(0, L1, 0), n, st, srcs, nullptr,
-                       fused ? c->d_modup_prep_f + (size_t)level * c->num_q : nullptr, muls, nullptr, mid ? NTT_LO : NTT_BOTH));  // (positions 0..level are moduli 0..level)
+                       fused ? c->d_modup_prep_f + (size_t)level * c->num_q : nullptr, muls, nullptr, mid ? NTT_LO : NTT_BOTH, gals));  // (positions 0..level are moduli 0..level)
     if (fused) {
         HIP_TRY(launch_ntt_modup(c, level, (const double*)ws.y, ws.y_b, ws.digits, n, st, hi_only, mid));
         return CKKS_OK;
@@ -572,42 +573,35 @@ hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64
     return hipSuccess;
 }
 
-// n <= CT_BATCH different ciphertexts srcs[b] ([2][level+1][N]) rotated, outs[b] = Rot(srcs[b]) with keys[b] / gal[b]
-// ([2][level+1][N], no overlap).  One inner-product launch for all of them (a key streams once for neighbouring items that
-// share it); it adds P sigma(c0), so that the division by P is the rotation.
+// n <= CT_BATCH ciphertexts srcs[b] ([2][level+1][N]) rotated, outs[b] = Rot(srcs[b]) with keys[b] / gal[b] ([2][level+1][N], no
+// overlap).  Where a key switch takes its inner product inside the forward transforms' second pass, the permuted polynomial is
+// decomposed (the digits of a permuted polynomial are the permuted digits), gathered as the inverse transform loads it: no
+// kernel for the automorphism, the extended digits are never written in evaluation form.  Elsewhere one inner-product launch for all of them reads
+// the digits through sigma (a key streams once for neighbouring items that share it).  Either adds P sigma(c0), so that the
+// division by P is the rotation.  At N = 2^16, two to four limbs, eight rotations in us, digits read through sigma / permuted: 143 / 118.
 // accs (optional): outs[b] = Rot(srcs[b]) + accs[b], the sum formed by the division's last step.
 int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, const u32* gal,
                      u64* const* outs, const KsWs& ws, hipStream_t st, const u64* const* accs = nullptr) {
-    const size_t N = c->N, L1 = level + 1;
-    const u64* c1s[CT_BATCH];
-    FinalItem items[CT_BATCH];
-    for (u32 b = 0; b < n; b++) c1s[b] = srcs[b] + L1 * N;
-    int rc = run_modup(c, level, c1s, n, ws, st);
-    if (rc) return rc;
-    const u64* kd[CT_BATCH];
-    for (u32 b = 0; b < n; b++) kd[b] = keys[b]->d_key;
-    HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), kd, gal, srcs, ws.v, ws.v_b, n, st));
-    for (u32 b = 0; b < n; b++) items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
-    return run_moddown(c, level, ws, n, items, st);
-}
-
-// The same for ciphertexts that are given permuted, sigma_gal(src), in contexts with the fused inner product (the digits of a
-// permuted polynomial are the permuted digits): the extended digits are never written in evaluation form.
-int run_rotate_permuted(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, u64* const* outs, const KsWs& ws,
-                        hipStream_t st) {
+    const size_t L1 = level + 1;
+    const bool mac = ntt_has_mac(c);
     const u64 *c1s[CT_BATCH], *kd[CT_BATCH];
     u64* vs[CT_BATCH];
     FinalItem items[CT_BATCH];
     for (u32 b = 0; b < n; b++) {
-        c1s[b] = srcs[b] + (size_t)(level + 1) * c->N;
+        c1s[b] = srcs[b] + L1 * c->N;
         kd[b] = keys[b]->d_key;
         vs[b] = ws.v + b * ws.v_b;
-        items[b] = FinalItem{srcs[b], nullptr, nullptr, outs[b], 1, 0};
+        items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
     }
-    int rc = run_modup(c, level, c1s, n, ws, st, true);
+    int rc = run_modup(c, level, c1s, n, ws, st, mac, nullptr, mac ? gal : nullptr);
     if (rc) return rc;
-    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st, dropped_from(level, false)));
-    return run_moddown(c, level, ws, n, items, st, false, true);
+    if (mac) {
+        const MacRotate rot = {srcs, gal};
+        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st, dropped_from(level, false), nullptr, &rot));
+    } else {
+        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), kd, gal, srcs, ws.v, ws.v_b, n, st));
+    }
+    return run_moddown(c, level, ws, n, items, st, false, mac);
 }
 
 size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) {
@@ -630,10 +624,8 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the merge");
     const u64* masks[KS_MAX_BATCH];
     u64* mouts[KS_MAX_BATCH];
-    u32 mg[KS_MAX_BATCH];
-    const bool permuted = ntt_has_mac(c);  // the blocks take their automorphism as they are masked
-    for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems, mg[i] = permuted && i ? gal[i] : 1;
-    HIP_TRY(launch_mask_mul(c, level, masks, cts, mouts, g, st, mg));
+    for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems;
+    HIP_TRY(launch_mask_mul(c, level, masks, cts, mouts, g, st));
     // blocks 1..g-1: every block has its own key; a batch shares the decomposition and ModDown launches
     for (u32 i0 = 1; i0 < g; i0 += nb) {
         const u32 n = g - i0 < nb ? g - i0 : nb;
@@ -643,8 +635,7 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
             srcs[b] = masked + (i0 + b) * ct_elems;
             outs[b] = rotated + (i0 + b) * ct_elems;
         }
-        int rc = permuted ? run_rotate_permuted(c, level, n, srcs, keys + i0, outs, ws, st) : run_rotate_batch(c, level, n, srcs, keys + i0, gal + i0, outs, ws, st);
-        if (rc) return rc;
+        if (int rc = run_rotate_batch(c, level, n, srcs, keys + i0, gal + i0, outs, ws, st)) return rc;
     }
     const u64* terms[KS_MAX_BATCH];
     terms[0] = masked;
@@ -1122,31 +1113,25 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     FinalItem items[CT_BATCH];
     const ckks_key* pend_key[CT_BATCH];
     u32 nb = 0, lane = 0;
-    // the pending unhoisted rotations: sigma_g(c1) of each, one decomposition and one ModDown for the batch
+    // the pending unhoisted rotations: one decomposition of sigma_g(c1) per rotation and one ModDown for the batch
     auto flush_unhoisted = [&]() -> int {
         const u64 *srcs[CT_BATCH], *ks[CT_BATCH];
+        u64* outs[CT_BATCH];
         u32 gs[CT_BATCH];
-        for (u32 b = 0; b < nb; b++) {
-            srcs[b] = pc1 + (size_t)b * L1 * N;
+        const u32 n = nb;
+        nb = 0;
+        for (u32 b = 0; b < n; b++) {
             gs[b] = items[b].g;
             ks[b] = pend_key[b]->d_key;
+            outs[b] = items[b].out;
+            srcs[b] = ntt_has_mac(c) ? ct : pc1 + (size_t)b * L1 * N;
         }
-        HIP_TRY(launch_automorph(c, (u32)L1, c1, gs, nb, pc1, st));
-        const bool mac = ntt_has_mac(c);
-        int rc = run_modup(c, level, srcs, nb, ws, st, mac);
-        if (rc) return rc;
-        // the digits already belong to sigma_g(c1): no gather in the inner product, only on c0
-        if (mac) {  // every item with its own key, inside the forward transforms' second pass
-            u64* vs[CT_BATCH];
-            for (u32 b = 0; b < nb; b++) vs[b] = ws.v + b * ws.v_b;
-            HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), ks, vs, nb, st, dropped_from(level, false)));
-        } else {
-            for (u32 b = 0; b < nb; b++) gs[b] = 1;
-            HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), ks, gs, nullptr, ws.v, ws.v_b, nb, st));
-        }
-        rc = run_moddown(c, level, ws, nb, items, st, false, mac);
-        nb = 0;
-        return rc;
+        if (ntt_has_mac(c)) return run_rotate_batch(c, level, n, srcs, pend_key, gs, outs, ws, st);
+        HIP_TRY(launch_automorph(c, (u32)L1, c1, gs, n, pc1, st));
+        if (int rc = run_modup(c, level, srcs, n, ws, st)) return rc;
+        for (u32 b = 0; b < n; b++) gs[b] = 1;  // the digits already belong to sigma_g(c1): no gather in the inner product, only on c0
+        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), ks, gs, nullptr, ws.v, ws.v_b, n, st));
+        return run_moddown(c, level, ws, n, items, st);
     };
     const bool fused_hoist = hoisted && c->live_digits(level) <= 4;
     auto flush_hoisted = [&]() -> int {

@@ -223,7 +223,8 @@ enum NttPasses { NTT_BOTH = 0, NTT_LO, NTT_HI };
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
                       size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs = nullptr,
                       const FwdEpilogue* epilogue = nullptr, const TwF* inv_scale = nullptr, const u64* const* mul_ptrs = nullptr,
-                      const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH);
+                      const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH, const u32* gals = nullptr);
+// gals (inverse, with src_ptrs, contexts with ntt_has_mac): batch item b is sigma_gals[b] of src_ptrs[b], gathered on load
 // passes (inverse, two-pass rings): the first pass alone (a kernel that goes on from there follows: ntt_mid_*), or the second alone, in place
 // (the first has been done: launch_ntt_lo_mac with inv_from)
 // mul_ptrs (inverse, with src_ptrs, double-precision arithmetic): batch item b is src_ptrs[b] (.) mul_ptrs[b], formed on load;
@@ -275,8 +276,14 @@ struct MacProduct {
     const u64* ka = nullptr;
     const u64* kb = nullptr;
 };
+// rot: item b is the rotation by the Galois element gs[b] of the ciphertext (c0[b], decomposed polynomial) that was decomposed under
+// sigma (launch_ntt with gals): P sigma(c0) joins component 0
+struct MacRotate {
+    const u64* const* c0;
+    const u32* gs;
+};
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr);
+                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr);
 // rings whose transforms run as one kernel (the whole limb-poly in one workgroup)
 inline bool ntt_one_pass(const ckks_ctx* c) { return c->log_hi == 1; }
 // whether a key switch takes its inner product inside the forward transforms' second pass (launch_ntt_lo_mac) rather than behind
@@ -320,8 +327,7 @@ hipError_t launch_rescale_final(const ckks_ctx* c, u32 level, const PtrList8& ct
                                 u32 n, hipStream_t st);
 hipError_t launch_tensor(const ckks_ctx* c, u32 level, const PtrList8& a, size_t a_cstride, const PtrList8& b, size_t b_cstride,
                          u64* d0, u64* d1, u64* d2, u32 n, const u64* add, size_t add_bstride, hipStream_t st);
-hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st,
-                           const u32* gs = nullptr);
+hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st);
 hipError_t launch_key_expand_a(const ckks_ctx* c, u64 seed, u64* key, hipStream_t st);
 hipError_t launch_add_plain(const ckks_ctx* c, u32 level, const u64* pt, u64* ct, hipStream_t st);
 hipError_t launch_ct_sum(const ckks_ctx* c, u32 level, const PtrList8& items, u32 n, u64* out, hipStream_t st, bool extended = false);

@@ -257,6 +257,7 @@ struct NttArgs {
     // loop variant of the forward lo pass, ModUp: the items are (polynomial, digit) pairs, digits fastest, `beta` of them per
     // polynomial; limb e <= level is transformed for every digit but the one it belongs to, e / alpha (0: plain items)
     u32 beta, alpha, level, pad3;
+    u32 gal[KS_MAX_BATCH];  // inverse, first pass, automorphism variant: batch item b is sigma_gal[b] of src_list.p[b]
     const TwF* inv_scale;  // inverse, last pass (double-precision arithmetic): the limb of modulus m is scaled by inv_scale[m]
                            // instead of 1/N and stored as the centred residue in a double (the form ModUp's conversion reads)
 };
@@ -633,11 +634,17 @@ struct MacEpilogue {
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
     // addends are d0 = a0 (.) b0 and d1 = a0 (.) b1 + a1 (.) b0 (D.own is not read)
     PtrList8 a0, a1, b0, b1;
+    // ROT: item b is a rotation by gal[b] of the ciphertext (a0, D.own): the digits are those of sigma(D.own), the own-limb term and the
+    // addend P sigma(a0) are gathered as they are read
+    u32 gal[KS_MAX_BATCH];
     // LIN (with PROD): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
     PtrList8 lx, ly;
     size_t x_cstride, y_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
 };
+
+// poly[x] through a wave-uniform base and a 32-bit offset (a polynomial is at most 1 MiB): half the address registers
+__device__ __forceinline__ u64 word_at(const u64* poly, u32 x) { return *reinterpret_cast<const u64*>(reinterpret_cast<const char*>(poly) + 8 * x); }
 
 // The inverse lo pass of a slice whose points tid + 256 i the workgroup's threads hold, |v| <= q / 2 + 1 (ntt_inv_lo_kernel's rounds
 // behind one more exchange), for both components of an inner product one after the other: the slice's inverse twiddles are fetched
@@ -696,10 +703,10 @@ __device__ __forceinline__ void mac_inverse_lo(double (&r0)[8], double (&r1)[8],
     }
 }
 
-// PROD, LIN (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
+// PROD, LIN, ROT (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
 // use, one round trip to memory per point.
-template <bool PROD, bool LIN>
+template <bool PROD, bool LIN, bool ROT>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs args, PolyList pl, MacEpilogue ep) {
     typedef ArithF64 A;
     typedef double E;
@@ -852,18 +859,34 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     } else if (!PROD && e <= ep.level) {
         // the digit that owns this limb
         const u64* kj = key + (size_t)own * 2 * kstride;
-        const u64* yo = ep.D.own.p[b] + (size_t)e * N + off;
-        u64 ry[8], rk0[8], rk1[8];
+        const u64* yo = ep.D.own.p[b] + (size_t)e * N;
+        const u64* co = ROT ? ep.a0.p[b] + (size_t)e * N : nullptr;
+        const u32 g = ROT ? ep.gal[b] : 1;
+        const double pres = ROT ? mc.q - A::from_u64(ep.negp[e]) : 0.0;  // P mod q_e
+        u32 x0 = (u32)off + tid;
+        if (ROT) asm volatile("" : "+v"(x0));  // not the same for every item as far as the compiler can tell: it would keep what the index is made of
+        constexpr int HP = ROT ? 4 : 8;  // points requested before the first is used
 #pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const u32 x = tid + 256 * i;
-            ry[i] = yo[x], rk0[i] = kj[x], rk1[i] = kj[kstride + x];
-        }
+        for (int h = 0; h < 8; h += HP) {
+            u64 ry[HP], rc[HP], rk0[HP], rk1[HP];
 #pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const double y = A::from_u64(ry[i]);
-            acc0[i] += A::mulmod_any(y, A::from_u64(rk0[i]), mc.q, mc.qinv);
-            acc1[i] += A::mulmod_any(y, A::from_u64(rk1[i]), mc.q, mc.qinv);
+            for (int i = 0; i < HP; i++) {
+                const u32 x = tid + 256 * (h + i);
+                if (ROT) {
+                    const u32 xs = galois_gather_index(x0 + 256 * (h + i), g, args.log_n);
+                    ry[i] = word_at(yo, xs), rc[i] = word_at(co, xs);
+                } else {
+                    ry[i] = yo[off + x];
+                }
+                rk0[i] = kj[x], rk1[i] = kj[kstride + x];
+            }
+#pragma unroll
+            for (int i = 0; i < HP; i++) {
+                const double y = A::from_u64(ry[i]);
+                acc0[h + i] += A::mulmod_any(y, A::from_u64(rk0[i]), mc.q, mc.qinv);
+                if (ROT) acc0[h + i] += A::mulmod_any(A::from_u64(rc[i]), pres, mc.q, mc.qinv);
+                acc1[h + i] += A::mulmod_any(y, A::from_u64(rk1[i]), mc.q, mc.qinv);
+            }
         }
     }
     if (LIN) request_next();
@@ -912,9 +935,19 @@ __device__ __forceinline__ void inv_first_points(const NttArgs& args, const type
     }
 }
 
+// the eight points 8 t + j of a slice of sigma_g of a polynomial: the map takes them to an aligned run of eight
+__device__ __forceinline__ void load_permuted(const u64* __restrict__ poly, u32 x0, u32 g, u32 log_n, ulonglong2* raw) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        raw[j].x = word_at(poly, galois_gather_index(x0 + 2 * j, g, log_n));
+        raw[j].y = word_at(poly, galois_gather_index(x0 + 2 * j + 1, g, log_n));
+    }
+}
+
 // MUL (double-precision arithmetic, first pass, source list): the transform's input is the pointwise product of two
 // polynomials (the d2 = a1 (.) b1 of a ciphertext product), formed as the points are loaded: d2 itself is never stored.
-template <class A, int IT, bool MUL = false>
+// GAL (likewise): it is the polynomial under the item's automorphism, gathered as it is loaded.
+template <class A, int IT, bool MUL = false, bool GAL = false>
 __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 8))) void ntt_inv_lo_kernel(NttArgs args, PolyList pl) {
     typedef typename A::E E;
     __shared__ E lds0[LDS_PADDED_WORDS];
@@ -936,7 +969,9 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
     load_lo_tw<A, 2>(P, 512 * TA + 2 * tid + 1, wd + 3);
     load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
     const size_t moff = ((size_t)pl_at(pl.spos, tile.a) << args.log_n) + off + 8 * tid;  // MUL: the multiplier's point
-    {
+    if constexpr (GAL) {
+        load_permuted(P.src, (u32)off + 8 * tid, args.gal[b0], args.log_n, raw);
+    } else {
         const ulonglong2* in = reinterpret_cast<const ulonglong2*>(P.src + off + 8 * tid);
 #pragma unroll
         for (int j = 0; j < 4; j++) raw[j] = in[j];
@@ -953,9 +988,14 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
         E* buf1 = (it & 1) ? lds0 : lds1;
         inv_first_points<A, MUL>(args, P.mc, raw, raw2, v);
         if (it + 1 < IT && (u32)(it + 1) < cnt) {  // the next item's points, a tile ahead
-            const ulonglong2* in = reinterpret_cast<const ulonglong2*>(item_src<A>(args, pl, b0 + it + 1, tile.a) + off + 8 * tid);
+            const u64* next = item_src<A>(args, pl, b0 + it + 1, tile.a);
+            if constexpr (GAL) {
+                load_permuted(next, (u32)off + 8 * tid, args.gal[b0 + it + 1], args.log_n, raw);
+            } else {
+                const ulonglong2* in = reinterpret_cast<const ulonglong2*>(next + off + 8 * tid);
 #pragma unroll
-            for (int j = 0; j < 4; j++) raw[j] = in[j];
+                for (int j = 0; j < 4; j++) raw[j] = in[j];
+            }
             if constexpr (MUL) {
                 const ulonglong2* in2 = reinterpret_cast<const ulonglong2*>(args.mul_list.p[b0 + it + 1] + moff);
 #pragma unroll
@@ -1763,7 +1803,13 @@ static u32 lo_items(u32 slices, u32 batch, u32 most) {
 }
 
 template <class A, int IT>
-static void launch_inv_lo_it(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul = false) {
+static void launch_inv_lo_it(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul, bool gal) {
+    if constexpr (std::is_same<A, ArithF64>::value) {
+        if (gal) {
+            hipLaunchKernelGGL((ntt_inv_lo_kernel<A, IT, false, true>), grid, dim3(NTT_THREADS), 0, st, args, pl);
+            return;
+        }
+    }
     if constexpr (std::is_same<A, ArithF64>::value && IT == 1) {  // the product-forming variant takes one item
         if (mul) {
             hipLaunchKernelGGL((ntt_inv_lo_kernel<A, IT, true>), grid, dim3(NTT_THREADS), 0, st, args, pl);
@@ -1812,9 +1858,9 @@ static void launch_lo_div(dim3 grid, hipStream_t st, const NttArgs& args, const 
 #undef LO_DIV_LAUNCH
 }
 template <class A>
-static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul = false) {
-    if (items == 2 && !mul) launch_inv_lo_it<A, 2>(grid, st, args, pl, false);
-    else launch_inv_lo_it<A, 1>(grid, st, args, pl, mul);
+static void launch_inv_lo(u32 items, dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul, bool gal) {
+    if (items == 2 && !mul) launch_inv_lo_it<A, 2>(grid, st, args, pl, false, gal);
+    else launch_inv_lo_it<A, 1>(grid, st, args, pl, mul, gal);
 }
 
 // Target limbs per workgroup: four share one fetch of the source residues; in a launch that would not give every CU two
@@ -2017,13 +2063,14 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                                  size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs,
                                  const FwdEpilogue* epilogue, const TwF* inv_scale, const ConvPrologue* conv,
                                  const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH,
-                                 const MidPrologue* mid = nullptr) {
+                                 const MidPrologue* mid = nullptr, const u32* gals = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
     if (passes != NTT_BOTH && (!inverse || c->log_hi < 2)) return hipErrorInvalidValue;
     if (passes == NTT_HI && (src != dst || src_ptrs)) return hipErrorInvalidValue;
     if (mid && (!conv || !conv->per || c->log_hi < 2)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
+    if (gals && (!inverse || !src_ptrs || mul_ptrs || !ntt_has_mac(c))) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
     if (src_ptrs && batch > KS_MAX_BATCH) return hipErrorInvalidValue;
     if (epilogue && (inverse || !ntt_has_epilogue(c) || batch > 2 * KS_MAX_BATCH)) return hipErrorInvalidValue;
@@ -2055,6 +2102,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
     for (u32 b = 0; b < KS_MAX_BATCH; b++) {
         args.src_list.p[b] = (src_ptrs && b < batch) ? src_ptrs[b] : nullptr;
         args.mul_list.p[b] = (mul_ptrs && b < batch) ? mul_ptrs[b] : nullptr;
+        args.gal[b] = (gals && b < batch) ? gals[b] : 1;
     }
     args.inv_scale = inv_scale;
     args.use_lin = lin_k ? 1 : 0;
@@ -2103,8 +2151,8 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             if (f64) launch_fwd_lo_loop<ArithF64>(batch, grid_lo, st, a, l);
             else launch_fwd_lo_loop<ArithU64>(batch, grid_lo, st, a, l);
         } else {
-            if (f64) launch_inv_lo<ArithF64>(per_wg, grid_lo, st, a, l);
-            else launch_inv_lo<ArithU64>(per_wg, grid_lo, st, a, l);
+            if (f64) launch_inv_lo<ArithF64>(per_wg, grid_lo, st, a, l, false, gals != nullptr);
+            else launch_inv_lo<ArithU64>(per_wg, grid_lo, st, a, l, false, false);
         }
     };
     if (!inverse) {
@@ -2137,7 +2185,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                 dim3 g1 = grid_lo;
                 if (args.lo_group) g1.y = batch;
                 else g1.x = batch;
-                launch_inv_lo<ArithF64>(1, g1, st, args, pl, true);
+                launch_inv_lo<ArithF64>(1, g1, st, args, pl, true, false);
             }
             else lo(args, pl);
         }
@@ -2148,8 +2196,8 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
 
 hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst, size_t dst_bstride,
                       const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs, const FwdEpilogue* epilogue,
-                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k, NttPasses passes) {
-    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k, passes);
+                      const TwF* inv_scale, const u64* const* mul_ptrs, const u64* lin_k, NttPasses passes, const u32* gals) {
+    return launch_ntt_any(c, inverse, src, src_bstride, dst, dst_bstride, pl, batch, st, src_ptrs, epilogue, inv_scale, nullptr, mul_ptrs, lin_k, passes, nullptr, gals);
 }
 
 // Small launches take all digits at once: one converting hi pass and (unless the inner product takes it from there) one lo pass,
@@ -2320,8 +2368,8 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 }
 
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod) {
-    if (!ntt_has_modup(c) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH) return hipErrorInvalidValue;
+                             hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot) {
+    if (!ntt_has_modup(c) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     NttArgs args = {};
     args.mc = c->d_mcf;
@@ -2345,7 +2393,9 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
         ep.key.p[b] = b < n ? keys[b] : nullptr;
         ep.out.p[b] = b < n ? outs[b] : nullptr;
         if (b < n && !ep.key.p[b]) return hipErrorInvalidValue;
-        ep.a0.p[b] = (prod && b < n) ? prod->a0[b] : nullptr;
+        ep.a0.p[b] = b < n ? (prod ? prod->a0[b] : (rot ? rot->c0[b] : nullptr)) : nullptr;
+        ep.gal[b] = (rot && b < n) ? rot->gs[b] : 1;
+        if (rot && b < n && !ep.a0.p[b]) return hipErrorInvalidValue;
         ep.a1.p[b] = (prod && b < n) ? prod->a1[b] : nullptr;
         ep.b0.p[b] = (prod && b < n) ? prod->b0[b] : nullptr;
         ep.b1.p[b] = (prod && b < n) ? prod->b1[b] : nullptr;
@@ -2383,13 +2433,14 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     const dim3 grid = args.lo_group ? dim3(args.lo_group, b_ext, slices / args.lo_group) : dim3(b_ext, slices);
     // in: the transformed rows, the own limbs, the addends, the keys (once per distinct key); out: two components
     if (lin) n_add = 4.0 * n;  // two components of two ciphertexts
-    ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (n_tr + (prod ? 4.0 : 1.0) * (level + 1.0) + 2.0 * E) + n_add * (level + 1.0) + n_keys * 2.0 * beta * E),
+    ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (n_tr + (prod ? 4.0 : (rot ? 2.0 : 1.0)) * (level + 1.0) + 2.0 * E) + n_add * (level + 1.0) + n_keys * 2.0 * beta * E),
                    0.5 * n * n_tr * c->N * c->log_lo);
     // which operands join after the digits is the same for the whole launch: one instantiation per case
-#define LO_MAC_LAUNCH(PROD, LIN) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<PROD, LIN>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
-    if (lin) LO_MAC_LAUNCH(true, true);
-    else if (prod) LO_MAC_LAUNCH(true, false);
-    else LO_MAC_LAUNCH(false, false);
+#define LO_MAC_LAUNCH(PROD, LIN, ROT) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<PROD, LIN, ROT>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
+    if (lin) LO_MAC_LAUNCH(true, true, false);
+    else if (prod) LO_MAC_LAUNCH(true, false, false);
+    else if (rot) LO_MAC_LAUNCH(false, false, true);
+    else LO_MAC_LAUNCH(false, false, false);
 #undef LO_MAC_LAUNCH
     return hipGetLastError();
 }

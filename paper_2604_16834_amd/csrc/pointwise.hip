@@ -292,36 +292,29 @@ hipError_t launch_tensor(const ckks_ctx* c, u32 level, const PtrList8& a, size_t
 }
 
 // ---- convolution operands -----------------------------------------------------------------------
-// out[comp][i] = sigma_g(mask[i] * ct[comp][i]): ciphertexts times plaintexts, each through the automorphism of its item (g = 1:
-// none), blockIdx.z = 2 item + comp
-__global__ __launch_bounds__(PW_THREADS) void mask_mul_kernel(PtrList8 masks, PtrList8 cts, OutList8 outs, GaloisList gl,
-                                                              const ModConst* __restrict__ mc, u32 log_n, u32 level) {
-    const u32 N = 1u << log_n;
+// out[comp][i] = mask[i] * ct[comp][i]: ciphertexts times plaintexts, blockIdx.z = 2 item + comp
+__global__ __launch_bounds__(PW_THREADS) void mask_mul_kernel(PtrList8 masks, PtrList8 cts, OutList8 outs, const ModConst* __restrict__ mc, u32 N, u32 level) {
     const u32 x = blockIdx.x * PW_THREADS + threadIdx.x;
     if (x >= N) return;
-    const u32 i = blockIdx.y, r = blockIdx.z >> 1, comp = blockIdx.z & 1, g = gl.g[r];
-    const u32 xs = g == 1 ? x : galois_gather_index(x, g, log_n);
+    const u32 i = blockIdx.y, r = blockIdx.z >> 1, comp = blockIdx.z & 1;
     const size_t row = ((size_t)comp * (level + 1) + i) * N;
-    outs.p[r][row + x] = mulmod_barrett(masks.p[r][(size_t)i * N + xs], cts.p[r][row + xs], mc[i]);
+    outs.p[r][row + x] = mulmod_barrett(masks.p[r][(size_t)i * N + x], cts.p[r][row + x], mc[i]);
 }
 
-// host arrays of n device pointers ([level+1][N]; [2][level+1][N] twice) and, optionally, Galois elements; KS_MAX_BATCH of them per launch
-hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st,
-                           const u32* gs) {
+// host arrays of n device pointers ([level+1][N]; [2][level+1][N] twice); KS_MAX_BATCH of them per launch
+hipError_t launch_mask_mul(const ckks_ctx* c, u32 level, const u64* const* masks, const u64* const* cts, u64* const* outs, u32 n, hipStream_t st) {
     for (u32 r0 = 0; r0 < n; r0 += KS_MAX_BATCH) {
         const u32 m = n - r0 < KS_MAX_BATCH ? n - r0 : KS_MAX_BATCH;
         PtrList8 ml, cl;
         OutList8 ol;
-        GaloisList gl;
         for (u32 r = 0; r < KS_MAX_BATCH; r++) {
-            gl.g[r] = (gs && r < m) ? gs[r0 + r] : 1;
             ml.p[r] = r < m ? masks[r0 + r] : nullptr;
             cl.p[r] = r < m ? cts[r0 + r] : nullptr;
             ol.p[r] = r < m ? outs[r0 + r] : nullptr;
         }
         dim3 grid((c->N + PW_THREADS - 1) / PW_THREADS, level + 1, 2 * m);
         ProfScope ps__(c, K_MASK_MUL, st, 40.0 * m * c->N * (level + 1.0), 2.0 * m * c->N * (level + 1.0));
-        hipLaunchKernelGGL(mask_mul_kernel, grid, dim3(PW_THREADS), 0, st, ml, cl, ol, gl, c->d_mc, c->log_n, level);
+        hipLaunchKernelGGL(mask_mul_kernel, grid, dim3(PW_THREADS), 0, st, ml, cl, ol, c->d_mc, c->N, level);
     }
     return hipGetLastError();
 }
