@@ -116,7 +116,7 @@ size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
 // hi_only (double-precision transforms only): the forward transforms stop after their first pass; the caller finishes them
 // inside the inner product (launch_ntt_lo_mac).
 // muls (with hi_only): the polynomial to decompose is srcs[b] (.) muls[b], formed as the inverse transform loads it.
-// gals (with hi_only, ntt_has_mac): it is sigma_gals[b](srcs[b]); the own limbs stay where they are, not permuted.
+// gals (with hi_only, ntt_has_modup): it is sigma_gals[b](srcs[b]); the own limbs stay where they are, not permuted.
 int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const KsWs& ws, hipStream_t st, bool hi_only = false,
               const u64* const* muls = nullptr, const u32* gals = nullptr) {
     const u32 N = c->N, L1 = level + 1, E = c->ext_limbs(level), beta = c->live_digits(level);
@@ -188,7 +188,7 @@ u32 dropped_from(u32 level, bool merged) { return merged ? level : level + 1; }
 int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const FinalItem* items, hipStream_t st, bool merged = false,
                 bool lo_done = false) {
     const u32 L1 = level + 1, E = c->ext_limbs(level), k = c->num_p;
-    const u32 mid = ntt_mid_moddown(c, level, merged, 2 * n);
+    const u32 mid = ntt_mid_moddown(c, level, merged, 2 * n, lo_done);
     if (merged) {
         PolyList dl = range_list(level, k + 1, c->num_q - 1);  // positions level.. ; moduli fixed up below
         dl.mod[0] = (unsigned char)level;
@@ -248,7 +248,8 @@ int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_c
     if (ntt_has_modup(c)) {
         // the rescale as a division by one dropped limb through the fused passes: the inverse transform leaves centred doubles,
         // the forward transform reduces them modulo each remaining limb as it loads and applies (c_i - w_i) q_level^-1 as it stores
-        HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f, nullptr, nullptr, mid ? NTT_LO : NTT_BOTH));
+        const bool one = ntt_rescale_one_launch(c, level, 2 * n);
+        if (!one) HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last, nullptr, c->d_rescale_prep_f, nullptr, nullptr, mid ? NTT_LO : NTT_BOTH));
         FwdEpilogue ep;
         ep.v = nullptr;
         ep.cinv = c->d_rescale_ep + (size_t)level * 2 * c->num_q;
@@ -264,7 +265,7 @@ int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_c
             ep.vl.p[b] = b < n ? cts[b] : nullptr;
             ep.B.it[b] = b < n ? FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0} : FinalItem{nullptr, nullptr, nullptr, nullptr, 1, 0};
         }
-        HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep, mid));
+        HIP_TRY(launch_ntt_rescale(c, level, (const double*)r, w, 2 * n, st, &ep, mid, one ? last : nullptr));
         return CKKS_OK;
     }
     HIP_TRY(launch_ntt(c, true, nullptr, 0, r, 1, range_list(0, 1, level), 2 * n, st, last));
@@ -352,9 +353,8 @@ int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstr
         prod.y_cstride = lin->y_cstride;
         prod.kb = lin->kb;
     }
-    const bool inv = ntt_has_mac(c);
-    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, inv ? dropped_from(level, merged) : c->ext_limbs(level), &prod));
-    return run_moddown(c, level, ws, n, items, st, merged, inv);
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, dropped_from(level, merged), &prod));
+    return run_moddown(c, level, ws, n, items, st, merged, true);
 }
 
 // n <= CT_BATCH products a[b]*b[b] with relinearisation (operands possibly at a higher level:
@@ -364,7 +364,7 @@ int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride
     const size_t N = c->N, L1 = level + 1;
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
-    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);  // at N = 2^12 too: see ntt_has_mac
+    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);
     u64* d0 = ar.take(n * L1 * N);
     u64* d1 = ar.take(n * L1 * N);
     u64* d2 = ar.take(n * L1 * N);
@@ -583,7 +583,7 @@ hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64
 int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, const u32* gal,
                      u64* const* outs, const KsWs& ws, hipStream_t st, const u64* const* accs = nullptr) {
     const size_t L1 = level + 1;
-    const bool mac = ntt_has_mac(c);
+    const bool mac = ntt_has_modup(c);
     const u64 *c1s[CT_BATCH], *kd[CT_BATCH];
     u64* vs[CT_BATCH];
     FinalItem items[CT_BATCH];
@@ -1026,7 +1026,7 @@ int ckks_keyswitch(const ckks_ctx* c, const uint64_t* d_c, uint32_t level, const
     if (!carve_ks(c, level, 1, 1, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for key switch");
     hipStream_t st = (hipStream_t)stream;
     const u64* src = (const u64*)d_c;
-    const bool mac = ntt_has_mac(c);
+    const bool mac = ntt_has_modup(c);
     int rc = run_modup(c, level, &src, 1, ws, st, mac);
     if (rc) return rc;
     if (mac) {
@@ -1124,9 +1124,9 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             gs[b] = items[b].g;
             ks[b] = pend_key[b]->d_key;
             outs[b] = items[b].out;
-            srcs[b] = ntt_has_mac(c) ? ct : pc1 + (size_t)b * L1 * N;
+            srcs[b] = ntt_has_modup(c) ? ct : pc1 + (size_t)b * L1 * N;
         }
-        if (ntt_has_mac(c)) return run_rotate_batch(c, level, n, srcs, pend_key, gs, outs, ws, st);
+        if (ntt_has_modup(c)) return run_rotate_batch(c, level, n, srcs, pend_key, gs, outs, ws, st);
         HIP_TRY(launch_automorph(c, (u32)L1, c1, gs, n, pc1, st));
         if (int rc = run_modup(c, level, srcs, n, ws, st)) return rc;
         for (u32 b = 0; b < n; b++) gs[b] = 1;  // the digits already belong to sigma_g(c1): no gather in the inner product, only on c0

@@ -224,7 +224,7 @@ hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t sr
                       size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs = nullptr,
                       const FwdEpilogue* epilogue = nullptr, const TwF* inv_scale = nullptr, const u64* const* mul_ptrs = nullptr,
                       const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH, const u32* gals = nullptr);
-// gals (inverse, with src_ptrs, contexts with ntt_has_mac): batch item b is sigma_gals[b] of src_ptrs[b], gathered on load
+// gals (inverse, with src_ptrs, contexts with ntt_has_modup): batch item b is sigma_gals[b] of src_ptrs[b], gathered on load
 // passes (inverse, two-pass rings): the first pass alone (a kernel that goes on from there follows: ntt_mid_*), or the second alone, in place
 // (the first has been done: launch_ntt_lo_mac with inv_from)
 // mul_ptrs (inverse, with src_ptrs, double-precision arithmetic): batch item b is src_ptrs[b] (.) mul_ptrs[b], formed on load;
@@ -242,7 +242,8 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
 // The same for the rescale: y [batch][N] is the dropped limb `level` of every component (centred doubles, from launch_ntt
 // with d_rescale_prep_f), dst [batch][level][N] scratch, epilogue the subtraction and the multiplication by q_level^-1.
 hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue, u32 mid_per = 0);
+                              const FwdEpilogue* epilogue, u32 mid_per = 0, const u64* const* dropped = nullptr);
+// (dropped, where ntt_rescale_one_launch: the dropped limbs themselves, in evaluation form; y and dst are not used)
 // hi_only: stop after the converting hi pass; launch_ntt_lo_mac then runs the lo passes of all digits and multiplies the
 // results by the switching keys (keys[b]: [dnum][2][M][N], one per batch item) as they come out, adding P * add0s[b] /
 // add1s[b] (optional, [level+1][N]) on the q-limbs: outs[b] [2][E][N] is the finished inner product on the extended basis.
@@ -252,8 +253,9 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
 // targets per workgroup (mid_per of the call above, whose y then has been through the inverse transform's first pass only), or 0 where
 // the passes go one by one.  n, polys: polynomials converted.
 u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n);
-u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys);
+u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys, bool lo_done);
 u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys);
+bool ntt_rescale_one_launch(const ckks_ctx* c, u32 level, u32 polys);
 // contexts with a modulus of 2^50 or more, two-pass transforms: digits [n][beta][E][N], coefficient form (but each digit's own
 // limbs, which are not touched) -> evaluation form
 hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, hipStream_t st);
@@ -284,14 +286,11 @@ struct MacRotate {
 };
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
                              hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr);
-// rings whose transforms run as one kernel (the whole limb-poly in one workgroup)
+// rings whose whole transforms run as one kernel (the whole limb-poly in one workgroup); key switches and rescales take them pass by
+// pass like the larger rings (see ntt_mid_moddown for what remains).  N = 2^12, whole-ring kernels / passes in us: one unhoisted rotation of
+// 4 + 2 limbs 38.7 / 29.1, of 21 + 8 45.7 / 37.2, eight 81.7 / 59.5; one hoisted 34.8 / 29.7; a product with its rescale 51.2 / 44.0;
+// activation of eight at 7 + 3 limbs 185 / 170; fully connected layer 16 -> 10 568 / 451
 inline bool ntt_one_pass(const ckks_ctx* c) { return c->log_hi == 1; }
-// whether a key switch takes its inner product inside the forward transforms' second pass (launch_ntt_lo_mac) rather than behind
-// whole transforms.  A product does so on the rings of 2^12 points too (ntt_has_modup decides there): with it goes the tensor product's
-// kernel and d0..d2 in memory.  Products at N = 2^12, 4 to 20 limbs, us: 50.5-56.7 in the second pass, 53.5-60.6 behind whole-ring
-// transforms (54.5 either way with four digits); activation of one, four, eight and sixteen ciphertexts at 7 + 3 limbs 165, 174,
-// 182, 213 and 173, 202, 235, 322.
-inline bool ntt_has_mac(const ckks_ctx* c) { return ntt_has_modup(c) && !ntt_one_pass(c); }
 // whether launch_ntt can apply an epilogue in this ring (it needs the two-pass transform)
 inline bool ntt_has_epilogue(const ckks_ctx* c) { return c->log_n > CKKS_TILE_LOG; }
 // keyswitch.hip

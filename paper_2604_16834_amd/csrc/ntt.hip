@@ -1127,7 +1127,8 @@ __device__ __forceinline__ double conv_sum(const double (&yv)[AP], const double*
 
 // The source limbs of a conversion that are still to go through the last pass of their inverse transform.
 struct MidPrologue {
-    const TwF* itw;     // [M][N] inverse twiddles
+    const TwF* itw;     // [M][N] inverse twiddles, and their values alone
+    const double* itw_val;
     const TwF* scale;   // by modulus: what the inverse transform's last step multiplies by
     u32 first, next;    // source limb k has the modulus k ? next + k - 1 : first (a digit's first limb is added to both)
 };
@@ -1557,33 +1558,114 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_kernel(NttArgs args,
 // each is worth a launch (about 2 us) and a chain of dependent loads (1 to 2 us) whatever it computes: a rescale in two
 // kernels instead of four takes 14.2 us instead of 20.7, five limbs forward and back 17.4 instead of 23.5, and a filled chip gains
 // the memory traffic (1536 limb-polys 58 us instead of 88).  With four blocks (2^13 points) the
-// compute units next door, which the two passes use, are missed more than the launches: key switches 58 -> 64 us.
+// compute units next door, which the two passes use, are missed more than the launches: key switches 58 -> 64 us.  What a round waits
+// for through the scalar path (the outer stage's twiddle, the scale) is asked for before the first round: requested at its use each was a round
+// trip of 0.6 to 1 us (direct convolution of five channels, 14 + 4 limbs, 306 -> 294 us).
 // AP: 0 = the source is a polynomial, else rows of conversion constants as in ntt_fwd_hi_conv_kernel, ND of them real.  DIV: the
 // results go through a division's last step (em as in div_request) instead of being stored.
 // grid = (entries of the list or most targets of a digit, batch, digits)
 #define RING_LOG_HI 1
 #define RING_THREADS (NTT_THREADS << RING_LOG_HI)
-template <class A, int AP, int ND, bool DIV>
-__device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const FwdEpilogue* ep, int em) {
+// the inverse transform likewise: the lo pass' rounds mirrored, an exchange, the hi pass' stages; v[j] ends as the ring's point
+// ((j / KC) << 11) + (j % KC) * THREADS + tid, to be scaled.  src: the limb-poly; tw, tw_val: its modulus' inverse twiddles.  The last
+// reads of LDS are of lds1.
+#define RING_R (1 << RING_LOG_HI)
+template <class A>
+__device__ __forceinline__ void inv_ring_rounds(const u64* src, const PolyRef<A>& P, typename A::E* lds0, typename A::E* lds1, u32 tid, typename A::E* v) {
+    typedef typename LoTw<A>::TW TW;
+    typedef typename LoTw<A>::AR AR;
+    constexpr int R = RING_R, KC = 8 / R, THREADS = RING_THREADS;
+    const u32 blk = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
+    const size_t off = (size_t)blk << 11;
+    const u32 TA = R + blk;
+    const u32 d3 = t >> 5, x5 = t & 31, d2 = (t >> 2) & 7, d0 = t & 3;
+    typename A::E* buf0 = lds0 + blk * LDS_PADDED_WORDS;
+    typename A::E* buf1 = lds1 + blk * LDS_PADDED_WORDS;
+    TW wa[7], wb[7], wc[7], wd[6];
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t, wd);
+    load_lo_tw<A, 2>(P, 512 * TA + 2 * t + 1, wd + 3);
+    load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
+    ulonglong2 raw[4];
+    const ulonglong2* in = reinterpret_cast<const ulonglong2*>(src + off + 8 * t);
+#pragma unroll
+    for (int j = 0; j < 4; j++) raw[j] = in[j];
+    typename A::TW wl[R - 1];  // the last stage's: asked for now, a scalar load at its use is a round trip to memory
+#pragma unroll
+    for (int i = 0; i < R - 1; i++) wl[i] = P.tw[1 + i];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        v[2 * j] = A::load_first(raw[j].x, P.mc, true);
+        v[2 * j + 1] = A::load_first(raw[j].y, P.mc, true);
+    }
+    inv_rows_pre<AR, 2>(v, wd, P.mc);
+    inv_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
+    A::inv_end2(v, P.mc);
+    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(8 * t + j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
+    inv_rows_pre<AR, 3>(v, wc, P.mc);
+    A::inv_end(v, P.mc);
+    load_lo_tw<A, 3>(P, TA, wa);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + 32 * j + x5)];
+    inv_rows_pre<AR, 3>(v, wb, P.mc);
+    A::inv_end(v, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(t + 256 * j)];
+    inv_rows_pre<AR, 3>(v, wa, P.mc);
+    A::inv_end(v, P.mc);
+#pragma unroll
+    for (int j = 0; j < 8; j++) buf1[LDS_PAD(t + 256 * j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = lds1[(j / KC) * LDS_PADDED_WORDS + LDS_PAD((j % KC) * THREADS + tid)];
+    static_assert(R == 2, "one stage");
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) A::inv_bf(v[kc], v[KC + kc], wl[0], P.mc);
+    A::template inv_mid<KC>(v, P.mc);
+}
+// grid = (entries of the list, batch)
+template <class A>
+__global__ __launch_bounds__(RING_THREADS) void ntt_inv_ring_kernel(NttArgs args, PolyList pl) {
+    typedef typename A::E E;
+    constexpr int R = RING_R, KC = 8 / R, THREADS = RING_THREADS;
+    __shared__ E lds0[R * LDS_PADDED_WORDS];
+    __shared__ E lds1[R * LDS_PADDED_WORDS];
+    const u32 tid = threadIdx.x, a = blockIdx.x;
+    const PolyRef<A> P = poly_ref<A>(args, pl, blockIdx.y, a);
+    const bool scaled = std::is_same<A, ArithF64>::value && args.inv_scale;
+    const TwF scale = scaled ? args.inv_scale[pl_at(pl.mod, a)] : TwF{0.0, 0.0};
+    E v[8];
+    inv_ring_rounds<A>(P.src, P, lds0, lds1, tid, v);
+#pragma unroll
+    for (int j = 0; j < 8; j++) P.dst[((size_t)(j / KC) << 11) + (j % KC) * THREADS + tid] = inv_last_store<A>(v[j], P.mc, scaled ? &scale : nullptr);
+}
+
+// MID: the source is one limb in evaluation form that goes through its whole inverse transform here first (a rescale in one launch).
+template <class A, int AP, int ND, bool DIV, bool MID>
+__device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const FwdEpilogue* ep, int em, const MidPrologue& mp) {
     typedef typename A::E E;
     typedef typename LoTw<A>::TW TW;
     typedef typename LoTw<A>::AR AR;
-    constexpr int R = 1 << RING_LOG_HI, KC = 8 / R, THREADS = RING_THREADS;
-    __shared__ E lds0[R * LDS_PADDED_WORDS];
-    __shared__ E lds1[R * LDS_PADDED_WORDS];
-    const u32 tid = threadIdx.x, b = blockIdx.y;
-    u32 a = blockIdx.x;
-    const u32 dig = cp.digit0 + blockIdx.z, lo = cp.lo + dig * cp.alpha;
-    u32 nd = cp.nd;
-    if (AP) {
-        if (cp.alpha) nd = min(cp.alpha, cp.n_src - lo);
-        if (a >= (cp.alpha ? pl.n - nd : pl.n)) return;  // whole workgroup: a digit with more limbs has fewer targets
-        if (cp.alpha && a >= lo) a += nd;
-    } else if constexpr (!std::is_same<A, ArithF64>::value) {
+    constexpr int R = RING_R, KC = 8 / R, THREADS = RING_THREADS;
+    __shared__ E lds_a[R * LDS_PADDED_WORDS];
+    __shared__ E lds_b[R * LDS_PADDED_WORDS];
+    E* lds0 = MID ? lds_b : lds_a;  // (the inverse rounds read lds_b last: the first write here goes to the other one)
+    E* lds1 = MID ? lds_a : lds_b;
+    const u32 tid = threadIdx.x, b = blockIdx.y, a = blockIdx.x;
+    if constexpr (AP == 0 && !std::is_same<A, ArithF64>::value) {
         if (own_limb(args, b, a)) return;  // whole workgroup
     }
-    PolyRef<A> P = poly_ref<A>(args, pl, b, a);
-    if (AP) P.dst += dig * cp.dst_dstride;
+    const PolyRef<A> P = poly_ref<A>(args, pl, b, a);
     const u32 blk = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
     const size_t N = (size_t)1 << args.log_n, off = (size_t)blk << 11;
     const u32 TA = R + blk;
@@ -1592,9 +1674,26 @@ __device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyLis
     load_lo_tw<A, 3>(P, TA, wa);
     load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
     E v[8];
-    if constexpr (AP > 0) {
-        const double* y = cp.y + b * cp.y_bstride + (size_t)lo * N;
-        const TwF* ce = cp.convf + dig * cp.convf_dstride + (size_t)pl_at(pl.dpos, a) * AP;
+    typename A::TW wl[R - 1];  // the first stage's (see inv_ring_rounds)
+#pragma unroll
+    for (int i = 0; i < R - 1; i++) wl[i] = P.tw[1 + i];
+    if constexpr (MID) {
+        PolyRef<A> S;
+        S.tw = mp.itw + ((size_t)mp.first << args.log_n);
+        S.tw_val = mp.itw_val + ((size_t)mp.first << args.log_n);
+        S.mc = ((const ModConstF*)args.mc)[mp.first];
+        const TwF scale = mp.scale[mp.first];
+        const double cw[1] = {(cp.convf + (size_t)pl_at(pl.dpos, a) * AP)->w};
+        inv_ring_rounds<A>(args.src_list.p[b], S, lds_a, lds_b, tid, v);
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const double yv[1] = {f64m_centre(A::mulmod(v[j], scale.w, scale.wq, S.mc.q), S.mc.q)};
+            v[j] = f64m_dot_w<1>(yv, cw, P.mc.q, P.mc.qinv);
+        }
+    } else if constexpr (AP > 0) {
+        const double* y = cp.y + b * cp.y_bstride + (size_t)cp.lo * N;
+        const TwF* ce = cp.convf + (size_t)pl_at(pl.dpos, a) * AP;
+        const u32 nd = cp.nd;
         double cw[ND];
 #pragma unroll
         for (int k = 0; k < ND; k++) cw[k] = ce[k].w;
@@ -1611,7 +1710,9 @@ __device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyLis
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = A::load_first(raw[j], P.mc, false);
     }
-    fwd_rows<A, RING_LOG_HI, KC>(v, P.tw, 1, P.mc);
+    static_assert(R == 2, "one stage");
+#pragma unroll
+    for (int kc = 0; kc < KC; kc++) A::fwd_bf(v[kc], v[KC + kc], wl[0], P.mc);
     E* buf0 = lds0 + blk * LDS_PADDED_WORDS;
     E* buf1 = lds1 + blk * LDS_PADDED_WORDS;
 #pragma unroll
@@ -1669,82 +1770,13 @@ __device__ __forceinline__ void fwd_ring_body(const NttArgs& args, const PolyLis
         for (int j = 0; j < 8; j++) dst[t + 256 * j] = A::store_fwd_final(buf1[LDS_PAD(t + 256 * j)], P.mc);
     }
 }
-template <class A, int AP, int ND>
-__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
-    fwd_ring_body<A, AP, ND, false>(args, pl, cp, nullptr, 0);
+template <class A>
+__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_kernel(NttArgs args, PolyList pl) {
+    fwd_ring_body<A, 0, 1, false, false>(args, pl, ConvPrologue{}, nullptr, 0, MidPrologue{});
 }
-template <class A, int AP, int ND>
-__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_div_kernel(NttArgs args, PolyList pl, ConvPrologue cp, FwdEpilogue ep, int em) {
-    fwd_ring_body<A, AP, ND, true>(args, pl, cp, &ep, em);
-}
-
-// the inverse transform likewise: the lo pass' rounds mirrored, an exchange, the hi pass' stages.  grid = (entries of the list, batch)
-template <class A, bool MUL>
-__global__ __launch_bounds__(RING_THREADS) void ntt_inv_ring_kernel(NttArgs args, PolyList pl) {
-    typedef typename A::E E;
-    typedef typename LoTw<A>::TW TW;
-    typedef typename LoTw<A>::AR AR;
-    constexpr int R = 1 << RING_LOG_HI, KC = 8 / R, THREADS = RING_THREADS;
-    __shared__ E lds0[R * LDS_PADDED_WORDS];
-    __shared__ E lds1[R * LDS_PADDED_WORDS];
-    const u32 tid = threadIdx.x, a = blockIdx.x, b = blockIdx.y;
-    const PolyRef<A> P = poly_ref<A>(args, pl, b, a);
-    const u32 blk = __builtin_amdgcn_readfirstlane(tid >> 8), t = tid & 255;
-    const size_t off = (size_t)blk << 11;
-    const u32 TA = R + blk;
-    const u32 d3 = t >> 5, x5 = t & 31, d2 = (t >> 2) & 7, d0 = t & 3;
-    E* buf0 = lds0 + blk * LDS_PADDED_WORDS;
-    E* buf1 = lds1 + blk * LDS_PADDED_WORDS;
-    TW wa[7], wb[7], wc[7], wd[6];
-    load_lo_tw<A, 2>(P, 512 * TA + 2 * t, wd);
-    load_lo_tw<A, 2>(P, 512 * TA + 2 * t + 1, wd + 3);
-    load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
-    ulonglong2 raw[4], raw2[MUL ? 4 : 1];
-    const ulonglong2* in = reinterpret_cast<const ulonglong2*>(P.src + off + 8 * t);
-#pragma unroll
-    for (int j = 0; j < 4; j++) raw[j] = in[j];
-    if constexpr (MUL) {
-        const ulonglong2* in2 = reinterpret_cast<const ulonglong2*>(args.mul_list.p[b] + ((size_t)pl_at(pl.spos, a) << args.log_n) + off + 8 * t);
-#pragma unroll
-        for (int j = 0; j < 4; j++) raw2[j] = in2[j];
-    }
-    const TwF* scale = args.inv_scale ? args.inv_scale + pl_at(pl.mod, a) : nullptr;
-    E v[8];
-    inv_first_points<A, MUL>(args, P.mc, raw, raw2, v);
-    inv_rows_pre<AR, 2>(v, wd, P.mc);
-    inv_rows_pre<AR, 2>(v + 4, wd + 3, P.mc);
-    A::inv_end2(v, P.mc);
-    load_lo_tw<A, 3>(P, 8 * TA + d3, wb);
-#pragma unroll
-    for (int j = 0; j < 8; j++) buf0[LDS_PAD(8 * t + j)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)];
-    inv_rows_pre<AR, 3>(v, wc, P.mc);
-    A::inv_end(v, P.mc);
-    load_lo_tw<A, 3>(P, TA, wa);
-#pragma unroll
-    for (int j = 0; j < 8; j++) buf1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * j + d0)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = buf1[LDS_PAD(d3 * 256 + 32 * j + x5)];
-    inv_rows_pre<AR, 3>(v, wb, P.mc);
-    A::inv_end(v, P.mc);
-#pragma unroll
-    for (int j = 0; j < 8; j++) buf0[LDS_PAD(d3 * 256 + 32 * j + x5)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = buf0[LDS_PAD(t + 256 * j)];
-    inv_rows_pre<AR, 3>(v, wa, P.mc);
-    A::inv_end(v, P.mc);
-#pragma unroll
-    for (int j = 0; j < 8; j++) buf1[LDS_PAD(t + 256 * j)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = lds1[(j / KC) * LDS_PADDED_WORDS + LDS_PAD((j % KC) * THREADS + tid)];
-    inv_rows<A, RING_LOG_HI, KC>(v, P.tw, 1, P.mc);
-#pragma unroll
-    for (int j = 0; j < 8; j++) P.dst[((size_t)(j / KC) << 11) + (j % KC) * THREADS + tid] = inv_last_store<A>(v[j], P.mc, scale);
+template <class A, int AP, int ND, bool MID>
+__global__ __launch_bounds__(RING_THREADS) void ntt_fwd_ring_div_kernel(NttArgs args, PolyList pl, ConvPrologue cp, FwdEpilogue ep, int em, MidPrologue mp) {
+    fwd_ring_body<A, AP, ND, true, MID>(args, pl, cp, &ep, em, mp);
 }
 
 // ================================= rings below 2^11: one tile per poly (integer arithmetic) ==============
@@ -1954,7 +1986,7 @@ static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t 
 //     rotations 160 / 141), or two of four rows and more (7 + 8 limbs: one rotation 60.4 / 61.5, eight 233 / 222; with 13 + 8, four groups,
 //     eight 428 / 450)
 static u32 mid_conv_per(const ckks_ctx* c, u32 nd, u32 ap, u32 n_targets, u32 rows) {
-    if (!ntt_has_modup(c) || ntt_one_pass(c)) return 0;
+    if (!ntt_has_modup(c)) return 0;
     if (c->log_hi > 3) {
         const u32 groups = (n_targets + HC_T - 1) / HC_T, wgs = groups * rows << c->log_hi;
         bool together;
@@ -1973,8 +2005,19 @@ u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n) {
     const u32 nd = c->alpha < level + 1 ? c->alpha : level + 1;
     return mid_conv_per(c, nd, c->alpha_pad, c->ext_limbs(level) - nd, n * c->live_digits(level));
 }
-u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys) { return mid_conv_per(c, c->num_p + (merged ? 1 : 0), merged ? c->k2_pad : c->k_pad, merged ? level : level + 1, polys); }
+// Rings of 2^12 points: a division that starts from whole sums (lo_done: they have been through the inverse transform's first pass) takes
+// the whole-ring kernels where they give between half of the CUs and every CU a limb-poly of the result.  Hoisted rotations, pass by pass / whole ring
+// in us, by limb-polys: 84 36.0 / 37.6, 112 38.5 / 39.0, 168 46.2 / 43.9, 224 45.2 / 42.8, 336 53.9 / 58.2; direct convolution of five channels
+// of 14 + 4 limbs (224) 315 / 297
+u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys, bool lo_done) {
+    const u32 n_out = merged ? level : level + 1;
+    if (ntt_one_pass(c) && !lo_done && n_out * polys > 112 && n_out * polys <= 256) return 0;
+    return mid_conv_per(c, c->num_p + (merged ? 1 : 0), merged ? c->k2_pad : c->k_pad, n_out, polys);
+}
 u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys) { return mid_conv_per(c, 1, 4, level, polys); }
+// The rescale of a ring of 2^12 points in one launch, the dropped limb's inverse transform repeated by every target's workgroup, while every
+// limb-poly of the result has a CU of its own: one ciphertext of 4 limbs 14.2 us in two launches (or three: pass by pass), 10.5 in one
+bool ntt_rescale_one_launch(const ckks_ctx* c, u32 level, u32 polys) { return ntt_has_modup(c) && ntt_one_pass(c) && level * polys <= 256; }
 
 template <int LOG_HI>
 static void launch_mid_conv_hi(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue& mp) {
@@ -1989,14 +2032,19 @@ static void launch_mid_conv_hi(dim3 grid, hipStream_t st, const NttArgs& args, c
         else if (cp.nd == 7) MID_CONV(7);
         else if (cp.nd == 8) MID_CONV(8);
         else if (cp.nd == 9) MID_CONV(9);
-        else MID_CONV(10);
+        else if (cp.nd == 10) MID_CONV(10);
+        else if constexpr (LOG_HI < 2) {
+            if (cp.nd <= 12) MID_CONV(12);
+            else MID_CONV(16);
+        }
     }
 #undef MID_CONV
 }
 static void launch_mid_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue& mp) {
     cp.groups = (n_targets + cp.per - 1) / cp.per;
     const dim3 grid((1u << CKKS_TILE_LOG) / NTT_THREADS, cp.groups * batch, digits);
-    if (log_hi == 2) launch_mid_conv_hi<2>(grid, st, args, pl, cp, mp);
+    if (log_hi == 1) launch_mid_conv_hi<1>(grid, st, args, pl, cp, mp);
+    else if (log_hi == 2) launch_mid_conv_hi<2>(grid, st, args, pl, cp, mp);
     else launch_mid_conv_hi<3>(grid, st, args, pl, cp, mp);
 }
 
@@ -2007,7 +2055,6 @@ static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hip
         return;
     }
     switch (log_hi) {
-        case 1: launch_hi_conv_ap<1>(n_targets, digits, batch, st, args, pl, cp, mp); break;
         case 2: launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp, mp); break;
         case 3: launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp, mp); break;
         case 4: launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp, mp); break;
@@ -2016,47 +2063,41 @@ static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hip
     }
 }
 
-// The whole-ring kernels: `entries` list entries (a conversion: the most targets of a digit), all digits at once.
+// The whole-ring kernels: a workgroup per entry of the list and batch item.
 template <class A>
-static void launch_ring_as(bool inverse, bool mul, u32 entries, u32 digits, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue* conv,
-                           const FwdEpilogue* ep) {
-    const dim3 grid(entries, args.batch, digits), block(RING_THREADS);
+static void launch_ring_as(bool inverse, u32 entries, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue* conv, const FwdEpilogue* ep,
+                           const MidPrologue* mid) {
+    const dim3 grid(entries, args.batch), block(RING_THREADS);
     if (inverse) {
-        if constexpr (std::is_same<A, ArithF64>::value) {
-            if (mul) {
-                hipLaunchKernelGGL((ntt_inv_ring_kernel<A, true>), grid, block, 0, st, args, pl);
-                return;
-            }
-        }
-        hipLaunchKernelGGL((ntt_inv_ring_kernel<A, false>), grid, block, 0, st, args, pl);
+        hipLaunchKernelGGL((ntt_inv_ring_kernel<A>), grid, block, 0, st, args, pl);
         return;
     }
-    ConvPrologue cp = {};
-    if (conv) cp = *conv;
-    const int em = ep ? div_operands(args, *ep) : 0;
-#define RING_LAUNCH(AP, ND)                                                                                                          \
-    do {                                                                                                                             \
-        if (ep) hipLaunchKernelGGL((ntt_fwd_ring_div_kernel<A, AP, ND>), grid, block, 0, st, args, pl, cp, *ep, em);         \
-        else hipLaunchKernelGGL((ntt_fwd_ring_kernel<A, AP, ND>), grid, block, 0, st, args, pl, cp);                         \
-    } while (0)
+    if (!ep) {
+        hipLaunchKernelGGL((ntt_fwd_ring_kernel<A>), grid, block, 0, st, args, pl);
+        return;
+    }
+    const ConvPrologue cp = conv ? *conv : ConvPrologue{};
+    const MidPrologue mp = mid ? *mid : MidPrologue{};
+    const int em = div_operands(args, *ep);
+#define RING_LAUNCH(AP, ND, MID) hipLaunchKernelGGL((ntt_fwd_ring_div_kernel<A, AP, ND, MID>), grid, block, 0, st, args, pl, cp, *ep, em, mp)
     if constexpr (std::is_same<A, ArithF64>::value) {
         if (conv) {
-            if (cp.ap == 4 && cp.nd == 1) RING_LAUNCH(4, 1);
-            else if (cp.ap == 4) RING_LAUNCH(4, 4);
-            else if (cp.ap == 8) RING_LAUNCH(8, 8);
-            else if (cp.ap == 12 && cp.nd == 9) RING_LAUNCH(12, 9);
-            else if (cp.ap == 12) RING_LAUNCH(12, 12);
-            else RING_LAUNCH(16, 16);
+            if (mid) RING_LAUNCH(4, 1, true);
+            else if (cp.ap == 4) RING_LAUNCH(4, 4, false);
+            else if (cp.ap == 8) RING_LAUNCH(8, 8, false);
+            else if (cp.ap == 12 && cp.nd == 9) RING_LAUNCH(12, 9, false);
+            else if (cp.ap == 12) RING_LAUNCH(12, 12, false);
+            else RING_LAUNCH(16, 16, false);
             return;
         }
     }
-    RING_LAUNCH(0, 1);
+    RING_LAUNCH(0, 1, false);
 #undef RING_LAUNCH
 }
-static void launch_ring(const ckks_ctx* c, bool inverse, bool mul, u32 entries, u32 digits, hipStream_t st, const NttArgs& args, const PolyList& pl,
-                        const ConvPrologue* conv, const FwdEpilogue* ep) {
-    if (c->ntt_f64) launch_ring_as<ArithF64>(inverse, mul, entries, digits, st, args, pl, conv, ep);
-    else launch_ring_as<ArithU64>(inverse, mul, entries, digits, st, args, pl, conv, ep);
+static void launch_ring(const ckks_ctx* c, bool inverse, u32 entries, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue* conv,
+                        const FwdEpilogue* ep, const MidPrologue* mid = nullptr) {
+    if (c->ntt_f64) launch_ring_as<ArithF64>(inverse, entries, st, args, pl, conv, ep, mid);
+    else launch_ring_as<ArithU64>(inverse, entries, st, args, pl, conv, ep, mid);
 }
 
 static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src, size_t src_bstride, u64* dst,
@@ -2065,12 +2106,13 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                                  const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH,
                                  const MidPrologue* mid = nullptr, const u32* gals = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
-    if (passes != NTT_BOTH && (!inverse || c->log_hi < 2)) return hipErrorInvalidValue;
-    if (passes == NTT_HI && (src != dst || src_ptrs)) return hipErrorInvalidValue;
-    if (mid && (!conv || !conv->per || c->log_hi < 2)) return hipErrorInvalidValue;
+    if (passes != NTT_BOTH && (!inverse || c->log_hi < 1)) return hipErrorInvalidValue;
+    if (passes == NTT_HI && (src != dst || src_ptrs || ntt_one_pass(c))) return hipErrorInvalidValue;
+    if ((mul_ptrs || gals) && ntt_one_pass(c) && passes != NTT_LO) return hipErrorInvalidValue;
+    if (mid && (!conv || !conv->per || c->log_hi < 1)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
-    if (gals && (!inverse || !src_ptrs || mul_ptrs || !ntt_has_mac(c))) return hipErrorInvalidValue;
+    if (gals && (!inverse || !src_ptrs || mul_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
     if (src_ptrs && batch > KS_MAX_BATCH) return hipErrorInvalidValue;
     if (epilogue && (inverse || !ntt_has_epilogue(c) || batch > 2 * KS_MAX_BATCH)) return hipErrorInvalidValue;
@@ -2119,10 +2161,10 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
         else hipLaunchKernelGGL(ntt_small_kernel<false>, dim3(1, polys), block, 0, st, args, pl);
         return hipGetLastError();
     }
-    if (ntt_one_pass(c)) {
-        const double ring_bytes = conv ? 8.0 * c->N * batch * ((double)conv->nd + (epilogue ? 2.0 : 1.0) * pl.n) : (mul_ptrs || epilogue ? 1.5 : 1.0) * pass_bytes;
+    if (ntt_one_pass(c) && passes == NTT_BOTH && !mid) {
+        const double ring_bytes = conv ? 8.0 * c->N * batch * ((double)conv->nd + (epilogue ? 2.0 : 1.0) * pl.n) : (epilogue ? 1.5 : 1.0) * pass_bytes;
         ProfScope ps__(c, inverse ? K_NTT_INV_LO : K_NTT_FWD_LO, st, ring_bytes, 0.5 * polys * c->N * c->log_n);
-        launch_ring(c, inverse, mul_ptrs != nullptr, pl.n, 1, st, args, pl, conv, epilogue);
+        launch_ring(c, inverse, pl.n, st, args, pl, conv, epilogue);
         return hipGetLastError();
     }
     const dim3 grid(c->N >> CKKS_TILE_LOG, polys);  // hi pass: one workgroup per 2^11 points
@@ -2235,7 +2277,7 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
     args.log_n = c->log_n;
     args.log_lo = c->log_lo;
     args.log_hi = c->log_hi;
-    const MidPrologue mp = {c->d_itwf, c->d_modup_prep_f + (size_t)level * c->num_q, 0, 1};
+    const MidPrologue mp = {c->d_itwf, c->d_itwf_val, c->d_modup_prep_f + (size_t)level * c->num_q, 0, 1};
     cp.per = mid_per;
     const bool together = (mid_per && c->log_hi <= 3) || ((E - cp.nd + 3) / 4 * n << c->log_hi) < 768;
     for (u32 j0 = 0; j0 < beta; j0 += together ? beta : 1) {
@@ -2256,11 +2298,6 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
         args.last = 0;
         args.batch = n;
         args.beta = 0;
-        if (!hi_only && ntt_one_pass(c)) {  // (a launch of these rings is always small: all digits)
-            ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (double)L1 + rows), 0.5 * rows * c->N * c->log_n);
-            launch_ring(c, false, false, most, nj, st, args, all, &cp, nullptr);
-            continue;
-        }
         {
             ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * (n * (together ? (double)L1 : (double)(E - most)) + rows), 0.5 * rows * c->N * c->log_hi);
             launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp, mid_per ? &mp : nullptr);
@@ -2329,7 +2366,7 @@ hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, h
     if (ntt_one_pass(c)) {
         args.last = 1;
         ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * rows * c->N, 0.5 * rows * c->N * c->log_n);
-        launch_ring(c, false, false, E, 1, st, args, all, nullptr, nullptr);
+        launch_ring(c, false, E, st, args, all, nullptr, nullptr);
         return hipGetLastError();
     }
     {
@@ -2348,8 +2385,9 @@ hipError_t launch_ntt_digits(const ckks_ctx* c, u32 level, u64* digits, u32 n, h
 }
 
 hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64* dst, u32 batch, hipStream_t st,
-                              const FwdEpilogue* epilogue, u32 mid_per) {
+                              const FwdEpilogue* epilogue, u32 mid_per, const u64* const* dropped) {
     if (level == 0 || !c->d_rescale_conv_f) return hipErrorInvalidValue;
+    if (dropped && (!ntt_rescale_one_launch(c, level, batch) || batch > KS_MAX_BATCH || epilogue->use_vl == 2)) return hipErrorInvalidValue;
     ConvPrologue cp;
     cp.y = y;
     cp.y_bstride = c->N;  // one limb per batch item
@@ -2362,7 +2400,22 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < level ? a : 0);
     pl.n = level;
-    const MidPrologue mp = {c->d_itwf, c->d_rescale_prep_f, level, level};
+    const MidPrologue mp = {c->d_itwf, c->d_itwf_val, c->d_rescale_prep_f, level, level};
+    if (dropped) {
+        NttArgs args = {};
+        args.mc = c->d_mcf;
+        args.tw = c->d_twf;
+        args.tw_val = c->d_twf_val;
+        args.log_n = c->log_n;
+        args.log_lo = c->log_lo;
+        args.log_hi = c->log_hi;
+        args.batch = batch;
+        for (u32 b = 0; b < batch; b++) args.src_list.p[b] = dropped[b];
+        // in: the dropped limbs and the others, out: the quotients
+        ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * batch * (1.0 + 2.0 * level), 0.5 * batch * (1.0 + level) * c->N * c->log_n);
+        launch_ring(c, false, level, st, args, pl, &cp, epilogue, &mp);
+        return hipGetLastError();
+    }
     cp.per = mid_per;
     return launch_ntt_any(c, false, dst, level, dst, level, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);
 }
@@ -2461,7 +2514,7 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
     PolyList pl;
     for (u32 a = 0; a < CKKS_MAX_MODULI; a++) pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < n_out ? a : 0);
     pl.n = n_out;
-    const MidPrologue mp = {c->d_itwf, merged ? c->d_moddown_rs_prep_f + (size_t)level * c->M : c->d_moddown_prep_f, merged ? level : c->num_q,
+    const MidPrologue mp = {c->d_itwf, c->d_itwf_val, merged ? c->d_moddown_rs_prep_f + (size_t)level * c->M : c->d_moddown_prep_f, merged ? level : c->num_q,
                             merged ? c->num_q : c->num_q + 1};
     cp.per = mid_per;
     return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);

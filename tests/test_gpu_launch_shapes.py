@@ -266,11 +266,11 @@ def test_inner_products_go_on_into_the_inverse_pass(log_n, num_q, num_p, dnum, l
         assert np.array_equal(hx.to_host(out), want[i % 2]), f"ciphertext {i}"
 
 
-@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(13, 10, 10, 1, 9), (13, 11, 9, 2, 10), (13, 5, 1, 5, 4), (14, 9, 4, 3, 8), (14, 6, 6, 1, 5),
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(12, 5, 1, 5, 4), (12, 12, 12, 1, 11), (12, 16, 14, 1, 15), (12, 25, 9, 3, 24), (13, 10, 10, 1, 9), (13, 11, 9, 2, 10), (13, 5, 1, 5, 4), (14, 9, 4, 3, 8), (14, 6, 6, 1, 5),
                                                           (15, 5, 1, 5, 4), (15, 5, 8, 2, 4), (15, 13, 5, 3, 12), (16, 5, 1, 5, 4), (17, 3, 2, 2, 2)])
 def test_inverse_pass_inside_the_conversion(log_n, num_q, num_p, dnum, level):
     """The inverse transform's second pass inside the converting first pass and on its own: one source limb (rescales; digits of one limb,
-    each with a modulus of its own), ragged digits, the most points a thread takes on the small rings (ten limbs of four, five of
+    each with a modulus of its own), ragged digits, up to sixteen source limbs of the ring of 2^12 points, the most points a thread takes on the small rings (ten limbs of four, five of
     eight) and one more (six of eight: pass by pass), two to nine limbs through LDS with one group of targets (eight special primes and
     the level's limb in a merged division) and more, N = 2^17."""
     p = make_params(log_n, num_q, num_p, dnum)
@@ -290,3 +290,26 @@ def test_inverse_pass_inside_the_conversion(log_n, num_q, num_p, dnum, level):
         k = (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
         (got,) = hx.he_poly_act_deg7(ctx, [d_ct], level, k, hx.ckks_key_load(ctx, hx.from_host(key), 0), merged=True)
         assert np.array_equal(hx.to_host(got), orc.poly_activation_merged(ct, level, k, key)), "activation"
+
+
+def test_rescales_of_the_whole_ring_kernel():
+    """N = 2^12: a rescale is one launch up to 256 limb-polys of results (a single output), pass by pass above (eight outputs of 17
+    limbs); its input's last limb at the extremes."""
+    p = make_params(12, 18, 6, 3)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(9500)
+    level, q = 17, p.moduli
+    ct = rand_ct(rng, q, level, orc.N)
+    offs = conv_tap_offsets(4)
+    keys = {o: np.stack([np.stack([rand_poly(rng, q, orc.N) for _ in range(2)]) for _ in range(p.dnum)]) for o in offs if o}
+    masks = np.stack([rand_poly(rng, q[:level + 1], orc.N) for _ in range(9)])
+    w = rng.integers(-2 ** 31, 2 ** 31, size=(9, 1, 9))
+    want = orc.he_conv([ct], level, 4, keys, masks, w)
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(keys[o]), hx.ckks_galois_element(ctx, o)) if o else None for o in offs]
+    outs = hx.he_conv_batched(ctx, 4, 4, 2, level, [hx.from_host(ct)], dkeys, hx.from_host(masks), hx.from_host(w_residues(w, q, level)), 9)
+    for o in range(9):
+        assert np.array_equal(hx.to_host(outs[o]), want[o]), f"output {o}"
+    ct[:, level, :3] = [[0, q[level] - 1, q[level] // 2]] * 2
+    for lv in (1, 7, level):
+        c = np.ascontiguousarray(ct[:, :lv + 1])
+        assert np.array_equal(hx.to_host(hx.ckks_rescale(ctx, hx.from_host(c), lv)), orc.rescale(c, lv))
