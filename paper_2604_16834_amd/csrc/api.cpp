@@ -76,14 +76,14 @@ bool level_ok(const ckks_ctx* c, u32 level) { return level < c->num_q; }
 struct KsWs {
     u64 *y, *digits, *v, *w;
     size_t y_b, dig_b, v_b, w_b;  // per-item strides in elements
-    mutable const u64* own[CT_BATCH] = {};  // the polynomials run_modup decomposed last (the digits' own limbs stay there)
+    mutable const u64* own[KS_MAX_BATCH] = {};  // the polynomials run_modup decomposed last (the digits' own limbs stay there)
 };
 // the digits of items b0, b0 + 1, ... of the batch in ws, as the inner-product kernels take them
 DigitSrc dsrc(const ckks_ctx* c, const KsWs& ws, u32 b0) {
     DigitSrc d;
     d.digits = ws.digits + b0 * ws.dig_b;
     d.bstride = ws.dig_b;
-    for (u32 b = 0; b < KS_MAX_BATCH; b++) d.own.p[b] = b0 + b < CT_BATCH ? ws.own[b0 + b] : nullptr;
+    for (u32 b = 0; b < KS_MAX_BATCH; b++) d.own.p[b] = b0 + b < KS_MAX_BATCH ? ws.own[b0 + b] : nullptr;
     d.alpha = c->alpha;
     d.pad = 0;
     return d;
@@ -104,6 +104,23 @@ bool carve_ks(const ckks_ctx* c, u32 level, u32 n_dig, u32 n_v, Arena& ar, KsWs&
     b.w = ar.take(n_v * b.w_b);
     return ar.ok();
 }
+// Most key switches that go through the kernels together: as many as the pointer lists hold.  A small launch takes as long as its longest
+// workgroup, so a second batch costs nearly what the first does, and large ones share the keys and the twiddles of twice as many.
+// Sixteen unhoisted rotations in batches of eight / together in us: N = 2^12, 7 + 3 limbs 82 / 46, 2^14 140 / 112, 2^16 477 / 443,
+// 21 + 8 limbs 1353 / 1310; activation of eight, x^3 and x^4 in one batch: 2^12, 7 + 3 limbs 169 / 134, 2^16, 21 + 8 2681 / 2619.
+// (Eight with integer arithmetic, whose inner-product launch takes no more.)
+u32 ks_batch(const ckks_ctx* c) { return ntt_has_modup(c) ? KS_MAX_BATCH : CT_BATCH; }
+// Calls with more than eight independent items: together on the caller's stream while a polynomial of the extended basis has no more
+// coefficients than `limit`, in batches of eight that alternate between two streams above.  A fork and a join are worth 45 us; from some size on
+// the kernels of one batch beside another's are worth more, the sooner the more kinds of kernels there are.  Two streams / together, us:
+//   twelve hoisted rotations: N = 2^12, 4 + 2 limbs 99 / 47, 2^13, 14 + 6 107 / 80, 2^14, 14 + 6 (0.33 M coefficients) 152.5 / 152.0, 2^15, 13 + 8
+//     (0.69 M) 247 / 249
+//   activation of sixteen: 2^12, 7 + 3 limbs 268 / 202, 2^14, 7 + 3 (0.16 M) 432 / 402, 2^13, 24 + 8 (0.26 M) 810 / 827, 2^14, 14 + 6 (0.33 M) 884 / 948
+//   merged convolution from sixteen channels: 2^12, 7 + 3 limbs 175 / 158, 24 + 8 (0.13 M) 392 / 369, 2^14, 7 + 3 (0.16 M) 461 / 467; from three to
+//     twelve (only the divisions come in two batches): 2^12, 7 + 3 95 / 59, 2^14, 14 + 6 (0.33 M) 261 / 253, 24 + 8 (0.52 M) 400 / 391; with a rescale
+//     of its own, 2^13, 24 + 8 (0.26 M) 266 / 259, 2^14, 14 + 6 310 / 317
+bool together(const ckks_ctx* c, u32 level, size_t limit) { return ntt_has_modup(c) && (size_t)c->ext_limbs(level) * c->N <= limit; }
+constexpr size_t TOGETHER_ROTATIONS = (size_t)1 << 19, TOGETHER_ACTIVATION = (size_t)3 << 16;
 size_t ws_rescale(const ckks_ctx* c, u32 level, u32 n) { return blk(2 * (size_t)n * c->N) + blk(2 * (size_t)n * level * c->N); }
 // a product's scratch: the key switch's, and the three polynomials of the tensor product where a kernel forms them (elsewhere they
 // are not stored: run_product)
@@ -111,7 +128,7 @@ size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
     return (ntt_has_modup(c) ? 0 : 3 * blk((size_t)n * (level + 1) * c->N)) + ws_ks(c, level, n, n);
 }
 
-// Decompose + ModUp of n <= CT_BATCH polynomials srcs[b] ([level+1][N], NTT form) into
+// Decompose + ModUp of n <= ks_batch polynomials srcs[b] ([level+1][N], NTT form) into
 // ws.digits + b*ws.dig_b ([beta][E][N], NTT form).
 // hi_only (double-precision transforms only): the forward transforms stop after their first pass; the caller finishes them
 // inside the inner product (launch_ntt_lo_mac).
@@ -120,7 +137,7 @@ size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
 int run_modup(const ckks_ctx* c, u32 level, const u64* const* srcs, u32 n, const KsWs& ws, hipStream_t st, bool hi_only = false,
               const u64* const* muls = nullptr, const u32* gals = nullptr) {
     const u32 N = c->N, L1 = level + 1, E = c->ext_limbs(level), beta = c->live_digits(level);
-    for (u32 b = 0; b < CT_BATCH; b++) ws.own[b] = (b < n && !muls) ? srcs[b] : nullptr;  // a product has no stored own limbs
+    for (u32 b = 0; b < KS_MAX_BATCH; b++) ws.own[b] = (b < n && !muls) ? srcs[b] : nullptr;  // a product has no stored own limbs
     if (muls && !hi_only) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: product source without the fused inner product");
     // all live limbs of every polynomial to coefficient form at once.  With double-precision transforms the inverse scales
     // limb i by N^-1 (Q_j/q_i)^-1 and leaves the centred residue as a double, and each digit's basis conversion happens
@@ -327,17 +344,16 @@ struct LinAddend {
     const u64* kb;
 };
 
-// n <= CT_BATCH ciphertext products with relinearisation in contexts with the fused inner product: no tensor-product kernel, d2 =
+// n <= ks_batch ciphertext products with relinearisation in contexts with the fused inner product: no tensor-product kernel, d2 =
 // a1 (.) b1 is formed as the inverse transform loads it, P d0, P d1 and the own-limb term as the inner product's last terms, all
-// from the operands themselves; dividing the sums by P (merged: by P*q_level) is then the whole product.
-int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride, const u64* d_rlk,
+// from the operands themselves (b, b1: the two components of the second one); dividing the sums by P (merged: by P*q_level) is then the whole product.
+int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, const u64* const* b1, const u64* d_rlk,
                 u64* const* outs, u32 n, const KsWs& ws, hipStream_t st, bool merged, const LinAddend* lin = nullptr) {
-    const u64 *a1[CT_BATCH], *b1[CT_BATCH], *keys[CT_BATCH];
-    u64* vs[CT_BATCH];
-    FinalItem items[CT_BATCH];
+    const u64 *a1[KS_MAX_BATCH], *keys[KS_MAX_BATCH];
+    u64* vs[KS_MAX_BATCH];
+    FinalItem items[KS_MAX_BATCH];
     for (u32 i = 0; i < n; i++) {
         a1[i] = a[i] + a_cstride;
-        b1[i] = b[i] + b_cstride;
         vs[i] = ws.v + i * ws.v_b;
         keys[i] = d_rlk;
         items[i] = FinalItem{nullptr, nullptr, nullptr, outs[i], 1, 0};
@@ -357,14 +373,16 @@ int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstr
     return run_moddown(c, level, ws, n, items, st, merged, true);
 }
 
-// n <= CT_BATCH products a[b]*b[b] with relinearisation (operands possibly at a higher level:
+// n products a[b]*b[b] (as many as ks_batch, CT_BATCH without the fused inner product) with relinearisation (operands possibly at a higher level:
 // component strides given); outs[b] = [2][level+1][N]
 int run_ctct(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, size_t b_cstride,
              const u64* d_rlk, u64* const* outs, u32 n, Arena ar, hipStream_t st) {
     const size_t N = c->N, L1 = level + 1;
     KsWs ws;
     if (!carve_ks(c, level, n, n, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for ct-ct multiply");
-    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, false);
+    const u64* b1[KS_MAX_BATCH];
+    for (u32 i = 0; i < n; i++) b1[i] = b[i] + b_cstride;
+    if (ntt_has_modup(c)) return run_product(c, level, a, a_cstride, b, b1, d_rlk, outs, n, ws, st, false);
     u64* d0 = ar.take(n * L1 * N);
     u64* d1 = ar.take(n * L1 * N);
     u64* d2 = ar.take(n * L1 * N);
@@ -398,7 +416,9 @@ int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_
     const bool mac = ntt_has_modup(c);  // the inner product inside the forward transforms' second pass
     if (lin && (!mac || addend)) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: linear addend without the fused inner product");
     if (mac && addend) return set_err(c, CKKS_ERR_INVALID_ARG, "internal: with the fused inner product the addend is given as a linear combination");
-    if (mac) return run_product(c, level, a, a_cstride, b, b_cstride, d_rlk, outs, n, ws, st, true, lin);
+    const u64* b1[KS_MAX_BATCH];
+    for (u32 i = 0; i < n; i++) b1[i] = b[i] + b_cstride;
+    if (mac) return run_product(c, level, a, a_cstride, b, b1, d_rlk, outs, n, ws, st, true, lin);
     u64* d0 = ar.take(n * L1 * N);
     u64* d1 = ar.take(n * L1 * N);
     u64* d2 = ar.take(n * L1 * N);
@@ -420,22 +440,40 @@ int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_
     return run_moddown(c, level, ws, n, items, st, true);
 }
 
-size_t ws_poly_act(const ckks_ctx* c, u32 level, u32 n) {
-    const size_t N = c->N;
+// whether x^3 = x^2 x and x^4 = x^2 x^2 of n ciphertexts go through the kernels as one batch of products (merged divisions)
+bool act_pairs(const ckks_ctx* c, u32 level, u32 n) { return ntt_has_modup(c) && 2 * n <= ks_batch(c); }
+size_t ws_poly_act_in(const ckks_ctx* c, u32 level, u32 n, bool pairs) {
+    const size_t N = c->N, one = ws_ctct(c, level, n) + ws_rescale(c, level, n), two = pairs ? ws_ctct(c, level - 1, 2 * n) : 0;
     return blk(2 * (size_t)n * level * N) + 2 * blk(2 * (size_t)n * (level - 1) * N) + blk(2 * (size_t)n * (level - 2) * N) +
-           blk(2 * (size_t)n * (level + 1) * N) + ws_ctct(c, level, n) + ws_rescale(c, level, n);
+           blk(2 * (size_t)n * (level + 1) * N) + (one > two ? one : two);
 }
+size_t ws_poly_act(const ckks_ctx* c, u32 level, u32 n) { return ws_poly_act_in(c, level, n, act_pairs(c, level, n)); }
+// ciphertexts of a batch of the activation with merged divisions, of n_ct in all
+u32 act_batch(const ckks_ctx* c, u32 level, u32 n_ct) { return n_ct > CT_BATCH && together(c, level, TOGETHER_ACTIVATION) ? KS_MAX_BATCH : CT_BATCH; }
 
 // The convolution with one division by P per output channel: every aligned copy stays on the extended
 // basis Q_level P (inner product + P * sigma_g(c0), times the tap's mask), the sum over (input channel,
 // tap) is taken there, and only the C_out sums go through ModDown and the rescale.  gs: Galois
 // elements of the nine taps (1 = no rotation); masks [9][E][N], w_res [C_out][C_in][9][E].
 // per-lane scratch of the deferred convolution: the key-switch buffers, a batch of un-rescaled outputs, the rescale's scratch
-size_t ws_conv_lane(const ckks_ctx* c, u32 level) {
-    return ws_ks(c, level, CT_BATCH, CT_BATCH) + blk((size_t)CT_BATCH * 2 * (level + 1) * c->N) + ws_rescale(c, level, CT_BATCH);
+size_t ws_conv_lane(const ckks_ctx* c, u32 level, u32 kb) {
+    return ws_ks(c, level, kb, kb) + blk((size_t)kb * 2 * (level + 1) * c->N) + ws_rescale(c, level, CT_BATCH);
 }
-u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {  // two batches in flight when there is more than one
-    return (c->side_stream() && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;
+bool conv_together(const ckks_ctx* c, const he_conv_desc* d) {
+    return together(c, d->level, d->c_in > CT_BATCH ? (size_t)1 << 17 : (d->alignment == HE_CONV_DEFERRED_MERGED ? (size_t)1 << 19 : (size_t)1 << 18));
+}
+// channels of a batch, and whether two batches are in flight when there is more than one
+u32 conv_batch(const ckks_ctx* c, const he_conv_desc* d) { return conv_together(c, d) && (d->c_in > CT_BATCH || d->c_out > CT_BATCH) ? KS_MAX_BATCH : CT_BATCH; }
+u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {
+    return (!conv_together(c, d) && c->side_stream() && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;
+}
+
+// the schedules that divide every rotation by P, kb of them at a time
+size_t ws_conv_rotated(const ckks_ctx* c, const he_conv_desc* d, u32 kb) {
+    const size_t N = c->N, L1 = d->level + 1;
+    return ws_ks(c, d->level, CT_BATCH, kb) + blk((size_t)d->c_in * 9 * 2 * L1 * N) + blk((size_t)d->c_out * 2 * L1 * N) +
+           blk(weighted_sum_scratch_elems(c, (u32)L1, d->c_in * 9, d->c_out)) + ws_rescale(c, d->level, CT_BATCH) +
+           (d->alignment == HE_CONV_ALIGN_FOUR_KEYS ? 2 * blk((size_t)CT_BATCH * 2 * L1 * N) : 0);
 }
 
 int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const uint64_t* const* h_d_in,
@@ -450,7 +488,9 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     u64* wscratch = ar.take(weighted_sum_scratch_elems(c, E, d->c_in * 9, d->c_out));
     // Batches of input channels (alignment) and of output channels (division) are independent: with room for two sets of
     // scratch every other batch runs on the library's side stream, between a fork and a join on the caller's stream.
-    const size_t lane_bytes = ws_conv_lane(c, level);
+    u32 kb = conv_batch(c, d);
+    if (ar.ok() && ar.used + ws_conv_lane(c, level, kb) > ar.cap) kb = CT_BATCH;  // in a smaller workspace
+    const size_t lane_bytes = ws_conv_lane(c, level, kb);
     const u32 n_lanes = (conv_lanes(c, d) == 2 && ar.ok() && ar.used + 2 * lane_bytes <= ar.cap) ? 2 : 1;
     struct Lane {
         KsWs ws;
@@ -461,8 +501,8 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     Lane lanes[2] = {{KsWs{}, nullptr, Arena(nullptr, 0), st0}, {KsWs{}, nullptr, Arena(nullptr, 0), c->side}};
     bool ok = ar.ok();
     for (u32 l = 0; l < n_lanes && ok; l++) {
-        ok = carve_ks(c, level, CT_BATCH, CT_BATCH, ar, lanes[l].ws);
-        lanes[l].tmp = ar.take((size_t)CT_BATCH * ct_elems);
+        ok = carve_ks(c, level, kb, kb, ar, lanes[l].ws);
+        lanes[l].tmp = ar.take((size_t)kb * ct_elems);
         u64* r = ar.take(ws_rescale(c, level, CT_BATCH) / sizeof(u64));
         lanes[l].rest = Arena(r, ws_rescale(c, level, CT_BATCH));
         ok = ok && ar.ok();
@@ -489,8 +529,8 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     auto align_batch = [&](u32 c0, const Lane& L) -> int {
         const KsWs& ws = L.ws;
         hipStream_t st = L.st;
-        const u32 n = d->c_in - c0 < CT_BATCH ? d->c_in - c0 : CT_BATCH;
-        const u64 *in[CT_BATCH], *c1s[CT_BATCH];
+        const u32 n = d->c_in - c0 < kb ? d->c_in - c0 : kb;
+        const u64 *in[KS_MAX_BATCH], *c1s[KS_MAX_BATCH];
         for (u32 b = 0; b < n; b++) {
             in[b] = (const u64*)h_d_in[c0 + b];
             c1s[b] = in[b] + L1 * N;
@@ -518,40 +558,44 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
             ttap[n_taps++] = t;
         }
         if (fused_taps) {
-            HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, 0), tkeys, tg, tmasks, ttap, n_taps, in, xs, xl, c0 * 9, 9, n, st, centre_mask,
-                                          centre_tap));
+            for (u32 b0 = 0; b0 < n; b0 += CT_BATCH)
+                HIP_TRY(launch_key_inner_taps(c, level, dsrc(c, ws, b0), tkeys, tg, tmasks, ttap, n_taps, in + b0, xs, xl, (c0 + b0) * 9, 9,
+                                              n - b0 < CT_BATCH ? n - b0 : CT_BATCH, st, centre_mask, centre_tap));
         } else {  // many digits: one launch per tap (classic layout: every term is a [2][E][N] array)
-            for (u32 i = 0; i < n_taps; i++) {
-                u64* outs[CT_BATCH];
-                for (u32 b = 0; b < n; b++) outs[b] = xs + ((size_t)(c0 + b) * 9 + ttap[i]) * x_elems;
-                HIP_TRY(launch_key_inner_ext(c, level, dsrc(c, ws, 0), tkeys[i], tg[i], in, nullptr, tmasks[i], outs, n, st));
-            }
+            for (u32 i = 0; i < n_taps; i++)
+                for (u32 b0 = 0; b0 < n; b0 += CT_BATCH) {
+                    const u32 m = n - b0 < CT_BATCH ? n - b0 : CT_BATCH;
+                    u64* outs[CT_BATCH];
+                    for (u32 b = 0; b < m; b++) outs[b] = xs + ((size_t)(c0 + b0 + b) * 9 + ttap[i]) * x_elems;
+                    HIP_TRY(launch_key_inner_ext(c, level, dsrc(c, ws, b0), tkeys[i], tg[i], in + b0, nullptr, tmasks[i], outs, m, st));
+                }
         }
         return CKKS_OK;
     };
     int rc;
-    if (d->c_in > CT_BATCH && (rc = fork())) return rc;
-    for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += CT_BATCH, k++)
+    if (d->c_in > kb && (rc = fork())) return rc;
+    for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += kb, k++)
         if ((rc = align_batch(c0, lanes[forked ? k & 1 : 0]))) return join(rc);
     if ((rc = join(CKKS_OK))) return rc;
     HIP_TRY(launch_weighted_sum(c, level, true, xs, xl, d->c_in * 9, w_res, d->c_out, acc, wscratch, d->weight_bits, st0));
-    if (d->c_out > CT_BATCH && (rc = fork())) return rc;
-    for (u32 o0 = 0, k = 0; o0 < d->c_out; o0 += CT_BATCH, k++) {
+    if (d->c_out > kb && (rc = fork())) return rc;
+    for (u32 o0 = 0, k = 0; o0 < d->c_out; o0 += kb, k++) {
         const Lane& L = lanes[forked ? k & 1 : 0];
-        const u32 n = d->c_out - o0 < CT_BATCH ? d->c_out - o0 : CT_BATCH;
+        const u32 n = d->c_out - o0 < kb ? d->c_out - o0 : kb;
         KsWs wd = L.ws;
         wd.v = acc + (size_t)o0 * x_elems;  // the sums take the place of a batch of inner products
         wd.v_b = x_elems;
-        FinalItem items[CT_BATCH];
-        const u64* ins[CT_BATCH];
-        u64* outs[CT_BATCH];
+        FinalItem items[KS_MAX_BATCH];
+        const u64* ins[KS_MAX_BATCH];
+        u64* outs[KS_MAX_BATCH];
         for (u32 b = 0; b < n; b++) {
             ins[b] = L.tmp + (size_t)b * ct_elems;
             outs[b] = (u64*)h_d_out[o0 + b];
             items[b] = FinalItem{nullptr, nullptr, nullptr, merged ? outs[b] : L.tmp + (size_t)b * ct_elems, 1, 0};
         }
         if ((rc = run_moddown(c, level, wd, n, items, L.st, merged))) return join(rc);
-        if (!merged && (rc = run_rescale(c, level, ins, L1 * N, outs, n, L.rest, L.st))) return join(rc);
+        for (u32 b0 = 0; b0 < n && !merged; b0 += CT_BATCH)
+            if ((rc = run_rescale(c, level, ins + b0, L1 * N, outs + b0, n - b0 < CT_BATCH ? n - b0 : CT_BATCH, L.rest, L.st))) return join(rc);
     }
     return join(CKKS_OK);
 }
@@ -561,9 +605,14 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
 // allows it, else one per tap.
 hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64* const* cts, u32 n, const u64* const* keys, const u32* gs,
                          const u32* pos, u32 n_taps, hipStream_t st) {
-    if (c->live_digits(level) <= 4)
-        return launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys, gs, nullptr, pos, n_taps, cts, ws.v, XLayout::classic(c->ext_limbs(level), c->N),
-                                     0, 1, n, st);
+    if (c->live_digits(level) <= 4) {
+        for (u32 i0 = 0; i0 < n_taps; i0 += 8) {
+            const u32 m = n_taps - i0 < 8 ? n_taps - i0 : 8;
+            if (hipError_t e = launch_key_inner_taps(c, level, dsrc(c, ws, 0), keys + i0, gs + i0, nullptr, pos + i0, m, cts, ws.v,
+                                                     XLayout::classic(c->ext_limbs(level), c->N), 0, 1, n, st); e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     for (u32 i = 0; i < n_taps; i++) {
         const u64* k[CT_BATCH];
         u32 g[CT_BATCH];
@@ -573,7 +622,7 @@ hipError_t rotated_inner(const ckks_ctx* c, u32 level, const KsWs& ws, const u64
     return hipSuccess;
 }
 
-// n <= CT_BATCH ciphertexts srcs[b] ([2][level+1][N]) rotated, outs[b] = Rot(srcs[b]) with keys[b] / gal[b] ([2][level+1][N], no
+// n <= ks_batch ciphertexts srcs[b] ([2][level+1][N]) rotated, outs[b] = Rot(srcs[b]) with keys[b] / gal[b] ([2][level+1][N], no
 // overlap).  Where a key switch takes its inner product inside the forward transforms' second pass, the permuted polynomial is
 // decomposed (the digits of a permuted polynomial are the permuted digits), gathered as the inverse transform loads it: no
 // kernel for the automorphism, the extended digits are never written in evaluation form.  Elsewhere one inner-product launch for all of them reads
@@ -584,9 +633,9 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
                      u64* const* outs, const KsWs& ws, hipStream_t st, const u64* const* accs = nullptr) {
     const size_t L1 = level + 1;
     const bool mac = ntt_has_modup(c);
-    const u64 *c1s[CT_BATCH], *kd[CT_BATCH];
-    u64* vs[CT_BATCH];
-    FinalItem items[CT_BATCH];
+    const u64 *c1s[KS_MAX_BATCH], *kd[KS_MAX_BATCH];
+    u64* vs[KS_MAX_BATCH];
+    FinalItem items[KS_MAX_BATCH];
     for (u32 b = 0; b < n; b++) {
         c1s[b] = srcs[b] + L1 * c->N;
         kd[b] = keys[b]->d_key;
@@ -604,17 +653,20 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
     return run_moddown(c, level, ws, n, items, st, false, mac);
 }
 
-size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) {
+// rotations of a merge of g blocks that share their launches, at most `most`
+u32 merge_batch(u32 g, u32 most) { return g - 1 < most ? (g > 1 ? g - 1 : 1) : most; }
+size_t ws_merge_in(const ckks_ctx* c, u32 level, u32 g, u32 nb) {
     const size_t N = c->N, L1 = level + 1;
-    const u32 nb = g - 1 < CT_BATCH ? (g > 1 ? g - 1 : 1) : CT_BATCH;
     return ws_ks(c, level, nb, nb) + 2 * blk((size_t)g * 2 * L1 * N) + blk(2 * L1 * N) + ws_rescale(c, level, 1);
 }
+size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) { return ws_merge_in(c, level, g, merge_batch(g, ks_batch(c))); }
 
 // out = Rescale( sum_{i<g} Rot(cts[i] (.) mask, -i*sts) ), g <= KS_MAX_BATCH; keys[i] / gal[i] for i >= 1 (validated by the caller)
 int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const u64* mask, const ckks_key* const* keys, const u32* gal,
               u64* out, Arena ar, hipStream_t st) {
     const size_t N = c->N, L1 = level + 1, ct_elems = 2 * L1 * N;
-    const u32 nb = g - 1 < CT_BATCH ? (g > 1 ? g - 1 : 1) : CT_BATCH;
+    u32 nb = merge_batch(g, ks_batch(c));
+    if (ar.used + ws_merge_in(c, level, g, nb) > ar.cap) nb = merge_batch(g, CT_BATCH);  // in a smaller workspace
     KsWs ws;
     bool ok = carve_ks(c, level, nb, nb, ar, ws);
     u64* masked = ar.take((size_t)g * ct_elems);   // C_i (.) M
@@ -629,8 +681,8 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
     // blocks 1..g-1: every block has its own key; a batch shares the decomposition and ModDown launches
     for (u32 i0 = 1; i0 < g; i0 += nb) {
         const u32 n = g - i0 < nb ? g - i0 : nb;
-        const u64* srcs[CT_BATCH];
-        u64* outs[CT_BATCH];
+        const u64* srcs[KS_MAX_BATCH];
+        u64* outs[KS_MAX_BATCH];
         for (u32 b = 0; b < n; b++) {
             srcs[b] = masked + (i0 + b) * ct_elems;
             outs[b] = rotated + (i0 + b) * ct_elems;
@@ -650,11 +702,18 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
 // g_lo / g_hi: Galois elements (1 = no rotation, key ignored); masks: device pointers [level+1][N] or null; every h has
 // at least one mask (validated by the caller).  First rotations: one decomposition per ciphertext, every key read once per
 // batch of up to CT_BATCH (ciphertext, offset) pairs; second rotations batched the same way over (h, ciphertext).
-size_t ws_relayout(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_lo, u32 n_hi) {
+// the key-switch buffers of both levels, `most` (ciphertext, offset) pairs at a time
+size_t ws_relayout_ks(const ckks_ctx* c, u32 level, u32 most) {
+    const size_t lo = ws_ks(c, level, CT_BATCH, most), hi = ws_ks(c, level - 1, most, most);
+    return lo > hi ? lo : hi;
+}
+size_t ws_relayout_in(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_lo, u32 n_hi, u32 most) {
     const size_t N = c->N, ctl = 2 * (size_t)(level + 1) * N, ctl1 = 2 * (size_t)level * N;
     const size_t nb = n_ct < CT_BATCH ? n_ct : CT_BATCH;
-    return blk(nb * n_lo * ctl) + blk(nb * n_hi * ctl) + 2 * blk(nb * n_hi * ctl1) + ws_ks(c, level, CT_BATCH, CT_BATCH) +
-           ws_rescale(c, level, CT_BATCH);
+    return blk(nb * n_lo * ctl) + blk(nb * n_hi * ctl) + 2 * blk(nb * n_hi * ctl1) + ws_relayout_ks(c, level, most) + ws_rescale(c, level, CT_BATCH);
+}
+size_t ws_relayout(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_lo, u32 n_hi) {
+    return ws_relayout_in(c, level, n_ct, n_lo, n_hi, ks_batch(c));
 }
 
 int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, u32 n_lo, const ckks_key* const* lo_keys, const u32* g_lo,
@@ -666,29 +725,31 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
     u64* Vacc = ar.take((size_t)nb_max * n_hi * ctl);   // masked sums before their rescale
     u64* V = ar.take((size_t)nb_max * n_hi * ctl1);     // level-1
     u64* Vrot = ar.take((size_t)nb_max * n_hi * ctl1);
-    const size_t ks_bytes = ws_ks(c, level, CT_BATCH, CT_BATCH);
+    u32 kb = ks_batch(c);  // rotations at a time
+    if (ar.ok() && ar.used + ws_relayout_ks(c, level, kb) + ws_rescale(c, level, CT_BATCH) > ar.cap) kb = CT_BATCH;  // in a smaller workspace
+    const size_t ks_bytes = ws_relayout_ks(c, level, kb);
     u64* ks_region = ar.take(ks_bytes / sizeof(u64));
     if (!ar.ok() || ar.used + ws_rescale(c, level, CT_BATCH) > ar.cap)
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the re-layout");
     KsWs ws;
-    auto ks_at = [&](u32 lv) {  // the key-switch buffers are carved again for the lower level
+    auto ks_at = [&](u32 lv, u32 n_dig) {  // the key-switch buffers are carved again for the lower level
         Arena sub(ks_region, ks_bytes);
-        return carve_ks(c, lv, CT_BATCH, CT_BATCH, sub, ws);
+        return carve_ks(c, lv, n_dig, kb, sub, ws);
     };
     int rc;
     for (u32 c0 = 0; c0 < n_ct; c0 += CT_BATCH) {
         const u32 n = n_ct - c0 < CT_BATCH ? n_ct - c0 : CT_BATCH;
         auto r_at = [&](u32 b, u32 l) { return R + ((size_t)b * n_lo + l) * ctl; };
         // first rotations
-        ks_at(level);
+        ks_at(level, CT_BATCH);
         const u64* c1s[CT_BATCH];
         for (u32 b = 0; b < n; b++) c1s[b] = cts[c0 + b] + (size_t)(level + 1) * N;
         if ((rc = run_modup(c, level, c1s, n, ws, st))) return rc;
-        const u32 per = CT_BATCH / n;  // offsets per ModDown batch
+        const u32 per = kb / n;  // offsets per ModDown batch
         for (u32 la = 0; la < n_lo; la += per) {
-            FinalItem items[CT_BATCH];
-            const u64* tkeys[CT_BATCH];
-            u32 tg[CT_BATCH], pos[CT_BATCH], nt = 0, nk = 0;
+            FinalItem items[KS_MAX_BATCH];
+            const u64* tkeys[KS_MAX_BATCH];
+            u32 tg[KS_MAX_BATCH], pos[KS_MAX_BATCH], nt = 0, nk = 0;
             for (u32 l = la; l < n_lo && l < la + per; l++) {
                 if (g_lo[l] == 1) {
                     for (u32 b = 0; b < n; b++) HIP_TRY(launch_copy(cts[c0 + b], r_at(b, l), ctl, st));
@@ -716,11 +777,11 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
             if ((rc = run_rescale(c, level, pv, (size_t)(level + 1) * N, ov, m, ar.rest(), st))) return rc;
         }
         // second rotations, ordered by h so that the ciphertexts of a batch share each key
-        ks_at(l1);
-        const u64* srcs[CT_BATCH];
-        const ckks_key* ks[CT_BATCH];
-        u32 gs[CT_BATCH], nk = 0;
-        u64* dsts[CT_BATCH];
+        ks_at(l1, kb);
+        const u64* srcs[KS_MAX_BATCH];
+        const ckks_key* ks[KS_MAX_BATCH];
+        u32 gs[KS_MAX_BATCH], nk = 0;
+        u64* dsts[KS_MAX_BATCH];
         for (u32 h = 0; h < n_hi; h++) {
             if (g_hi[h] == 1) continue;
             for (u32 b = 0; b < n; b++) {
@@ -728,7 +789,7 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
                 dsts[nk] = Vrot + ((size_t)b * n_hi + h) * ctl1;
                 ks[nk] = hi_keys[h];
                 gs[nk++] = g_hi[h];
-                if (nk == CT_BATCH) {
+                if (nk == kb) {
                     if ((rc = run_rotate_batch(c, l1, nk, srcs, ks, gs, dsts, ws, st))) return rc;
                     nk = 0;
                 }
@@ -901,29 +962,34 @@ size_t ckks_workspace_bytes(const ckks_ctx* c, int op, uint32_t level, uint32_t 
             // unhoisted: every rotation of a batch has its own permuted copy and its own digits
             const size_t hoisted = ws_ks(c, level, 1, nb) + blk(L1 * N) +
                                    (count > CT_BATCH && c->side ? blk((size_t)nb * 2 * c->ext_limbs(level) * N) + blk((size_t)nb * 2 * L1 * N) : 0);
-            const size_t unhoisted = ws_ks(c, level, nb, nb) + blk((size_t)nb * L1 * N);
+            const u32 most = ks_batch(c), ub = count < most ? (count ? count : 1) : most;
+            const size_t unhoisted = ws_ks(c, level, ub, ub) + blk((size_t)ub * L1 * N);
             return hoisted > unhoisted ? hoisted : unhoisted;
         }
         case CKKS_OP_RESCALE: return level >= 1 ? ws_rescale(c, level, 1) : 0;
         case CKKS_OP_CTCT_MUL_RELIN: return c->dnum ? ws_ctct(c, level, 1) : 0;
         // more than one batch of channels: two batches in flight (one on the library's side stream), each with its own scratch
-        case CKKS_OP_POLY_ACT: return (c->dnum && level >= 4) ? ws_poly_act(c, level, nb) * (count > CT_BATCH && c->side ? 2 : 1) : 0;  // sized for overlap on
+        case CKKS_OP_POLY_ACT: {
+            if (!c->dnum || level < 4) return 0;
+            const size_t lanes = ws_poly_act(c, level, nb) * (count > CT_BATCH && c->side ? 2 : 1);  // sized for overlap on
+            const u32 most = act_batch(c, level, count);
+            const size_t one = ws_poly_act(c, level, count < most ? (count ? count : 1) : most);
+            return one > lanes ? one : lanes;
+        }
         default: return 0;
     }
 }
 
 size_t he_conv_workspace_bytes(const ckks_ctx* c, const he_conv_desc* d) {
     if (!c || !d || !c->dnum || !level_ok(c, d->level) || d->level < 1) return 0;
-    const size_t N = c->N, L1 = d->level + 1;
+    const size_t N = c->N;
     if (d->alignment == HE_CONV_DEFERRED_MODDOWN || d->alignment == HE_CONV_DEFERRED_MERGED) {
         const size_t E = c->ext_limbs(d->level);
-        const u32 lanes = (c->side && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;  // sized for overlap on
-        return lanes * ws_conv_lane(c, d->level) + blk((size_t)d->c_in * 9 * 2 * E * N) + blk((size_t)d->c_out * 2 * E * N) +
+        const u32 lanes = (!conv_together(c, d) && c->side && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;  // sized for overlap on
+        return lanes * ws_conv_lane(c, d->level, conv_batch(c, d)) + blk((size_t)d->c_in * 9 * 2 * E * N) + blk((size_t)d->c_out * 2 * E * N) +
                blk(weighted_sum_scratch_elems(c, (u32)E, d->c_in * 9, d->c_out));
     }
-    return ws_ks(c, d->level, CT_BATCH, CT_BATCH) + blk((size_t)d->c_in * 9 * 2 * L1 * N) + blk((size_t)d->c_out * 2 * L1 * N) +
-           blk(weighted_sum_scratch_elems(c, (u32)L1, d->c_in * 9, d->c_out)) + ws_rescale(c, d->level, CT_BATCH) +
-           (d->alignment == HE_CONV_ALIGN_FOUR_KEYS ? 2 * blk((size_t)CT_BATCH * 2 * L1 * N) : 0);
+    return ws_conv_rotated(c, d, ks_batch(c));
 }
 
 int ckks_ctx_set_overlap(ckks_ctx* c, int on) {
@@ -1059,15 +1125,17 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
         if (!keys || !keys[t]) return set_err(c, CKKS_ERR_NO_KEY, "rotation key missing");
         if (keys[t]->galois_elt != g) return set_err(c, CKKS_ERR_NO_KEY, "rotation key was made for another offset");
     }
-    // rotations go through the kernels in batches of up to CT_BATCH: hoisted ones share the digits and batch their ModDown;
+    // rotations go through the kernels in batches of up to CT_BATCH (unhoisted: ks_batch): hoisted ones share the digits and batch their ModDown;
     // unhoisted ones each have their own permuted polynomial and digits and batch everything but the inner product (one key
     // each), in batches as large as the workspace holds (one at a time in the smallest workspace that is accepted)
-    u32 rb = n_keyed < CT_BATCH ? (n_keyed ? n_keyed : 1) : CT_BATCH;
+    const u32 most = hoisted && !together(c, level, TOGETHER_ROTATIONS) ? CT_BATCH : ks_batch(c);
+    u32 rb = n_keyed < most ? (n_keyed ? n_keyed : 1) : most;
     Arena ar(d_ws, ws_bytes);
     KsWs ws = {};
     u64* pc1 = nullptr;
     if (n_keyed) {
         if (hoisted) {
+            if (rb > CT_BATCH && ws_bytes < ws_ks(c, level, 1, rb)) rb = CT_BATCH;  // in a smaller workspace
             if (!carve_ks(c, level, 1, rb, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rotation");
         } else {
             for (;; rb--) {
@@ -1086,7 +1154,7 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     // other batch runs on the context's second stream (its traffic-bound inner products next to the other batch's ModDown).
     KsWs lane_ws[2] = {ws, ws};
     bool two_lanes = false;
-    if (hoisted && n_keyed > rb && c->side_stream()) {
+    if (hoisted && n_keyed > rb && c->side_stream() && !together(c, level, TOGETHER_ROTATIONS)) {
         Arena extra = ar;
         lane_ws[1].v = extra.take(rb * ws.v_b);
         lane_ws[1].w = extra.take(rb * ws.w_b);
@@ -1110,14 +1178,14 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
         if (e == hipSuccess) e = hipStreamWaitEvent(st, c->ev_join, 0);
         return (e != hipSuccess && rc == CKKS_OK) ? set_hip_err(c, e) : rc;
     };
-    FinalItem items[CT_BATCH];
-    const ckks_key* pend_key[CT_BATCH];
+    FinalItem items[KS_MAX_BATCH];
+    const ckks_key* pend_key[KS_MAX_BATCH];
     u32 nb = 0, lane = 0;
     // the pending unhoisted rotations: one decomposition of sigma_g(c1) per rotation and one ModDown for the batch
     auto flush_unhoisted = [&]() -> int {
-        const u64 *srcs[CT_BATCH], *ks[CT_BATCH];
-        u64* outs[CT_BATCH];
-        u32 gs[CT_BATCH];
+        const u64 *srcs[KS_MAX_BATCH], *ks[KS_MAX_BATCH];
+        u64* outs[KS_MAX_BATCH];
+        u32 gs[KS_MAX_BATCH];
         const u32 n = nb;
         nb = 0;
         for (u32 b = 0; b < n; b++) {
@@ -1137,18 +1205,15 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     auto flush_hoisted = [&]() -> int {
         const KsWs& lw = lane_ws[lane];
         hipStream_t ls = lane ? c->side : st;
-        const u64* tkeys[8];
-        u32 tg[8], ttap[8];
+        const u64* tkeys[KS_MAX_BATCH];
+        u32 tg[KS_MAX_BATCH], ttap[KS_MAX_BATCH];
         for (u32 b = 0; b < nb; b++) {
             tkeys[b] = pend_key[b]->d_key;
             tg[b] = items[b].g;
             ttap[b] = b;
             items[b].g = 1;  // the division's last step adds nothing: c0 is inside the sum already
         }
-        if (hipError_t e = launch_key_inner_taps(c, level, dsrc(c, lw, 0), tkeys, tg, nullptr, ttap, nb, &ct, lw.v,
-                                                 XLayout::classic(c->ext_limbs(level), N), 0, 0, 1, ls);
-            e != hipSuccess)
-            return set_hip_err(c, e);
+        if (hipError_t e = rotated_inner(c, level, lw, &ct, 1, tkeys, tg, ttap, nb, ls); e != hipSuccess) return set_hip_err(c, e);
         int rc = run_moddown(c, level, lw, nb, items, ls);
         nb = 0;
         if (two_lanes) lane ^= 1;
@@ -1292,7 +1357,9 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
                              (hipStream_t)stream);
     Arena ar(d_ws, ws_bytes);
     KsWs ws;
-    bool ok = carve_ks(c, level, CT_BATCH, CT_BATCH, ar, ws);
+    u32 kb = ks_batch(c);  // rotations divided at a time
+    if (ws_bytes < ws_conv_rotated(c, d, kb)) kb = CT_BATCH;  // in a smaller workspace
+    bool ok = carve_ks(c, level, CT_BATCH, kb, ar, ws);
     u64* xs = ar.take((size_t)d->c_in * 9 * ct_elems);
     u64* acc = ar.take((size_t)d->c_out * ct_elems);
     u64* wscratch = ar.take(weighted_sum_scratch_elems(c, (u32)L1, d->c_in * 9, d->c_out));
@@ -1316,15 +1383,15 @@ int he_conv_batched(const ckks_ctx* c, const he_conv_desc* d, const uint64_t* co
         u64* outs[CT_BATCH];
         const u64* masks[CT_BATCH];
     };
-    // The rotations `jobs` of the n ciphertexts `base`, whose digits are in ws: as many taps per launch as fill a batch of
-    // CT_BATCH key switches (eight for a single channel, one for eight channels).
+    // The rotations `jobs` of the n ciphertexts `base`, whose digits are in ws: as many taps at a time as fill a batch of
+    // kb key switches (all eight for one or two channels, two for eight).
     auto rotate_jobs = [&](const u64* const* base, u32 n, const TapJob* jobs, u32 n_jobs) -> int {
-        const u32 per = CT_BATCH / n;
+        const u32 per = kb / n;
         for (u32 j0 = 0; j0 < n_jobs; j0 += per) {
             const u32 m = n_jobs - j0 < per ? n_jobs - j0 : per;
-            FinalItem items[CT_BATCH];
-            const u64* keys[CT_BATCH];
-            u32 g[CT_BATCH], pos[CT_BATCH];
+            FinalItem items[KS_MAX_BATCH];
+            const u64* keys[KS_MAX_BATCH];
+            u32 g[KS_MAX_BATCH], pos[KS_MAX_BATCH];
             for (u32 j = 0; j < m; j++) {
                 const TapJob& job = jobs[j0 + j];
                 keys[j] = rot_keys[job.kt]->d_key;
@@ -1513,13 +1580,22 @@ static u32 fc_base(const he_fc_desc* d) {
 
 static size_t max3(size_t a, size_t b, size_t c3) { return a > b ? (a > c3 ? a : c3) : (b > c3 ? b : c3); }
 
-size_t he_fc_workspace_bytes(const ckks_ctx* c, const he_fc_desc* d) {
-    if (!c || !d || !c->dnum || !level_ok(c, d->level) || d->level < 3 || d->d_out == 0 || d->d_out > KS_MAX_BATCH || d->batch == 0) return 0;
+// inner sums that share their launches
+static u32 fc_batch(const ckks_ctx* c, const he_fc_desc* d) {
+    const u32 most = ks_batch(c);
+    return d->d_out > CT_BATCH ? (d->d_out < most ? d->d_out : most) : CT_BATCH;
+}
+// nb inner sums, mb rotations of the merge and rb of the layout at a time
+static size_t fc_workspace_in(const ckks_ctx* c, const he_fc_desc* d, u32 nb, u32 mb, u32 rb) {
     const size_t N = c->N;
     const u32 level = d->level, base = fc_base(d), n_lo = base < d->batch ? base : d->batch, n_hi = (d->batch + base - 1) / base;
     const size_t ct0 = 2 * (size_t)(level + 1) * N, ct1 = 2 * (size_t)level * N, ct2 = 2 * (size_t)(level - 1) * N;
-    return blk(CT_BATCH * ct0) + blk(d->d_out * ct1) + blk(CT_BATCH * ct1) + blk(ct2) + ws_ks(c, level - 1, CT_BATCH, CT_BATCH) +
-           max3(ws_merge(c, level - 1, d->d_out), ws_rescale(c, level, CT_BATCH), ws_relayout(c, level - 2, 1, n_lo, n_hi));
+    return blk(CT_BATCH * ct0) + blk(d->d_out * ct1) + blk(nb * ct1) + blk(ct2) + ws_ks(c, level - 1, nb, nb) +
+           max3(ws_merge_in(c, level - 1, d->d_out, merge_batch(d->d_out, mb)), ws_rescale(c, level, CT_BATCH), ws_relayout_in(c, level - 2, 1, n_lo, n_hi, rb));
+}
+size_t he_fc_workspace_bytes(const ckks_ctx* c, const he_fc_desc* d) {
+    if (!c || !d || !c->dnum || !level_ok(c, d->level) || d->level < 3 || d->d_out == 0 || d->d_out > KS_MAX_BATCH || d->batch == 0) return 0;
+    return fc_workspace_in(c, d, fc_batch(c, d), ks_batch(c), ks_batch(c));
 }
 
 int he_fc_batched(const ckks_ctx* c, const he_fc_desc* d, const uint64_t* d_in, const uint64_t* d_w_enc, const ckks_key* const* sum_keys,
@@ -1561,40 +1637,48 @@ int he_fc_batched(const ckks_ctx* c, const he_fc_desc* d, const uint64_t* d_in, 
     }
     const size_t N = c->N;
     const size_t ct0 = 2 * (size_t)(level + 1) * N, ct1 = 2 * (size_t)(l1 + 1) * N, ct2 = 2 * (size_t)(l2 + 1) * N, ct3 = 2 * (size_t)(l3 + 1) * N;
+    if (!d_ws || ws_bytes < fc_workspace_in(c, d, CT_BATCH, CT_BATCH, CT_BATCH))  // what every batch of eight needs
+        return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the layer");
+    // all inner sums together where the workspace is as large as asked for (the merge and the layout look at what is left themselves)
+    const u32 nb = ws_bytes >= fc_workspace_in(c, d, fc_batch(c, d), CT_BATCH, CT_BATCH) ? fc_batch(c, d) : CT_BATCH;
     Arena ar(d_ws, ws_bytes);
     u64* prod = ar.take(CT_BATCH * ct0);        // C_in (.) w_i before its rescale
     u64* S = ar.take(d->d_out * ct1);           // running inner sums, level-1
-    u64* Srot = ar.take(CT_BATCH * ct1);        // their rotations
+    u64* Srot = ar.take(nb * ct1);              // their rotations
     u64* U = ar.take(ct2);                      // merged, level-2
     KsWs ws;
-    bool ok = carve_ks(c, l1, CT_BATCH, CT_BATCH, ar, ws);
-    if (!ok || !ar.ok() ||
-        ar.used + max3(ws_merge(c, l1, d->d_out), ws_rescale(c, level, CT_BATCH), ws_relayout(c, l2, 1, n_lo, n_hi)) > ar.cap)
+    if (!carve_ks(c, l1, nb, nb, ar, ws))
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the layer");
     hipStream_t st = (hipStream_t)stream;
     const u64* in = (const u64*)d_in;
     int rc;
-    // 1. per-output products, rescale, inner sums over d_in slots (all outputs of a batch share each rotation key)
+    // 1. per-output products and their rescale
     for (u32 i0 = 0; i0 < d->d_out; i0 += CT_BATCH) {
         const u32 n = d->d_out - i0 < CT_BATCH ? d->d_out - i0 : CT_BATCH;
-        const u64 *pp[CT_BATCH], *ps[CT_BATCH], *mm[CT_BATCH], *mi[CT_BATCH];
-        u64 *os[CT_BATCH], *orot[CT_BATCH], *mo[CT_BATCH];
+        const u64 *pp[CT_BATCH], *mm[CT_BATCH], *mi[CT_BATCH];
+        u64 *os[CT_BATCH], *mo[CT_BATCH];
         for (u32 b = 0; b < n; b++) {
             mm[b] = (const u64*)d_w_enc + (size_t)(i0 + b) * (level + 1) * N;
             mi[b] = in;
             pp[b] = mo[b] = prod + b * ct0;
-            ps[b] = os[b] = S + (i0 + b) * ct1;
-            orot[b] = Srot + b * ct1;
+            os[b] = S + (i0 + b) * ct1;
         }
         HIP_TRY(launch_mask_mul(c, level, mm, mi, mo, n, st));
         if ((rc = run_rescale(c, level, pp, (size_t)(level + 1) * N, os, n, ar.rest(), st))) return rc;
-        // T <- T + Rot(T, 2^s): the sum rides on the rotation's last kernel, the running sums alternate between two buffers
-        const u64* cur[CT_BATCH];
-        u64* nxt[CT_BATCH];
-        for (u32 b = 0; b < n; b++) cur[b] = ps[b];
+    }
+    // inner sums over d_in slots (all outputs of a batch share each rotation key): T <- T + Rot(T, 2^s), the sum rides on the
+    // rotation's last kernel, the running sums alternate between two buffers
+    for (u32 i0 = 0; i0 < d->d_out; i0 += nb) {
+        const u32 n = d->d_out - i0 < nb ? d->d_out - i0 : nb;
+        const u64* cur[KS_MAX_BATCH];
+        u64 *nxt[KS_MAX_BATCH], *os[KS_MAX_BATCH], *orot[KS_MAX_BATCH];
+        for (u32 b = 0; b < n; b++) {
+            cur[b] = os[b] = S + (i0 + b) * ct1;
+            orot[b] = Srot + b * ct1;
+        }
         for (u32 s = 0; s < n_sum; s++) {
-            const ckks_key* ks[CT_BATCH];
-            u32 gs[CT_BATCH];
+            const ckks_key* ks[KS_MAX_BATCH];
+            u32 gs[KS_MAX_BATCH];
             for (u32 b = 0; b < n; b++) {
                 ks[b] = sum_keys[s];
                 gs[b] = g_sum[s];
@@ -1604,7 +1688,7 @@ int he_fc_batched(const ckks_ctx* c, const he_fc_desc* d, const uint64_t* d_in, 
             for (u32 b = 0; b < n; b++) cur[b] = nxt[b];
         }
         if (n_sum & 1)  // an odd number of steps ends in the second buffer
-            for (u32 b = 0; b < n; b++) HIP_TRY(launch_copy(orot[b], os[b], ct1, st));
+            HIP_TRY(launch_copy(Srot, os[0], n * ct1, st));
     }
     // 2. merge over the outputs: element (j, i) to slot j*d_in + i
     {
@@ -1637,14 +1721,20 @@ int he_poly_act_deg7(const ckks_ctx* c, const uint64_t* const* h_d_x, uint32_t n
     for (u32 i = 0; i < n_ct; i++)
         if (!h_d_x[i] || !h_d_out[i]) return set_err(c, CKKS_ERR_INVALID_ARG, "null ciphertext pointer");
     const size_t N = c->N;
-    const u32 nb_max = n_ct < CT_BATCH ? n_ct : CT_BATCH;
     const u32 l1 = level - 1, l2 = level - 2, l3 = level - 3;
     const size_t xs = (size_t)(level + 1) * N;  // component stride of x
     const size_t x2s = (size_t)(l1 + 1) * N, x3s = (size_t)(l2 + 1) * N, Bs = (size_t)(l3 + 1) * N;
     // Batches of channels are independent: with room for two sets of scratch, every other batch goes to the library's side
     // stream (fork after the caller's earlier work, join before the call returns to the caller's stream).
-    const size_t lane_bytes = ws_poly_act(c, level, nb_max);
-    const u32 n_lanes = (n_ct > CT_BATCH && c->side_stream() && ws_bytes >= 2 * lane_bytes) ? 2 : 1;
+    // (In a small call sixteen go together instead: see act_batch.)
+    u32 most = merged_division ? act_batch(c, level, n_ct) : CT_BATCH;
+    if (most > CT_BATCH && ws_bytes < ws_poly_act(c, level, n_ct < most ? n_ct : most)) most = CT_BATCH;  // in a smaller workspace
+    const u32 nb_max = n_ct < most ? n_ct : most;
+    const bool want_pairs = merged_division && act_pairs(c, level, nb_max);
+    const u32 want_lanes = n_ct > most && most == CT_BATCH && c->side_stream() ? 2 : 1;
+    const bool pairs = want_pairs && ws_bytes >= want_lanes * ws_poly_act_in(c, level, nb_max, true);  // else in what one product at a time needs
+    const size_t lane_bytes = ws_poly_act_in(c, level, nb_max, pairs);
+    const u32 n_lanes = (want_lanes == 2 && ws_bytes >= 2 * lane_bytes) ? 2 : 1;
     if (ws_bytes < lane_bytes || !d_ws) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the activation");
     hipStream_t st0 = (hipStream_t)stream;
     auto residues = [&](int64_t k, u32 lv, u64* out) {
@@ -1670,8 +1760,8 @@ int he_poly_act_deg7(const ckks_ctx* c, const uint64_t* const* h_d_x, uint32_t n
         return rc;
     };
 
-    for (u32 i0 = 0, batch_no = 0; i0 < n_ct; i0 += CT_BATCH, batch_no++) {
-        const u32 n = n_ct - i0 < CT_BATCH ? n_ct - i0 : CT_BATCH;
+    for (u32 i0 = 0, batch_no = 0; i0 < n_ct; i0 += most, batch_no++) {
+        const u32 n = n_ct - i0 < most ? n_ct - i0 : most;
         const u32 lane = n_lanes == 2 ? (batch_no & 1) : 0;
         hipStream_t st = lane ? c->side : st0;
         Arena ar((char*)d_ws + (size_t)lane * lane_bytes, lane_bytes);
@@ -1682,8 +1772,8 @@ int he_poly_act_deg7(const ckks_ctx* c, const uint64_t* const* h_d_x, uint32_t n
         u64* tmp = ar.take(nb_max * 2 * xs);        // un-rescaled products
         if (!ar.ok()) return join(set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the activation"));
         // pointer lists of this batch: inputs, and the per-item slices of the intermediates
-        const u64 *px[CT_BATCH], *px2[CT_BATCH], *px3[CT_BATCH], *px4[CT_BATCH], *pB[CT_BATCH], *ptmp[CT_BATCH];
-        u64 *ox2[CT_BATCH], *ox3[CT_BATCH], *ox4[CT_BATCH], *oB[CT_BATCH], *otmp[CT_BATCH], *oout[CT_BATCH];
+        const u64 *px[KS_MAX_BATCH], *px2[KS_MAX_BATCH], *px3[KS_MAX_BATCH], *px4[KS_MAX_BATCH], *pB[KS_MAX_BATCH], *ptmp[KS_MAX_BATCH];
+        u64 *ox2[KS_MAX_BATCH], *ox3[KS_MAX_BATCH], *ox4[KS_MAX_BATCH], *oB[KS_MAX_BATCH], *otmp[KS_MAX_BATCH], *oout[KS_MAX_BATCH];
         for (u32 b = 0; b < n; b++) {
             px[b] = (const u64*)h_d_x[i0 + b];
             px2[b] = ox2[b] = x2 + b * 2 * x2s;
@@ -1698,12 +1788,27 @@ int he_poly_act_deg7(const ckks_ctx* c, const uint64_t* const* h_d_x, uint32_t n
         int rc;
         if (merged_division) {  // every relinearise-then-rescale pair as one division by P*q_level
             if ((rc = run_ctct_merged(c, level, px, xs, px, xs, nullptr, 0, rlk->d_key, ox2, n, ar.rest(), st))) return join(rc);
-            if ((rc = run_ctct_merged(c, l1, px2, x2s, px, xs, nullptr, 0, rlk->d_key, ox3, n, ar.rest(), st))) return join(rc);
-            if ((rc = run_ctct_merged(c, l1, px2, x2s, px2, x2s, nullptr, 0, rlk->d_key, ox4, n, ar.rest(), st))) return join(rc);
+            if (pairs) {  // the products by x and by x^2 side by side: operands with two component strides
+                const u64 *pa[KS_MAX_BATCH], *pb0[KS_MAX_BATCH], *pb1[KS_MAX_BATCH];
+                u64* po[KS_MAX_BATCH];
+                for (u32 b = 0; b < n; b++) {
+                    pa[b] = pa[n + b] = px2[b];
+                    pb0[b] = px[b], pb1[b] = px[b] + xs, po[b] = ox3[b];
+                    pb0[n + b] = px2[b], pb1[n + b] = px2[b] + x2s, po[n + b] = ox4[b];
+                }
+                KsWs ws;
+                Arena sub = ar.rest();
+                if (!carve_ks(c, l1, 2 * n, 2 * n, sub, ws)) return join(set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the activation"));
+                if ((rc = run_product(c, l1, pa, x2s, pb0, pb1, rlk->d_key, po, 2 * n, ws, st, true))) return join(rc);
+            } else {
+                if ((rc = run_ctct_merged(c, l1, px2, x2s, px, xs, nullptr, 0, rlk->d_key, ox3, n, ar.rest(), st))) return join(rc);
+                if ((rc = run_ctct_merged(c, l1, px2, x2s, px2, x2s, nullptr, 0, rlk->d_key, ox4, n, ar.rest(), st))) return join(rc);
+            }
             residues(h_k[2], l2, ka);
             residues(h_k[3], l2, kb);
             if (ntt_has_modup(c)) {  // B = Rescale(k5 * x + k7 * x3) without storing the linear combination
-                if ((rc = run_rescale_lin(c, l2, px, xs, ka, px3, x3s, kb, oB, n, ar.rest(), st))) return join(rc);
+                for (u32 b0 = 0; b0 < n; b0 += CT_BATCH)
+                    if ((rc = run_rescale_lin(c, l2, px + b0, xs, ka, px3 + b0, x3s, kb, oB + b0, n - b0 < CT_BATCH ? n - b0 : CT_BATCH, ar.rest(), st))) return join(rc);
             } else {
                 tmp_at(x3s);
                 if (hipError_t he_ = (launch_lincomb2(c, l2, ptr_list(px, n), xs, ka, ptr_list(px3, n), x3s, kb, nullptr, 0, tmp, 2 * x3s, n, st)); he_ != hipSuccess) return join(set_hip_err(c, he_));

@@ -313,3 +313,77 @@ def test_rescales_of_the_whole_ring_kernel():
     for lv in (1, 7, level):
         c = np.ascontiguousarray(ct[:, :lv + 1])
         assert np.array_equal(hx.to_host(hx.ckks_rescale(ctx, hx.from_host(c), lv)), orc.rescale(c, lv))
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(12, 6, 2, 3, 5), (12, 7, 1, 7, 6), (13, 24, 8, 3, 22)])
+def test_more_than_eight_items_in_a_call(log_n, num_q, num_p, dnum, level):
+    """Up to sixteen items share every launch: rotations (hoisted in launches of eight taps, unhoisted), activation of eleven and of five (the
+    two middle products of a ciphertext in one batch), merge of eleven blocks, fully connected layer with eleven outputs, and convolutions
+    from and to eleven channels; in the queried workspace and in the one that batches of eight need; seven digits; a ring where
+    activation and convolution alternate between two streams."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(9700 + log_n + dnum)
+    q, n = p.moduli, orc.N
+    pt = lambda lv: rand_poly(rng, q[:lv + 1], n)
+    keys, dkeys = {}, {}
+
+    def key(r):
+        if r % orc.n == 0:
+            return None
+        if r not in keys:
+            keys[r] = np.stack([np.stack([rand_poly(rng, q, n) for _ in range(2)]) for _ in range(dnum)])
+            dkeys[r] = hx.ckks_key_load(ctx, hx.from_host(keys[r]), hx.ckks_galois_element(ctx, r))
+        return dkeys[r]
+
+    same = lambda got, want: bool(np.array_equal(hx.to_host(got), want))
+    cts = [rand_ct(rng, q, level, n) for _ in range(3)]
+    d_cts = [hx.from_host(c) for c in cts]
+    beta = lambda lv: -(-(lv + 1) // -(-num_q // dnum))
+    ks = lambda lv, nd, nv: 8 * n * (nd * (lv + 1) + nd * beta(lv) * (lv + 1 + num_p) + nv * 2 * (2 * lv + 2 + num_p))  # a key switch's scratch
+    offs = [1 + 3 * i for i in range(11)]
+    dk = [key(r) for r in offs]
+    want = orc.rotate_many(cts[0], level, offs, [keys[r] for r in offs], True)
+    full = hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_ROTATE, level, 11)
+    for hoisted in (True, False):
+        for nbytes in (full, hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_ROTATE, level, 8)):
+            outs = hx.ckks_rotate_hoisted(ctx, d_cts[0], level, offs, dk, hoisted, ws=hx.empty(nbytes // 8))
+            assert all(same(o, w) for o, w in zip(outs, want)), f"rotations, hoisted = {hoisted}, {nbytes} bytes"
+    rlk = np.stack([np.stack([rand_poly(rng, q, n) for _ in range(2)]) for _ in range(dnum)])
+    d_rlk, k = hx.ckks_key_load(ctx, hx.from_host(rlk), 0), (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+    want = [orc.poly_activation_merged(c, level, k, rlk) for c in cts[:2]]
+    for n_ct in (11, 5):
+        full = hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_POLY_ACT, level, n_ct)
+        m = min(n_ct, 8)  # a batch without the pairs of products
+        small = 8 * n * 2 * m * (level + 2 * (level - 1) + level - 2 + level + 1) + ks(level, m, m) + 8 * n * 2 * m * (1 + level) + 4096
+        assert small < full
+        for nbytes in (full, small):
+            outs = hx.he_poly_act_deg7(ctx, [d_cts[i % 2] for i in range(n_ct)], level, k, d_rlk, ws=hx.empty(nbytes // 8), merged=True)
+            assert all(same(o, want[i % 2]) for i, o in enumerate(outs)), f"activation of {n_ct}, {nbytes} bytes"
+    if level > 8:
+        return
+    sts, mask = orc.n // 16, pt(level)
+    got = hx.he_accumulator_merge(ctx, [d_cts[i % 3] for i in range(11)], level, sts, hx.from_host(mask), [key(-i * sts) for i in range(11)])
+    assert same(got, orc.accumulator_merge([cts[i % 3] for i in range(11)], level, sts, mask, keys)), "merge"
+    d_in, d_out, batch, base = 16, 11, 6, 3
+    _, lo, hi = orc.fc_shifts(d_in, d_out, batch, base)
+    ops = (np.stack([pt(level) for _ in range(d_out)]), pt(level - 1), np.stack([pt(level - 2) for _ in range(batch)]), pt(level - 3))
+    fc_keys = ([key(1 << s) for s in range(4)], [key(-i) for i in range(d_out)], [key(r) for r in lo], [key(r) for r in hi])
+    want = orc.fc_batched(cts[0], level, d_in, d_out, batch, base, *ops, keys)
+    full = hx.he_fc_workspace_bytes(ctx, d_in, d_out, batch, level, base)
+    for nbytes in (full, full - 8 * n * 3 * 2 * (2 * level + num_p)):  # room for the eight, not for the eleven
+        got = hx.he_fc_batched(ctx, d_cts[0], level, d_in, d_out, batch, base, *[hx.from_host(o) for o in ops], *fc_keys, ws=hx.empty(nbytes // 8))
+        assert same(got, want), f"fully connected layer, {nbytes} bytes"
+    toffs = conv_tap_offsets(4)
+    tkeys = [key(o) for o in toffs]
+    for c_in, c_out in ((11, 2), (2, 11)):
+        w = rng.integers(-2 ** 31, 2 ** 31, size=(c_out, c_in, 9))
+        ins = [cts[i % 3] for i in range(c_in)]
+        for al in (hx.HE_CONV_ALIGN_DIRECT, hx.HE_CONV_DEFERRED_MODDOWN, hx.HE_CONV_DEFERRED_MERGED):
+            ext = al != hx.HE_CONV_ALIGN_DIRECT
+            idx = orc.ext_moduli_idx(level) if ext else list(range(level + 1))
+            masks = np.stack([rand_poly(rng, [q[t] for t in idx], n) for _ in range(9)])
+            w_res = np.array([[[[int(w[o, i, t]) % q[m] for m in idx] for t in range(9)] for i in range(c_in)] for o in range(c_out)], dtype=np.uint64)
+            want = orc.he_conv_deferred(ins, level, 4, keys, masks, w, merged=al == hx.HE_CONV_DEFERRED_MERGED) if ext else orc.he_conv(ins, level, 4, keys, masks, w)
+            outs = hx.he_conv_batched(ctx, 4, 4, 2, level, [d_cts[i % 3] for i in range(c_in)], tkeys, hx.from_host(masks), hx.from_host(w_res), c_out, alignment=al)
+            assert all(same(o, want[i]) for i, o in enumerate(outs)), f"convolution {c_in} -> {c_out}, schedule {al}"
