@@ -18,7 +18,7 @@
 //
 // Two butterfly arithmetics, chosen per context (both give the same canonical residues):
 //   ArithU64  any modulus below 2^58: 64-bit Shoup multiplication (twiddle + precomputed quotient), lazy
-//             values (forward: no correction at all, below 35q < 2^64; inverse: kept in [0, 2q)).
+//             values (forward: below 60q < 2^64; inverse: kept in [0, 4q)).
 //   ArithF64  every modulus below 2^50: residues are integers held in doubles and the twiddle product is
 //             reduced with fused multiply-adds: for |y| < 2^51, h = y*w rounded, l = fma(y, w, -h) its
 //             exact error, c = the integer nearest to y*(w/q) (one fma against 1.5*2^52), and
@@ -37,6 +37,7 @@
 #include "ctx.h"
 #include "f64mod.h"
 #include "galois.h"
+#include "shoup.h"
 
 #define NTT_THREADS 256
 #define NTT_TILE 2048
@@ -50,9 +51,10 @@
 #define LDS_PADDED_WORDS NTT_TILE
 
 // ---- 64-bit integer arithmetic --------------------------------------------------------------------------
-// Forward butterfly with no correction at all: the Shoup product t is in [0, 2q) for ANY 64-bit y, so
-// both outputs stay non-negative and grow by at most 2q per stage: below (1 + 2*17) q < 2^64 for every
-// supported modulus (q < 2^58) over a whole transform.  One word reduction at the very end.
+// Forward butterfly without a correction: the lazy Shoup product t (shoup.h) is in [0, 4q) for ANY 64-bit y, so
+// both outputs stay non-negative and grow by at most 4q per stage: below 49q over the twelve stages of a whole ring in one
+// kernel, below 25q over the up to six of a first pass, whose results are brought below 16q before the eleven that follow: 60q < 2^64 for
+// every supported modulus (q < 2^58).  One word reduction at the very end.  The inverse keeps values in [0, 4q).
 struct ArithU64 {
     typedef u64 E;
     typedef TwPair TW;
@@ -63,18 +65,20 @@ struct ArithU64 {
     static __device__ __forceinline__ u64 store_fwd_final(E v, const MC& m) { return reduce_word(v, m); }
     static __device__ __forceinline__ u64 store_inv_final(E v, const MC& m) { return mul_shoup(v, m.n_inv, m.n_inv_sh, m.q); }
     static __device__ __forceinline__ void fwd_bf(E& x, E& y, const TW w, const MC& m) {
-        const u64 t = mul_shoup_lazy(y, w.w, w.s, m.q);
-        y = x + 2 * m.q - t;
+        const u64 t = mul_shoup_lazy4(y, w.w, w.s, 0 - m.q);
+        y = x + 4 * m.q - t;
         x = x + t;
     }
     static __device__ __forceinline__ void inv_bf(E& x, E& y, const TW w, const MC& m) {
-        const u64 two_q = 2 * m.q;
+        const u64 four_q = 4 * m.q;
         u64 s = x + y;
-        if (s >= two_q) s -= two_q;
-        const u64 d = x + two_q - y;
+        if (s >= four_q) s -= four_q;
+        const u64 d = x + four_q - y;
         x = s;
-        y = mul_shoup_lazy(d, w.w, w.s, m.q);
+        y = mul_shoup_lazy4(d, w.w, w.s, 0 - m.q);
     }
+    // between the passes of a forward transform: below 25q after up to six stages, 16q here, 60q after eleven more
+    static __device__ __forceinline__ E load_second(u64 raw, const MC& m) { return raw >= 16 * m.q ? raw - 16 * m.q : raw; }
     static __device__ __forceinline__ void fwd_begin(E*, const MC&) {}
     static __device__ __forceinline__ void fwd_end(E*, const MC&) {}
     template <int KC>
@@ -101,6 +105,7 @@ struct ArithF64 {
     static __device__ __forceinline__ u64 canonical(double v, const MC& m) { return f64m_canonical(v, m.q); }  // |v| <= q/2 + 1 -> [0, q)
     static __device__ __forceinline__ E load_first(u64 raw, const MC&, bool) { return from_u64(raw); }  // canonical: in [0, q)
     static __device__ __forceinline__ E load_mid(u64 raw) { return __longlong_as_double((long long)raw); }
+    static __device__ __forceinline__ E load_second(u64 raw, const MC&) { return load_mid(raw); }
     static __device__ __forceinline__ u64 store_mid(E v) { return (u64)__double_as_longlong(v); }
     static __device__ __forceinline__ u64 store_fwd_final(E v, const MC& m) { return canonical(v, m); }  // after fwd_end
     static __device__ __forceinline__ u64 store_inv_final(E v, const MC& m) { return canonical(mulmod(v, m.ninv, m.ninv_q, m.q), m); }
@@ -508,7 +513,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_loop_kernel(NttArgs ar
             for (int j = 0; j < 8; j++) v[j] = A::load_first(raw[j], P.mc, false);
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = A::load_mid(raw[j]);
+            for (int j = 0; j < 8; j++) v[j] = A::load_second(raw[j], P.mc);
         }
         if (b + b_step < n_items) {  // the next item's points, a tile ahead
             const u64* src = item_src<A>(args, pl, row_of(b + b_step), tile.a) + off;
@@ -574,7 +579,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_div_kernel(NttArgs arg
 #pragma unroll
     for (int j = 0; j < 8; j++) raw[j] = P.src[off + tid + 256 * j];
 #pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = A::load_mid(raw[j]);
+    for (int j = 0; j < 8; j++) v[j] = A::load_second(raw[j], P.mc);
     A::fwd_begin(v, P.mc);
     fwd_rows_pre<AR, 3>(v, wa, P.mc);
     load_lo_tw<A, 3>(P, 64 * TA + 8 * d3 + d2, wc);
