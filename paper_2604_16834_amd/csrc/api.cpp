@@ -460,7 +460,8 @@ size_t ws_conv_lane(const ckks_ctx* c, u32 level, u32 kb) {
     return ws_ks(c, level, kb, kb) + blk((size_t)kb * 2 * (level + 1) * c->N) + ws_rescale(c, level, CT_BATCH);
 }
 bool conv_together(const ckks_ctx* c, const he_conv_desc* d) {
-    return together(c, d->level, d->c_in > CT_BATCH ? (size_t)1 << 17 : (d->alignment == HE_CONV_DEFERRED_MERGED ? (size_t)1 << 19 : (size_t)1 << 18));
+    const bool batches = d->c_in > CT_BATCH || d->c_out > KS_MAX_BATCH;  // of channels, or of divisions: 2 -> 17 channels at 2^14, 14 + 6 limbs 280 / 283
+    return together(c, d->level, batches ? (size_t)1 << 17 : (d->alignment == HE_CONV_DEFERRED_MERGED ? (size_t)1 << 19 : (size_t)1 << 18));
 }
 // channels of a batch, and whether two batches are in flight when there is more than one
 u32 conv_batch(const ckks_ctx* c, const he_conv_desc* d) { return conv_together(c, d) && (d->c_in > CT_BATCH || d->c_out > CT_BATCH) ? KS_MAX_BATCH : CT_BATCH; }

@@ -52,7 +52,8 @@ struct ProfState {
 };
 
 // Batched kernels take up to KS_MAX_BATCH items; item b's operand starts at p[b].
-#define KS_MAX_BATCH 16   // pointer-list capacity; ciphertext batches are at most CT_BATCH = 8 (two components each)
+#define KS_MAX_BATCH 16   // pointer-list capacity: key switches, products and divisions of a batch; CT_BATCH = 8: ciphertexts of a batch whose two
+                          // components are listed one by one (rescales), whose digits a thread holds (taps), or without the fused inner product
 #define CT_BATCH 8
 struct PtrList8 {
     const u64* p[KS_MAX_BATCH];
