@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "ctx.h"
+#include "convrule.h"
 #include "f64mod.h"
 #include "galois.h"
 #include "shoup.h"
@@ -1276,7 +1277,7 @@ __device__ __forceinline__ ConstPtr<V> const_ptr(const V* p) { return (ConstPtr<
 template <int LOG_HI, int AP, int ND, bool MID>
 __global__ __launch_bounds__(HC_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ntt_fwd_hi_conv_lds_kernel(NttArgs args, PolyList pl, ConvPrologue cp,
                                                                                                                    MidPrologue mp) {
-    static_assert(!MID || ND <= 9, "");
+    static_assert(!MID || ND <= CONV_MID_TERMS, "");
     typedef ArithF64 A;
     constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R, PTS = NTT_TILE / HC_THREADS, PP = ND <= 9 ? PTS : 2;
     constexpr int R8 = R / 8, S2 = LOG_HI - 3, KC2 = 8 / R8;
@@ -1927,7 +1928,7 @@ template <int LOG_HI, int AP, int ND>
 static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue* mp) {
     cp.groups = (n_targets + HC_T - 1) / HC_T;
     const dim3 grid(1u << LOG_HI, cp.groups * batch, digits), block(HC_THREADS);
-    if constexpr (ND <= 9) {
+    if constexpr (ND <= CONV_MID_TERMS) {
         if (mp) {
             hipLaunchKernelGGL((ntt_fwd_hi_conv_lds_kernel<LOG_HI, AP, ND, true>), grid, block, 0, st, args, pl, cp, *mp);
             return;
@@ -1937,78 +1938,30 @@ static void launch_hi_conv_lds(u32 n_targets, u32 digits, u32 batch, hipStream_t
 }
 // n_targets: the most targets a digit of the launch has
 template <int LOG_HI>
-static void launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue* mp) {
-#define HI_CONV(HOW, AP, ND) launch_hi_conv_##HOW<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp, mp)
-    if (cp.ap == 4 && cp.nd == 1) {  // the rescale: one dropped limb
-        HI_CONV(regs, 4, 1);
-        return;
+static hipError_t launch_hi_conv_ap(u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue* mp) {
+    if (mp && !conv_has_mid(LOG_HI, cp.ap, cp.nd)) return hipErrorInvalidValue;
+    const u32 terms = hi_conv_terms(LOG_HI, cp.ap, cp.nd);
+#define HI_CONV(AP, ND)                                                                                                              \
+    if constexpr (hi_conv_terms(LOG_HI, AP, ND) == ND) {                                                                             \
+        if (cp.ap == AP && terms == ND) {                                                                                            \
+            if constexpr (LOG_HI < 4 || (AP == 4 && ND == 1)) launch_hi_conv_regs<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp, mp); \
+            else launch_hi_conv_lds<LOG_HI, AP, ND>(n_targets, digits, batch, st, args, pl, cp, mp);                                 \
+            return hipSuccess;                                                                                                       \
+        }                                                                                                                            \
     }
-    if constexpr (LOG_HI >= 4) {
-        // as many terms as the launch has source limbs: the rest of a row is padding (digits of 7, 7 and 4 or 5
-        // limbs in rows of eight: 41.0 us a launch with eight terms everywhere, 38.0 with their own).  Whole calls with two equal
-        // digits at N = 2^16 take this much longer with full rows (product / activation of eight / eight rotations low in the
-        // chain): digits of 2 limbs 1.02 / - / 1.04, of 3 1.02 / 1.00 / 1.02, of 5 1.03 / 1.02 / 1.03, of 6 1.04 / 1.00 / 1.03, of 7
-        // 1.03 / 1.00 / 1.01, of 9 1.06 / 1.04 / 1.06, of 10 1.02 / 1.02 / 1.06, of 11 1.02 / 1.02 / 1.03, of 12 1.03 / 1.02 / 1.04
-        if (cp.ap == 4) {
-            if (cp.nd == 2) HI_CONV(lds, 4, 2);
-            else if (cp.nd == 3) HI_CONV(lds, 4, 3);
-            else HI_CONV(lds, 4, 4);
-        } else if (cp.ap == 8) {
-            if (cp.nd <= 4) HI_CONV(lds, 8, 4);
-            else if (cp.nd == 5) HI_CONV(lds, 8, 5);
-            else if (cp.nd == 6) HI_CONV(lds, 8, 6);
-            else if (cp.nd == 7) HI_CONV(lds, 8, 7);
-            else HI_CONV(lds, 8, 8);
-        } else if (cp.ap == 12) {  // nine: eight special primes and the dropped limb
-            if (cp.nd == 9) HI_CONV(lds, 12, 9);
-            else if (cp.nd == 10) HI_CONV(lds, 12, 10);
-            else HI_CONV(lds, 12, 12);
-        } else {
-            if (cp.nd <= 8) HI_CONV(lds, 16, 8);
-            else if (cp.nd <= 10) HI_CONV(lds, 16, 10);
-            else if (cp.nd <= 12) HI_CONV(lds, 16, 12);
-            else HI_CONV(lds, 16, 16);
-        }
-    } else {
-        if (cp.ap == 4) HI_CONV(regs, 4, 4);
-        else if (cp.ap == 8) HI_CONV(regs, 8, 8);
-        else if (cp.ap == 12 && cp.nd == 9) HI_CONV(regs, 12, 9);
-        else if (cp.ap == 12) HI_CONV(regs, 12, 12);
-        else HI_CONV(regs, 16, 16);
-    }
+    HI_CONV(4, 1) HI_CONV(4, 2) HI_CONV(4, 3) HI_CONV(4, 4)
+    HI_CONV(8, 4) HI_CONV(8, 5) HI_CONV(8, 6) HI_CONV(8, 7) HI_CONV(8, 8)
+    HI_CONV(12, 9) HI_CONV(12, 10) HI_CONV(12, 12)
+    HI_CONV(16, 8) HI_CONV(16, 10) HI_CONV(16, 12) HI_CONV(16, 16)
 #undef HI_CONV
+    return hipErrorInvalidValue;
 }
-// Whether the inverse transform's second pass goes inside the converting first pass, for a launch of `rows` (polynomial, digit) rows of nd
-// source limbs (rows of ap constants) and up to n_targets targets each: 0, or the targets per workgroup.  It saves a launch with its
-// round trip through memory and repeats the inverse stages per group of targets.  Measured in whole calls, one by one / together in us:
-//   rescale: at every size (N = 2^13, 4 limbs 18.5 / 14.5, 2^16, 13 limbs 27.9 / 24.2; eight ciphertexts of 24 limbs the same)
-//   rings up to 2^14 (ntt_mid_conv_kernel) while a thread's points of all source limbs are at most 40: one rotation at N = 2^13 of 4 + 2
-//     limbs 45.6 / 33.0, of 21 + 8 50.1 / 48.9, eight 112 / 107; at 2^14 of 7 + 3 45.8 / 41.1, but of 13 + 7 (56 points) 46.1 / 49.6, of
-//     21 + 8 (64) 59.9 / 66.6
-//   larger rings, up to four source limbs: up to 1200 workgroups or two groups of targets (2^15, 13 + 4 limbs, one rotation 67.3 / 62.0, eight
-//     276 / 275; activation of eight at 2^16 1628 / 1624, with no such line 1659); five and six: up to 300 or two groups (9 + 6 limbs
-//     60.6 / 58.1, two 69.2 / 66.9, four 95.5 / 95.1, with no line 99.1); more: a single group (nothing repeated: 2^16, 3 + 8 limbs, eight
-//     rotations 160 / 141), or two of four rows and more (7 + 8 limbs: one rotation 60.4 / 61.5, eight 233 / 222; with 13 + 8, four groups,
-//     eight 428 / 450)
-static u32 mid_conv_per(const ckks_ctx* c, u32 nd, u32 ap, u32 n_targets, u32 rows) {
-    if (!ntt_has_modup(c)) return 0;
-    if (c->log_hi > 3) {
-        const u32 groups = (n_targets + HC_T - 1) / HC_T, wgs = groups * rows << c->log_hi;
-        bool together;
-        if (nd == 1) together = true;
-        else if (nd <= 4) together = groups <= 2 || wgs <= 1200;
-        else if (nd <= 6) together = groups <= 2 || wgs <= 300;
-        else together = (nd <= 8 || (nd == 9 && ap == 12)) && (groups == 1 || (groups == 2 && rows >= 4));  // (ntt_fwd_hi_conv_lds_kernel: up to nine)
-        return together ? HC_T : 0;
-    }
-    if (nd > 1 && (nd << c->log_hi) > 40) return 0;
-    u32 per = 4;  // fewer, and more workgroups, until every CU has one
-    while (per > 1 && (1u << CKKS_TILE_LOG) / NTT_THREADS * rows * ((n_targets + per - 1) / per) < 256) per >>= 1;
-    return per;
+static u32 mid_conv_per_of(const ckks_ctx* c, u32 nd, u32 ap, u32 n_targets, u32 rows) {
+    return ntt_has_modup(c) ? mid_conv_per(c->log_hi, nd, ap, n_targets, rows) : 0;
 }
 u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n) {
     const u32 nd = c->alpha < level + 1 ? c->alpha : level + 1;
-    return mid_conv_per(c, nd, c->alpha_pad, c->ext_limbs(level) - nd, n * c->live_digits(level));
+    return mid_conv_per_of(c, nd, c->alpha_pad, c->ext_limbs(level) - nd, n * c->live_digits(level));
 }
 // Rings of 2^12 points: a division that starts from whole sums (lo_done: they have been through the inverse transform's first pass) takes
 // the whole-ring kernels where they give between half of the CUs and every CU a limb-poly of the result.  Hoisted rotations, pass by pass / whole ring
@@ -2017,54 +1970,49 @@ u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n) {
 u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys, bool lo_done) {
     const u32 n_out = merged ? level : level + 1;
     if (ntt_one_pass(c) && !lo_done && n_out * polys > 112 && n_out * polys <= 256) return 0;
-    return mid_conv_per(c, c->num_p + (merged ? 1 : 0), merged ? c->k2_pad : c->k_pad, n_out, polys);
+    return mid_conv_per_of(c, c->num_p + (merged ? 1 : 0), merged ? c->k2_pad : c->k_pad, n_out, polys);
 }
-u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys) { return mid_conv_per(c, 1, 4, level, polys); }
+u32 ntt_mid_rescale(const ckks_ctx* c, u32 level, u32 polys) { return mid_conv_per_of(c, 1, 4, level, polys); }
 // The rescale of a ring of 2^12 points in one launch, the dropped limb's inverse transform repeated by every target's workgroup, while every
 // limb-poly of the result has a CU of its own: one ciphertext of 4 limbs 14.2 us in two launches (or three: pass by pass), 10.5 in one
 bool ntt_rescale_one_launch(const ckks_ctx* c, u32 level, u32 polys) { return ntt_has_modup(c) && ntt_one_pass(c) && level * polys <= 256; }
 
 template <int LOG_HI>
-static void launch_mid_conv_hi(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue& mp) {
-#define MID_CONV(ND) hipLaunchKernelGGL((ntt_mid_conv_kernel<LOG_HI, ND>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp, mp)
-    if (cp.nd == 1) MID_CONV(1);
-    else if (cp.nd == 2) MID_CONV(2);
-    else if (cp.nd == 3) MID_CONV(3);
-    else if (cp.nd == 4) MID_CONV(4);
-    else if (cp.nd == 5) MID_CONV(5);
-    else if constexpr (LOG_HI < 3) {
-        if (cp.nd == 6) MID_CONV(6);
-        else if (cp.nd == 7) MID_CONV(7);
-        else if (cp.nd == 8) MID_CONV(8);
-        else if (cp.nd == 9) MID_CONV(9);
-        else if (cp.nd == 10) MID_CONV(10);
-        else if constexpr (LOG_HI < 2) {
-            if (cp.nd <= 12) MID_CONV(12);
-            else MID_CONV(16);
-        }
+static hipError_t launch_mid_conv_hi(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp, const MidPrologue& mp) {
+    const u32 terms = mid_conv_terms(LOG_HI, cp.nd);
+#define MID_CONV(ND)                                                                                                                 \
+    if constexpr (mid_conv_terms(LOG_HI, ND) == ND) {                                                                                \
+        if (terms == ND) {                                                                                                           \
+            hipLaunchKernelGGL((ntt_mid_conv_kernel<LOG_HI, ND>), grid, dim3(NTT_THREADS), 0, st, args, pl, cp, mp);                 \
+            return hipSuccess;                                                                                                       \
+        }                                                                                                                            \
     }
+    MID_CONV(1) MID_CONV(2) MID_CONV(3) MID_CONV(4) MID_CONV(5) MID_CONV(6) MID_CONV(7) MID_CONV(8) MID_CONV(9) MID_CONV(10) MID_CONV(12) MID_CONV(16)
 #undef MID_CONV
+    return hipErrorInvalidValue;
 }
-static void launch_mid_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue& mp) {
+static hipError_t launch_mid_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, ConvPrologue cp, const MidPrologue& mp) {
     cp.groups = (n_targets + cp.per - 1) / cp.per;
     const dim3 grid((1u << CKKS_TILE_LOG) / NTT_THREADS, cp.groups * batch, digits);
-    if (log_hi == 1) launch_mid_conv_hi<1>(grid, st, args, pl, cp, mp);
-    else if (log_hi == 2) launch_mid_conv_hi<2>(grid, st, args, pl, cp, mp);
-    else launch_mid_conv_hi<3>(grid, st, args, pl, cp, mp);
+    switch (log_hi) {
+        case 1: return launch_mid_conv_hi<1>(grid, st, args, pl, cp, mp);
+        case 2: return launch_mid_conv_hi<2>(grid, st, args, pl, cp, mp);
+        case 3: return launch_mid_conv_hi<3>(grid, st, args, pl, cp, mp);
+        default: return hipErrorInvalidValue;
+    }
 }
 
-static void launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp,
-                           const MidPrologue* mp) {
-    if (mp && log_hi <= 3) {
-        launch_mid_conv(log_hi, n_targets, digits, batch, st, args, pl, cp, *mp);
-        return;
-    }
+static hipError_t launch_hi_conv(u32 log_hi, u32 n_targets, u32 digits, u32 batch, hipStream_t st, const NttArgs& args, const PolyList& pl, const ConvPrologue& cp,
+                                 const MidPrologue* mp) {
+    if (mp && !cp.per) return hipErrorInvalidValue;
+    if (mp && log_hi <= 3) return launch_mid_conv(log_hi, n_targets, digits, batch, st, args, pl, cp, *mp);
     switch (log_hi) {
-        case 2: launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp, mp); break;
-        case 3: launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp, mp); break;
-        case 4: launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp, mp); break;
-        case 5: launch_hi_conv_ap<5>(n_targets, digits, batch, st, args, pl, cp, mp); break;
-        default: launch_hi_conv_ap<6>(n_targets, digits, batch, st, args, pl, cp, mp); break;
+        case 2: return launch_hi_conv_ap<2>(n_targets, digits, batch, st, args, pl, cp, mp);
+        case 3: return launch_hi_conv_ap<3>(n_targets, digits, batch, st, args, pl, cp, mp);
+        case 4: return launch_hi_conv_ap<4>(n_targets, digits, batch, st, args, pl, cp, mp);
+        case 5: return launch_hi_conv_ap<5>(n_targets, digits, batch, st, args, pl, cp, mp);
+        case 6: return launch_hi_conv_ap<6>(n_targets, digits, batch, st, args, pl, cp, mp);
+        default: return hipErrorInvalidValue;  // a ring of 2^12 points has no converting pass of its own
     }
 }
 
@@ -2207,7 +2155,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             args.last = 0;
             if (conv) {  // reads the digit's nd limbs for every target limb (from cache after the first), writes the target limbs
                 ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * batch * ((double)conv->nd + pl.n), hi_ops);
-                launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv, mid);
+                if (hipError_t e = launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv, mid); e != hipSuccess) return e;
             } else {
                 ProfScope ps__(c, K_NTT_FWD_HI, st, pass_bytes, hi_ops);
                 hi(args, pl);
@@ -2305,7 +2253,7 @@ hipError_t launch_ntt_modup(const ckks_ctx* c, u32 level, const double* y, size_
         args.beta = 0;
         {
             ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * (n * (together ? (double)L1 : (double)(E - most)) + rows), 0.5 * rows * c->N * c->log_hi);
-            launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp, mid_per ? &mp : nullptr);
+            if (hipError_t e = launch_hi_conv(c->log_hi, most, nj, n, st, args, all, cp, mid_per ? &mp : nullptr); e != hipSuccess) return e;
         }
         if (hi_only) continue;  // the caller's own lo pass follows (launch_ntt_lo_mac)
         PolyList pl = all;
