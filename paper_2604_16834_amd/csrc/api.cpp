@@ -112,15 +112,14 @@ bool carve_ks(const ckks_ctx* c, u32 level, u32 n_dig, u32 n_v, Arena& ar, KsWs&
 u32 ks_batch(const ckks_ctx* c) { return ntt_has_modup(c) ? KS_MAX_BATCH : CT_BATCH; }
 // Calls with more than eight independent items: together on the caller's stream while a polynomial of the extended basis has no more
 // coefficients than `limit`, in batches of eight that alternate between two streams above.  A fork and a join are worth 45 us; from some size on
-// the kernels of one batch beside another's are worth more, the sooner the more kinds of kernels there are.  Two streams / together, us:
-//   twelve hoisted rotations: N = 2^12, 4 + 2 limbs 99 / 47, 2^13, 14 + 6 107 / 80, 2^14, 14 + 6 (0.33 M coefficients) 152.5 / 152.0, 2^15, 13 + 8
-//     (0.69 M) 247 / 249
-//   activation of sixteen: 2^12, 7 + 3 limbs 268 / 202, 2^14, 7 + 3 (0.16 M) 432 / 402, 2^13, 24 + 8 (0.26 M) 810 / 827, 2^14, 14 + 6 (0.33 M) 884 / 948
-//   merged convolution from sixteen channels: 2^12, 7 + 3 limbs 175 / 158, 24 + 8 (0.13 M) 392 / 369, 2^14, 7 + 3 (0.16 M) 461 / 467; from three to
-//     twelve (only the divisions come in two batches): 2^12, 7 + 3 95 / 59, 2^14, 14 + 6 (0.33 M) 261 / 253, 24 + 8 (0.52 M) 400 / 391; with a rescale
-//     of its own, 2^13, 24 + 8 (0.26 M) 266 / 259, 2^14, 14 + 6 310 / 317
+// the kernels of one batch beside another's are worth more, and the sooner where sixteen are not all of them: several batches on one
+// stream come one after the other.
 bool together(const ckks_ctx* c, u32 level, size_t limit) { return ntt_has_modup(c) && (size_t)c->ext_limbs(level) * c->N <= limit; }
-constexpr size_t TOGETHER_ROTATIONS = (size_t)1 << 19, TOGETHER_ACTIVATION = (size_t)3 << 16;
+// Hoisted rotations, two streams / together in us, 12 / 16: N = 2^12, 7 + 3 limbs 101 / 46, 105 / 47, 24 + 8 (0.13 M coefficients) 99 / 79, 106 / 90,
+// 2^14, 14 + 6 (0.33 M) 158 / 157, 189 / 190, 2^15, 7 + 3 (0.33 M) 156 / 152, 191 / 185, 2^14, 24 + 8 (0.52 M) 221 / 227, 275 / 277;
+// 17 / 24 / 64: 2^12, 7 + 3 (0.04 M) 115 / 66, 124 / 74, 238 / 157, 24 + 8 (0.13 M) 122 / 113, 135 / 132, 276 / 303, 2^13, 14 + 6 (0.16 M) 133 / 128, 147 / 151,
+// 321 / 348, 2^14, 14 + 6 211 / 220, 275 / 283, 631 / 678
+bool rotations_together(const ckks_ctx* c, u32 level, u32 n) { return together(c, level, n <= KS_MAX_BATCH ? (size_t)3 << 17 : (size_t)1 << 17); }
 size_t ws_rescale(const ckks_ctx* c, u32 level, u32 n) { return blk(2 * (size_t)n * c->N) + blk(2 * (size_t)n * level * c->N); }
 // a product's scratch: the key switch's, and the three polynomials of the tensor product where a kernel forms them (elsewhere they
 // are not stored: run_product)
@@ -441,15 +440,20 @@ int run_ctct_merged(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_
 }
 
 // whether x^3 = x^2 x and x^4 = x^2 x^2 of n ciphertexts go through the kernels as one batch of products (merged divisions)
-bool act_pairs(const ckks_ctx* c, u32 level, u32 n) { return ntt_has_modup(c) && 2 * n <= ks_batch(c); }
+bool act_pairs(const ckks_ctx* c, u32 n) { return ntt_has_modup(c) && 2 * n <= ks_batch(c); }
 size_t ws_poly_act_in(const ckks_ctx* c, u32 level, u32 n, bool pairs) {
     const size_t N = c->N, one = ws_ctct(c, level, n) + ws_rescale(c, level, n), two = pairs ? ws_ctct(c, level - 1, 2 * n) : 0;
     return blk(2 * (size_t)n * level * N) + 2 * blk(2 * (size_t)n * (level - 1) * N) + blk(2 * (size_t)n * (level - 2) * N) +
            blk(2 * (size_t)n * (level + 1) * N) + (one > two ? one : two);
 }
-size_t ws_poly_act(const ckks_ctx* c, u32 level, u32 n) { return ws_poly_act_in(c, level, n, act_pairs(c, level, n)); }
-// ciphertexts of a batch of the activation with merged divisions, of n_ct in all
-u32 act_batch(const ckks_ctx* c, u32 level, u32 n_ct) { return n_ct > CT_BATCH && together(c, level, TOGETHER_ACTIVATION) ? KS_MAX_BATCH : CT_BATCH; }
+size_t ws_poly_act(const ckks_ctx* c, u32 level, u32 n) { return ws_poly_act_in(c, level, n, act_pairs(c, n)); }
+// ciphertexts of a batch of the activation with merged divisions, of n_ct in all: sixteen together leave no room for the pairs of products.  Two
+// streams with pairs / together in us, 9 / 12 / 16: N = 2^12, 5 + 2 limbs (0.03 M coefficients) 211 / 161, 216 / 165, 226 / 174, 7 + 3 204 / 181, 211 / 187,
+// 219 / 197, 10 + 4 (0.06 M) 206 / 205, 219 / 225, 226 / 243, 2^13, 5 + 2 (0.06 M) 209 / 181, 216 / 187, 220 / 212, 2^12, 14 + 6 (0.08 M) 206 / 242, 225 / 265, 268 / 327,
+// 2^14, 7 + 3 (0.16 M) 264 / 312, 290 / 353, 348 / 415; in two batches, 24: 2^12, 5 + 2 269 / 321, 7 + 3 307 / 362, 2^14, 7 + 3 587 / 694
+u32 act_batch(const ckks_ctx* c, u32 level, u32 n_ct) {
+    return n_ct > CT_BATCH && n_ct <= KS_MAX_BATCH && together(c, level, (size_t)1 << 16) ? KS_MAX_BATCH : CT_BATCH;
+}
 
 // The convolution with one division by P per output channel: every aligned copy stays on the extended
 // basis Q_level P (inner product + P * sigma_g(c0), times the tap's mask), the sum over (input channel,
@@ -459,9 +463,13 @@ u32 act_batch(const ckks_ctx* c, u32 level, u32 n_ct) { return n_ct > CT_BATCH &
 size_t ws_conv_lane(const ckks_ctx* c, u32 level, u32 kb) {
     return ws_ks(c, level, kb, kb) + blk((size_t)kb * 2 * (level + 1) * c->N) + ws_rescale(c, level, CT_BATCH);
 }
+// Two streams / together in us, merged: 9 -> 4 channels at N = 2^12, 4 + 2 limbs (0.02 M coefficients) 94 / 63, 24 + 8 (0.13 M) 183 / 169, 16 -> 16 162 / 108,
+// 372 / 359, 16 -> 32 with 7 + 3 limbs 232 / 210, 24 + 8 461 / 455; more than sixteen inputs: 4 + 2 limbs 17 -> 4 116 / 107, 24 -> 8 137 / 144, 64 -> 64 411 / 399,
+// 7 + 3 (0.04 M) 162 / 171, 217 / 227, 565 / 586, 24 + 8 296 / 314, 429 / 443, 1182 / 1239; only the divisions in two batches, 3 -> 12: 7 + 3 97 / 55, 2^14, 14 + 6
+// (0.33 M) 259 / 248, 24 + 8 (0.52 M) 388 / 382, but with a rescale of its own 2^12, 24 + 8 158 / 158, 2^13, 14 + 6 (0.16 M) 177 / 185, 24 + 8 255 / 261
 bool conv_together(const ckks_ctx* c, const he_conv_desc* d) {
-    const bool batches = d->c_in > CT_BATCH || d->c_out > KS_MAX_BATCH;  // of channels, or of divisions: 2 -> 17 channels at 2^14, 14 + 6 limbs 280 / 283
-    return together(c, d->level, batches ? (size_t)1 << 17 : (d->alignment == HE_CONV_DEFERRED_MERGED ? (size_t)1 << 19 : (size_t)1 << 18));
+    const bool one_division = d->c_in <= CT_BATCH && d->c_out <= KS_MAX_BATCH && d->alignment == HE_CONV_DEFERRED_MERGED;
+    return together(c, d->level, d->c_in > KS_MAX_BATCH ? (size_t)1 << 15 : (one_division ? (size_t)1 << 19 : (size_t)1 << 17));
 }
 // channels of a batch, and whether two batches are in flight when there is more than one
 u32 conv_batch(const ckks_ctx* c, const he_conv_desc* d) { return conv_together(c, d) && (d->c_in > CT_BATCH || d->c_out > CT_BATCH) ? KS_MAX_BATCH : CT_BATCH; }
@@ -1126,10 +1134,11 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
         if (!keys || !keys[t]) return set_err(c, CKKS_ERR_NO_KEY, "rotation key missing");
         if (keys[t]->galois_elt != g) return set_err(c, CKKS_ERR_NO_KEY, "rotation key was made for another offset");
     }
-    // rotations go through the kernels in batches of up to CT_BATCH (unhoisted: ks_batch): hoisted ones share the digits and batch their ModDown;
-    // unhoisted ones each have their own permuted polynomial and digits and batch everything but the inner product (one key
-    // each), in batches as large as the workspace holds (one at a time in the smallest workspace that is accepted)
-    const u32 most = hoisted && !together(c, level, TOGETHER_ROTATIONS) ? CT_BATCH : ks_batch(c);
+    // rotations go through the kernels in batches of up to ks_batch (hoisted: see rotations_together): hoisted ones share the digits and batch their
+    // ModDown; unhoisted ones each have their own digits, of the permuted polynomial, and share every launch, in batches as large as the
+    // workspace holds (one at a time in the smallest workspace that is accepted)
+    const bool one_stream = rotations_together(c, level, n_keyed);
+    const u32 most = hoisted && !one_stream ? CT_BATCH : ks_batch(c);
     u32 rb = n_keyed < most ? (n_keyed ? n_keyed : 1) : most;
     Arena ar(d_ws, ws_bytes);
     KsWs ws = {};
@@ -1155,7 +1164,7 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     // other batch runs on the context's second stream (its traffic-bound inner products next to the other batch's ModDown).
     KsWs lane_ws[2] = {ws, ws};
     bool two_lanes = false;
-    if (hoisted && n_keyed > rb && c->side_stream() && !together(c, level, TOGETHER_ROTATIONS)) {
+    if (hoisted && n_keyed > rb && c->side_stream() && !one_stream) {
         Arena extra = ar;
         lane_ws[1].v = extra.take(rb * ws.v_b);
         lane_ws[1].w = extra.take(rb * ws.w_b);
@@ -1727,12 +1736,12 @@ int he_poly_act_deg7(const ckks_ctx* c, const uint64_t* const* h_d_x, uint32_t n
     const size_t x2s = (size_t)(l1 + 1) * N, x3s = (size_t)(l2 + 1) * N, Bs = (size_t)(l3 + 1) * N;
     // Batches of channels are independent: with room for two sets of scratch, every other batch goes to the library's side
     // stream (fork after the caller's earlier work, join before the call returns to the caller's stream).
-    // (In a small call sixteen go together instead: see act_batch.)
+    // (In a small call up to sixteen go together instead: see act_batch.)
     u32 most = merged_division ? act_batch(c, level, n_ct) : CT_BATCH;
-    if (most > CT_BATCH && ws_bytes < ws_poly_act(c, level, n_ct < most ? n_ct : most)) most = CT_BATCH;  // in a smaller workspace
+    if (most > CT_BATCH && ws_bytes < ws_poly_act(c, level, n_ct)) most = CT_BATCH;  // in a smaller workspace
     const u32 nb_max = n_ct < most ? n_ct : most;
-    const bool want_pairs = merged_division && act_pairs(c, level, nb_max);
-    const u32 want_lanes = n_ct > most && most == CT_BATCH && c->side_stream() ? 2 : 1;
+    const bool want_pairs = merged_division && act_pairs(c, nb_max);
+    const u32 want_lanes = n_ct > most && c->side_stream() ? 2 : 1;
     const bool pairs = want_pairs && ws_bytes >= want_lanes * ws_poly_act_in(c, level, nb_max, true);  // else in what one product at a time needs
     const size_t lane_bytes = ws_poly_act_in(c, level, nb_max, pairs);
     const u32 n_lanes = (want_lanes == 2 && ws_bytes >= 2 * lane_bytes) ? 2 : 1;

@@ -205,10 +205,11 @@ def test_whole_ring_kernels(bits, dnum, level):
             assert np.array_equal(hx.to_host(got), want)
 
 
-@pytest.mark.parametrize("log_n,bits,stored", [(13, 50, False), (12, 50, False), (11, 50, True), (13, 57, True)])
+@pytest.mark.parametrize("log_n,bits,stored", [(14, 50, False), (13, 50, False), (12, 50, False), (11, 50, True), (13, 57, True)])
 def test_products_stay_within_their_workspace(log_n, bits, stored):
     """The scratch of a product is a key switch's, plus the tensor product's three polynomials only where a kernel stores them; product
-    and activation (two batches in flight) with exactly the queried bytes give the oracle's residues and touch nothing around them."""
+    and activation (two batches in flight, or with merged divisions on the double-precision rings up to 2^13 all nine together) with exactly
+    the queried bytes give the oracle's residues and touch nothing around them."""
     p = make_params(log_n, 6, 2, 3, bits=bits)
     orc, ctx = Oracle(p), hx.Context(p)
     rng = np.random.default_rng(7000 + log_n + bits)
@@ -320,7 +321,7 @@ def test_more_than_eight_items_in_a_call(log_n, num_q, num_p, dnum, level):
     """Up to sixteen items share every launch: rotations (hoisted in launches of eight taps, unhoisted), activation of eleven and of five (the
     two middle products of a ciphertext in one batch), merge of eleven blocks, fully connected layer with eleven outputs, and convolutions
     from and to eleven channels; in the queried workspace and in the one that batches of eight need; seven digits; a ring where
-    activation and convolution alternate between two streams."""
+    the activation alternates between two streams (convolutions that do: test_convolutions_on_two_streams)."""
     p = make_params(log_n, num_q, num_p, dnum)
     orc, ctx = Oracle(p), hx.Context(p)
     rng = np.random.default_rng(9700 + log_n + dnum)
@@ -387,3 +388,53 @@ def test_more_than_eight_items_in_a_call(log_n, num_q, num_p, dnum, level):
             want = orc.he_conv_deferred(ins, level, 4, keys, masks, w, merged=al == hx.HE_CONV_DEFERRED_MERGED) if ext else orc.he_conv(ins, level, 4, keys, masks, w)
             outs = hx.he_conv_batched(ctx, 4, 4, 2, level, [d_cts[i % 3] for i in range(c_in)], tkeys, hx.from_host(masks), hx.from_host(w_res), c_out, alignment=al)
             assert all(same(o, want[i]) for i, o in enumerate(outs)), f"convolution {c_in} -> {c_out}, schedule {al}"
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,c_in,c_out,limit", [(13, 3, 2, 2, 17, 2, 15), (15, 4, 2, 2, 9, 2, 17), (15, 4, 2, 2, 2, 17, 17),
+                                                                         (16, 7, 2, 4, 1, 9, 19)])
+def test_convolutions_on_two_streams(log_n, num_q, num_p, dnum, c_in, c_out, limit):
+    """Deferred convolutions whose batches of input channels, or of output channels, alternate between the context's two streams: more than eight
+    of either on rings above the size up to which they go together (2^17 coefficients of the extended basis, 2^15 from more than sixteen
+    channels, 2^19 where the merged divisions alone come in batches and sixteen would hold them); with the overlap on, off and on
+    again, and replayed from a graph."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    assert (num_q + num_p) << log_n > 1 << limit
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(9900 + log_n + c_in)
+    level, q, n = p.num_q - 1, p.moduli, orc.N
+    toffs = conv_tap_offsets(4)
+    keys = {o: np.stack([np.stack([rand_poly(rng, q, n) for _ in range(2)]) for _ in range(dnum)]) for o in toffs if o}
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(keys[o]), hx.ckks_galois_element(ctx, o)) if o else None for o in toffs]
+    cts = [rand_ct(rng, q, level, n) for _ in range(c_in)]
+    d_in = [hx.from_host(c) for c in cts]
+    idx = orc.ext_moduli_idx(level)
+    masks = np.stack([rand_poly(rng, [q[t] for t in idx], n) for _ in range(9)])
+    w = rng.integers(-2 ** 31, 2 ** 31, size=(c_out, c_in, 9))
+    d_masks, d_w = hx.from_host(masks), hx.from_host(w_residues(w, [q[t] for t in idx], len(idx) - 1))
+    for al in (hx.HE_CONV_DEFERRED_MERGED, hx.HE_CONV_DEFERRED_MODDOWN):
+        want = orc.he_conv_deferred(cts, level, 4, keys, masks, w, merged=al == hx.HE_CONV_DEFERRED_MERGED)
+        outs = [hx.empty(2, level, n) for _ in range(c_out)]
+        ws = hx.empty(hx.he_conv_workspace_bytes(ctx, c_in, c_out, 4, 4, 2, level, al) // 8 + 1)
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        run = lambda: hx.he_conv_batched(ctx, 4, 4, 2, level, d_in, dkeys, d_masks, d_w, c_out, outs=outs, ws=ws, alignment=al, stream=st.cuda_stream)
+
+        def check(what):
+            st.synchronize()
+            assert all(np.array_equal(hx.to_host(o), want[i]) for i, o in enumerate(outs)), f"{what}, schedule {al}"
+            for o in outs:
+                o.zero_()
+            torch.cuda.synchronize()
+
+        for on in (True, False, True):
+            hx.ckks_ctx_set_overlap(ctx, on)
+            run()
+            check(f"overlap {on}")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            run()
+        for _ in range(3):
+            torch.randn(1 << 16, device="cuda").sum().item()  # eager work and a synchronisation between replays
+            graph.replay()
+            torch.cuda.synchronize()
+            check("replay")
