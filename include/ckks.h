@@ -149,9 +149,11 @@ int ckks_keyswitch(const ckks_ctx* ctx, const uint64_t* d_c, uint32_t level, con
  * ("fast rotations"); hoisted = 0: each rotation permutes the ciphertext and key-switches the
  * permuted c1.  Both orders give the same residues (centred digits commute with the automorphism).
  * h_d_outs: host array of n_rot device pointers, each uint64[2][level+1][N].
- * Workspace: ckks_workspace_bytes(ctx, CKKS_OP_ROTATE, level, n_rot) lets up to 16 rotations (8 hoisted ones in large contexts, 8 with moduli above 2^50) share every launch
- * but the inner products; a smaller one is accepted down to the size for n_rot = 1 (unhoisted rotations then go
- * in smaller batches, same residues), below that CKKS_ERR_WORKSPACE_TOO_SMALL. */
+ * Workspace: ckks_workspace_bytes(ctx, CKKS_OP_ROTATE, level, n_rot) is enough for both orders; with it up to 16 rotations share their
+ * launches (8 with a modulus of 2^50 or more, and 8 hoisted ones on large rings).  Less is accepted, with the same residues:
+ * unhoisted down to the size for n_rot = 1 (smaller batches); hoisted, which decompose one polynomial only, down to
+ * 8 N (l + 1 + beta E + 2 m (E + l + 1)) bytes for m = min(n_rot, 8), E = l + 1 + num_p limbs and beta digits alive at level l
+ * (rotations by 0 not counted).  Below that CKKS_ERR_WORKSPACE_TOO_SMALL. */
 int ckks_rotate_hoisted(const ckks_ctx* ctx, const uint64_t* d_ct, uint32_t level,
                         const int32_t* h_offsets, uint32_t n_rot, const ckks_key* const* keys,
                         uint64_t* const* h_d_outs, int hoisted, void* d_ws, size_t ws_bytes, void* stream);

@@ -121,6 +121,9 @@ bool together(const ckks_ctx* c, u32 level, size_t limit) { return ntt_has_modup
 // 321 / 348, 2^14, 14 + 6 211 / 220, 275 / 283, 631 / 678
 bool rotations_together(const ckks_ctx* c, u32 level, u32 n) { return together(c, level, n <= KS_MAX_BATCH ? (size_t)3 << 17 : (size_t)1 << 17); }
 size_t ws_rescale(const ckks_ctx* c, u32 level, u32 n) { return blk(2 * (size_t)n * c->N) + blk(2 * (size_t)n * level * c->N); }
+// n unhoisted rotations: their key switches, and a permuted copy of each polynomial where no transform gathers it (run_rotate_batch)
+size_t ws_permuted(const ckks_ctx* c, u32 level, u32 n) { return ntt_has_modup(c) ? 0 : blk((size_t)n * (level + 1) * c->N); }
+size_t ws_rotate_unhoisted(const ckks_ctx* c, u32 level, u32 n) { return ws_ks(c, level, n, n) + ws_permuted(c, level, n); }
 // a product's scratch: the key switch's, and the three polynomials of the tensor product where a kernel forms them (elsewhere they
 // are not stored: run_product)
 size_t ws_ctct(const ckks_ctx* c, u32 level, u32 n) {
@@ -968,11 +971,11 @@ size_t ckks_workspace_bytes(const ckks_ctx* c, int op, uint32_t level, uint32_t 
         case CKKS_OP_ROTATE: {
             if (!c->dnum) return 0;
             // hoisted, more than one batch: a second set of inner-product and conversion buffers (two batches in flight);
-            // unhoisted: every rotation of a batch has its own permuted copy and its own digits
-            const size_t hoisted = ws_ks(c, level, 1, nb) + blk(L1 * N) +
+            // unhoisted: every rotation of a batch has its own digits
+            const size_t hoisted = ws_ks(c, level, 1, nb) +
                                    (count > CT_BATCH && c->side ? blk((size_t)nb * 2 * c->ext_limbs(level) * N) + blk((size_t)nb * 2 * L1 * N) : 0);
             const u32 most = ks_batch(c), ub = count < most ? (count ? count : 1) : most;
-            const size_t unhoisted = ws_ks(c, level, ub, ub) + blk((size_t)ub * L1 * N);
+            const size_t unhoisted = ws_rotate_unhoisted(c, level, ub);
             return hoisted > unhoisted ? hoisted : unhoisted;
         }
         case CKKS_OP_RESCALE: return level >= 1 ? ws_rescale(c, level, 1) : 0;
@@ -1148,15 +1151,10 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             if (rb > CT_BATCH && ws_bytes < ws_ks(c, level, 1, rb)) rb = CT_BATCH;  // in a smaller workspace
             if (!carve_ks(c, level, 1, rb, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rotation");
         } else {
-            for (;; rb--) {
-                Arena probe(d_ws, ws_bytes);
-                KsWs w;
-                const bool fits = carve_ks(c, level, rb, rb, probe, w) && (probe.take((size_t)rb * L1 * N), probe.ok());
-                if (fits) break;
-                if (rb == 1) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rotation");
-            }
-            carve_ks(c, level, rb, rb, ar, ws);
-            pc1 = ar.take((size_t)rb * L1 * N);
+            while (rb > 1 && ws_bytes < ws_rotate_unhoisted(c, level, rb)) rb--;
+            if (!carve_ks(c, level, rb, rb, ar, ws)) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rotation");
+            if (!ntt_has_modup(c)) pc1 = ar.take((size_t)rb * L1 * N);
+            if (!ar.ok()) return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for rotation");
         }
     }
     hipStream_t st = (hipStream_t)stream;

@@ -240,6 +240,38 @@ def test_products_stay_within_their_workspace(log_n, bits, stored):
         assert ok and untouched(buf), f"merged = {merged}"
 
 
+@pytest.mark.parametrize("log_n,bits", [(13, 50), (12, 50), (11, 50), (13, 57)])
+def test_rotations_stay_within_their_workspace(log_n, bits):
+    """The scratch of unhoisted rotations is their key switches', plus a permuted copy of each polynomial only where no transform gathers it: five
+    rotations with exactly the queried bytes, and in the size for one, give the oracle's residues and touch nothing around
+    them.  Hoisted ones likewise in the least that is accepted: one decomposition and the inner products of the call."""
+    p = make_params(log_n, 6, 2, 3, bits=bits)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(7300 + log_n + bits)
+    level, n, offs = p.num_q - 1, orc.N, [3, -1, 7, 2, -9]
+    L1, E, beta = level + 1, level + 1 + p.num_p, 3
+    one = hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_KEYSWITCH, level)
+    assert one == 8 * n * (L1 + beta * E + 2 * E + 2 * L1)
+    copies = 0 if bits == 50 and log_n > 11 else 8 * n * L1
+    for m in (1, 5, 8) + ((16,) if not copies else ()):
+        assert hx.ckks_workspace_bytes(ctx, hx.CKKS_OP_ROTATE, level, m) == m * (one + copies)
+    ct = rand_ct(rng, p.moduli, level, n)
+    d_ct = hx.from_host(ct)
+    keys = [np.stack([np.stack([rand_poly(rng, p.moduli, n) for _ in range(2)]) for _ in range(p.dnum)]) for _ in offs]
+    dkeys = [hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, r)) for k, r in zip(keys, offs)]
+    want = orc.rotate_many(ct, level, offs, keys, False)
+    least = 8 * n * (L1 + beta * E + 2 * len(offs) * (E + L1))
+    for hoisted, nbytes in ((False, 5 * (one + copies)), (False, one + copies), (True, least)):
+        buf = torch.full((nbytes // 8 + 128,), 0x5A5A5A5A, dtype=torch.int64, device="cuda")
+        outs = hx.ckks_rotate_hoisted(ctx, d_ct, level, offs, dkeys, hoisted, ws=buf[64:-64])
+        assert all(np.array_equal(hx.to_host(o), w) for o, w in zip(outs, want)), f"hoisted = {hoisted}, {nbytes} bytes"
+        assert bool((buf[:64] == 0x5A5A5A5A).all()) and bool((buf[-64:] == 0x5A5A5A5A).all()), f"hoisted = {hoisted}, {nbytes} bytes"
+    for hoisted, nbytes in ((False, one + copies - 256), (True, least - 256)):
+        with pytest.raises(hx.CkksError) as e:
+            hx.ckks_rotate_hoisted(ctx, d_ct, level, offs, dkeys, hoisted, ws=hx.empty(nbytes // 8))
+        assert e.value.code == hx.binding.CKKS_ERR_WORKSPACE_TOO_SMALL
+
+
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n_ct", [(13, 6, 2, 3, 5, 1), (13, 5, 5, 1, 4, 3), (14, 9, 3, 3, 6, 8), (13, 19, 2, 10, 18, 2),
                                                                (15, 7, 3, 3, 5, 1)])
 def test_inner_products_go_on_into_the_inverse_pass(log_n, num_q, num_p, dnum, level, n_ct):
