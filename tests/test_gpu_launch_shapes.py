@@ -178,9 +178,10 @@ def test_masked_sums_of_the_layout(batch, base):
 
 @pytest.mark.parametrize("bits,dnum,level", [(50, 3, 6), (50, 1, 6), (50, 7, 3), (57, 3, 5)])
 def test_whole_ring_kernels(bits, dnum, level):
-    """The one-workgroup transforms of N = 2^12, both arithmetics: in place and from a list, batches and any order of moduli,
-    conversions of digits of three (ragged), seven and one limbs, divisions without operands (key switch, rescale), with an addend
-    (unhoisted rotation) and with a mask (the single-channel convolution is compared in the other tests)."""
+    """The one-workgroup transforms of N = 2^12, both arithmetics: in place and from a list, batches and any order of moduli, the rescale in
+    one launch; and what goes pass by pass there with the double-precision arithmetic (with the integer one the whole-ring kernels take the
+    transforms): conversions of digits of three (ragged), seven and one limbs, divisions without operands (key switch) and
+    with an addend (unhoisted rotation).  The divisions of the double-precision whole-ring kernels: test_whole_ring_divisions."""
     p = make_params(12, 7, 7 if dnum == 1 else 3, dnum, bits=bits)
     orc, ctx = Oracle(p), hx.Context(p)
     rng = np.random.default_rng(5000 + bits + dnum)
@@ -203,6 +204,35 @@ def test_whole_ring_kernels(bits, dnum, level):
         outs = hx.ckks_rotate_hoisted(ctx, d_ct, level, offs, dkeys, hoisted)
         for got, want in zip(outs, orc.rotate_many(ct, level, offs, keys, hoisted)):
             assert np.array_equal(hx.to_host(got), want)
+
+
+@pytest.mark.parametrize("num_p", [3, 6, 8, 10, 14])
+def test_whole_ring_divisions(num_p):
+    """N = 2^12: divisions of whole sums into 113 to 256 limb-polys are one launch each way.  Six hoisted rotations, the eight of a direct convolution
+    and the merged divisions of a deferred one, by three to fourteen special primes (four, eight and sixteen terms) and with the
+    level's own limb (four, eight, nine and twelve of twelve, sixteen)."""
+    p = make_params(12, 12, num_p, 2)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(5200 + num_p)
+    level, q, n = p.num_q - 1, p.moduli, orc.N
+    n_rot, c_out = 6, 6
+    assert all(112 < rows <= 256 for rows in ((level + 1) * 2 * n_rot, (level + 1) * 2 * 8, level * 2 * c_out))  # ntt_mid_moddown's window
+    ct = rand_ct(rng, q, level, n)
+    toffs = conv_tap_offsets(4)
+    offs = [o for o in toffs if o][:n_rot]
+    keys = {o: np.stack([np.stack([rand_poly(rng, q, n) for _ in range(2)]) for _ in range(p.dnum)]) for o in toffs if o}
+    dkeys = {o: hx.ckks_key_load(ctx, hx.from_host(k), hx.ckks_galois_element(ctx, o)) for o, k in keys.items()}
+    outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, [dkeys[o] for o in offs], True)
+    for out, want in zip(outs, orc.rotate_many(ct, level, offs, [keys[o] for o in offs], True)):
+        assert np.array_equal(hx.to_host(out), want), "rotations"
+    w = rng.integers(-2 ** 31, 2 ** 31, size=(c_out, 1, 9))
+    for al in (hx.HE_CONV_ALIGN_DIRECT, hx.HE_CONV_DEFERRED_MERGED):
+        idx = orc.ext_moduli_idx(level) if al == hx.HE_CONV_DEFERRED_MERGED else list(range(level + 1))
+        masks = np.stack([rand_poly(rng, [q[t] for t in idx], n) for _ in range(9)])
+        w_res = w_residues(w, [q[t] for t in idx], len(idx) - 1)
+        want = orc.he_conv_deferred([ct], level, 4, keys, masks, w, merged=True) if al == hx.HE_CONV_DEFERRED_MERGED else orc.he_conv([ct], level, 4, keys, masks, w)
+        outs = hx.he_conv_batched(ctx, 4, 4, 2, level, [hx.from_host(ct)], [dkeys.get(o) for o in toffs], hx.from_host(masks), hx.from_host(w_res), c_out, alignment=al)
+        assert all(np.array_equal(hx.to_host(o), want[i]) for i, o in enumerate(outs)), f"convolution, schedule {al}"
 
 
 @pytest.mark.parametrize("log_n,bits,stored", [(14, 50, False), (13, 50, False), (12, 50, False), (11, 50, True), (13, 57, True)])
