@@ -9,8 +9,11 @@
 // with (nd or more; what is beyond nd multiplies the row's zeros), 0: there is no such kernel.
 constexpr uint32_t hi_conv_terms(uint32_t log_hi, uint32_t ap, uint32_t nd) {
     if (log_hi < 2 || log_hi > 6 || nd == 0 || nd > ap || (ap != 4 && ap != 8 && ap != 12 && ap != 16)) return 0;
+    if (log_hi < 4) {  // what the columns do not take (mid_conv_per): more than ten source limbs on rings of 2^13 points, five on those of 2^14
+        if (log_hi == 2) return ap == 16 || (ap == 12 && nd > 10) ? ap : 0;
+        return ap == 4 ? 0 : (ap == 12 && nd == 9 ? 9 : ap);
+    }
     if (ap == 4 && nd == 1) return 1;  // the rescale: one dropped limb
-    if (log_hi < 4) return ap == 12 && nd == 9 ? 9 : ap;
     // as many terms as the launch has source limbs: the rest of a row is padding (digits of 7, 7 and 4 or 5
     // limbs in rows of eight: 41.0 us a launch with eight terms everywhere, 38.0 with their own).  Whole calls with two equal
     // digits at N = 2^16 take this much longer with full rows (product / activation of eight / eight rotations low in the

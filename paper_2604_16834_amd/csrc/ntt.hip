@@ -1569,7 +1569,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_kernel(NttArgs args,
 // trip of 0.6 to 1 us (direct convolution of five channels, 14 + 4 limbs, 306 -> 294 us).
 // AP: 0 = the source is a polynomial, else rows of conversion constants as in ntt_fwd_hi_conv_kernel, ND of them real.  DIV: the
 // results go through a division's last step (em as in div_request) instead of being stored.
-// grid = (entries of the list or most targets of a digit, batch, digits)
+// grid = (entries of the list, batch)
 #define RING_LOG_HI 1
 #define RING_THREADS (NTT_THREADS << RING_LOG_HI)
 // the inverse transform likewise: the lo pass' rounds mirrored, an exchange, the hi pass' stages; v[j] ends as the ring's point

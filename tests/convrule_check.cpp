@@ -68,7 +68,20 @@ int main() {
         std::printf("a kernel for a size that has none\n");
         return 1;
     }
-    for (const auto& r : reached) std::printf("%u %u %u %d\n", std::get<0>(r), std::get<1>(r), std::get<2>(r), (int)std::get<3>(r));
+    // nothing is instantiated that no conversion reaches: the kernels of rows with their terms, and the columns
+    for (u32 log_hi = 1; log_hi <= 6; log_hi++) {
+        for (u32 ap = 4; ap <= 16; ap += 4)
+            for (u32 nd = 1; nd <= ap; nd++)
+                if (hi_conv_terms(log_hi, ap, nd) == nd && !reached.count({log_hi, ap, nd, false}) && !reached.count({log_hi, ap, nd, true})) {
+                    std::printf("not reached: log_hi %u, rows of %u, %u terms\n", log_hi, ap, nd);
+                    return 1;
+                }
+        for (u32 nd = 1; nd <= 16; nd++)
+            if (mid_conv_terms(log_hi, nd) == nd && !reached.count({log_hi, 0u, nd, true})) {
+                std::printf("not reached: log_hi %u, %u columns\n", log_hi, nd);
+                return 1;
+            }
+    }
     std::fprintf(stderr, "%llu conversions\n", n_sizes);
     return 0;
 }
