@@ -2,8 +2,8 @@
 // exported operation.  No arithmetic happens on the host; no call here allocates or synchronises.
 //
 // Work is batched wherever operands are independent: the channel ciphertexts of a layer share their
-// rotation and relinearisation keys, so up to CT_BATCH of them go through every kernel of a key
-// switch together (the key streams from HBM once per batch, NTT launches are large enough to fill
+// rotation and relinearisation keys, so eight or sixteen of them (see ks_batch) go through every kernel of a
+// key switch together (the key streams from HBM once per batch, NTT launches are large enough to fill
 // the chip); the rotations of one ciphertext share its extended digits (hoisting).
 #include <cstdio>
 #include <new>
