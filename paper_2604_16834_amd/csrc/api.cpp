@@ -1024,6 +1024,17 @@ uint32_t ckks_galois_element(const ckks_ctx* c, int32_t offset) {
     return (uint32_t)g;
 }
 
+// Polynomials of a large batch that go through both passes before the next ones do.  The first pass writes what the second reads: 240 MB of
+// it stay in the 256 MB last-level cache in between, at the price of a drain and a fill of the chip per launch (about 8 us).  Forward and inverse
+// together in us, all at once / in parts of about 240 MB: N = 2^16, 30 limbs, 472 MB 666 / 655, 692 MB 1016 / 959, 991 MB 1468 / 1381; 2^15, 24 limbs,
+// 478 MB 664 / 657, 994 MB 1423 / 1365; 2^13 480 MB 668 / 632, 999 MB 1451 / 1317; parts of 170 MB of 346 MB 467 / 497, of 126 MB of 991 MB 1493, so a
+// batch is cut from 444 MB on.  With 64-bit integer butterflies, which are bound by instruction issue: 994 MB 1868 / 1891, not cut.
+static u32 ntt_cached_batch(const ckks_ctx* c, u32 n_limbs, u32 batch) {
+    if (!c->ntt_f64 || c->log_hi == 0 || ntt_one_pass(c)) return batch;
+    const u64 part = 240000000, total = (u64)batch * n_limbs * c->N * sizeof(u64), parts = (total + part * 15 / 100) / part;
+    return parts > 1 ? (u32)((batch + parts - 1) / parts) : batch;
+}
+
 static int ntt_entry(const ckks_ctx* c, bool inverse, uint64_t* d_polys, const uint32_t* h_idx, uint32_t n_limbs, uint32_t batch,
                      void* stream) {
     if (!c) return CKKS_ERR_INVALID_ARG;
@@ -1036,7 +1047,8 @@ static int ntt_entry(const ckks_ctx* c, bool inverse, uint64_t* d_polys, const u
         pl.spos[a] = pl.dpos[a] = (unsigned char)(a < n_limbs ? a : 0);
         pl.mod[a] = (unsigned char)(a < n_limbs ? h_idx[a] : 0);
     }
-    const u32 max_batch = 65535 / n_limbs;  // grid.y limit
+    u32 max_batch = 65535 / n_limbs;  // grid.y limit
+    if (const u32 part = ntt_cached_batch(c, n_limbs, batch); part < max_batch) max_batch = part;
     u64* p = (u64*)d_polys;
     for (u32 b0 = 0; b0 < batch; b0 += max_batch) {
         const u32 nb = batch - b0 < max_batch ? batch - b0 : max_batch;
