@@ -480,6 +480,16 @@ u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {
     return (!conv_together(c, d) && c->side_stream() && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;
 }
 
+// Whether the inner products and the weighted sum of a deferred convolution are one kernel that stores no aligned copies (launch_key_inner_sum):
+// with up to four outputs, whose sums a thread holds; on small rings with up to eight, in two groups that form the inner products twice.  Merged
+// convolutions, copies and sum / one kernel in us: N = 2^12, 5 + 2 limbs, 1 -> 1 37.9 / 33.5, 4 -> 4 51.6 / 44.4, 16 -> 4 101.8 / 74.0, 64 -> 1 352 / 224, 8 -> 8 69.4 / 62.0,
+// 2^13, 5 + 2, 3 -> 2 56.9 / 44.8, 2^14, 12 + 4, 4 -> 4 158 / 133, 2^15, 9 + 3, 16 -> 4 675 / 510, 2^16, 24 + 8, 1 -> 1 453 / 351, 5 -> 3 1196 / 934, 16 -> 1 3069 / 2017,
+// 64 -> 1 11770 / 7420; eight outputs above 2^15 coefficients 2^12, 10 + 5, 1 -> 8 50.7 / 54.2, 2^16, 24 + 8, 8 -> 8 2027 / 2303
+bool conv_summed(const ckks_ctx* c, const he_conv_desc* d) {
+    if (!c->small_q || c->live_digits(d->level) > 4 || c->N % 64) return false;
+    return d->c_out <= 4 || (d->c_out <= 8 && (size_t)c->ext_limbs(d->level) * c->N <= (size_t)1 << 15);
+}
+
 // the schedules that divide every rotation by P, kb of them at a time
 size_t ws_conv_rotated(const ckks_ctx* c, const he_conv_desc* d, u32 kb) {
     const size_t N = c->N, L1 = d->level + 1;
@@ -523,6 +533,7 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     // the aligned copies are stored term-innermost when the fused inner product can write them that way
     const bool fused_taps = c->live_digits(level) <= 4;
     const XLayout xl = (fused_taps && N % 64 == 0) ? XLayout::tiled((size_t)d->c_in * 9, N) : XLayout::classic(E, N);
+    const bool summed = conv_summed(c, d);
     bool forked = false;
     auto fork = [&]() -> int {
         if (n_lanes < 2 || forked) return CKKS_OK;
@@ -549,6 +560,12 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
         }
         int rc = run_modup(c, level, c1s, n, ws, st);
         if (rc) return rc;
+        if (summed) {
+            const u64* skeys[9];
+            for (u32 t = 0; t < 9; t++) skeys[t] = gs[t] == 1 ? nullptr : rot_keys[t]->d_key;
+            HIP_TRY(launch_key_inner_sum(c, level, dsrc(c, ws, 0), skeys, gs, masks, in, n, w_res, c0, d->c_in, d->c_out, acc, st));
+            return CKKS_OK;
+        }
         // taps without a rotation (the centre) are a product with the mask; all the others go through one launch
         const u64 *tkeys[8], *tmasks[8], *centre_mask = nullptr;
         u32 tg[8], ttap[8], n_taps = 0, centre_tap = 0, n_centre = 0;
@@ -585,11 +602,11 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
         return CKKS_OK;
     };
     int rc;
-    if (d->c_in > kb && (rc = fork())) return rc;
+    if (d->c_in > kb && !summed && (rc = fork())) return rc;  // (the batches' sums go into the same place)
     for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += kb, k++)
         if ((rc = align_batch(c0, lanes[forked ? k & 1 : 0]))) return join(rc);
     if ((rc = join(CKKS_OK))) return rc;
-    HIP_TRY(launch_weighted_sum(c, level, true, xs, xl, d->c_in * 9, w_res, d->c_out, acc, wscratch, d->weight_bits, st0));
+    if (!summed) HIP_TRY(launch_weighted_sum(c, level, true, xs, xl, d->c_in * 9, w_res, d->c_out, acc, wscratch, d->weight_bits, st0));
     if (d->c_out > kb && (rc = fork())) return rc;
     for (u32 o0 = 0, k = 0; o0 < d->c_out; o0 += kb, k++) {
         const Lane& L = lanes[forked ? k & 1 : 0];

@@ -310,6 +310,9 @@ hipError_t launch_key_inner_taps(const ckks_ctx* c, u32 level, const DigitSrc& d
                                  const u32* gs, const u64* const* masks, const u32* taps, u32 n_taps, const u64* const* c0s,
                                  u64* xs, XLayout xl, u32 k0, u32 k_bstride, u32 n, hipStream_t st, const u64* centre_mask = nullptr,
                                  u32 centre_tap = 0);
+// the same inner products, their masks and the weighted sum over channels and taps in one kernel (few outputs, moduli below 2^50, at most four digits)
+hipError_t launch_key_inner_sum(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs, const u64* masks,
+                                const u64* const* cts, u32 n, const u64* w_res, u32 ch0, u32 n_ch, u32 c_out, u64* acc, hipStream_t st);
 // merged: the dropped limbs are q_level and the special primes (division by P*q_level, results on limbs 0..level-1)
 hipError_t launch_moddown_conv(const ckks_ctx* c, u32 level, bool merged, const u64* v, u64* w, u32 batch, hipStream_t st);
 hipError_t launch_moddown_final(const ckks_ctx* c, u32 level, bool merged, const u64* v, const u64* w, const FinalItem* items, u32 n,

@@ -132,6 +132,18 @@ F64M_FN double f64m_centre(double t, double q) {
 // step can take T past 2^103, where it rounds to a multiple of 2^51 and leaves a remainder of at most 2^50; D, the high
 // part and the sum of the remainders (at most 8 * 2^49 + 2^50) are still exact, the quotient stays below 2^52.
 #define F64M_DOT_BASE 0x1.8p+102  /* 1.5 * 2^102 */
+// one term of a chain (running sum t, remainders lo), and what the chain stands for, reduced
+F64M_FN void f64m_chain_add(double& t, double& lo, double y, double w) {
+    const double tn = __builtin_fma(y, w, t);
+    const double d = tn - t;
+    lo += __builtin_fma(y, w, -d);
+    t = tn;
+}
+F64M_FN double f64m_chain_join(double t, double lo, double q, double qinv) {
+    const double hi = t - F64M_DOT_BASE;
+    const double c = __builtin_rint(hi * qinv);
+    return f64m_reduce(__builtin_fma(-c, q, hi) + lo, q, qinv);
+}
 template <int ND>
 F64M_FN double f64m_dot_w(const double* y, const double* w, double q, double qinv) {  // w[a]: the centred constants
     constexpr int CHAIN = ND == 9 ? 9 : 8;
@@ -140,15 +152,8 @@ F64M_FN double f64m_dot_w(const double* y, const double* w, double q, double qin
     for (int a0 = 0; a0 < ND; a0 += CHAIN) {
         double t = F64M_DOT_BASE, lo = 0.0;
 #pragma unroll
-        for (int a = a0; a < a0 + CHAIN && a < ND; a++) {
-            const double tn = __builtin_fma(y[a], w[a], t);
-            const double d = tn - t;
-            lo += __builtin_fma(y[a], w[a], -d);
-            t = tn;
-        }
-        const double hi = t - F64M_DOT_BASE;
-        const double c = __builtin_rint(hi * qinv);
-        const double v = f64m_reduce(__builtin_fma(-c, q, hi) + lo, q, qinv);
+        for (int a = a0; a < a0 + CHAIN && a < ND; a++) f64m_chain_add(t, lo, y[a], w[a]);
+        const double v = f64m_chain_join(t, lo, q, qinv);
         r = a0 == 0 ? v : f64m_reduce(r + v, q, qinv);
     }
     return r;

@@ -586,6 +586,201 @@ hipError_t launch_key_inner_taps(const ckks_ctx* c, u32 level, const DigitSrc& d
     return hipGetLastError();
 }
 
+// The deferred convolution's inner products, masks and weighted sum in one kernel, for few output channels: the aligned copies are not stored.
+//   acc[o][comp][e][x] (+)= sum_t mask_t[x] * sum_b w[o][b][t] * ( <digits_b[s_t x], key_t[x]> + P c0_b[s_t x] )
+// organised by DESTINATION point, so that a thread holds the sums of its point: digits and c0 are gathered through the tap's automorphism s_t
+// (a wavefront's 64 points are one aligned run of 512 bytes), once per tap, from cache after the first.  What a copy costs otherwise, two words
+// written and read again per (channel, tap), was most of the time of the two launches that this one replaces.  A workgroup is 64 points
+// times TW wavefronts that take 9 / TW taps each and add up their sums in LDS; the operands of the next NB
+// channels, or of the next tap's first, are requested while the current ones are multiplied.  A tap without a rotation has no key:
+// P times the ciphertext itself, whose component 1 comes in place of the first digit.  Three channels, two outputs, 5 + 2 limbs at N = 2^13: 16.4 us
+// with the workgroups of a limb on all dies, 13 with them on one (25 in two launches, 25 MB of copies written and read); 16 channels, four
+// outputs, 24 + 8 limbs at 2^16: a layer takes 2.5 ms instead of 3.3, bound by the double-precision units.
+struct SumTaps {
+    const u64* key[9];  // null: no rotation
+    u32 g[9];
+};
+#define KSUM_MAX_CH KS_MAX_BATCH
+template <int BETA, int OT, int NB, int TW>
+__global__ __launch_bounds__(64 * TW) void key_inner_sum_kernel(DigitSrc digits, SumTaps T, PtrList8 cts, const u64* __restrict__ masks,
+                                                                const u64* __restrict__ w_res, u64* __restrict__ acc, const u64* __restrict__ negp,
+                                                                const ModConstF* __restrict__ mcf, u32 log_n, u32 level, u32 num_q, u32 M, u32 E, u32 n,
+                                                                u32 ch0, u32 n_ch, u32 c_out) {
+    constexpr u32 TPW = 9 / TW;
+    __shared__ double lw[9 * KSUM_MAX_CH * OT];  // [tap][channel][output], centred; zero beyond the last channel or output
+    __shared__ double ls[TW > 1 ? TW - 1 : 1][2][OT][64];
+    const u32 N = 1u << log_n, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups are dealt to the eight dies in turn: each die takes a contiguous eighth of the (limb, points) list, so that what its taps
+    // gather stays in its own L2 cache
+    const u32 log_xw = log_n - 6, list = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3), e = list >> log_xw, o0 = blockIdx.y * OT;
+    if (e >= E) return;  // whole workgroup
+    const u32 x = (list & ((1u << log_xw) - 1)) * 64 + lane;
+    const u32 t_mod = e <= level ? e : num_q + (e - level - 1), el = e <= level ? e : level;
+    const u32 own = e <= level ? e / digits.alpha : 0xffffffffu;
+    const double q = mcf[t_mod].q, qinv = mcf[t_mod].qinv, halfq = 0.5 * q;
+    auto centred = [&](u64 v) {
+        const double d = f64m_from_u64(v);
+        return d > halfq ? d - q : d;
+    };
+    // up to four products of a residue as it is, below 2^50, with a centred word, below 2^49, keep a chain's sum below 2^101 (f64m_dot_w): nothing to
+    // centre
+    auto plain = [&](u64 v) { return BETA < 4 ? f64m_from_u64(v) : centred(v); };
+    const double pres = e <= level ? centred((u64)q - negp[el]) : 0.0;  // P mod q_e; nothing is added on the special primes
+    const u32 groups = (n + NB - 1) / NB;
+    u64 dv[NB][BETA], cv[NB], k0[BETA], k1[BETA], mk;
+    auto load = [&](u32 t, u32 grp) {  // the operands of tap t, channels grp * NB ..
+        const u64* key = T.key[t];
+        const u32 xs = galois_gather_index(x, T.g[t], log_n);
+        if (grp == 0) {
+            // without a key any address that can be read: the words meet zero weights
+            const u64* kp = (key ? key + (size_t)t_mod * N : masks) + x;
+            const size_t kstride = key ? (size_t)M * N : 0;
+#pragma unroll
+            for (int j = 0; j < BETA; j++) k0[j] = kp[2 * j * kstride], k1[j] = kp[(2 * j + 1) * kstride];
+            mk = masks[((size_t)t * E + e) * N + x];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+            const u32 b = min(grp * NB + i, n - 1);
+            const u64* ct = cts.p[b] + (size_t)el * N;
+#pragma unroll
+            for (int j = 0; j < BETA; j++) {
+                const u64* row = own == (u32)j ? digits.own.p[b] + (size_t)e * N : digits.digits + b * digits.bstride + ((size_t)j * E + e) * N;
+                if (j == 0 && !key) row = ct + (size_t)(level + 1) * N;
+                dv[i][j] = row[xs];
+            }
+            cv[i] = ct[xs];
+        }
+    };
+    const u32 t0 = wave * TPW;
+    load(t0, 0);
+    for (u32 i = tid; i < 9 * KSUM_MAX_CH * OT; i += 64 * TW) {
+        const u32 o = o0 + i % OT, b = i / OT % KSUM_MAX_CH, t = i / (OT * KSUM_MAX_CH);
+        lw[i] = (b < n && o < c_out) ? centred(w_res[(((size_t)o * n_ch + ch0 + b) * 9 + t) * E + e]) : 0.0;
+    }
+    __syncthreads();
+    double s[2][OT];
+#pragma unroll
+    for (int o = 0; o < OT; o++) s[0][o] = s[1][o] = 0.0;
+    for (u32 t = t0; t < t0 + TPW; t++) {
+        const bool rot = T.key[t] != nullptr;
+        double w0[BETA + 1], w1[BETA], st[2][OT], ct_[2][OT], cl[2][OT];
+        const double md = f64m_from_u64(mk);
+#pragma unroll
+        for (int j = 0; j < BETA; j++) {
+            w0[j] = rot ? centred(k0[j]) : 0.0;
+            w1[j] = rot ? centred(k1[j]) : (j == 0 ? pres : 0.0);
+        }
+        w0[BETA] = pres;
+        auto chain_begin = [&]() {
+#pragma unroll
+            for (int o = 0; o < OT; o++) ct_[0][o] = ct_[1][o] = F64M_DOT_BASE, cl[0][o] = cl[1][o] = 0.0;
+        };
+        chain_begin();
+        bool first = true;
+        for (u32 grp = 0; grp < groups; grp++) {
+            double X[2][NB];
+#pragma unroll
+            for (int i = 0; i < NB; i++) {
+                double y[BETA + 1];
+#pragma unroll
+                for (int j = 0; j < BETA; j++) y[j] = plain(dv[i][j]);
+                y[BETA] = plain(cv[i]);
+                X[0][i] = f64m_dot_w<BETA + 1>(y, w0, q, qinv);
+                X[1][i] = f64m_dot_w<BETA>(y, w1, q, qinv);
+            }
+            const bool last = grp + 1 == groups;
+            if (!last || t + 1 < t0 + TPW) load(last ? t + 1 : t, last ? 0 : grp + 1);
+            const double* lwt = lw + ((size_t)t * KSUM_MAX_CH + grp * NB) * OT;
+#pragma unroll
+            for (int o = 0; o < OT; o++)
+#pragma unroll
+                for (int i = 0; i < NB; i++) {
+                    const double wo = lwt[i * OT + o];
+#pragma unroll
+                    for (int c = 0; c < 2; c++) f64m_chain_add(ct_[c][o], cl[c][o], X[c][i], wo);
+                }
+            if (last || (grp + 1) % (8 / NB) == 0) {  // a chain takes eight terms
+#pragma unroll
+                for (int c = 0; c < 2; c++)
+#pragma unroll
+                    for (int o = 0; o < OT; o++) {
+                        const double r = f64m_chain_join(ct_[c][o], cl[c][o], q, qinv);
+                        st[c][o] = first ? r : f64m_reduce(st[c][o] + r, q, qinv);
+                    }
+                first = false;
+                if (!last) chain_begin();
+            }
+        }
+        // nine products below 0.63 q in all
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int o = 0; o < OT; o++) s[c][o] += f64m_mulmod_any(st[c][o], md, q, qinv);
+    }
+    if (TW > 1) {
+        if (wave)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int o = 0; o < OT; o++) ls[wave - 1][c][o][lane] = s[c][o];
+        __syncthreads();
+        if (wave) return;
+    }
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int o = 0; o < OT; o++) {
+            double r = s[c][o];
+#pragma unroll
+            for (int i = 0; i < TW - 1; i++) r += ls[i][c][o][lane];
+            if (o0 + o < c_out) {
+                u64* a = acc + (((size_t)(o0 + o) * 2 + c) * E + e) * N + x;
+                if (ch0) r += f64m_from_u64(*a);
+                *a = f64m_canonical(f64m_reduce(r, q, qinv), q);
+            }
+        }
+}
+
+// Channels ch0 .. ch0 + n - 1 of n_ch (n <= KSUM_MAX_CH, their digits and ciphertexts; the sums of the channels before are in acc), keys[t] null and gs[t] = 1 for a
+// tap without a rotation, masks [9][E][N], w_res [c_out][n_ch][9][E], acc [c_out][2][E][N]
+hipError_t launch_key_inner_sum(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, const u32* gs, const u64* masks,
+                                const u64* const* cts, u32 n, const u64* w_res, u32 ch0, u32 n_ch, u32 c_out, u64* acc, hipStream_t st) {
+    const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
+    if (n == 0 || n > KSUM_MAX_CH || ch0 + n > n_ch || c_out == 0 || c_out > 8 || beta > 4 || !c->small_q || c->N % 64) return hipErrorInvalidValue;
+    SumTaps T;
+    for (u32 t = 0; t < 9; t++) {
+        if ((gs[t] == 1) != (keys[t] == nullptr)) return hipErrorInvalidValue;
+        T.key[t] = keys[t];
+        T.g[t] = gs[t];
+    }
+    // TW: three taps per wavefront and a sum in LDS; one wavefront for all nine only where a chip full of workgroups makes the sum of several
+    // outputs the dearer part.  Whole convolutions, TW = 1 / 3 in us: N = 2^12, 5 + 2 limbs, 4 -> 4 56.3 / 44.4, 2^14, 12 + 4 132.9 / 132.9, 2^15, 9 + 3 182.5 / 186.0,
+    // 2^16, 24 + 8, 1 -> 4 510 / 553, 16 -> 1 2079 / 2017.  NB = 2, four channels at once 2 % faster on rings of 2^12 and 15 % slower on large ones (188 registers
+    // for four outputs), three where they come out even (3 -> 2 at 2^13 48.3 / 44.8).
+    const u32 xw = c->N / 64, ot = c_out <= 4 ? c_out : (c_out + 1) / 2, nb = n == 1 ? 1 : (n % 3 == 0 ? 3 : 2), tw = ot > 1 && xw * E >= 5120 ? 1 : 3;
+    const u64* negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
+    const dim3 grid((xw * E + 7) / 8 * 8, (c_out + ot - 1) / ot);
+    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (n * (double)beta + 9 * (2.0 * beta + 1.0) + 2.0 * c_out) + 2.0 * n * (level + 1.0)),
+                   2.0 * c->N * E * n * (9 * (beta + 1.0) + 9.0 * c_out));
+    PtrList8 ptrs;
+    for (u32 b = 0; b < KS_MAX_BATCH; b++) ptrs.p[b] = b < n ? cts[b] : nullptr;
+#define KS_SUM(B_, O_, NB_, TW_)                                                                                                       \
+    if (beta == B_ && ot == O_ && nb == NB_ && tw == TW_) {                                                                            \
+        hipLaunchKernelGGL((key_inner_sum_kernel<B_, O_, NB_, TW_>), grid, dim3(64 * TW_), 0, st, digits, T, ptrs, masks, w_res, acc, negp, c->d_mcf, c->log_n, level, c->num_q, c->M, E, n, ch0, n_ch, c_out); \
+        return hipGetLastError();                                                                                                      \
+    }
+#define KS_SUM_O(B_, NB_)                                                                                                              \
+    KS_SUM(B_, 1, NB_, 3) KS_SUM(B_, 2, NB_, 3) KS_SUM(B_, 3, NB_, 3) KS_SUM(B_, 4, NB_, 3)                                            \
+    KS_SUM(B_, 2, NB_, 1) KS_SUM(B_, 3, NB_, 1) KS_SUM(B_, 4, NB_, 1)
+#define KS_SUM_N(B_) KS_SUM_O(B_, 1) KS_SUM_O(B_, 2) KS_SUM_O(B_, 3)
+    KS_SUM_N(1) KS_SUM_N(2) KS_SUM_N(3) KS_SUM_N(4)
+#undef KS_SUM_N
+#undef KS_SUM_O
+#undef KS_SUM
+    return hipErrorInvalidValue;
+}
+
 // ---- ModDown, conversion of the P-part ----------------------------------------------------------
 // v [2][E][N]: limbs level+1.. hold the P-part in coefficient form.  w [2][level+1][N] (coefficients)
 // Dropped limbs: positions first..first+k-1 of v's E limbs; their moduli: `merged` ? (q_level, p_0, ...) : (p_0, ...).

@@ -10,7 +10,8 @@ if not torch.cuda.is_available():
 
 import paper_2604_16834_amd as hx  # noqa: E402
 from oracle import Oracle  # noqa: E402
-from workloads import make_params  # noqa: E402
+from workloads import conv_tap_offsets, make_params  # noqa: E402
+from gpu_common import rand_ct, rand_poly, w_residues  # noqa: E402
 
 
 @pytest.mark.parametrize("batch", [141, 143])
@@ -29,3 +30,62 @@ def test_large_ntt_batches_in_parts(batch):
         assert np.array_equal(hx.to_host(d[b]), orc.ntt_many(hx.to_host(first[b])[None], idx)[0]), b
     hx.ckks_ntt_inv(ctx, d, idx)
     assert torch.equal(d, first)
+
+
+def deferred_conv(ctx, p, level, width, cts, keys, masks, w, merged):
+    """cts, masks: on the device; keys by offset, None where nothing is rotated; w [c_out][c_in][9] integers."""
+    ext = [p.moduli[t] for t in list(range(level + 1)) + list(range(p.num_q, p.num_q + p.num_p))]
+    offs = conv_tap_offsets(width)
+    dkeys = [hx.ckks_key_load(ctx, keys[o], hx.ckks_galois_element(ctx, o)) if o in keys else None for o in offs]
+    outs = hx.he_conv_batched(ctx, 1, width, 1, level, cts, dkeys, masks, hx.from_host(w_residues(w, ext, len(ext) - 1)), w.shape[0],
+                              alignment=hx.HE_CONV_DEFERRED_MERGED if merged else hx.HE_CONV_DEFERRED_MODDOWN)
+    return [hx.to_host(o) for o in outs]
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,c_in,c_out,merged",
+                         [(12, 4, 2, 2, 3, 1, 1, True), (12, 5, 2, 3, 4, 3, 8, True), (12, 4, 1, 4, 3, 2, 5, False), (6, 3, 2, 2, 2, 3, 2, True),
+                          (13, 3, 3, 1, 2, 5, 3, True)])
+def test_inner_products_and_sum_in_one_kernel(log_n, num_q, num_p, dnum, level, c_in, c_out, merged):
+    """One to four digits, one to four outputs per thread and two groups of outputs (5, 8), channels in ones, twos and threes with a ragged
+    last pair, a ring of one workgroup per limb; uniform operands, weights of both signs up to 2^48."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    rng = np.random.default_rng(100 * c_in + c_out)
+    ext = [p.moduli[t] for t in orc.ext_moduli_idx(level)]
+    cts = [rand_ct(rng, p.moduli, level, orc.N) for _ in range(c_in)]
+    keys = {o: np.stack([np.stack([rand_poly(rng, p.moduli, orc.N) for _ in range(2)]) for _ in range(dnum)]) for o in conv_tap_offsets(4) if o}
+    masks = np.stack([rand_poly(rng, ext, orc.N) for _ in range(9)])
+    w = rng.integers(-2 ** 48, 2 ** 48, size=(c_out, c_in, 9))
+    want = orc.he_conv_deferred(cts, level, 4, keys, masks, w, merged=merged)
+    got = deferred_conv(ctx, p, level, 4, [hx.from_host(c) for c in cts], {o: hx.from_host(k) for o, k in keys.items()}, hx.from_host(masks), w, merged)
+    for o in range(c_out):
+        assert np.array_equal(got[o], want[o]), f"output {o}"
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,width,c_in,c_out",
+                         [(12, 5, 2, 3, 4, 2048, 2, 2), (13, 6, 2, 4, 5, 8, 19, 4), (13, 9, 3, 3, 6, 8, 33, 1), (14, 20, 5, 4, 17, 16, 9, 2),
+                          (15, 7, 2, 4, 6, 8, 16, 3), (16, 12, 8, 2, 11, 8, 9, 4), (16, 12, 12, 1, 11, 8, 17, 1)])
+@pytest.mark.parametrize("low", [False, True])
+def test_inner_products_and_sum_equal_stored_copies(log_n, num_q, num_p, dnum, level, width, c_in, c_out, low):
+    """Against the same layer with enough outputs for the stored copies, whose first outputs are the same: three taps without a rotation (rows as
+    long as the slots), more channels than a launch takes (the sums go on from the last one's), one wavefront for all taps of several
+    outputs and three; every operand at q - 1 (low: at 0 and 1 in turn) beside uniform ones."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx = hx.Context(p)
+    gen = torch.Generator(device="cuda").manual_seed(c_in)
+    live = list(range(level + 1))
+    q = torch.tensor(p.moduli, dtype=torch.int64, device="cuda")
+
+    def residues(*lead, limbs):
+        r = torch.randint(0, (1 << 63) - 1, (*lead, len(limbs), ctx.N), generator=gen, device="cuda").remainder_(q[limbs].unsqueeze(-1))
+        edge = (torch.arange(1024, device="cuda") & 1).expand(len(limbs), 1024) if low else (q[limbs] - 1).unsqueeze(-1).expand(len(limbs), 1024)
+        r[..., 512:1536] = edge
+        return r
+    cts = [residues(2, limbs=live) for _ in range(c_in)]
+    keys = {o: residues(dnum, 2, limbs=list(range(ctx.M))) for o in conv_tap_offsets(width) if o % (ctx.N // 2)}
+    masks = residues(9, limbs=live + list(range(num_q, ctx.M)))
+    w = np.random.default_rng(c_out).integers(-2 ** 31, 2 ** 31, size=(9, c_in, 9))
+    few = deferred_conv(ctx, p, level, width, cts, keys, masks, w[:c_out], True)
+    many = deferred_conv(ctx, p, level, width, cts, keys, masks, w, True)
+    for o in range(c_out):
+        assert np.array_equal(few[o], many[o]), f"output {o}"
