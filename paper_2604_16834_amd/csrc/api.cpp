@@ -682,11 +682,33 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
     return run_moddown(c, level, ws, n, items, st, false, mac);
 }
 
+// out = sum_b Rot(srcs[b] (.) mask) + add (.) add_mask for n <= ks_batch ciphertexts (mask, add, add_mask optional), where a key switch takes its
+// inner product inside the forward transforms' second pass: the products with the mask are formed as they are read, the inner products and, past
+// each item's rounding, the divisions by P are added up (launch_ntt_moddown_sum).  out may be add.
+int run_rotate_sum(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, const ckks_key* const* keys, const u32* gal, const u64* mask, const u64* add,
+                   const u64* add_mask, u64* out, const KsWs& ws, hipStream_t st) {
+    const u64 *c1s[KS_MAX_BATCH], *kd[KS_MAX_BATCH], *masks[KS_MAX_BATCH];
+    u64* vs[KS_MAX_BATCH];
+    for (u32 b = 0; b < n; b++) {
+        c1s[b] = srcs[b] + (size_t)(level + 1) * c->N;
+        kd[b] = keys[b]->d_key;
+        masks[b] = mask;
+        vs[b] = ws.v + b * ws.v_b;
+    }
+    if (int rc = run_modup(c, level, c1s, n, ws, st, true, mask ? masks : nullptr, gal)) return rc;
+    for (u32 b = 0; b < n; b++) ws.own[b] = c1s[b];  // (their products with the mask are formed where they are read)
+    const MacRotate rot = {srcs, gal, mask};
+    u32 n_part = 0;
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st, dropped_from(level, false), nullptr, &rot, &n_part));
+    HIP_TRY(launch_ntt_moddown_sum(c, level, ws.v, ws.v_b, n, n_part, ws.w, FinalItem{nullptr, nullptr, add_mask, out, 1, 0, add}, st));
+    return CKKS_OK;
+}
+
 // rotations of a merge of g blocks that share their launches, at most `most`
 u32 merge_batch(u32 g, u32 most) { return g - 1 < most ? (g > 1 ? g - 1 : 1) : most; }
 size_t ws_merge_in(const ckks_ctx* c, u32 level, u32 g, u32 nb) {
     const size_t N = c->N, L1 = level + 1;
-    return ws_ks(c, level, nb, nb) + 2 * blk((size_t)g * 2 * L1 * N) + blk(2 * L1 * N) + ws_rescale(c, level, 1);
+    return ws_ks(c, level, nb, nb) + (ntt_has_modup(c) ? 0 : 2 * blk((size_t)g * 2 * L1 * N)) + blk(2 * L1 * N) + ws_rescale(c, level, 1);
 }
 size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) { return ws_merge_in(c, level, g, merge_batch(g, ks_batch(c))); }
 
@@ -698,11 +720,22 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
     if (ar.used + ws_merge_in(c, level, g, nb) > ar.cap) nb = merge_batch(g, CT_BATCH);  // in a smaller workspace
     KsWs ws;
     bool ok = carve_ks(c, level, nb, nb, ar, ws);
-    u64* masked = ar.take((size_t)g * ct_elems);   // C_i (.) M
-    u64* rotated = ar.take((size_t)g * ct_elems);  // Rot(C_i (.) M, -i*sts), i >= 1
+    const bool sums = ntt_has_modup(c);                                   // run_rotate_sum
+    u64* masked = sums ? nullptr : ar.take((size_t)g * ct_elems);   // C_i (.) M
+    u64* rotated = sums ? nullptr : ar.take((size_t)g * ct_elems);  // Rot(C_i (.) M, -i*sts), i >= 1
     u64* total = ar.take(ct_elems);
     if (!ok || !ar.ok() || ar.used + ws_rescale(c, level, 1) > ar.cap)
         return set_err(c, CKKS_ERR_WORKSPACE_TOO_SMALL, "workspace too small for the merge");
+    const u64* in = total;
+    if (sums) {
+        for (u32 i0 = 1; i0 < g; i0 += nb) {
+            const u32 n = g - i0 < nb ? g - i0 : nb;
+            if (int rc = run_rotate_sum(c, level, n, cts + i0, keys + i0, gal + i0, mask, i0 == 1 ? cts[0] : total, i0 == 1 ? mask : nullptr, total, ws, st))
+                return rc;
+        }
+        if (g == 1) HIP_TRY(launch_mask_mul(c, level, &mask, cts, &total, 1, st));
+        return run_rescale(c, level, &in, L1 * N, &out, 1, ar.rest(), st);
+    }
     const u64* masks[KS_MAX_BATCH];
     u64* mouts[KS_MAX_BATCH];
     for (u32 i = 0; i < g; i++) masks[i] = mask, mouts[i] = masked + i * ct_elems;
@@ -722,7 +755,6 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
     terms[0] = masked;
     for (u32 i = 1; i < g; i++) terms[i] = rotated + i * ct_elems;
     HIP_TRY(launch_ct_sum(c, level, ptr_list(terms, g), g, total, st));
-    const u64* in = total;
     return run_rescale(c, level, &in, L1 * N, &out, 1, ar.rest(), st);
 }
 
@@ -811,6 +843,38 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
         const ckks_key* ks[KS_MAX_BATCH];
         u32 gs[KS_MAX_BATCH], nk = 0;
         u64* dsts[KS_MAX_BATCH];
+        // One ciphertext's rotations are added up in the division (several share each key instead), from a size on: with less to do the items that one
+        // workgroup takes in turn are a longer chain than the launches of the sum.  Fully connected layers, one by one / added up in us: 2^12, 6 + 3
+        // limbs 327 / 333, 2^13, 8 + 3 406 / 414, 2^14, 6 + 3 434 / 436, 16 + 8 (0.18 M coefficients) 790 / 772, 2^15, 12 + 4 1274 / 1246, 2^16, 24 + 8 2131 / 2080
+        if (n == 1 && ntt_has_modup(c) && (size_t)c->ext_limbs(l1) * N >= (size_t)1 << 17) {
+            const u64* terms[KS_MAX_BATCH];
+            u64* out = outs[c0];
+            const u64* add = nullptr;  // the blocks that stay where they are
+            u32 nt = 0;
+            for (u32 h = 0; h <= n_hi; h++) {
+                if (h < n_hi && g_hi[h] == 1) terms[nt++] = V + (size_t)h * ctl1;
+                if (nt == KS_MAX_BATCH || (h == n_hi && nt > 1) || (h == n_hi && nt == 1 && n_hi == 1)) {
+                    HIP_TRY(launch_ct_sum(c, l1, ptr_list(terms, nt), nt, out, st));
+                    add = terms[0] = out;
+                    nt = 1;
+                } else if (h == n_hi && nt == 1) {
+                    add = terms[0];
+                }
+            }
+            for (u32 h = 0; h <= n_hi; h++) {
+                if (h < n_hi && g_hi[h] != 1) {
+                    srcs[nk] = V + (size_t)h * ctl1;
+                    ks[nk] = hi_keys[h];
+                    gs[nk++] = g_hi[h];
+                }
+                if (nk == kb || (h == n_hi && nk)) {
+                    if ((rc = run_rotate_sum(c, l1, nk, srcs, ks, gs, nullptr, add, nullptr, out, ws, st))) return rc;
+                    add = out;
+                    nk = 0;
+                }
+            }
+            continue;
+        }
         for (u32 h = 0; h < n_hi; h++) {
             if (g_hi[h] == 1) continue;
             for (u32 b = 0; b < n; b++) {

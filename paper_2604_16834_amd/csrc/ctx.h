@@ -113,6 +113,9 @@ struct FwdEpilogue {
     PtrList8 vl2;
     size_t v2_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
+    // a sum of items (launch_ntt_moddown_sum): v is n_part partial sums, v_pstride apart
+    u32 n_part, pad;
+    size_t v_pstride;
     FinalBatch B;
 };
 
@@ -225,7 +228,8 @@ hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t sr
                       size_t dst_bstride, const PolyList& pl, u32 batch, hipStream_t st, const u64* const* src_ptrs = nullptr,
                       const FwdEpilogue* epilogue = nullptr, const TwF* inv_scale = nullptr, const u64* const* mul_ptrs = nullptr,
                       const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH, const u32* gals = nullptr);
-// gals (inverse, with src_ptrs, contexts with ntt_has_modup): batch item b is sigma_gals[b] of src_ptrs[b], gathered on load
+// gals (inverse, with src_ptrs, contexts with ntt_has_modup): batch item b is sigma_gals[b] of src_ptrs[b], gathered on load; with mul_ptrs
+// (without lin_k) sigma_gals[b] of the product
 // passes (inverse, two-pass rings): the first pass alone (a kernel that goes on from there follows: ntt_mid_*), or the second alone, in place
 // (the first has been done: launch_ntt_lo_mac with inv_from)
 // mul_ptrs (inverse, with src_ptrs, double-precision arithmetic): batch item b is src_ptrs[b] (.) mul_ptrs[b], formed on load;
@@ -284,9 +288,13 @@ struct MacProduct {
 struct MacRotate {
     const u64* const* c0;
     const u32* gs;
+    const u64* mask = nullptr;  // with n_part, [level+1][N]: the rotated ciphertexts are products with it (launch_ntt with gals and mul_ptrs)
 };
+// n_part (with rot): the positions below inv_from are added up over the items, into *n_part partial sums at outs[0], outs[1], ...
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr);
+                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr, u32* n_part = nullptr);
+// the division by P of the sum of n such items, one result: the item's `acc` is added, times `mask` if there is one
+hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v_bstride, u32 n, u32 n_part, u64* w, const FinalItem& item, hipStream_t st);
 // rings whose whole transforms run as one kernel (the whole limb-poly in one workgroup); key switches and rescales take them pass by
 // pass like the larger rings (see ntt_mid_moddown for what remains).  N = 2^12, whole-ring kernels / passes in us: one unhoisted rotation of
 // 4 + 2 limbs 38.7 / 29.1, of 21 + 8 45.7 / 37.2, eight 81.7 / 59.5; one hoisted 34.8 / 29.7; a product with its rescale 51.2 / 44.0;

@@ -362,8 +362,14 @@ __device__ __forceinline__ u64* item_dst(const NttArgs& args, const PolyList& pl
 // point (eight rotations of two limbs each at N = 2^16, sums added: 17.7 us in case 0, 14.2 us in case 3 with the rotated addend
 // inside the inner product).
 // i: limb (the list's dpos entry), bb: batch item (2 ciphertext + component), off: the slice's first point, t = 0..255
+// EM_SUM*: one result for several items (launch_ntt_moddown_sum): v is the sum of ep.n_part partial sums, and one ciphertext is added, masked
+// (EM_SUM_MASK), as it is (EM_SUM_ADD), or none.
+#define EM_SUM 5
+#define EM_SUM_ADD 6
+#define EM_SUM_MASK 7
 struct DivOperands {
     u64 v[8], v2[8], op[8];
+    double vs[8];
 };
 template <class A, int EM>
 __device__ __forceinline__ void div_request(const NttArgs& args, const FwdEpilogue& ep, u32 i, u32 bb, size_t off, u32 t, DivOperands& O) {
@@ -381,10 +387,40 @@ __device__ __forceinline__ void div_request(const NttArgs& args, const FwdEpilog
 #pragma unroll
             for (int j = 0; j < 8; j++) O.op[j] = 0;
         }
-    } else if (EM == 3 || EM == 4) {
-        const u64* op = (EM == 3 ? fi.acc + ((size_t)((bb & 1) * ep.n_out + i) << args.log_n) : fi.mask + ((size_t)i << args.log_n)) + off;
+    } else if (EM == 3 || EM == 4 || EM == EM_SUM_ADD || EM == EM_SUM_MASK) {
+        if (EM == EM_SUM_MASK) {
+            const u64* mask = fi.mask + ((size_t)i << args.log_n) + off;
+#pragma unroll
+            for (int j = 0; j < 8; j++) O.v2[j] = mask[t + 256 * j];
+        }
+        const u64* op = (EM != 4 ? fi.acc + ((size_t)((bb & 1) * ep.n_out + i) << args.log_n) : fi.mask + ((size_t)i << args.log_n)) + off;
 #pragma unroll
         for (int j = 0; j < 8; j++) O.op[j] = op[t + 256 * j];
+    }
+    if constexpr (EM >= EM_SUM) {  // residues below 2^50: four of them on a reduced sum stay below 2^53
+        const u64* part = ep.v + (((size_t)bb * ep.E + i) << args.log_n) + off + t;
+        const ModConstF mc = ((const ModConstF*)args.mc)[i];
+#pragma unroll
+        for (int j = 0; j < 8; j++) O.vs[j] = 0.0;
+        auto add_parts = [&](auto many, u32 s) {  // so many parts' words requested together
+            constexpr int M = decltype(many)::value;
+            u64 w[M][8];
+#pragma unroll
+            for (int i = 0; i < M; i++)
+#pragma unroll
+                for (int j = 0; j < 8; j++) w[i][j] = (part + min(s + i, ep.n_part - 1) * ep.v_pstride)[256 * j];
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                double sum = O.vs[j];
+#pragma unroll
+                for (int i = 0; i < M; i++) sum += s + i < ep.n_part ? f64m_from_u64(w[i][j]) : 0.0;
+                O.vs[j] = f64m_reduce(sum, mc.q, mc.qinv);
+            }
+        };
+        if (ep.n_part <= 2) add_parts(std::integral_constant<int, 2>(), 0);
+        else
+            for (u32 s = 0; s < ep.n_part; s += 4) add_parts(std::integral_constant<int, 4>(), s);
+        return;
     }
     const u64* vrow = (ep.use_vl ? ep.vl.p[bb >> 1] + (bb & 1) * ep.v_cstride + ((size_t)i << args.log_n)
                                  : ep.v + (((size_t)bb * ep.E + i) << args.log_n)) + off;
@@ -411,7 +447,10 @@ __device__ __forceinline__ void div_store(const NttArgs& args, const FwdEpilogue
         // below 0.75 q, one more reduction after the addend; every value below is exact
         const double q = mc.q, cvd = A::from_u64(cv), cvq = cvd / q;
         double vd[8];
-        if (ep.use_vl == 2) {  // v = ka * x + kb * y
+        if constexpr (EM >= EM_SUM) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) vd[j] = O.vs[j];
+        } else if (ep.use_vl == 2) {  // v = ka * x + kb * y
             const double ka = A::from_u64(ep.ka[i]), kb = A::from_u64(ep.kb[i]);
 #pragma unroll
             for (int j = 0; j < 8; j++)
@@ -424,8 +463,10 @@ __device__ __forceinline__ void div_store(const NttArgs& args, const FwdEpilogue
         for (int j = 0; j < 8; j++) {
             const u32 p = t + 256 * j;
             double r = A::mulmod(vd[j] - buf[LDS_PAD(p)], cvd, cvq, q);
-            if (EM == 1 || EM == 3) {
+            if (EM == 1 || EM == 3 || EM == EM_SUM_ADD) {
                 r = A::reduce(r + A::from_u64(O.op[j]), mc);
+            } else if (EM == EM_SUM_MASK) {
+                r = A::reduce(r + A::mulmod_any(A::from_u64(O.op[j]), A::from_u64(O.v2[j]), q, mc.qinv), mc);
             } else if (EM == 4) {
                 r = A::mulmod_any(r, A::from_u64(O.op[j]), q, mc.qinv);
             } else if (EM == 0) {
@@ -635,6 +676,7 @@ struct MacEpilogue {
     // the positions from inv_from on are what a division that follows drops: their sums leave in the form between the two passes of an
     // inverse transform (E: none of them)
     const double* itw_val;  // [M][N], NttArgs::tw_val of inverse transforms
+    // SUM (with ROT): the other positions' sums of all items of a workgroup are added up and stored once, as item tile.b's
     u32 inv_from, pad;
     // PROD: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
@@ -643,6 +685,8 @@ struct MacEpilogue {
     // ROT: item b is a rotation by gal[b] of the ciphertext (a0, D.own): the digits are those of sigma(D.own), the own-limb term and the
     // addend P sigma(a0) are gathered as they are read
     u32 gal[KS_MAX_BATCH];
+    // MASK (with SUM): the rotated ciphertext is the product of (a0, D.own) with mask [level+1][N]
+    const u64* mask;
     // LIN (with PROD): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
     PtrList8 lx, ly;
     size_t x_cstride, y_cstride;
@@ -709,10 +753,10 @@ __device__ __forceinline__ void mac_inverse_lo(double (&r0)[8], double (&r1)[8],
     }
 }
 
-// PROD, LIN, ROT (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
+// PROD, LIN, ROT, SUM, MASK (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
 // use, one round trip to memory per point.
-template <bool PROD, bool LIN, bool ROT>
+template <bool PROD, bool LIN, bool ROT, bool SUM = false, bool MASK = false>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs args, PolyList pl, MacEpilogue ep) {
     typedef ArithF64 A;
     typedef double E;
@@ -748,12 +792,15 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
 #pragma unroll
         for (int i = 0; i < 8; i++) raw[i] = hi0[(size_t)j0 * dstride + tid + 256 * i];
     }
+    const bool summed = SUM && e < ep.inv_from;
+    E acc0[8], acc1[8];
     for (u32 b = tile.b; b < args.batch; b += b_step) {
     const u64* key = ep.key.p[b] + (size_t)m_idx * N + off;
     const double* hi = (const double*)(ep.D.digits + b * ep.D.bstride) + (size_t)e * N + off;
-    E acc0[8], acc1[8];
+    if (!SUM || b == tile.b || !summed) {  // a sum over items starts from the last one's reduced sum (f64m_sum_due: so it may)
 #pragma unroll
-    for (int j = 0; j < 8; j++) acc0[j] = acc1[j] = 0.0;
+        for (int j = 0; j < 8; j++) acc0[j] = acc1[j] = 0.0;
+    }
     u32 j = j0;
     while (j < ep.beta) {
         u32 jn = j + 1;
@@ -867,6 +914,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
         const u64* kj = key + (size_t)own * 2 * kstride;
         const u64* yo = ep.D.own.p[b] + (size_t)e * N;
         const u64* co = ROT ? ep.a0.p[b] + (size_t)e * N : nullptr;
+        const u64* mo = MASK ? ep.mask + (size_t)e * N : nullptr;
         const u32 g = ROT ? ep.gal[b] : 1;
         const double pres = ROT ? mc.q - A::from_u64(ep.negp[e]) : 0.0;  // P mod q_e
         u32 x0 = (u32)off + tid;
@@ -874,13 +922,14 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
         constexpr int HP = ROT ? 4 : 8;  // points requested before the first is used
 #pragma unroll
         for (int h = 0; h < 8; h += HP) {
-            u64 ry[HP], rc[HP], rk0[HP], rk1[HP];
+            u64 ry[HP], rc[HP], rm[HP], rk0[HP], rk1[HP];
 #pragma unroll
             for (int i = 0; i < HP; i++) {
                 const u32 x = tid + 256 * (h + i);
                 if (ROT) {
                     const u32 xs = galois_gather_index(x0 + 256 * (h + i), g, args.log_n);
                     ry[i] = word_at(yo, xs), rc[i] = word_at(co, xs);
+                    if (MASK) rm[i] = word_at(mo, xs);
                 } else {
                     ry[i] = yo[off + x];
                 }
@@ -888,18 +937,24 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
             }
 #pragma unroll
             for (int i = 0; i < HP; i++) {
-                const double y = A::from_u64(ry[i]);
+                double y = A::from_u64(ry[i]), cc = ROT ? A::from_u64(rc[i]) : 0.0;
+                if (MASK) {  // below 0.75 q
+                    const double m = A::from_u64(rm[i]);
+                    y = A::mulmod_any(y, m, mc.q, mc.qinv);
+                    cc = A::mulmod_any(cc, m, mc.q, mc.qinv);
+                }
                 acc0[h + i] += A::mulmod_any(y, A::from_u64(rk0[i]), mc.q, mc.qinv);
-                if (ROT) acc0[h + i] += A::mulmod_any(A::from_u64(rc[i]), pres, mc.q, mc.qinv);
+                if (ROT) acc0[h + i] += A::mulmod_any(cc, pres, mc.q, mc.qinv);
                 acc1[h + i] += A::mulmod_any(y, A::from_u64(rk1[i]), mc.q, mc.qinv);
             }
         }
     }
     if (LIN) request_next();
-    u64* o0 = ep.out.p[b] + (size_t)e * N + off;
+    u64* o0 = ep.out.p[summed ? tile.b : b] + (size_t)e * N + off;
     u64* o1 = o0 + (size_t)ep.E * N;
 #pragma unroll
     for (int i = 0; i < 8; i++) acc0[i] = A::reduce(acc0[i], mc), acc1[i] = A::reduce(acc1[i], mc);
+    if (SUM && summed && b + b_step < args.batch) continue;  // uniform over the workgroup
     if (e >= ep.inv_from) {
         mac_inverse_lo(acc0, acc1, lds0, lds1, ep.itw_val + ((size_t)m_idx << args.log_n), TA, tid, mc, o0, o1);
     } else {
@@ -952,9 +1007,10 @@ __device__ __forceinline__ void load_permuted(const u64* __restrict__ poly, u32 
 
 // MUL (double-precision arithmetic, first pass, source list): the transform's input is the pointwise product of two
 // polynomials (the d2 = a1 (.) b1 of a ciphertext product), formed as the points are loaded: d2 itself is never stored.
-// GAL (likewise): it is the polynomial under the item's automorphism, gathered as it is loaded.
+// GAL (likewise): it is the polynomial under the item's automorphism, gathered as it is loaded (with MUL: the product under it).
 template <class A, int IT, bool MUL = false, bool GAL = false>
 __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 8))) void ntt_inv_lo_kernel(NttArgs args, PolyList pl) {
+    static_assert(!MUL || IT == 1, "the variants with two operands take one item");
     typedef typename A::E E;
     __shared__ E lds0[LDS_PADDED_WORDS];
     __shared__ E lds1[LDS_PADDED_WORDS];
@@ -977,6 +1033,7 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
     const size_t moff = ((size_t)pl_at(pl.spos, tile.a) << args.log_n) + off + 8 * tid;  // MUL: the multiplier's point
     if constexpr (GAL) {
         load_permuted(P.src, (u32)off + 8 * tid, args.gal[b0], args.log_n, raw);
+        if constexpr (MUL) load_permuted(args.mul_list.p[b0] + ((size_t)pl_at(pl.spos, tile.a) << args.log_n), (u32)off + 8 * tid, args.gal[b0], args.log_n, raw2);
     } else {
         const ulonglong2* in = reinterpret_cast<const ulonglong2*>(P.src + off + 8 * tid);
 #pragma unroll
@@ -1001,11 +1058,6 @@ __global__ __launch_bounds__(NTT_THREADS) __attribute__((amdgpu_waves_per_eu(3, 
                 const ulonglong2* in = reinterpret_cast<const ulonglong2*>(next + off + 8 * tid);
 #pragma unroll
                 for (int j = 0; j < 4; j++) raw[j] = in[j];
-            }
-            if constexpr (MUL) {
-                const ulonglong2* in2 = reinterpret_cast<const ulonglong2*>(args.mul_list.p[b0 + it + 1] + moff);
-#pragma unroll
-                for (int j = 0; j < 4; j++) raw2[j] = in2[j];
             }
         }
         inv_rows_pre<AR, 2>(v, wd, P.mc);
@@ -1470,6 +1522,140 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_inv_hi_kernel(NttArgs args, P
     }
 }
 
+// Division of a SUM of items by dropped moduli (launch_ntt_moddown_sum).  Each item rounds by itself, so each one's dropped limbs go through
+// their inverse transform and are centred; from there on the division is linear: sum_r (v_r - NTT(conv(y_r))) / P = (sum_r v_r - NTT(conv(sum_r y_r))) / P,
+// limb by limb modulo q_i.  So the centred residues are added up as integers (at most 16 of them, below 2^53) and there is one conversion and one
+// forward transform for all items, where each had its own.  Four blocks of 19 + 8 limbs merged at N = 2^16: 352 -> 283 us (a rotation's product with
+// its mask is formed as it is read, too).
+// The inverse transform's last pass of the items 2 r + comp, r < n_items, added up into item comp.  grid = (tiles, components x list)
+template <int LOG_HI>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_inv_hi_sum_kernel(NttArgs args, PolyList pl, u32 n_items) {
+    typedef ArithF64 A;
+    constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R;
+    const u32 tid = threadIdx.x, comp = blockIdx.y / pl.n, a = blockIdx.y % pl.n;
+    const PolyRef<A> P = poly_ref<A>(args, pl, comp, a);
+    u64* dst = P.dst + (size_t)blockIdx.x * CC;
+    const size_t item = (2 * args.dst_bstride) << args.log_n;
+    const TwF scale = args.inv_scale[pl_at(pl.mod, a)];
+    double raw[8], sum[8];
+    if constexpr (LOG_HI <= 3) {
+        constexpr int KC = 8 / R;
+        auto load = [&](u32 r) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) raw[i] = A::load_mid((dst + r * item)[((size_t)(i / KC) << 11) + (i % KC) * 256 + tid]);
+        };
+        load(0);
+        for (u32 r = 0; r < n_items; r++) {
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i] = raw[i];
+            if (r + 1 < n_items) load(r + 1);
+            inv_rows<A, LOG_HI, KC>(v, P.tw, 1, P.mc);
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const double t = f64m_centre(A::mulmod(v[i], scale.w, scale.wq, P.mc.q), P.mc.q);
+                sum[i] = r ? sum[i] + t : t;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i++) dst[((size_t)(i / KC) << 11) + (i % KC) * 256 + tid] = A::store_mid(sum[i]);
+    } else {
+        __shared__ __attribute__((aligned(16))) double lds[2][NTT_TILE];  // in turn: an item's reads and the next one's writes do not meet
+        constexpr int R8 = R / 8, S2 = LOG_HI - 3, KC2 = 8 / R8;
+        const u32 G = tid >> 5, cg = tid & 31, r0 = tid / CC, col = tid % CC;
+        auto load = [&](u32 r) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) raw[i] = A::load_mid((dst + r * item)[((size_t)(G * R8 + i / KC2) << 11) + cg * KC2 + i % KC2]);
+        };
+        load(0);
+        for (u32 r = 0; r < n_items; r++) {
+            double v[8];
+            double* buf = lds[r & 1];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i] = raw[i];
+            if (r + 1 < n_items) load(r + 1);
+            inv_rows<A, S2, KC2>(v, P.tw, 8 + G, P.mc);
+            if (S2 == 3) A::inv_end(v, P.mc);
+#pragma unroll
+            for (int i = 0; i < 8; i++) buf[(G * R8 + i / KC2) * CC + cg * KC2 + i % KC2] = v[i];
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 8; j++) v[j] = buf[(r0 + R8 * j) * CC + col];
+            inv_rows<A, 3, 1>(v, P.tw, 1, P.mc);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const double t = f64m_centre(A::mulmod(v[j], scale.w, scale.wq, P.mc.q), P.mc.q);
+                sum[j] = r ? sum[j] + t : t;
+            }
+        }
+        // (item 0's points of this tile were all read before the first barrier)
+#pragma unroll
+        for (int j = 0; j < 8; j++) dst[((size_t)(r0 + R8 * j) << 11) + col] = A::store_mid(sum[j]);
+    }
+}
+
+// The conversion of such a sum with the first pass of its forward transform, a target limb per workgroup.  The sums, up to 2^53, are reduced modulo the
+// target first; the constants' rows are taken four at a time (padded with zeros).  One launch of a kind per sum: neither source limbs that
+// several targets share (two: 21.8 us for 2 x 8 -> 19 limbs at N = 2^16, one: 20.9, twice the waves) nor numbers of terms known to the
+// compiler, as the kernel for every item has them, are worth their instantiations here.
+// grid = (tiles, targets x components)
+template <int LOG_HI>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_hi_conv_sum_kernel(NttArgs args, PolyList pl, ConvPrologue cp) {
+    typedef ArithF64 A;
+    constexpr int R = 1 << LOG_HI, CC = NTT_TILE / R, KC = LOG_HI <= 3 ? 8 / R : 1, R8 = LOG_HI <= 3 ? 1 : R / 8, S2 = LOG_HI <= 3 ? 1 : LOG_HI - 3, KC2 = 8 / R8;
+    const u32 tid = threadIdx.x, b = blockIdx.y / pl.n, a = blockIdx.y % pl.n, m_idx = pl_at(pl.mod, a), pos = pl_at(pl.dpos, a);
+    const size_t N = (size_t)1 << args.log_n;
+    const u32 r0 = tid / CC, col = tid % CC;
+    auto at = [&](int j) { return LOG_HI <= 3 ? ((u32)(j / KC) << 11) + (j % KC) * 256 + tid : ((r0 + R8 * j) << 11) + col; };
+    const double* y = cp.y + b * cp.y_bstride + (size_t)cp.lo * N + (size_t)blockIdx.x * CC;
+    ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+    const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+    ConstPtr<TwF> ce = const_ptr(cp.convf + (size_t)pos * cp.ap);
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) v[j] = 0.0;
+    for (u32 k8 = 0; k8 < cp.nd; k8 += 8) {  // a chain takes eight terms
+        double s[8], lo[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) s[j] = F64M_DOT_BASE, lo[j] = 0.0;
+        for (u32 k0 = k8; k0 < k8 + 8 && k0 < cp.nd; k0 += 4) {
+            double yv[4][8];
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+#pragma unroll
+                for (int j = 0; j < 8; j++) yv[k][j] = y[(size_t)min(k0 + k, cp.nd - 1) * N + at(j)];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const double w = ce[k0 + k].w;
+#pragma unroll
+                for (int j = 0; j < 8; j++) f64m_chain_add(s[j], lo[j], f64m_reduce(yv[k][j], mc.q, mc.qinv), w);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = f64m_reduce(v[j] + f64m_chain_join(s[j], lo[j], mc.q, mc.qinv), mc.q, mc.qinv);
+    }
+    const TwF* tw = (const TwF*)args.tw + ((size_t)m_idx << args.log_n);
+    u64* dst = args.dst + (((size_t)b * args.dst_bstride + pos) << args.log_n) + (size_t)blockIdx.x * CC;
+    if constexpr (LOG_HI <= 3) {
+        fwd_rows<A, LOG_HI, KC>(v, tw, 1, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) dst[at(j)] = A::store_mid(v[j]);
+    } else {
+        __shared__ __attribute__((aligned(16))) double lds[NTT_TILE];
+        const u32 G = tid >> 5, cg = tid & 31;
+        fwd_rows<A, 3, 1>(v, tw, 1, mc);
+#pragma unroll
+        for (int j = 0; j < 8; j++) lds[(r0 + R8 * j) * CC + col] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[i] = lds[(G * R8 + i / KC2) * CC + cg * KC2 + i % KC2];
+        A::fwd_begin(v, mc);
+        fwd_rows<A, S2, KC2>(v, tw, 8 + G, mc);
+#pragma unroll
+        for (int i = 0; i < 8; i++) dst[((size_t)(G * R8 + i / KC2) << 11) + cg * KC2 + i % KC2] = A::store_mid(v[i]);
+    }
+}
+
 // The last pass of an inverse transform, a basis conversion and the first pass of the forward transforms of its targets in one
 // kernel, for the rings of 2^13 and 2^14 points: a thread owns the R = 2^LOG_HI points of one column, which is all that the three act
 // on, so nothing goes through LDS.  It takes the column of every source limb through the inverse pass' LOG_HI stages (scaled and
@@ -1555,6 +1741,72 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_kernel(NttArgs args,
 #pragma unroll
         for (int r = 0; r < R; r++) dst[(size_t)r << 11] = A::store_mid(v[r]);
     }
+}
+
+// The two kernels of a sum's division (ntt_inv_hi_sum_kernel, ntt_fwd_hi_conv_sum_kernel) in one, for rings of up to 2^14 points: a thread takes its
+// column of every (source limb, item) through the inverse pass, adds the items up, and keeps the conversion's chain of one target.  The inverse
+// passes are repeated for every target, which costs less than a launch up to a count (see launch_ntt_moddown_sum).
+// grid = (2^11 columns / NTT_THREADS, targets x components)
+template <int LOG_HI>
+__global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_sum_kernel(NttArgs args, PolyList pl, ConvPrologue cp, MidPrologue mp, u32 n_items) {
+    typedef ArithF64 A;
+    constexpr int R = 1 << LOG_HI, AHEAD = 4;  // items requested together, while the AHEAD before them are transformed
+    const u32 col = blockIdx.x * NTT_THREADS + threadIdx.x, b = blockIdx.y / pl.n, a = blockIdx.y % pl.n, m_idx = pl_at(pl.mod, a), pos = pl_at(pl.dpos, a);
+    const size_t N = (size_t)1 << args.log_n, item = 2 * cp.y_bstride;
+    const double* y = cp.y + b * cp.y_bstride + (size_t)cp.lo * N + col;
+    ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
+    const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
+    ConstPtr<TwF> ce = const_ptr(cp.convf + (size_t)pos * cp.ap);
+    double raw[AHEAD][R], v[R], s[R], lo[R];
+    auto load = [&](u32 k, u32 r0) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++)
+#pragma unroll
+            for (int r = 0; r < R; r++) raw[i][r] = (y + (size_t)k * N + min(r0 + i, n_items - 1) * item)[(size_t)r << 11];
+    };
+    load(0, 0);
+#pragma unroll
+    for (int r = 0; r < R; r++) v[r] = 0.0, s[r] = F64M_DOT_BASE, lo[r] = 0.0;
+    for (u32 k = 0; k < cp.nd; k++) {
+        const u32 m_src = k ? mp.next + k - 1 : mp.first;
+        ConstPtr<ModConstF> ps = const_ptr((const ModConstF*)args.mc + m_src);
+        ConstPtr<TwF> pk = const_ptr(mp.scale + m_src), tw = const_ptr(mp.itw + ((size_t)m_src << args.log_n));
+        const ModConstF ms = {ps->q, ps->qinv, 0.0, 0.0};
+        const TwF scale = {pk->w, pk->wq};
+        const double w = ce[k].w;
+        double sum[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) sum[r] = 0.0;
+        for (u32 r0 = 0; r0 < n_items; r0 += AHEAD) {
+            double u[AHEAD][R];
+#pragma unroll
+            for (int i = 0; i < AHEAD; i++)
+#pragma unroll
+                for (int r = 0; r < R; r++) u[i][r] = raw[i][r];
+            if (r0 + AHEAD < n_items) load(k, r0 + AHEAD);
+            else if (k + 1 < cp.nd) load(k + 1, 0);
+#pragma unroll
+            for (int i = 0; i < AHEAD; i++) {
+                if (r0 + i >= n_items) break;  // uniform
+                inv_column<LOG_HI>(u[i], tw, ms);
+#pragma unroll
+                for (int r = 0; r < R; r++) sum[r] += f64m_centre(A::mulmod(u[i][r], scale.w, scale.wq, ms.q), ms.q);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) f64m_chain_add(s[r], lo[r], f64m_reduce(sum[r], mc.q, mc.qinv), w);
+        if ((k & 7) == 7 || k + 1 == cp.nd) {  // a chain takes eight terms
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                v[r] = f64m_reduce(v[r] + f64m_chain_join(s[r], lo[r], mc.q, mc.qinv), mc.q, mc.qinv);
+                s[r] = F64M_DOT_BASE, lo[r] = 0.0;
+            }
+        }
+    }
+    fwd_column<LOG_HI>(v, const_ptr((const TwF*)args.tw + ((size_t)m_idx << args.log_n)), mc);
+    u64* dst = args.dst + (((size_t)b * args.dst_bstride + pos) << args.log_n) + col;
+#pragma unroll
+    for (int r = 0; r < R; r++) dst[(size_t)r << 11] = A::store_mid(v[r]);
 }
 
 // ============================ rings of 2^12 points: the whole transform in one workgroup ============================
@@ -1843,6 +2095,12 @@ static u32 lo_items(u32 slices, u32 batch, u32 most) {
 template <class A, int IT>
 static void launch_inv_lo_it(dim3 grid, hipStream_t st, const NttArgs& args, const PolyList& pl, bool mul, bool gal) {
     if constexpr (std::is_same<A, ArithF64>::value) {
+        if constexpr (IT == 1) {
+            if (gal && mul) {
+                hipLaunchKernelGGL((ntt_inv_lo_kernel<A, IT, true, true>), grid, dim3(NTT_THREADS), 0, st, args, pl);
+                return;
+            }
+        }
         if (gal) {
             hipLaunchKernelGGL((ntt_inv_lo_kernel<A, IT, false, true>), grid, dim3(NTT_THREADS), 0, st, args, pl);
             return;
@@ -2065,7 +2323,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
     if (mid && (!conv || !conv->per || c->log_hi < 1)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (lin_k && (!mul_ptrs || pl.n != 1)) return hipErrorInvalidValue;
-    if (gals && (!inverse || !src_ptrs || mul_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
+    if (gals && (!inverse || !src_ptrs || lin_k || !ntt_has_modup(c))) return hipErrorInvalidValue;
     if (epilogue && epilogue->use_vl == 2 && !c->ntt_f64) return hipErrorInvalidValue;
     if (src_ptrs && batch > KS_MAX_BATCH) return hipErrorInvalidValue;
     if (epilogue && (inverse || !ntt_has_epilogue(c) || batch > 2 * KS_MAX_BATCH)) return hipErrorInvalidValue;
@@ -2180,7 +2438,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                 dim3 g1 = grid_lo;
                 if (args.lo_group) g1.y = batch;
                 else g1.x = batch;
-                launch_inv_lo<ArithF64>(1, g1, st, args, pl, true, false);
+                launch_inv_lo<ArithF64>(1, g1, st, args, pl, true, gals != nullptr);
             }
             else lo(args, pl);
         }
@@ -2374,8 +2632,8 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 }
 
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot) {
-    if (!ntt_has_modup(c) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
+                             hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot, u32* n_part) {
+    if (!ntt_has_modup(c) || (n_part && !rot) || (rot && rot->mask && !n_part) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     NttArgs args = {};
     args.mc = c->d_mcf;
@@ -2416,6 +2674,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     ep.itw_val = c->d_itwf_val;
     ep.inv_from = inv_from;
     ep.pad = 0;
+    ep.mask = rot ? rot->mask : nullptr;
     const bool lin = prod && prod->lin_x;
     if (lin && (!prod->lin_y || !prod->ka || !prod->kb)) return hipErrorInvalidValue;
     ep.x_cstride = lin ? prod->x_cstride : 0;
@@ -2437,14 +2696,17 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     const u32 items = lo_items(slices, n, 4), b_least = n < 2 ? n : 2;
     const u32 b_ext = (n + items - 1) / items < b_least ? b_least : (n + items - 1) / items;
     const dim3 grid = args.lo_group ? dim3(args.lo_group, b_ext, slices / args.lo_group) : dim3(b_ext, slices);
+    if (n_part) *n_part = b_ext;
     // in: the transformed rows, the own limbs, the addends, the keys (once per distinct key); out: two components
     if (lin) n_add = 4.0 * n;  // two components of two ciphertexts
     ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (n_tr + (prod ? 4.0 : (rot ? 2.0 : 1.0)) * (level + 1.0) + 2.0 * E) + n_add * (level + 1.0) + n_keys * 2.0 * beta * E),
                    0.5 * n * n_tr * c->N * c->log_lo);
     // which operands join after the digits is the same for the whole launch: one instantiation per case
-#define LO_MAC_LAUNCH(PROD, LIN, ROT) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<PROD, LIN, ROT>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
+#define LO_MAC_LAUNCH(...) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<__VA_ARGS__>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
     if (lin) LO_MAC_LAUNCH(true, true, false);
     else if (prod) LO_MAC_LAUNCH(true, false, false);
+    else if (rot && rot->mask) LO_MAC_LAUNCH(false, false, true, true, true);
+    else if (n_part) LO_MAC_LAUNCH(false, false, true, true);
     else if (rot) LO_MAC_LAUNCH(false, false, true);
     else LO_MAC_LAUNCH(false, false, false);
 #undef LO_MAC_LAUNCH
@@ -2471,4 +2733,99 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
                             merged ? c->num_q : c->num_q + 1};
     cp.per = mid_per;
     return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);
+}
+
+// v: [2][E][N] per item, v_bstride apart: the items' dropped limbs have been through the first pass of their inverse transform, their other limbs are
+// n_part partial sums in the places of the first n_part items (launch_ntt_lo_mac with n_part).  w: [2][level+1][N] scratch.
+hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v_bstride, u32 n, u32 n_part, u64* w, const FinalItem& item, hipStream_t st) {
+    const u32 E = c->ext_limbs(level), n_out = level + 1, k = c->num_p;
+    if (!ntt_has_modup(c) || n == 0 || n > KS_MAX_BATCH || n_part == 0 || n_part > n || (item.mask && !item.acc) || item.add0 || item.add1 || v_bstride != 2 * (size_t)E * c->N)
+        return hipErrorInvalidValue;
+    NttArgs args = {};
+    args.mc = c->d_mcf;
+    args.log_n = c->log_n;
+    args.log_lo = c->log_lo;
+    args.log_hi = c->log_hi;
+    PolyList dropped, pl;
+    for (u32 a = 0; a < CKKS_MAX_MODULI; a++) {
+        dropped.spos[a] = dropped.dpos[a] = (unsigned char)(a < k ? n_out + a : 0);
+        dropped.mod[a] = (unsigned char)(a < k ? c->num_q + a : 0);
+        pl.spos[a] = pl.dpos[a] = pl.mod[a] = (unsigned char)(a < n_out ? a : 0);
+    }
+    dropped.n = k;
+    pl.n = n_out;
+    ConvPrologue cp = {};
+    cp.y = (const double*)v;
+    cp.y_bstride = (size_t)E * c->N;
+    cp.convf = c->d_moddown_f;
+    cp.lo = n_out;
+    cp.nd = k;
+    cp.ap = c->k_pad;
+    const MidPrologue mp = {c->d_itwf, c->d_itwf_val, c->d_moddown_prep_f, c->num_q, c->num_q + 1};
+    const u32 tiles = c->N >> CKKS_TILE_LOG;
+    const dim3 block(NTT_THREADS);
+#define BY_LOG_HI(LAUNCH)                     \
+    switch (c->log_hi) {                      \
+        case 1: LAUNCH(1); break;             \
+        case 2: LAUNCH(2); break;             \
+        case 3: LAUNCH(3); break;             \
+        case 4: LAUNCH(4); break;             \
+        case 5: LAUNCH(5); break;             \
+        case 6: LAUNCH(6); break;             \
+        default: return hipErrorInvalidValue; \
+    }
+    // In one kernel on rings of 2^12, and on those of 2^13 with few targets (the inverse passes are repeated for each), while a thread's columns are not
+    // too many.  Merges in us, in two / in one: 2^12, 5 + 2 limbs, one item (2 columns) 48.8 / 45.7, 7 + 4, seven (28) 54.5 / 54.0, 24 + 8, seven
+    // (56) 70.8 / 77.4; 2^13, 7 + 3, one (3, seven targets) 52.8 / 51.5, 14 + 7, three
+    // (21, eleven targets) 61.1 / 65.1; 2^14, 14 + 7, two 66.9 / 77.1
+    const bool mid = (c->log_hi == 1 && n * k <= 48) || (c->log_hi == 2 && n_out <= 6 && n * k <= 12);
+    if (!mid) {
+        args.tw = c->d_itwf;
+        args.src = args.dst = v;
+        args.src_bstride = args.dst_bstride = E;
+        args.inv_scale = c->d_moddown_prep_f;
+        ProfScope ps__(c, K_NTT_INV_HI, st, 16.0 * c->N * k * (n + 1.0), (double)n * c->N * k * c->log_hi);
+#define INV_HI_SUM(H) hipLaunchKernelGGL((ntt_inv_hi_sum_kernel<H>), dim3(tiles, 2 * k), block, 0, st, args, dropped, n)
+        BY_LOG_HI(INV_HI_SUM)
+#undef INV_HI_SUM
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    args.tw = c->d_twf;
+    args.tw_val = c->d_twf_val;
+    args.src = args.dst = w;
+    args.src_bstride = args.dst_bstride = n_out;
+    args.inv_scale = nullptr;
+    args.batch = 2;
+    {
+        ProfScope ps__(c, K_NTT_FWD_HI, st, 16.0 * c->N * ((mid ? n : 1.0) * k + n_out), (double)c->N * n_out * c->log_hi);
+#define CONV_SUM(H) hipLaunchKernelGGL((ntt_fwd_hi_conv_sum_kernel<H>), dim3(tiles, 2 * n_out), block, 0, st, args, pl, cp)
+#define MID_SUM(H) hipLaunchKernelGGL((ntt_mid_conv_sum_kernel<H>), dim3((1u << CKKS_TILE_LOG) / NTT_THREADS, 2 * n_out), block, 0, st, args, pl, cp, mp, n)
+        if (!mid) {
+            BY_LOG_HI(CONV_SUM)
+        } else if (c->log_hi == 1) MID_SUM(1);
+        else MID_SUM(2);
+#undef CONV_SUM
+#undef MID_SUM
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+#undef BY_LOG_HI
+    FwdEpilogue ep = {};
+    ep.v = v;
+    ep.cinv = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q;
+    ep.mci = c->d_mc;
+    ep.E = E;
+    ep.n_out = n_out;
+    ep.num_q = c->num_q;
+    ep.n_part = n_part;
+    ep.v_pstride = v_bstride;
+    ep.B.it[0] = item;
+    const u32 slices = n_out << c->log_hi;
+    for (u32 g = 64; g >= 8; g >>= 1)
+        if (slices % g == 0) { args.lo_group = g; break; }
+    const dim3 grid = args.lo_group ? dim3(args.lo_group, 2, slices / args.lo_group) : dim3(2, slices);
+    ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * c->N * n_out * (2.0 + n_part + (item.acc ? 1.0 : 0.0)), (double)c->N * n_out * c->log_lo);
+    if (item.mask) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM_MASK>), grid, block, 0, st, args, pl, ep);
+    else if (item.acc) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM_ADD>), grid, block, 0, st, args, pl, ep);
+    else hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM>), grid, block, 0, st, args, pl, ep);
+    return hipGetLastError();
 }

@@ -89,3 +89,58 @@ def test_inner_products_and_sum_equal_stored_copies(log_n, num_q, num_p, dnum, l
     many = deferred_conv(ctx, p, level, width, cts, keys, masks, w, True)
     for o in range(c_out):
         assert np.array_equal(few[o], many[o]), f"output {o}"
+
+
+def uniform(ctx, p, seed):
+    """A source of [*lead][limbs][N] residues on the device; the first kilobyte of words is q - 1, the next 0 and 1 in turn."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.tensor(p.moduli, dtype=torch.int64, device="cuda")
+
+    def residues(*lead, limbs):
+        r = torch.randint(0, (1 << 63) - 1, (*lead, len(limbs), ctx.N), generator=gen, device="cuda").remainder_(q[limbs].unsqueeze(-1))
+        r[..., :128] = (q[limbs] - 1).unsqueeze(-1)
+        r[..., 128:256] = torch.arange(128, device="cuda") & 1
+        return r
+    return residues, q
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g", [(12, 4, 1, 4, 3, 16), (12, 9, 12, 1, 8, 2), (13, 5, 3, 2, 4, 5), (14, 9, 9, 1, 7, 3), (14, 8, 2, 4, 1, 16),
+                                                            (15, 20, 7, 3, 18, 4), (16, 12, 4, 4, 11, 2), (16, 3, 3, 1, 2, 9), (17, 3, 2, 2, 2, 3)])
+def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
+    """Products, rotations, sum and rescale one by one: one to three items per partial sum and sums of up to fifteen, one to twelve special
+    primes, one and two targets per workgroup with a ragged last group, every number of rows."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx = hx.Context(p)
+    residues, q = uniform(ctx, p, 31 * g + log_n)
+    live = list(range(level + 1))
+    sts = ctx.N // 2 // g
+    cts, mask = [residues(2, limbs=live) for _ in range(g)], residues(limbs=live)
+    keys = [None] + [hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, -i * sts)) for i in range(1, g)]
+    got = hx.he_accumulator_merge(ctx, cts, level, sts, mask, keys)
+    total = torch.zeros_like(cts[0])
+    for i in range(g):
+        t = hx.ckks_ptct_mac(ctx, [mask], [cts[i]], level)
+        if i:
+            t = hx.ckks_rotate_hoisted(ctx, t, level, [-i * sts], [keys[i]], False)[0]
+        total = (total + t).remainder_(q[live].unsqueeze(-1))
+    assert torch.equal(got, hx.ckks_rescale(ctx, total, level))
+
+
+@pytest.mark.parametrize("log_n,num_p,lo,hi", [(13, 13, [0, 5], [0, 7, 9]), (15, 2, [1], list(range(3, 40, 2))), (16, 4, [0, 3], [0, 0, 4, 0]), (15, 2, [2], [0]),
+                                               (15, 2, [2], [0] * 17 + [5, 6])])
+def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_p, lo, hi):
+    """One ciphertext's second rotations are added up in the division; two, which share their keys, take them one by one.  With more blocks than a
+    launch takes, several blocks that stay where they are, and nothing else."""
+    p = make_params(log_n, 5, num_p, 3)
+    ctx = hx.Context(p)
+    level = 3
+    residues, _ = uniform(ctx, p, log_n + len(hi))
+    live = list(range(level + 1))
+    cts, keys = [residues(2, limbs=live) for _ in range(2)], {}
+    for o in set(lo + hi) - {0}:
+        keys[o] = hx.ckks_key_load(ctx, residues(3, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o))
+    masks = [[residues(limbs=live) for _ in lo] for _ in hi]
+    run = lambda c: hx.he_relayout_two_rotations(ctx, c, level, lo, [keys.get(o) for o in lo], hi, [keys.get(o) for o in hi], masks)
+    two = run(cts)
+    for i in range(2):
+        assert torch.equal(run(cts[i:i + 1])[0], two[i]), i
