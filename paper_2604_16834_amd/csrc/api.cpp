@@ -203,6 +203,7 @@ u32 dropped_from(u32 level, bool merged) { return merged ? level : level + 1; }
 // items[r] says what is added to / multiplied into the r-th result and where it goes ([2][level+1][N]).
 // merged: the division is by P*q_level (ModDown and rescale in one): the dropped limbs are position
 // level and the special primes, the results are [2][level][N].
+// items null (with lo_done): all but the second pass of the converted parts' forward transforms and the last step (run_inner_divide).
 // lo_done: the dropped limbs have been through the first pass of their inverse transform (launch_ntt_lo_mac with inv_from).
 int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const FinalItem* items, hipStream_t st, bool merged = false,
                 bool lo_done = false) {
@@ -216,6 +217,10 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
             if (!lo_done || !mid)
                 HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, dl, 2 * n, st, nullptr, nullptr, c->d_moddown_rs_prep_f + (size_t)level * c->M,
                                    nullptr, nullptr, lo_done ? NTT_HI : (mid ? NTT_LO : NTT_BOTH)));
+            if (!items) {
+                HIP_TRY(launch_ntt_moddown(c, level, true, (const double*)ws.v, ws.w, 2 * n, st, nullptr, mid));
+                return CKKS_OK;
+            }
             const FwdEpilogue ep = moddown_epilogue(c, level, true, ws.v, items, n);
             HIP_TRY(launch_ntt_moddown(c, level, true, (const double*)ws.v, ws.w, 2 * n, st, &ep, mid));
             return CKKS_OK;
@@ -235,6 +240,10 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
         if (!lo_done || !mid)
             HIP_TRY(launch_ntt(c, true, ws.v, E, ws.v, E, range_list(L1, k, c->num_q), 2 * n, st, nullptr, nullptr, c->d_moddown_prep_f, nullptr, nullptr,
                                lo_done ? NTT_HI : (mid ? NTT_LO : NTT_BOTH)));
+        if (!items) {
+            HIP_TRY(launch_ntt_moddown(c, level, false, (const double*)ws.v, ws.w, 2 * n, st, nullptr, mid));
+            return CKKS_OK;
+        }
         const FwdEpilogue ep = moddown_epilogue(c, level, false, ws.v, items, n);
         HIP_TRY(launch_ntt_moddown(c, level, false, (const double*)ws.v, ws.w, 2 * n, st, &ep, mid));
         return CKKS_OK;
@@ -248,6 +257,34 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
     }
     HIP_TRY(launch_ntt(c, false, ws.w, L1, ws.w, L1, range_list(0, L1, 0), 2 * n, st));
     HIP_TRY(launch_moddown_final(c, level, false, ws.v, ws.w, items, n, st));
+    return CKKS_OK;
+}
+
+// Inner products (launch_ntt_lo_mac: prod or rot) and their division, outs[b] = (..) / P + accs[b] (merged: / (P q_level)).  Large launches take the inner
+// products of the limbs that stay inside the division's last pass, when the converted dropped limbs are there: the sums are neither written
+// nor read back, and one fetch of a slice's twiddles serves the digits and both components of the converted part.  Small ones take
+// all positions at once, as the dropped limbs' launch alone leaves CUs idle and the other limbs' digits wait behind it.  All at once / inside the division in us,
+// by slices (limbs that stay x items x blocks of 2^11): six rotations at N = 2^13, 7 + 3 limbs (168) 42 / 52, one at 2^15, 14 + 5 (208) 60 / 68, a product at
+// 2^16, 13 + 8 (416) 101 / 103, twelve rotations at 2^13, 14 + 7 (624) 83 / 86; a product at 2^16, 24 + 8 (768) 163 / 159, six rotations, 6 + 3 (960) 130 / 125,
+// twelve at 2^14, 14 + 5 (1248) 166 / 158, at 2^16, 21 + 8 (8064) 981 / 935, activations of sixteen, 20 + 7, 2^14 (1152) 1151 / 1061, 2^16 (4608) 4443 / 4107
+#define DIVIDE_INSIDE_SLICES 768
+int run_inner_divide(const ckks_ctx* c, u32 level, const KsWs& ws, const u64* const* keys, u32 n, u64* const* outs, const u64* const* accs, hipStream_t st,
+                     bool merged, const MacProduct* prod, const MacRotate* rot) {
+    u64* vs[KS_MAX_BATCH];
+    for (u32 b = 0; b < n; b++) vs[b] = ws.v + b * ws.v_b;
+    const u32 from = dropped_from(level, merged);
+    if (c->log_hi < 2 || (from * n << c->log_hi) < DIVIDE_INSIDE_SLICES) {
+        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, from, prod, rot));
+        FinalItem items[KS_MAX_BATCH];
+        for (u32 b = 0; b < n; b++) items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
+        return run_moddown(c, level, ws, n, items, st, merged, true);
+    }
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, from, prod, rot, nullptr, nullptr, true));
+    if (int rc = run_moddown(c, level, ws, n, nullptr, st, merged, true)) return rc;
+    const u64* tab = merged ? c->moddown_rs_table(level) : c->d_moddown;
+    const u32 kp = merged ? c->k2_pad : c->k_pad;
+    const MacDivide div = {(const double*)ws.w, tab + 2 * kp + (size_t)kp * c->num_q, outs, accs};
+    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, from, prod, rot, nullptr, &div));
     return CKKS_OK;
 }
 
@@ -352,13 +389,9 @@ struct LinAddend {
 int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstride, const u64* const* b, const u64* const* b1, const u64* d_rlk,
                 u64* const* outs, u32 n, const KsWs& ws, hipStream_t st, bool merged, const LinAddend* lin = nullptr) {
     const u64 *a1[KS_MAX_BATCH], *keys[KS_MAX_BATCH];
-    u64* vs[KS_MAX_BATCH];
-    FinalItem items[KS_MAX_BATCH];
     for (u32 i = 0; i < n; i++) {
         a1[i] = a[i] + a_cstride;
-        vs[i] = ws.v + i * ws.v_b;
         keys[i] = d_rlk;
-        items[i] = FinalItem{nullptr, nullptr, nullptr, outs[i], 1, 0};
     }
     int rc = run_modup(c, level, a1, n, ws, st, true, b1);
     if (rc) return rc;
@@ -371,8 +404,7 @@ int run_product(const ckks_ctx* c, u32 level, const u64* const* a, size_t a_cstr
         prod.y_cstride = lin->y_cstride;
         prod.kb = lin->kb;
     }
-    HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, dropped_from(level, merged), &prod));
-    return run_moddown(c, level, ws, n, items, st, merged, true);
+    return run_inner_divide(c, level, ws, keys, n, outs, nullptr, st, merged, &prod, nullptr);
 }
 
 // n products a[b]*b[b] (as many as ks_batch, CT_BATCH without the fused inner product) with relinearisation (operands possibly at a higher level:
@@ -663,23 +695,20 @@ int run_rotate_batch(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs
     const size_t L1 = level + 1;
     const bool mac = ntt_has_modup(c);
     const u64 *c1s[KS_MAX_BATCH], *kd[KS_MAX_BATCH];
-    u64* vs[KS_MAX_BATCH];
     FinalItem items[KS_MAX_BATCH];
     for (u32 b = 0; b < n; b++) {
         c1s[b] = srcs[b] + L1 * c->N;
         kd[b] = keys[b]->d_key;
-        vs[b] = ws.v + b * ws.v_b;
         items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
     }
     int rc = run_modup(c, level, c1s, n, ws, st, mac, nullptr, mac ? gal : nullptr);
     if (rc) return rc;
     if (mac) {
         const MacRotate rot = {srcs, gal};
-        HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), kd, vs, n, st, dropped_from(level, false), nullptr, &rot));
-    } else {
-        HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), kd, gal, srcs, ws.v, ws.v_b, n, st));
+        return run_inner_divide(c, level, ws, kd, n, outs, accs, st, false, nullptr, &rot);
     }
-    return run_moddown(c, level, ws, n, items, st, false, mac);
+    HIP_TRY(launch_key_inner_items(c, level, dsrc(c, ws, 0), kd, gal, srcs, ws.v, ws.v_b, n, st));
+    return run_moddown(c, level, ws, n, items, st);
 }
 
 // out = sum_b Rot(srcs[b] (.) mask) + add (.) add_mask for n <= ks_batch ciphertexts (mask, add, add_mask optional), where a key switch takes its

@@ -241,7 +241,7 @@ hipError_t launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, size_t sr
 inline bool ntt_has_modup(const ckks_ctx* c) { return c->ntt_f64 && c->log_n > CKKS_TILE_LOG && c->d_modup_prep_f != nullptr; }
 // The same for ModDown's conversion: y are the 2*batch extended polynomials ([E][N] each, the dropped limbs left as scaled
 // centred doubles by launch_ntt with the moddown prep table), dst the converted dropped part ([n_out][N] per polynomial,
-// NTT form), epilogue what the second pass does with it.  merged: the dropped set is {q_level, p_0..p_{k-1}}.
+// NTT form), epilogue what the second pass does with it (null: the second pass is left out).  merged: the dropped set is {q_level, p_0..p_{k-1}}.
 hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const double* y, u64* dst, u32 batch, hipStream_t st,
                               const FwdEpilogue* epilogue, u32 mid_per = 0);
 // The same for the rescale: y [batch][N] is the dropped limb `level` of every component (centred doubles, from launch_ntt
@@ -291,8 +291,17 @@ struct MacRotate {
     const u64* mask = nullptr;  // with n_part, [level+1][N]: the rotated ciphertexts are products with it (launch_ntt with gals and mul_ptrs)
 };
 // n_part (with rot): the positions below inv_from are added up over the items, into *n_part partial sums at outs[0], outs[1], ...
+// dropped_only: nothing but the positions from inv_from on.  div: nothing but those below it, and the division's last step on them: outs[b] [2][inv_from][N] =
+// (sums - w) cinv + adds[b], w what launch_ntt_moddown left without an epilogue.
+struct MacDivide {
+    const double* w;
+    const u64* cinv;
+    u64* const* outs;
+    const u64* const* adds;  // or null
+};
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr, u32* n_part = nullptr);
+                             hipStream_t st, u32 inv_from, const MacProduct* prod = nullptr, const MacRotate* rot = nullptr, u32* n_part = nullptr,
+                             const MacDivide* div = nullptr, bool dropped_only = false);
 // the division by P of the sum of n such items, one result: the item's `acc` is added, times `mask` if there is one
 hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v_bstride, u32 n, u32 n_part, u64* w, const FinalItem& item, hipStream_t st);
 // rings whose whole transforms run as one kernel (the whole limb-poly in one workgroup); key switches and rescales take them pass by

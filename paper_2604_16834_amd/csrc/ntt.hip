@@ -677,7 +677,13 @@ struct MacEpilogue {
     // inverse transform (E: none of them)
     const double* itw_val;  // [M][N], NttArgs::tw_val of inverse transforms
     // SUM (with ROT): the other positions' sums of all items of a workgroup are added up and stored once, as item tile.b's
-    u32 inv_from, pad;
+    u32 inv_from, first;  // first: the position that the grid's first slices belong to
+    // DIV: the division's last step instead of stores: w are the converted dropped parts behind the first pass of their forward transform
+    // ([2 * item + component][n_out][N]), cinv the multipliers (FwdEpilogue), res the results, add what is added to them (entries may be null)
+    const double* w;
+    const u64* cinv;
+    PtrList8 add;
+    OutList8 res;
     // PROD: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
     // addends are d0 = a0 (.) b0 and d1 = a0 (.) b1 + a1 (.) b0 (D.own is not read)
@@ -753,10 +759,45 @@ __device__ __forceinline__ void mac_inverse_lo(double (&r0)[8], double (&r1)[8],
     }
 }
 
-// PROD, LIN, ROT, SUM, MASK (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
+// The forward lo pass' four rounds on v; the results sit in lds1, point p at LDS_PAD(p), behind a barrier.
+__device__ __forceinline__ void fwd_lo_rounds(double (&v)[8], double* lds0, double* lds1, u32 tid, const double (&wa)[7], const double (&wb)[7],
+                                              const double (&wc)[7], const double (&wd)[6], const ModConstF& mc) {
+    typedef ArithF64 A;
+    typedef ArithF64W AW;
+    const u32 d3 = tid >> 5, x5 = tid & 31, d2 = (tid >> 2) & 7, d0 = tid & 3;
+    A::fwd_begin(v, mc);
+    fwd_rows_pre<AW, 3>(v, wa, mc);
+#pragma unroll
+    for (int i = 0; i < 8; i++) lds0[LDS_PAD(tid + 256 * i)] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = lds0[LDS_PAD(d3 * 256 + 32 * i + x5)];
+    A::fwd_begin(v, mc);
+    fwd_rows_pre<AW, 3>(v, wb, mc);
+#pragma unroll
+    for (int i = 0; i < 8; i++) lds1[LDS_PAD(d3 * 256 + 32 * i + x5)] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = lds1[LDS_PAD(d3 * 256 + d2 * 32 + 4 * i + d0)];
+    A::fwd_begin(v, mc);
+    fwd_rows_pre<AW, 3>(v, wc, mc);
+#pragma unroll
+    for (int i = 0; i < 8; i++) lds0[LDS_PAD(d3 * 256 + d2 * 32 + 4 * i + d0)] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = lds0[LDS_PAD(8 * tid + i)];
+    fwd_rows_pre<AW, 2>(v, wd, mc);
+    fwd_rows_pre<AW, 2>(v + 4, wd + 3, mc);
+    A::fwd_end(v, mc);
+#pragma unroll
+    for (int i = 0; i < 8; i++) lds1[LDS_PAD(8 * tid + i)] = v[i];
+    __syncthreads();
+}
+
+// PROD, LIN, ROT, SUM, MASK, DIV (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
 // use, one round trip to memory per point.
-template <bool PROD, bool LIN, bool ROT, bool SUM = false, bool MASK = false>
+template <bool PROD, bool LIN, bool ROT, bool SUM = false, bool MASK = false, bool DIV = false>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs args, PolyList pl, MacEpilogue ep) {
     typedef ArithF64 A;
     typedef double E;
@@ -764,7 +805,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     __shared__ E lds1[LDS_PADDED_WORDS];
     const u32 tid = threadIdx.x;
     const LoTile tile = lo_tile(args.log_hi, args.lo_group);
-    const u32 e_at = tile.a + ep.inv_from, e = e_at < ep.E ? e_at : e_at - ep.E;  // the dropped limbs, the longer work, first
+    static_assert(!DIV || !SUM, "");
+    const u32 e_at = tile.a + ep.first, e = e_at < ep.E ? e_at : e_at - ep.E;  // the dropped limbs, the longer work, first
     const u32 blk = tile.blk, m_idx = pl_at(pl.mod, e);
     // the batch items of this workgroup: tile.b, tile.b + (the grid's extent over items), ...: a workgroup that takes several
     // fetches the slice's twiddles (half as many bytes as an item's points) once for all of them and requests an item's first
@@ -787,11 +829,23 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     load_tw_w<2>(tw, 512 * TA + 2 * tid + 1, wd + 3);
     const u32 j0 = own == 0 ? 1 : 0;  // first digit to transform
     E v[8], raw[8];
-    if (j0 < ep.beta) {
-        const double* hi0 = (const double*)(ep.D.digits + tile.b * ep.D.bstride) + (size_t)e * N + off;
+    // DIV: the converted parts of item b
+    auto request_w = [&](u32 b, u32 comp) {
+        const double* w = ep.w + ((size_t)(2 * b + comp) * ep.inv_from + e) * N + off;
 #pragma unroll
-        for (int i = 0; i < 8; i++) raw[i] = hi0[(size_t)j0 * dstride + tid + 256 * i];
-    }
+        for (int i = 0; i < 8; i++) raw[i] = w[tid + 256 * i];
+    };
+    auto request_first = [&](u32 b) {  // the first points of item b
+        if (j0 < ep.beta) {
+            const double* hi0 = (const double*)(ep.D.digits + b * ep.D.bstride) + (size_t)e * N + off;
+#pragma unroll
+            for (int i = 0; i < 8; i++) raw[i] = hi0[(size_t)j0 * dstride + tid + 256 * i];
+        } else if (DIV && !LIN) {
+            request_w(b, 0);
+        }
+    };
+    request_first(tile.b);
+    const double cvd = DIV ? A::from_u64(ep.cinv[e]) : 0.0, cvq = DIV ? cvd / mc.q : 0.0;
     const bool summed = SUM && e < ep.inv_from;
     E acc0[8], acc1[8];
     for (u32 b = tile.b; b < args.batch; b += b_step) {
@@ -810,6 +864,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
         if (jn < ep.beta) {  // the next digit's points, a tile ahead
 #pragma unroll
             for (int i = 0; i < 8; i++) raw[i] = hi[(size_t)jn * dstride + tid + 256 * i];
+        } else if (DIV && !LIN) {
+            request_w(b, 0);
         }
         A::fwd_begin(v, mc);
         fwd_rows_pre<AW, 3>(v, wa, mc);
@@ -864,13 +920,9 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     // the next item's first points: requested before the operands of what follows, or, where those leave no registers (the
     // linear combination's twelve operands per point), after them
     auto request_next = [&]() {
-        if (b + b_step < args.batch && j0 < ep.beta) {
-            const double* hin = (const double*)(ep.D.digits + (b + b_step) * ep.D.bstride) + (size_t)e * N + off;
-#pragma unroll
-            for (int i = 0; i < 8; i++) raw[i] = hin[(size_t)j0 * dstride + tid + 256 * i];
-        }
+        if (b + b_step < args.batch) request_first(b + b_step);
     };
-    if (!LIN) request_next();
+    if (!LIN && !DIV) request_next();
     if (PROD && e <= ep.level) {
         // the tensor product of this slice, formed here: d2 feeds the digit that owns the limb, P d0 and P d1 join the sums
         const u64* kj = key + (size_t)own * 2 * kstride;
@@ -949,12 +1001,40 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
             }
         }
     }
-    if (LIN) request_next();
+    if (LIN && DIV) request_w(b, 0);
+    if (LIN && !DIV) request_next();
     u64* o0 = ep.out.p[summed ? tile.b : b] + (size_t)e * N + off;
     u64* o1 = o0 + (size_t)ep.E * N;
 #pragma unroll
     for (int i = 0; i < 8; i++) acc0[i] = A::reduce(acc0[i], mc), acc1[i] = A::reduce(acc1[i], mc);
     if (SUM && summed && b + b_step < args.batch) continue;  // uniform over the workgroup
+    if constexpr (DIV) {  // (v - w) cinv, and what is added
+        const u64* add = ep.add.p[b];
+        u64* res = ep.res.p[b] + (size_t)e * N + off;
+#pragma unroll
+        for (int comp = 0; comp < 2; comp++) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i] = raw[i];
+            if (comp == 0) request_w(b, 1);
+            else request_next();
+            fwd_lo_rounds(v, lds0, lds1, tid, wa, wb, wc, wd, mc);
+            const size_t at = (size_t)comp * ep.inv_from * N;
+            double r[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) r[i] = A::mulmod((comp ? acc1[i] : acc0[i]) - lds1[LDS_PAD(tid + 256 * i)], cvd, cvq, mc.q);
+            if (add) {  // uniform
+                const u64* ad = add + at + (size_t)e * N + off;
+                u64 ra[8];
+#pragma unroll
+                for (int i = 0; i < 8; i++) ra[i] = ad[tid + 256 * i];
+#pragma unroll
+                for (int i = 0; i < 8; i++) r[i] = A::reduce(r[i] + A::from_u64(ra[i]), mc);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; i++) res[at + tid + 256 * i] = A::canonical(r[i], mc);
+        }
+        continue;
+    }
     if (e >= ep.inv_from) {
         mac_inverse_lo(acc0, acc1, lds0, lds1, ep.itw_val + ((size_t)m_idx << args.log_n), TA, tid, mc, o0, o1);
     } else {
@@ -2317,7 +2397,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                                  const u64* const* mul_ptrs = nullptr, const u64* lin_k = nullptr, NttPasses passes = NTT_BOTH,
                                  const MidPrologue* mid = nullptr, const u32* gals = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
-    if (passes != NTT_BOTH && (!inverse || c->log_hi < 1)) return hipErrorInvalidValue;
+    if (passes != NTT_BOTH && ((!inverse && (!conv || epilogue || passes != NTT_HI)) || c->log_hi < 1)) return hipErrorInvalidValue;
     if (passes == NTT_HI && (src != dst || src_ptrs || ntt_one_pass(c))) return hipErrorInvalidValue;
     if ((mul_ptrs || gals) && ntt_one_pass(c) && passes != NTT_LO) return hipErrorInvalidValue;
     if (mid && (!conv || !conv->per || c->log_hi < 1)) return hipErrorInvalidValue;
@@ -2414,6 +2494,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
             if (conv) {  // reads the digit's nd limbs for every target limb (from cache after the first), writes the target limbs
                 ProfScope ps__(c, K_NTT_FWD_HI, st, 8.0 * c->N * batch * ((double)conv->nd + pl.n), hi_ops);
                 if (hipError_t e = launch_hi_conv(c->log_hi, pl.n, 1, batch, st, args, pl, *conv, mid); e != hipSuccess) return e;
+                if (passes == NTT_HI) return hipGetLastError();
             } else {
                 ProfScope ps__(c, K_NTT_FWD_HI, st, pass_bytes, hi_ops);
                 hi(args, pl);
@@ -2632,7 +2713,8 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 }
 
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
-                             hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot, u32* n_part) {
+                             hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot, u32* n_part, const MacDivide* div, bool dropped_only) {
+    if ((div || dropped_only) && (n_part || inv_from == 0 || inv_from >= c->ext_limbs(level) || (!prod && !rot))) return hipErrorInvalidValue;
     if (!ntt_has_modup(c) || (n_part && !rot) || (rot && rot->mask && !n_part) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     NttArgs args = {};
@@ -2643,7 +2725,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     args.log_lo = c->log_lo;
     args.log_hi = c->log_hi;
     args.batch = n;
-    const u32 slices = E << c->log_hi;
+    const u32 slices = (div ? inv_from : (dropped_only ? E - inv_from : E)) << c->log_hi;
     args.lo_group = 0;
     for (u32 g = 64; g >= 8; g >>= 1)
         if (slices % g == 0) { args.lo_group = g; break; }
@@ -2673,7 +2755,13 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     ep.beta = beta;
     ep.itw_val = c->d_itwf_val;
     ep.inv_from = inv_from;
-    ep.pad = 0;
+    ep.first = div ? 0 : (inv_from < E ? inv_from : 0);
+    ep.w = div ? div->w : nullptr;
+    ep.cinv = div ? div->cinv : nullptr;
+    for (u32 b = 0; b < KS_MAX_BATCH; b++) {
+        ep.add.p[b] = div && div->adds && b < n ? div->adds[b] : nullptr;
+        ep.res.p[b] = div && b < n ? div->outs[b] : nullptr;
+    }
     ep.mask = rot ? rot->mask : nullptr;
     const bool lin = prod && prod->lin_x;
     if (lin && (!prod->lin_y || !prod->ka || !prod->kb)) return hipErrorInvalidValue;
@@ -2703,6 +2791,12 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
                    0.5 * n * n_tr * c->N * c->log_lo);
     // which operands join after the digits is the same for the whole launch: one instantiation per case
 #define LO_MAC_LAUNCH(...) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<__VA_ARGS__>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
+    if (div) {
+        if (lin) LO_MAC_LAUNCH(true, true, false, false, false, true);
+        else if (prod) LO_MAC_LAUNCH(true, false, false, false, false, true);
+        else LO_MAC_LAUNCH(false, false, true, false, false, true);
+        return hipGetLastError();
+    }
     if (lin) LO_MAC_LAUNCH(true, true, false);
     else if (prod) LO_MAC_LAUNCH(true, false, false);
     else if (rot && rot->mask) LO_MAC_LAUNCH(false, false, true, true, true);
@@ -2732,7 +2826,7 @@ hipError_t launch_ntt_moddown(const ckks_ctx* c, u32 level, bool merged, const d
     const MidPrologue mp = {c->d_itwf, c->d_itwf_val, merged ? c->d_moddown_rs_prep_f + (size_t)level * c->M : c->d_moddown_prep_f, merged ? level : c->num_q,
                             merged ? c->num_q : c->num_q + 1};
     cp.per = mid_per;
-    return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, NTT_BOTH, mid_per ? &mp : nullptr);
+    return launch_ntt_any(c, false, dst, n_out, dst, n_out, pl, batch, st, nullptr, epilogue, nullptr, &cp, nullptr, nullptr, epilogue ? NTT_BOTH : NTT_HI, mid_per ? &mp : nullptr);
 }
 
 // v: [2][E][N] per item, v_bstride apart: the items' dropped limbs have been through the first pass of their inverse transform, their other limbs are

@@ -144,3 +144,31 @@ def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_p, lo, hi):
     two = run(cts)
     for i in range(2):
         assert torch.equal(run(cts[i:i + 1])[0], two[i]), i
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n", [(13, 13, 5, 3, 12, 15), (14, 9, 3, 3, 8, 16), (15, 4, 4, 1, 3, 13), (15, 12, 3, 4, 9, 5), (17, 4, 2, 2, 3, 4)])
+def test_rotations_together_equal_single_ones(log_n, num_q, num_p, dnum, level, n):
+    """Enough unhoisted rotations for the inner products to wait for the division, against one at a time; no digit to transform, ragged last digits."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx = hx.Context(p)
+    residues, _ = uniform(ctx, p, log_n)
+    ct = residues(2, limbs=list(range(level + 1)))
+    offs = [1 + 37 * i for i in range(n)]
+    keys = [hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o)) for o in offs]
+    got = hx.ckks_rotate_hoisted(ctx, ct, level, offs, keys, False)
+    for i, o in enumerate(offs):
+        assert torch.equal(got[i], hx.ckks_rotate_hoisted(ctx, ct, level, [o], [keys[i]], False)[0]), i
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level", [(13, 16, 6, 3, 15), (14, 14, 5, 3, 13), (15, 8, 8, 1, 7), (16, 7, 2, 4, 6)])
+def test_activations_together_equal_single_ones(log_n, num_q, num_p, dnum, level):
+    """Products with and without a linear addend whose inner products wait for the division (sixteen), against one ciphertext at a time."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx = hx.Context(p)
+    residues, _ = uniform(ctx, p, log_n)
+    cts = [residues(2, limbs=list(range(level + 1))) for _ in range(16)]
+    rlk = hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), 0)
+    k = (3 << 40, -(5 << 40), 7 << 40, -(9 << 40))
+    got = hx.he_poly_act_deg7(ctx, cts, level, k, rlk, merged=True)
+    for i, c in enumerate(cts):
+        assert torch.equal(got[i], hx.he_poly_act_deg7(ctx, [c], level, k, rlk, merged=True)[0]), i
