@@ -268,12 +268,18 @@ int run_moddown(const ckks_ctx* c, u32 level, const KsWs& ws, u32 n, const Final
 // 2^16, 13 + 8 (416) 101 / 103, twelve rotations at 2^13, 14 + 7 (624) 83 / 86; a product at 2^16, 24 + 8 (768) 163 / 159, six rotations, 6 + 3 (960) 130 / 125,
 // twelve at 2^14, 14 + 5 (1248) 166 / 158, at 2^16, 21 + 8 (8064) 981 / 935, activations of sixteen, 20 + 7, 2^14 (1152) 1151 / 1061, 2^16 (4608) 4443 / 4107
 #define DIVIDE_INSIDE_SLICES 768
+// Hoisted rotations likewise, whose finished digits are read through the rotation: a kernel of its own that scattered every position's sums, four launches behind the
+// digits / all at once, three launches / inside the division, in us: one at N = 2^12, 5 + 3 limbs (10) 33.9 / 32.1 / 36, three at 2^15, 7 + 3 (336)
+// 63.7 / 60.5 / 66.8, sixteen at 2^13, 14 + 7 (832) 88.3 / 82.2 / 85; six at 2^16, 6 + 2 (960) 104 / 107 / 102.5, two of 24 + 8 (1536) 204 / 194 / 181,
+// sixteen (6144 a batch) 993 / 981 / 840
+#define DIVIDE_INSIDE_HOISTED 900
 int run_inner_divide(const ckks_ctx* c, u32 level, const KsWs& ws, const u64* const* keys, u32 n, u64* const* outs, const u64* const* accs, hipStream_t st,
                      bool merged, const MacProduct* prod, const MacRotate* rot) {
     u64* vs[KS_MAX_BATCH];
     for (u32 b = 0; b < n; b++) vs[b] = ws.v + b * ws.v_b;
     const u32 from = dropped_from(level, merged);
-    if (c->log_hi < 2 || (from * n << c->log_hi) < DIVIDE_INSIDE_SLICES) {
+    const u32 slices = from * n << c->log_hi;
+    if (rot && rot->hoisted ? slices < DIVIDE_INSIDE_HOISTED : c->log_hi < 2 || slices < DIVIDE_INSIDE_SLICES) {
         HIP_TRY(launch_ntt_lo_mac(c, level, dsrc(c, ws, 0), keys, vs, n, st, from, prod, rot));
         FinalItem items[KS_MAX_BATCH];
         for (u32 b = 0; b < n; b++) items[b] = FinalItem{nullptr, nullptr, nullptr, outs[b], 1, 0, accs ? accs[b] : nullptr};
@@ -850,6 +856,14 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
                 pos[nt++] = nk;
                 for (u32 b = 0; b < n; b++) items[nk++] = FinalItem{nullptr, nullptr, nullptr, r_at(b, l), 1, 0};
             }
+            if (n == 1 && ntt_has_modup(c) && nt) {
+                const u64* same[KS_MAX_BATCH];
+                u64* to[KS_MAX_BATCH];
+                for (u32 i = 0; i < nt; i++) same[i] = cts[c0], to[i] = items[i].out;
+                const MacRotate rot = {same, tg, nullptr, true};
+                if ((rc = run_inner_divide(c, level, ws, tkeys, nt, to, nullptr, st, false, nullptr, &rot))) return rc;
+                continue;
+            }
             HIP_TRY(rotated_inner(c, level, ws, cts + c0, n, tkeys, tg, pos, nt, st));
             if (nk && (rc = run_moddown(c, level, ws, nk, items, st))) return rc;
         }
@@ -1335,13 +1349,23 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
     auto flush_hoisted = [&]() -> int {
         const KsWs& lw = lane_ws[lane];
         hipStream_t ls = lane ? c->side : st;
-        const u64* tkeys[KS_MAX_BATCH];
+        const u64 *tkeys[KS_MAX_BATCH], *cts[KS_MAX_BATCH];
+        u64* outs[KS_MAX_BATCH];
         u32 tg[KS_MAX_BATCH], ttap[KS_MAX_BATCH];
         for (u32 b = 0; b < nb; b++) {
             tkeys[b] = pend_key[b]->d_key;
             tg[b] = items[b].g;
             ttap[b] = b;
+            cts[b] = ct;
+            outs[b] = items[b].out;
             items[b].g = 1;  // the division's last step adds nothing: c0 is inside the sum already
+        }
+        if (ntt_has_modup(c)) {
+            const MacRotate rot = {cts, tg, nullptr, true};
+            int rc = run_inner_divide(c, level, lw, tkeys, nb, outs, nullptr, ls, false, nullptr, &rot);
+            nb = 0;
+            if (two_lanes) lane ^= 1;
+            return rc;
         }
         if (hipError_t e = rotated_inner(c, level, lw, &ct, 1, tkeys, tg, ttap, nb, ls); e != hipSuccess) return set_hip_err(c, e);
         int rc = run_moddown(c, level, lw, nb, items, ls);

@@ -289,6 +289,7 @@ struct MacRotate {
     const u64* const* c0;
     const u32* gs;
     const u64* mask = nullptr;  // with n_part, [level+1][N]: the rotated ciphertexts are products with it (launch_ntt with gals and mul_ptrs)
+    bool hoisted = false;  // all items rotate one ciphertext, whose own digits are finished (launch_ntt_modup without hi_only)
 };
 // n_part (with rot): the positions below inv_from are added up over the items, into *n_part partial sums at outs[0], outs[1], ...
 // dropped_only: nothing but the positions from inv_from on.  div: nothing but those below it, and the division's last step on them: outs[b] [2][inv_from][N] =

@@ -693,6 +693,8 @@ struct MacEpilogue {
     u32 gal[KS_MAX_BATCH];
     // MASK (with SUM): the rotated ciphertext is the product of (a0, D.own) with mask [level+1][N]
     const u64* mask;
+    // HOIST (with ROT): the digits are those of D.own.p[0] itself, one set for all items, finished (launch_ntt_modup without hi_only) and read through
+    // the item's automorphism
     // LIN (with PROD): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
     PtrList8 lx, ly;
     size_t x_cstride, y_cstride;
@@ -794,10 +796,10 @@ __device__ __forceinline__ void fwd_lo_rounds(double (&v)[8], double* lds0, doub
     __syncthreads();
 }
 
-// PROD, LIN, ROT, SUM, MASK, DIV (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
+// PROD, LIN, ROT, SUM, MASK, DIV, HOIST (see MacEpilogue) are template arguments so that what follows the digits is straight-line code: with the
 // operands behind conditions, even ones that are the same for the whole launch, the compiler keeps each request next to its
 // use, one round trip to memory per point.
-template <bool PROD, bool LIN, bool ROT, bool SUM = false, bool MASK = false, bool DIV = false>
+template <bool PROD, bool LIN, bool ROT, bool SUM = false, bool MASK = false, bool DIV = false, bool HOIST = false>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs args, PolyList pl, MacEpilogue ep) {
     typedef ArithF64 A;
     typedef double E;
@@ -805,7 +807,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     __shared__ E lds1[LDS_PADDED_WORDS];
     const u32 tid = threadIdx.x;
     const LoTile tile = lo_tile(args.log_hi, args.lo_group);
-    static_assert(!DIV || !SUM, "");
+    static_assert((!DIV || !SUM) && (!HOIST || (ROT && !SUM)), "");
     const u32 e_at = tile.a + ep.first, e = e_at < ep.E ? e_at : e_at - ep.E;  // the dropped limbs, the longer work, first
     const u32 blk = tile.blk, m_idx = pl_at(pl.mod, e);
     // the batch items of this workgroup: tile.b, tile.b + (the grid's extent over items), ...: a workgroup that takes several
@@ -822,12 +824,14 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
     const size_t dstride = (size_t)ep.E * N;
     typedef ArithF64W AW;
     double wa[7], wb[7], wc[7], wd[6];  // the slice's twiddles, fetched once for all digits of all items
-    load_tw_w<3>(tw, TA, wa);
-    load_tw_w<3>(tw, 8 * TA + d3, wb);
-    load_tw_w<3>(tw, 64 * TA + 8 * d3 + d2, wc);
-    load_tw_w<2>(tw, 512 * TA + 2 * tid, wd);
-    load_tw_w<2>(tw, 512 * TA + 2 * tid + 1, wd + 3);
-    const u32 j0 = own == 0 ? 1 : 0;  // first digit to transform
+    if (!HOIST || DIV) {
+        load_tw_w<3>(tw, TA, wa);
+        load_tw_w<3>(tw, 8 * TA + d3, wb);
+        load_tw_w<3>(tw, 64 * TA + 8 * d3 + d2, wc);
+        load_tw_w<2>(tw, 512 * TA + 2 * tid, wd);
+        load_tw_w<2>(tw, 512 * TA + 2 * tid + 1, wd + 3);
+    }
+    const u32 j0 = HOIST ? ep.beta : (own == 0 ? 1 : 0);  // first digit to transform
     E v[8], raw[8];
     // DIV: the converted parts of item b
     auto request_w = [&](u32 b, u32 comp) {
@@ -959,6 +963,40 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fwd_lo_mac_kernel(NttArgs arg
                 dd1 = A::reduce(dd1, mc);
                 acc0[h + i] += A::mulmod_any(dd2, A::from_u64(rk0[i]), mc.q, mc.qinv) + A::mulmod_any(dd0, pres, mc.q, mc.qinv);
                 acc1[h + i] += A::mulmod_any(dd2, A::from_u64(rk1[i]), mc.q, mc.qinv) + A::mulmod_any(dd1, pres, mc.q, mc.qinv);
+            }
+        }
+    } else if constexpr (HOIST) {
+        // every digit, whole, and c0 through the rotation: a slice's sources are one slice, a wavefront's 64 points an aligned run of them
+        const u64* co = ep.a0.p[b] + (size_t)e * N;
+        const bool live = e <= ep.level;  // uniform
+        const double pres = live ? mc.q - A::from_u64(ep.negp[e]) : 0.0;
+        u32 x0 = (u32)off + tid;
+        asm volatile("" : "+v"(x0));  // (see below)
+        u32 xs[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) xs[i] = galois_gather_index(x0 + 256 * i, ep.gal[b], args.log_n);
+        if (live) {
+            u64 rc[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) rc[i] = word_at(co, xs[i]);
+#pragma unroll
+            for (int i = 0; i < 8; i++) acc0[i] = A::mulmod_any(A::from_u64(rc[i]), pres, mc.q, mc.qinv);
+        }
+        for (u32 d = 0; d < ep.beta; d++) {
+            const u64* row = d == own ? ep.D.own.p[0] + (size_t)e * N : ep.D.digits + ((size_t)d * ep.E + e) * N;
+            const u64* kj = key + (size_t)d * 2 * kstride;
+            u64 ry[8], rk0[8], rk1[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) ry[i] = word_at(row, xs[i]), rk0[i] = kj[tid + 256 * i], rk1[i] = kj[kstride + tid + 256 * i];
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const double y = A::from_u64(ry[i]);
+                acc0[i] += A::mulmod_any(y, A::from_u64(rk0[i]), mc.q, mc.qinv);
+                acc1[i] += A::mulmod_any(y, A::from_u64(rk1[i]), mc.q, mc.qinv);
+            }
+            if ((d & 3) == 3) {  // products of residues that are not reduced: 0.75 q each
+#pragma unroll
+                for (int i = 0; i < 8; i++) acc0[i] = A::reduce(acc0[i], mc), acc1[i] = A::reduce(acc1[i], mc);
             }
         }
     } else if (!PROD && e <= ep.level) {
@@ -2398,7 +2436,7 @@ static hipError_t launch_ntt_any(const ckks_ctx* c, bool inverse, const u64* src
                                  const MidPrologue* mid = nullptr, const u32* gals = nullptr) {
     if (pl.n == 0 || batch == 0) return hipSuccess;
     if (passes != NTT_BOTH && ((!inverse && (!conv || epilogue || passes != NTT_HI)) || c->log_hi < 1)) return hipErrorInvalidValue;
-    if (passes == NTT_HI && (src != dst || src_ptrs || ntt_one_pass(c))) return hipErrorInvalidValue;
+    if (passes == NTT_HI && (src != dst || src_ptrs || (ntt_one_pass(c) && !mid))) return hipErrorInvalidValue;
     if ((mul_ptrs || gals) && ntt_one_pass(c) && passes != NTT_LO) return hipErrorInvalidValue;
     if (mid && (!conv || !conv->per || c->log_hi < 1)) return hipErrorInvalidValue;
     if (mul_ptrs && (!inverse || !src_ptrs || !ntt_has_modup(c))) return hipErrorInvalidValue;
@@ -2715,7 +2753,7 @@ hipError_t launch_ntt_rescale(const ckks_ctx* c, u32 level, const double* y, u64
 hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digits, const u64* const* keys, u64* const* outs, u32 n,
                              hipStream_t st, u32 inv_from, const MacProduct* prod, const MacRotate* rot, u32* n_part, const MacDivide* div, bool dropped_only) {
     if ((div || dropped_only) && (n_part || inv_from == 0 || inv_from >= c->ext_limbs(level) || (!prod && !rot))) return hipErrorInvalidValue;
-    if (!ntt_has_modup(c) || (n_part && !rot) || (rot && rot->mask && !n_part) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
+    if (!ntt_has_modup(c) || (n_part && !rot) || (rot && rot->mask && !n_part) || (rot && rot->hoisted && n_part) || c->log_hi == 0 || n == 0 || n > KS_MAX_BATCH || (prod && rot)) return hipErrorInvalidValue;
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     NttArgs args = {};
     args.mc = c->d_mcf;
@@ -2791,6 +2829,11 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
                    0.5 * n * n_tr * c->N * c->log_lo);
     // which operands join after the digits is the same for the whole launch: one instantiation per case
 #define LO_MAC_LAUNCH(...) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<__VA_ARGS__>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
+    if (rot && rot->hoisted) {
+        if (div) LO_MAC_LAUNCH(false, false, true, false, false, true, true);
+        else LO_MAC_LAUNCH(false, false, true, false, false, false, true);
+        return hipGetLastError();
+    }
     if (div) {
         if (lin) LO_MAC_LAUNCH(true, true, false, false, false, true);
         else if (prod) LO_MAC_LAUNCH(true, false, false, false, false, true);

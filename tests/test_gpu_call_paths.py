@@ -172,3 +172,21 @@ def test_activations_together_equal_single_ones(log_n, num_q, num_p, dnum, level
     got = hx.he_poly_act_deg7(ctx, cts, level, k, rlk, merged=True)
     for i, c in enumerate(cts):
         assert torch.equal(got[i], hx.he_poly_act_deg7(ctx, [c], level, k, rlk, merged=True)[0]), i
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n", [(12, 4, 1, 4, 3, 3), (12, 13, 13, 1, 12, 2), (13, 8, 4, 2, 7, 17), (14, 7, 3, 3, 5, 9), (15, 4, 2, 2, 3, 2), (16, 3, 3, 1, 1, 1),
+                                                            (13, 15, 5, 3, 14, 16), (16, 4, 2, 2, 3, 8)])
+def test_hoisted_rotations_of_every_row_count(log_n, num_q, num_p, dnum, level, n):
+    """One set of digits read through each rotation, against the oracle: one to four digits, several batches, rings of two to 32
+    rows, and enough of them for the inner products to wait for the division."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    orc, ctx = Oracle(p), hx.Context(p)
+    residues, _ = uniform(ctx, p, n)
+    ct = residues(2, limbs=list(range(level + 1)))
+    offs = [1 + 61 * i * i for i in range(n)]
+    raw = [residues(dnum, 2, limbs=list(range(ctx.M))) for _ in offs]
+    got = hx.ckks_rotate_hoisted(ctx, ct, level, offs, [hx.ckks_key_load(ctx, k, hx.ckks_galois_element(ctx, o)) for k, o in zip(raw, offs)], True)
+    host = hx.to_host(ct)
+    digits = orc.modup(host[1], level)
+    for i, o in enumerate(offs):
+        assert np.array_equal(hx.to_host(got[i]), orc.rotate(host, level, o, hx.to_host(raw[i]), True, digits)), i
