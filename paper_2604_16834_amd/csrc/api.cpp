@@ -739,11 +739,17 @@ int run_rotate_sum(const ckks_ctx* c, u32 level, u32 n, const u64* const* srcs, 
     return CKKS_OK;
 }
 
+// Whether sums of rotations share a division: with less to do, the items that one workgroup takes in turn are a longer chain than the launches that
+// go.  By coefficients of the extended basis, one by one / together in us: merges at N = 2^12, 7 + 4 limbs, eight (0.04 M) 53.6 / 54.6, 2^13, 7 + 3, five
+// (0.08 M) 60.5 / 62.7, 2^14, 6 + 3, eight (0.15 M) 79 / 73, 2^13, 14 + 7, eight (0.15 M) 82.5 / 76, 2^12, 24 + 8, eight (0.12 M) 78.7 / 73, 2^16, 19 + 8, four (1.8 M) 352 / 283;
+// fully connected layers 2^12, 7 + 3 291 / 300, 2^13, 8 + 3 402 / 415, 2^14, 6 + 3 (0.10 M) 426 / 423, 16 + 8 (0.18 M) 765 / 749, 2^16, 24 + 8 2131 / 2080
+bool sums_together(const ckks_ctx* c, u32 level) { return ntt_has_modup(c) && (size_t)c->ext_limbs(level) * c->N >= (size_t)3 << 15; }
+
 // rotations of a merge of g blocks that share their launches, at most `most`
 u32 merge_batch(u32 g, u32 most) { return g - 1 < most ? (g > 1 ? g - 1 : 1) : most; }
 size_t ws_merge_in(const ckks_ctx* c, u32 level, u32 g, u32 nb) {
     const size_t N = c->N, L1 = level + 1;
-    return ws_ks(c, level, nb, nb) + (ntt_has_modup(c) ? 0 : 2 * blk((size_t)g * 2 * L1 * N)) + blk(2 * L1 * N) + ws_rescale(c, level, 1);
+    return ws_ks(c, level, nb, nb) + (sums_together(c, level) ? 0 : 2 * blk((size_t)g * 2 * L1 * N)) + blk(2 * L1 * N) + ws_rescale(c, level, 1);
 }
 size_t ws_merge(const ckks_ctx* c, u32 level, u32 g) { return ws_merge_in(c, level, g, merge_batch(g, ks_batch(c))); }
 
@@ -755,7 +761,7 @@ int run_merge(const ckks_ctx* c, const u64* const* cts, u32 g, u32 level, const 
     if (ar.used + ws_merge_in(c, level, g, nb) > ar.cap) nb = merge_batch(g, CT_BATCH);  // in a smaller workspace
     KsWs ws;
     bool ok = carve_ks(c, level, nb, nb, ar, ws);
-    const bool sums = ntt_has_modup(c);                                   // run_rotate_sum
+    const bool sums = sums_together(c, level);                      // run_rotate_sum
     u64* masked = sums ? nullptr : ar.take((size_t)g * ct_elems);   // C_i (.) M
     u64* rotated = sums ? nullptr : ar.take((size_t)g * ct_elems);  // Rot(C_i (.) M, -i*sts), i >= 1
     u64* total = ar.take(ct_elems);
@@ -886,10 +892,7 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
         const ckks_key* ks[KS_MAX_BATCH];
         u32 gs[KS_MAX_BATCH], nk = 0;
         u64* dsts[KS_MAX_BATCH];
-        // One ciphertext's rotations are added up in the division (several share each key instead), from a size on: with less to do the items that one
-        // workgroup takes in turn are a longer chain than the launches of the sum.  Fully connected layers, one by one / added up in us: 2^12, 6 + 3
-        // limbs 327 / 333, 2^13, 8 + 3 406 / 414, 2^14, 6 + 3 434 / 436, 16 + 8 (0.18 M coefficients) 790 / 772, 2^15, 12 + 4 1274 / 1246, 2^16, 24 + 8 2131 / 2080
-        if (n == 1 && ntt_has_modup(c) && (size_t)c->ext_limbs(l1) * N >= (size_t)1 << 17) {
+        if (n == 1 && sums_together(c, l1)) {  // (several ciphertexts share each key instead)
             const u64* terms[KS_MAX_BATCH];
             u64* out = outs[c0];
             const u64* add = nullptr;  // the blocks that stay where they are

@@ -113,10 +113,10 @@ struct FwdEpilogue {
     PtrList8 vl2;
     size_t v2_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
+    FinalBatch B;
     // a sum of items (launch_ntt_moddown_sum): v is n_part partial sums, v_pstride apart
     u32 n_part, pad;
     size_t v_pstride;
-    FinalBatch B;
 };
 
 struct ckks_key {

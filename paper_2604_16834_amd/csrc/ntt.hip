@@ -678,12 +678,6 @@ struct MacEpilogue {
     const double* itw_val;  // [M][N], NttArgs::tw_val of inverse transforms
     // SUM (with ROT): the other positions' sums of all items of a workgroup are added up and stored once, as item tile.b's
     u32 inv_from, first;  // first: the position that the grid's first slices belong to
-    // DIV: the division's last step instead of stores: w are the converted dropped parts behind the first pass of their forward transform
-    // ([2 * item + component][n_out][N]), cinv the multipliers (FwdEpilogue), res the results, add what is added to them (entries may be null)
-    const double* w;
-    const u64* cinv;
-    PtrList8 add;
-    OutList8 res;
     // PROD: the decomposed polynomial is d2 = a1 (.) b1 of the ciphertext product (a0, a1) x (b0, b1), which exists
     // nowhere in evaluation form: the own-limb term is formed from a1, b1 ([level+1][N] each, per batch item), and the
     // addends are d0 = a0 (.) b0 and d1 = a0 (.) b1 + a1 (.) b0 (D.own is not read)
@@ -691,14 +685,20 @@ struct MacEpilogue {
     // ROT: item b is a rotation by gal[b] of the ciphertext (a0, D.own): the digits are those of sigma(D.own), the own-limb term and the
     // addend P sigma(a0) are gathered as they are read
     u32 gal[KS_MAX_BATCH];
-    // MASK (with SUM): the rotated ciphertext is the product of (a0, D.own) with mask [level+1][N]
-    const u64* mask;
     // HOIST (with ROT): the digits are those of D.own.p[0] itself, one set for all items, finished (launch_ntt_modup without hi_only) and read through
     // the item's automorphism
     // LIN (with PROD): the addends are ka * x + kb * y of two more ciphertexts (component 1 at + x_cstride, y_cstride)
     PtrList8 lx, ly;
     size_t x_cstride, y_cstride;
     u64 ka[CKKS_MAX_MODULI], kb[CKKS_MAX_MODULI];
+    // MASK (with SUM): the rotated ciphertext is the product of (a0, D.own) with mask [level+1][N]
+    const u64* mask;
+    // DIV: the division's last step instead of stores: w are the converted dropped parts behind the first pass of their forward transform
+    // ([2 * item + component][n_out][N]), cinv the multipliers (FwdEpilogue), res the results, add what is added to them (entries may be null)
+    const double* w;
+    const u64* cinv;
+    PtrList8 add;
+    OutList8 res;
 };
 
 // poly[x] through a wave-uniform base and a 32-bit offset (a polynomial is at most 1 MiB): half the address registers
@@ -1861,72 +1861,6 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_kernel(NttArgs args,
     }
 }
 
-// The two kernels of a sum's division (ntt_inv_hi_sum_kernel, ntt_fwd_hi_conv_sum_kernel) in one, for rings of up to 2^14 points: a thread takes its
-// column of every (source limb, item) through the inverse pass, adds the items up, and keeps the conversion's chain of one target.  The inverse
-// passes are repeated for every target, which costs less than a launch up to a count (see launch_ntt_moddown_sum).
-// grid = (2^11 columns / NTT_THREADS, targets x components)
-template <int LOG_HI>
-__global__ __launch_bounds__(NTT_THREADS) void ntt_mid_conv_sum_kernel(NttArgs args, PolyList pl, ConvPrologue cp, MidPrologue mp, u32 n_items) {
-    typedef ArithF64 A;
-    constexpr int R = 1 << LOG_HI, AHEAD = 4;  // items requested together, while the AHEAD before them are transformed
-    const u32 col = blockIdx.x * NTT_THREADS + threadIdx.x, b = blockIdx.y / pl.n, a = blockIdx.y % pl.n, m_idx = pl_at(pl.mod, a), pos = pl_at(pl.dpos, a);
-    const size_t N = (size_t)1 << args.log_n, item = 2 * cp.y_bstride;
-    const double* y = cp.y + b * cp.y_bstride + (size_t)cp.lo * N + col;
-    ConstPtr<ModConstF> pm = const_ptr((const ModConstF*)args.mc + m_idx);
-    const ModConstF mc = {pm->q, pm->qinv, 0.0, 0.0};
-    ConstPtr<TwF> ce = const_ptr(cp.convf + (size_t)pos * cp.ap);
-    double raw[AHEAD][R], v[R], s[R], lo[R];
-    auto load = [&](u32 k, u32 r0) {
-#pragma unroll
-        for (int i = 0; i < AHEAD; i++)
-#pragma unroll
-            for (int r = 0; r < R; r++) raw[i][r] = (y + (size_t)k * N + min(r0 + i, n_items - 1) * item)[(size_t)r << 11];
-    };
-    load(0, 0);
-#pragma unroll
-    for (int r = 0; r < R; r++) v[r] = 0.0, s[r] = F64M_DOT_BASE, lo[r] = 0.0;
-    for (u32 k = 0; k < cp.nd; k++) {
-        const u32 m_src = k ? mp.next + k - 1 : mp.first;
-        ConstPtr<ModConstF> ps = const_ptr((const ModConstF*)args.mc + m_src);
-        ConstPtr<TwF> pk = const_ptr(mp.scale + m_src), tw = const_ptr(mp.itw + ((size_t)m_src << args.log_n));
-        const ModConstF ms = {ps->q, ps->qinv, 0.0, 0.0};
-        const TwF scale = {pk->w, pk->wq};
-        const double w = ce[k].w;
-        double sum[R];
-#pragma unroll
-        for (int r = 0; r < R; r++) sum[r] = 0.0;
-        for (u32 r0 = 0; r0 < n_items; r0 += AHEAD) {
-            double u[AHEAD][R];
-#pragma unroll
-            for (int i = 0; i < AHEAD; i++)
-#pragma unroll
-                for (int r = 0; r < R; r++) u[i][r] = raw[i][r];
-            if (r0 + AHEAD < n_items) load(k, r0 + AHEAD);
-            else if (k + 1 < cp.nd) load(k + 1, 0);
-#pragma unroll
-            for (int i = 0; i < AHEAD; i++) {
-                if (r0 + i >= n_items) break;  // uniform
-                inv_column<LOG_HI>(u[i], tw, ms);
-#pragma unroll
-                for (int r = 0; r < R; r++) sum[r] += f64m_centre(A::mulmod(u[i][r], scale.w, scale.wq, ms.q), ms.q);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; r++) f64m_chain_add(s[r], lo[r], f64m_reduce(sum[r], mc.q, mc.qinv), w);
-        if ((k & 7) == 7 || k + 1 == cp.nd) {  // a chain takes eight terms
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                v[r] = f64m_reduce(v[r] + f64m_chain_join(s[r], lo[r], mc.q, mc.qinv), mc.q, mc.qinv);
-                s[r] = F64M_DOT_BASE, lo[r] = 0.0;
-            }
-        }
-    }
-    fwd_column<LOG_HI>(v, const_ptr((const TwF*)args.tw + ((size_t)m_idx << args.log_n)), mc);
-    u64* dst = args.dst + (((size_t)b * args.dst_bstride + pos) << args.log_n) + col;
-#pragma unroll
-    for (int r = 0; r < R; r++) dst[(size_t)r << 11] = A::store_mid(v[r]);
-}
-
 // ============================ rings of 2^12 points: the whole transform in one workgroup ============================
 // 256 R threads (R = 2 blocks of 2^11 points, eight points per thread) hold a whole limb-poly: the hi pass' stage acts
 // on the R points of a thread's columns, one more exchange through LDS takes the place of the trip through memory, and the lo
@@ -2898,7 +2832,6 @@ hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v
     cp.lo = n_out;
     cp.nd = k;
     cp.ap = c->k_pad;
-    const MidPrologue mp = {c->d_itwf, c->d_itwf_val, c->d_moddown_prep_f, c->num_q, c->num_q + 1};
     const u32 tiles = c->N >> CKKS_TILE_LOG;
     const dim3 block(NTT_THREADS);
 #define BY_LOG_HI(LAUNCH)                     \
@@ -2911,12 +2844,7 @@ hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v
         case 6: LAUNCH(6); break;             \
         default: return hipErrorInvalidValue; \
     }
-    // In one kernel on rings of 2^12, and on those of 2^13 with few targets (the inverse passes are repeated for each), while a thread's columns are not
-    // too many.  Merges in us, in two / in one: 2^12, 5 + 2 limbs, one item (2 columns) 48.8 / 45.7, 7 + 4, seven (28) 54.5 / 54.0, 24 + 8, seven
-    // (56) 70.8 / 77.4; 2^13, 7 + 3, one (3, seven targets) 52.8 / 51.5, 14 + 7, three
-    // (21, eleven targets) 61.1 / 65.1; 2^14, 14 + 7, two 66.9 / 77.1
-    const bool mid = (c->log_hi == 1 && n * k <= 48) || (c->log_hi == 2 && n_out <= 6 && n * k <= 12);
-    if (!mid) {
+    {
         args.tw = c->d_itwf;
         args.src = args.dst = v;
         args.src_bstride = args.dst_bstride = E;
@@ -2934,15 +2862,10 @@ hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v
     args.inv_scale = nullptr;
     args.batch = 2;
     {
-        ProfScope ps__(c, K_NTT_FWD_HI, st, 16.0 * c->N * ((mid ? n : 1.0) * k + n_out), (double)c->N * n_out * c->log_hi);
+        ProfScope ps__(c, K_NTT_FWD_HI, st, 16.0 * c->N * ((double)k + n_out), (double)c->N * n_out * c->log_hi);
 #define CONV_SUM(H) hipLaunchKernelGGL((ntt_fwd_hi_conv_sum_kernel<H>), dim3(tiles, 2 * n_out), block, 0, st, args, pl, cp)
-#define MID_SUM(H) hipLaunchKernelGGL((ntt_mid_conv_sum_kernel<H>), dim3((1u << CKKS_TILE_LOG) / NTT_THREADS, 2 * n_out), block, 0, st, args, pl, cp, mp, n)
-        if (!mid) {
-            BY_LOG_HI(CONV_SUM)
-        } else if (c->log_hi == 1) MID_SUM(1);
-        else MID_SUM(2);
+        BY_LOG_HI(CONV_SUM)
 #undef CONV_SUM
-#undef MID_SUM
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
 #undef BY_LOG_HI

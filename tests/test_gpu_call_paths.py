@@ -104,7 +104,7 @@ def uniform(ctx, p, seed):
     return residues, q
 
 
-@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g", [(12, 4, 1, 4, 3, 16), (12, 9, 12, 1, 8, 2), (13, 5, 3, 2, 4, 5), (14, 9, 9, 1, 7, 3), (14, 8, 2, 4, 1, 16),
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g", [(12, 4, 1, 4, 3, 16), (12, 24, 8, 3, 20, 16), (12, 14, 14, 1, 13, 2), (13, 10, 5, 2, 9, 5), (14, 9, 9, 1, 7, 3), (14, 8, 2, 4, 3, 16),
                                                             (15, 20, 7, 3, 18, 4), (16, 12, 4, 4, 11, 2), (16, 3, 3, 1, 2, 9), (17, 3, 2, 2, 2, 3)])
 def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
     """Products, rotations, sum and rescale one by one: one to three items per partial sum and sums of up to fifteen, one to twelve special
@@ -126,19 +126,19 @@ def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
     assert torch.equal(got, hx.ckks_rescale(ctx, total, level))
 
 
-@pytest.mark.parametrize("log_n,num_p,lo,hi", [(13, 13, [0, 5], [0, 7, 9]), (15, 2, [1], list(range(3, 40, 2))), (16, 4, [0, 3], [0, 0, 4, 0]), (15, 2, [2], [0]),
-                                               (15, 2, [2], [0] * 17 + [5, 6])])
-def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_p, lo, hi):
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,lo,hi", [(13, 5, 13, 3, [0, 5], [0, 7, 9]), (15, 5, 2, 3, [1], list(range(3, 40, 2))), (16, 5, 4, 3, [0, 3], [0, 0, 4, 0]),
+                                                          (15, 5, 2, 3, [2], [0]), (15, 5, 2, 3, [2], [0] * 17 + [5, 6]), (12, 10, 1, 10, [0, 3, 4], [1, 2])])
+def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_q, num_p, dnum, lo, hi):
     """One ciphertext's second rotations are added up in the division; two, which share their keys, take them one by one.  With more blocks than a
-    launch takes, several blocks that stay where they are, and nothing else."""
-    p = make_params(log_n, 5, num_p, 3)
+    launch takes, several blocks that stay where they are, and nothing else; nine digits read through the first rotations."""
+    p = make_params(log_n, num_q, num_p, dnum)
     ctx = hx.Context(p)
-    level = 3
+    level = num_q - 2
     residues, _ = uniform(ctx, p, log_n + len(hi))
     live = list(range(level + 1))
     cts, keys = [residues(2, limbs=live) for _ in range(2)], {}
     for o in set(lo + hi) - {0}:
-        keys[o] = hx.ckks_key_load(ctx, residues(3, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o))
+        keys[o] = hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o))
     masks = [[residues(limbs=live) for _ in lo] for _ in hi]
     run = lambda c: hx.he_relayout_two_rotations(ctx, c, level, lo, [keys.get(o) for o in lo], hi, [keys.get(o) for o in hi], masks)
     two = run(cts)
