@@ -749,7 +749,9 @@ hipError_t launch_key_inner_sum(const ckks_ctx* c, u32 level, const DigitSrc& di
     const u32 E = c->ext_limbs(level), beta = c->live_digits(level);
     if (n == 0 || n > KSUM_MAX_CH || ch0 + n > n_ch || c_out == 0 || c_out > 8 || beta > 4 || !c->small_q || c->N % 64) return hipErrorInvalidValue;
     SumTaps T;
+    double n_keys = 0.0;
     for (u32 t = 0; t < 9; t++) {
+        if (keys[t]) n_keys += 1.0;
         if ((gs[t] == 1) != (keys[t] == nullptr)) return hipErrorInvalidValue;
         T.key[t] = keys[t];
         T.g[t] = gs[t];
@@ -761,7 +763,8 @@ hipError_t launch_key_inner_sum(const ckks_ctx* c, u32 level, const DigitSrc& di
     const u32 xw = c->N / 64, ot = c_out <= 4 ? c_out : (c_out + 1) / 2, nb = n == 1 ? 1 : (n % 3 == 0 ? 3 : 2), tw = ot > 1 && xw * E >= 5120 ? 1 : 3;
     const u64* negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
     const dim3 grid((xw * E + 7) / 8 * 8, (c_out + ot - 1) / ot);
-    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (n * (double)beta + 9 * (2.0 * beta + 1.0) + 2.0 * c_out) + 2.0 * n * (level + 1.0)),
+    // in: the digits with their own limbs, c0, the keys, nine masks, the weights, the sums so far; out: the sums
+    ProfScope ps__(c, K_KEY_INNER, st, 8.0 * c->N * (E * (n * (double)beta + n_keys * 2.0 * beta + 9.0 + (ch0 ? 4.0 : 2.0) * c_out) + n * (level + 1.0)) + 72.0 * n * c_out * E,
                    2.0 * c->N * E * n * (9 * (beta + 1.0) + 9.0 * c_out));
     PtrList8 ptrs;
     for (u32 b = 0; b < KS_MAX_BATCH; b++) ptrs.p[b] = b < n ? cts[b] : nullptr;

@@ -2706,7 +2706,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     for (u32 e = 0; e < CKKS_MAX_MODULI; e++) pl.spos[e] = pl.dpos[e] = pl.mod[e] = (unsigned char)(e < E ? c->ext_modulus(level, e) : 0);
     MacEpilogue ep;
     ep.D = digits;
-    double n_add = 0.0, n_keys = 0.0;
+    double n_add = 0.0, n_keys = 0.0, n_src = 0.0;
     for (u32 b = 0; b < KS_MAX_BATCH; b++) {
         ep.key.p[b] = b < n ? keys[b] : nullptr;
         ep.out.p[b] = b < n ? outs[b] : nullptr;
@@ -2719,6 +2719,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
         ep.b1.p[b] = (prod && b < n) ? prod->b1[b] : nullptr;
         if (prod && b < n && (!ep.a0.p[b] || !ep.a1.p[b] || !ep.b0.p[b] || !ep.b1.p[b])) return hipErrorInvalidValue;
         if (b < n && (b == 0 || keys[b] != keys[b - 1])) n_keys += 1.0;
+        if (rot && b < n && (b == 0 || rot->c0[b] != rot->c0[b - 1])) n_src += 1.0;
     }
     ep.negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
     ep.level = level;
@@ -2733,6 +2734,7 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     for (u32 b = 0; b < KS_MAX_BATCH; b++) {
         ep.add.p[b] = div && div->adds && b < n ? div->adds[b] : nullptr;
         ep.res.p[b] = div && b < n ? div->outs[b] : nullptr;
+        if (ep.add.p[b]) n_add += 1.0;
     }
     ep.mask = rot ? rot->mask : nullptr;
     const bool lin = prod && prod->lin_x;
@@ -2748,8 +2750,6 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
         ep.ka[i] = (lin && i <= level) ? prod->ka[i] : 0;
         ep.kb[i] = (lin && i <= level) ? prod->kb[i] : 0;
     }
-    // digits transformed per batch item: every (digit, position) pair but the digits' own limbs
-    const double n_tr = (double)beta * E - (level + 1.0);
     // the grid's extent over the batch: two, i.e. four items per workgroup in a batch of eight (measured: 16.5 ms per step for
     // the lo-pass class with one item per workgroup, 16.35 with all eight, 16.15 with four, which still leave the chip's 256
     // CUs, two workgroups each, four rounds of workgroups); more of them where the launch is small (see lo_items)
@@ -2757,10 +2757,19 @@ hipError_t launch_ntt_lo_mac(const ckks_ctx* c, u32 level, const DigitSrc& digit
     const u32 b_ext = (n + items - 1) / items < b_least ? b_least : (n + items - 1) / items;
     const dim3 grid = args.lo_group ? dim3(args.lo_group, b_ext, slices / args.lo_group) : dim3(b_ext, slices);
     if (n_part) *n_part = b_ext;
-    // in: the transformed rows, the own limbs, the addends, the keys (once per distinct key); out: two components
-    if (lin) n_add = 4.0 * n;  // two components of two ciphertexts
-    ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * (n * (n_tr + (prod ? 4.0 : (rot ? 2.0 : 1.0)) * (level + 1.0) + 2.0 * E) + n_add * (level + 1.0) + n_keys * 2.0 * beta * E),
-                   0.5 * n * n_tr * c->N * c->log_lo);
+    // What this launch covers: np positions, `live` of them ciphertext limbs, `inverse` of them dropped limbs that go on into their inverse
+    // transform.  In: per item every (digit, position) row but the digits' own limbs, which come from the decomposed polynomial (finished digits once for all
+    // items), the operands at the live limbs (once per distinct ciphertext of a rotation), the keys (once per distinct key), the mask; for a division the converted
+    // parts and what is added.  Out: two components per item, of a sum the partial sums.
+    const bool hoisted = rot && rot->hoisted;
+    const double np = div ? inv_from : (dropped_only ? E - inv_from : E), kept = dropped_only ? 0.0 : (inv_from < E ? inv_from : E), inverse = div ? 0.0 : np - kept;
+    const double live = div ? inv_from : (dropped_only ? level + 1.0 - inv_from : level + 1.0);
+    const double rows = beta * np - live, n_tr = hoisted ? 0.0 : n * rows;  // n_tr: transformed
+    double words = (hoisted ? 1.0 : (double)n) * rows + n_keys * 2.0 * beta * np + (rot && rot->mask ? live : 0.0);
+    words += live * (prod ? (lin ? 8.0 : 4.0) * n : (rot ? 2.0 * n_src : 1.0 * n));  // (lin: two components of two ciphertexts)
+    words += 2.0 * (n * inverse + (n_part ? b_ext : n) * kept);
+    if (div) words += 2.0 * kept * (n + n_add);
+    ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * words, 0.5 * c->N * c->log_lo * (n_tr + 2.0 * n * (inverse + (div ? kept : 0.0))));
     // which operands join after the digits is the same for the whole launch: one instantiation per case
 #define LO_MAC_LAUNCH(...) hipLaunchKernelGGL((ntt_fwd_lo_mac_kernel<__VA_ARGS__>), grid, dim3(NTT_THREADS), 0, st, args, pl, ep)
     if (rot && rot->hoisted) {
@@ -2883,7 +2892,7 @@ hipError_t launch_ntt_moddown_sum(const ckks_ctx* c, u32 level, u64* v, size_t v
     for (u32 g = 64; g >= 8; g >>= 1)
         if (slices % g == 0) { args.lo_group = g; break; }
     const dim3 grid = args.lo_group ? dim3(args.lo_group, 2, slices / args.lo_group) : dim3(2, slices);
-    ProfScope ps__(c, K_NTT_FWD_LO, st, 16.0 * c->N * n_out * (2.0 + n_part + (item.acc ? 1.0 : 0.0)), (double)c->N * n_out * c->log_lo);
+    ProfScope ps__(c, K_NTT_FWD_LO, st, 8.0 * c->N * n_out * (4.0 + 2.0 * n_part + (item.acc ? 2.0 : 0.0) + (item.mask ? 1.0 : 0.0)), (double)c->N * n_out * c->log_lo);
     if (item.mask) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM_MASK>), grid, block, 0, st, args, pl, ep);
     else if (item.acc) hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM_ADD>), grid, block, 0, st, args, pl, ep);
     else hipLaunchKernelGGL((ntt_fwd_lo_div_kernel<ArithF64, EM_SUM>), grid, block, 0, st, args, pl, ep);
