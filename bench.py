@@ -166,6 +166,16 @@ def cpu_baseline(wl, params, alignment, act_merged):
     }
 
 
+def rotation_split(prof, n_rot):
+    """Where the time of one call of n_rot hoisted rotations goes: every kernel class that ckks_prof_end lists, whichever they are."""
+    return {"us_per_rotation": {k: 1e3 * v["ms"] / n_rot for k, v in prof.items()},
+            "GBs": {k: v["bytes"] / v["ms"] / 1e6 for k, v in prof.items()},
+            "launches": {k: v["launches"] for k, v in prof.items()},
+            "note": "one call of %d rotations with every launch bracketed, no overlap between batches; the timed rate above lets batches overlap.  Moduli "
+                    "below 2^50, up to four digits: ntt_fwd_lo holds the inner products (of the dropped limbs; of the others with the end of the division) and "
+                    "ntt_fwd_hi the conversions; each class also has its pass of the one ModUp" % n_rot}
+
+
 def rotation_microbench(hx, torch, ctx, ct, keys, level, N, ws, result, overlap=True):
     # rotation microbenchmark (24 limbs + 8 special primes, dnum 3): one ciphertext, 64 distinct offsets, 64 keys in
     # 64 separate 96 MiB buffers (their contents are clones of the eight seeded keys: only the addresses matter)
@@ -199,12 +209,7 @@ def rotation_microbench(hx, torch, ctx, ct, keys, level, N, ws, result, overlap=
     hx.ckks_rotate_hoisted(ctx, ct, level, mb_offs, mb_keys, True, outs=mb_outs, ws=ws)
     prof = hx.ckks_prof_end(ctx)
     prof.pop("dropped")
-    inner = prof.get("key_inner", {"ms": 0.0, "bytes": 0.0})
-    rest = sum(v["ms"] for k, v in prof.items() if k != "key_inner")
-    result["rotation_hoisted_split"] = {
-        "inner_product_us_per_rotation": 1e3 * inner["ms"] / n_rot_mb, "inner_product_GBs": inner["bytes"] / max(inner["ms"], 1e-9) / 1e6,
-        "moddown_and_shared_modup_us_per_rotation": 1e3 * rest / n_rot_mb,
-        "note": "one call of 64 rotations with every launch bracketed, no overlap between batches; the timed rate above lets batches overlap"}
+    result["rotation_hoisted_split"] = rotation_split(prof, n_rot_mb)
 
 
 def conv_microbench(hx, torch, name, result):
