@@ -231,7 +231,7 @@ typedef struct he_conv_desc {
 } he_conv_desc;
 
 /* Workspace bytes he_conv_batched needs for this shape (0 on invalid arguments): the shared
- * decomposition, 9*C_in masked aligned ciphertexts, C_out accumulators and rescale scratch. */
+ * decomposition, 9*C_in masked aligned ciphertexts (deferred schedules with few outputs: none), C_out accumulators and rescale scratch. */
 size_t he_conv_workspace_bytes(const ckks_ctx* ctx, const he_conv_desc* desc);
 
 int he_conv_batched(const ckks_ctx* ctx, const he_conv_desc* desc, const uint64_t* const* h_d_in,

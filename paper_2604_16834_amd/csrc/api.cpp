@@ -514,9 +514,6 @@ bool conv_together(const ckks_ctx* c, const he_conv_desc* d) {
 }
 // channels of a batch, and whether two batches are in flight when there is more than one
 u32 conv_batch(const ckks_ctx* c, const he_conv_desc* d) { return conv_together(c, d) && (d->c_in > CT_BATCH || d->c_out > CT_BATCH) ? KS_MAX_BATCH : CT_BATCH; }
-u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {
-    return (!conv_together(c, d) && c->side_stream() && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;
-}
 
 // Whether the inner products and the weighted sum of a deferred convolution are one kernel that stores no aligned copies (launch_key_inner_sum):
 // with up to four outputs, whose sums a thread holds; on small rings with up to eight, in two groups that form the inner products twice.  Merged
@@ -526,6 +523,18 @@ u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {
 bool conv_summed(const ckks_ctx* c, const he_conv_desc* d) {
     if (!c->small_q || c->live_digits(d->level) > 4 || c->N % 64) return false;
     return d->c_out <= 4 || (d->c_out <= 8 && (size_t)c->ext_limbs(d->level) * c->N <= (size_t)1 << 15);
+}
+
+// sets of scratch that a deferred convolution can use: two where batches run side by side (one kernel's sums over the channels go into the same place)
+u32 conv_lanes(const ckks_ctx* c, const he_conv_desc* d) {
+    return (!conv_summed(c, d) && !conv_together(c, d) && c->side && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;
+}
+// words of its aligned copies on the extended basis, and of the scratch of the kernel that sums them: none where they are not stored
+size_t conv_copies(const ckks_ctx* c, const he_conv_desc* d) {
+    return conv_summed(c, d) ? 0 : (size_t)d->c_in * 9 * 2 * c->ext_limbs(d->level) * c->N;
+}
+size_t conv_sum_scratch(const ckks_ctx* c, const he_conv_desc* d) {
+    return conv_summed(c, d) ? 0 : weighted_sum_scratch_elems(c, c->ext_limbs(d->level), d->c_in * 9, d->c_out);
 }
 
 // the schedules that divide every rotation by P, kb of them at a time
@@ -543,15 +552,15 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
     const bool merged = d->alignment == HE_CONV_DEFERRED_MERGED;  // ModDown and rescale of the sums as one division
     const size_t N = c->N, L1 = level + 1, ct_elems = 2 * L1 * N, x_elems = 2 * (size_t)E * N;
     Arena ar(d_ws, ws_bytes);
-    u64* xs = ar.take((size_t)d->c_in * 9 * x_elems);
+    u64* xs = ar.take(conv_copies(c, d));
     u64* acc = ar.take((size_t)d->c_out * x_elems);
-    u64* wscratch = ar.take(weighted_sum_scratch_elems(c, E, d->c_in * 9, d->c_out));
+    u64* wscratch = ar.take(conv_sum_scratch(c, d));
     // Batches of input channels (alignment) and of output channels (division) are independent: with room for two sets of
     // scratch every other batch runs on the library's side stream, between a fork and a join on the caller's stream.
     u32 kb = conv_batch(c, d);
     if (ar.ok() && ar.used + ws_conv_lane(c, level, kb) > ar.cap) kb = CT_BATCH;  // in a smaller workspace
     const size_t lane_bytes = ws_conv_lane(c, level, kb);
-    const u32 n_lanes = (conv_lanes(c, d) == 2 && ar.ok() && ar.used + 2 * lane_bytes <= ar.cap) ? 2 : 1;
+    const u32 n_lanes = (conv_lanes(c, d) == 2 && c->side_stream() && ar.ok() && ar.used + 2 * lane_bytes <= ar.cap) ? 2 : 1;
     struct Lane {
         KsWs ws;
         u64* tmp;
@@ -640,7 +649,7 @@ int conv_deferred(const ckks_ctx* c, const he_conv_desc* d, const u32* gs, const
         return CKKS_OK;
     };
     int rc;
-    if (d->c_in > kb && !summed && (rc = fork())) return rc;  // (the batches' sums go into the same place)
+    if (d->c_in > kb && (rc = fork())) return rc;
     for (u32 c0 = 0, k = 0; c0 < d->c_in; c0 += kb, k++)
         if ((rc = align_batch(c0, lanes[forked ? k & 1 : 0]))) return join(rc);
     if ((rc = join(CKKS_OK))) return rc;
@@ -1124,9 +1133,7 @@ size_t he_conv_workspace_bytes(const ckks_ctx* c, const he_conv_desc* d) {
     const size_t N = c->N;
     if (d->alignment == HE_CONV_DEFERRED_MODDOWN || d->alignment == HE_CONV_DEFERRED_MERGED) {
         const size_t E = c->ext_limbs(d->level);
-        const u32 lanes = (!conv_together(c, d) && c->side && (d->c_in > CT_BATCH || d->c_out > CT_BATCH)) ? 2 : 1;  // sized for overlap on
-        return lanes * ws_conv_lane(c, d->level, conv_batch(c, d)) + blk((size_t)d->c_in * 9 * 2 * E * N) + blk((size_t)d->c_out * 2 * E * N) +
-               blk(weighted_sum_scratch_elems(c, (u32)E, d->c_in * 9, d->c_out));
+        return conv_lanes(c, d) * ws_conv_lane(c, d->level, conv_batch(c, d)) + blk(conv_copies(c, d)) + blk((size_t)d->c_out * 2 * E * N) + blk(conv_sum_scratch(c, d));
     }
     return ws_conv_rotated(c, d, ks_batch(c));
 }

@@ -32,13 +32,13 @@ def test_large_ntt_batches_in_parts(batch):
     assert torch.equal(d, first)
 
 
-def deferred_conv(ctx, p, level, width, cts, keys, masks, w, merged):
+def deferred_conv(ctx, p, level, width, cts, keys, masks, w, merged, ws=None):
     """cts, masks: on the device; keys by offset, None where nothing is rotated; w [c_out][c_in][9] integers."""
     ext = [p.moduli[t] for t in list(range(level + 1)) + list(range(p.num_q, p.num_q + p.num_p))]
     offs = conv_tap_offsets(width)
     dkeys = [hx.ckks_key_load(ctx, keys[o], hx.ckks_galois_element(ctx, o)) if o in keys else None for o in offs]
     outs = hx.he_conv_batched(ctx, 1, width, 1, level, cts, dkeys, masks, hx.from_host(w_residues(w, ext, len(ext) - 1)), w.shape[0],
-                              alignment=hx.HE_CONV_DEFERRED_MERGED if merged else hx.HE_CONV_DEFERRED_MODDOWN)
+                              alignment=hx.HE_CONV_DEFERRED_MERGED if merged else hx.HE_CONV_DEFERRED_MODDOWN, ws=ws)
     return [hx.to_host(o) for o in outs]
 
 
@@ -102,6 +102,38 @@ def uniform(ctx, p, seed):
         r[..., 128:256] = torch.arange(128, device="cuda") & 1
         return r
     return residues, q
+
+
+def guarded(nbytes):
+    """A workspace of exactly so many bytes and the buffer around it."""
+    buf = torch.full((nbytes // 8 + 128,), 0x5A5A5A5A, dtype=torch.int64, device="cuda")
+    return buf, buf[64:-64]
+
+
+def untouched(buf):
+    return bool((buf[:64] == 0x5A5A5A5A).all()) and bool((buf[-64:] == 0x5A5A5A5A).all())
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,c_in,c_out,stored", [(12, 5, 2, 3, 20, 8, False), (13, 6, 2, 4, 19, 4, False), (15, 7, 2, 4, 17, 1, False), (13, 6, 2, 4, 19, 9, True)])
+def test_deferred_convolutions_stay_within_their_workspace(log_n, num_q, num_p, dnum, c_in, c_out, stored):
+    """With few outputs the queried workspace holds no aligned copies (nine per channel on the extended basis).  Exactly the queried bytes give the residues of
+    a larger workspace and touch nothing around them."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx, level = hx.Context(p), num_q - 1
+    residues, _ = uniform(ctx, p, log_n + c_out)
+    live = list(range(level + 1))
+    cts, masks = [residues(2, limbs=live) for _ in range(c_in)], residues(9, limbs=live + list(range(num_q, ctx.M)))
+    keys = {o: residues(dnum, 2, limbs=list(range(ctx.M))) for o in conv_tap_offsets(4) if o}
+    w = np.random.default_rng(c_in).integers(-2 ** 31, 2 ** 31, size=(c_out, c_in, 9))
+    for merged in (True, False):
+        nbytes = hx.he_conv_workspace_bytes(ctx, c_in, c_out, 1, 4, 1, level, hx.HE_CONV_DEFERRED_MERGED if merged else hx.HE_CONV_DEFERRED_MODDOWN)
+        assert (nbytes >= c_in * 9 * 2 * (num_q + num_p) * ctx.N * 8) == stored
+        want = deferred_conv(ctx, p, level, 4, cts, keys, masks, w, merged, hx.empty(nbytes // 4))
+        buf, ws = guarded(nbytes)
+        got = deferred_conv(ctx, p, level, 4, cts, keys, masks, w, merged, ws)
+        assert untouched(buf)
+        for o in range(c_out):
+            assert np.array_equal(got[o], want[o]), f"output {o}"
 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g", [(12, 4, 1, 4, 3, 16), (12, 24, 8, 3, 20, 16), (12, 14, 14, 1, 13, 2), (13, 10, 5, 2, 9, 5), (14, 9, 9, 1, 7, 3), (14, 8, 2, 4, 3, 16),
