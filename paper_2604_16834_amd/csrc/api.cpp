@@ -818,10 +818,15 @@ size_t ws_relayout_ks(const ckks_ctx* c, u32 level, u32 most) {
     const size_t lo = ws_ks(c, level, CT_BATCH, most), hi = ws_ks(c, level - 1, most, most);
     return lo > hi ? lo : hi;
 }
+// words of the second rotations' results: one ciphertext's that share a division are not stored
+size_t relayout_rotated(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_hi) {
+    const size_t nb = n_ct < CT_BATCH ? n_ct : CT_BATCH;
+    return n_ct == 1 && sums_together(c, level - 1) ? 0 : nb * n_hi * 2 * (size_t)level * c->N;
+}
 size_t ws_relayout_in(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_lo, u32 n_hi, u32 most) {
     const size_t N = c->N, ctl = 2 * (size_t)(level + 1) * N, ctl1 = 2 * (size_t)level * N;
     const size_t nb = n_ct < CT_BATCH ? n_ct : CT_BATCH;
-    return blk(nb * n_lo * ctl) + blk(nb * n_hi * ctl) + 2 * blk(nb * n_hi * ctl1) + ws_relayout_ks(c, level, most) + ws_rescale(c, level, CT_BATCH);
+    return blk(nb * n_lo * ctl) + blk(nb * n_hi * ctl) + blk(nb * n_hi * ctl1) + blk(relayout_rotated(c, level, n_ct, n_hi)) + ws_relayout_ks(c, level, most) + ws_rescale(c, level, CT_BATCH);
 }
 size_t ws_relayout(const ckks_ctx* c, u32 level, u32 n_ct, u32 n_lo, u32 n_hi) {
     return ws_relayout_in(c, level, n_ct, n_lo, n_hi, ks_batch(c));
@@ -835,7 +840,7 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
     u64* R = ar.take((size_t)nb_max * n_lo * ctl);      // Rot(ct_b, lo_l)
     u64* Vacc = ar.take((size_t)nb_max * n_hi * ctl);   // masked sums before their rescale
     u64* V = ar.take((size_t)nb_max * n_hi * ctl1);     // level-1
-    u64* Vrot = ar.take((size_t)nb_max * n_hi * ctl1);
+    u64* Vrot = ar.take(relayout_rotated(c, level, n_ct, n_hi));
     u32 kb = ks_batch(c);  // rotations at a time
     if (ar.ok() && ar.used + ws_relayout_ks(c, level, kb) + ws_rescale(c, level, CT_BATCH) > ar.cap) kb = CT_BATCH;  // in a smaller workspace
     const size_t ks_bytes = ws_relayout_ks(c, level, kb);

@@ -178,6 +178,27 @@ def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_q, num_p, dnum, 
         assert torch.equal(run(cts[i:i + 1])[0], two[i]), i
 
 
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,n_ct,stored", [(15, 5, 2, 3, 1, False), (16, 5, 4, 3, 1, False), (15, 5, 2, 3, 2, True), (12, 5, 2, 3, 1, True)])
+def test_layouts_stay_within_their_workspace(log_n, num_q, num_p, dnum, n_ct, stored):
+    """The queried workspace holds the second rotations' results only where they are stored: 2^12 points are below the line of shared divisions.  Exactly the
+    queried bytes give the residues of a larger workspace and touch nothing around them."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx, level, lo, hi = hx.Context(p), num_q - 2, [0, 3], [0, 7, 9]
+    nbytes = [hx.he_relayout_workspace_bytes(ctx, level, n_ct, len(lo), n) for n in (len(hi), len(hi) + 1)]
+    per_block = [8 * n_ct * 2 * limbs * ctx.N for limbs in (level + 1, level, level)]  # a masked sum, rescaled, rotated
+    assert nbytes[1] - nbytes[0] == sum(per_block if stored else per_block[:2])
+    residues, _ = uniform(ctx, p, log_n)
+    live = list(range(level + 1))
+    cts = [residues(2, limbs=live) for _ in range(n_ct)]
+    keys = {o: hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o)) for o in set(lo + hi) - {0}}
+    masks = [[residues(limbs=live) for _ in lo] for _ in hi]
+    buf, ws = guarded(nbytes[0])
+    want, got = [hx.he_relayout_two_rotations(ctx, cts, level, lo, [keys.get(o) for o in lo], hi, [keys.get(o) for o in hi], masks, ws=w) for w in (hx.empty(nbytes[0] // 4), ws)]
+    assert untouched(buf)
+    for i in range(n_ct):
+        assert torch.equal(got[i], want[i]), i
+
+
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n", [(13, 13, 5, 3, 12, 15), (14, 9, 3, 3, 8, 16), (15, 4, 4, 1, 3, 13), (15, 12, 3, 4, 9, 5), (17, 4, 2, 2, 3, 4)])
 def test_rotations_together_equal_single_ones(log_n, num_q, num_p, dnum, level, n):
     """Enough unhoisted rotations for the inner products to wait for the division, against one at a time; no digit to transform, ragged last digits."""
