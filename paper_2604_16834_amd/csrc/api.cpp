@@ -294,6 +294,12 @@ int run_inner_divide(const ckks_ctx* c, u32 level, const KsWs& ws, const u64* co
     return CKKS_OK;
 }
 
+// Whether n rotations of one ciphertext's finished digits in a layout take that kernel.  More than four digits, a launch of key_inner_items_kernel per rotation / this,
+// in us: sixteen at N = 2^12, 10 + 2 limbs in five digits 133 / 50, 24 + 1 in 24 391 / 215, 2^14, 24 + 3 in eight 356 / 334, 2^16, 24 + 3 in eight 1448 / 1230; four
+// 54 / 38, 106 / 77, 144 / 128, 491 / 418; but one, whose workgroups take the digits in turn, 34.4 / 35.3, 57.1 / 61.4, 73.2 / 71.1, 205 / 202.  Up to four digits: see
+// DIVIDE_INSIDE_HOISTED.  (ckks_rotate_hoisted keeps a launch per rotation with more than four digits.)
+bool hoisted_inside(const ckks_ctx* c, u32 level, u32 n) { return ntt_has_modup(c) && (n > 1 || c->live_digits(level) <= 4); }
+
 // n <= CT_BATCH ciphertexts cts[b] (component stride ct_cstride) rescaled from `level` into outs[b]
 int run_rescale(const ckks_ctx* c, u32 level, const u64* const* cts, size_t ct_cstride, u64* const* outs, u32 n, Arena ar,
                 hipStream_t st) {
@@ -876,7 +882,7 @@ int run_relayout(const ckks_ctx* c, u32 level, u32 n_ct, const u64* const* cts, 
                 pos[nt++] = nk;
                 for (u32 b = 0; b < n; b++) items[nk++] = FinalItem{nullptr, nullptr, nullptr, r_at(b, l), 1, 0};
             }
-            if (n == 1 && ntt_has_modup(c) && nt) {
+            if (n == 1 && nt && hoisted_inside(c, level, nt)) {
                 const u64* same[KS_MAX_BATCH];
                 u64* to[KS_MAX_BATCH];
                 for (u32 i = 0; i < nt; i++) same[i] = cts[c0], to[i] = items[i].out;

@@ -159,10 +159,10 @@ def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,lo,hi", [(13, 5, 13, 3, [0, 5], [0, 7, 9]), (15, 5, 2, 3, [1], list(range(3, 40, 2))), (16, 5, 4, 3, [0, 3], [0, 0, 4, 0]),
-                                                          (15, 5, 2, 3, [2], [0]), (15, 5, 2, 3, [2], [0] * 17 + [5, 6]), (12, 10, 1, 10, [0, 3, 4], [1, 2])])
+                                                          (15, 5, 2, 3, [2], [0]), (15, 5, 2, 3, [2], [0] * 17 + [5, 6]), (12, 10, 1, 10, [0, 3, 4], [1, 2]), (13, 8, 1, 8, [0, 3], [1, 2])])
 def test_layout_of_one_ciphertext_equals_that_of_two(log_n, num_q, num_p, dnum, lo, hi):
     """One ciphertext's second rotations are added up in the division; two, which share their keys, take them one by one.  With more blocks than a
-    launch takes, several blocks that stay where they are, and nothing else; nine digits read through the first rotations."""
+    launch takes, several blocks that stay where they are, and nothing else; nine digits read through two first rotations, seven through one."""
     p = make_params(log_n, num_q, num_p, dnum)
     ctx = hx.Context(p)
     level = num_q - 2
