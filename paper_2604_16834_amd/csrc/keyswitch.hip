@@ -758,9 +758,16 @@ hipError_t launch_key_inner_sum(const ckks_ctx* c, u32 level, const DigitSrc& di
     }
     // TW: three taps per wavefront and a sum in LDS; one wavefront for all nine only where a chip full of workgroups makes the sum of several
     // outputs the dearer part.  Whole convolutions, TW = 1 / 3 in us: N = 2^12, 5 + 2 limbs, 4 -> 4 56.3 / 44.4, 2^14, 12 + 4 132.9 / 132.9, 2^15, 9 + 3 182.5 / 186.0,
-    // 2^16, 24 + 8, 1 -> 4 510 / 553, 16 -> 1 2079 / 2017.  NB = 2, four channels at once 2 % faster on rings of 2^12 and 15 % slower on large ones (188 registers
-    // for four outputs), three where they come out even (3 -> 2 at 2^13 48.3 / 44.8).
-    const u32 xw = c->N / 64, ot = c_out <= 4 ? c_out : (c_out + 1) / 2, nb = n == 1 ? 1 : (n % 3 == 0 ? 3 : 2), tw = ot > 1 && xw * E >= 5120 ? 1 : 3;
+    // 2^16, 24 + 8, 1 -> 4 510 / 553, 16 -> 1 2079 / 2017.
+    const u32 xw = c->N / 64, ot = c_out <= 4 ? c_out : (c_out + 1) / 2, tw = ot > 1 && xw * E >= 5120 ? 1 : 3;
+    // NB: three channels at once where they come out even, else pairs (four: 2 % faster on rings of 2^12, 15 % slower on large ones, 188 registers for four
+    // outputs).  But not where three take more than the 168 registers that leave three waves per SIMD and pairs do not: four outputs with one digit (170 / 164),
+    // and with three and one wavefront for all taps (170 / 158); four digits are at two waves either way.  Three channels, which leave a pair half empty, stay
+    // together there too.  Pairs / three, us: 3 -> 3 channels at 2^16, 8 + 8 limbs in one digit 264 / 241, 16 + 8 in two 434 / 393, 24 + 8 in three 690 / 638, 24 + 6 in
+    // four 772 / 710, 3 -> 4 294 / 297, 504 / 459, 764 / 743, 884 / 806; 6 -> 4 357 / 380, 657 / 644, 1035 / 1092, 1243 / 1231; at 2^12, 5 + 5 in one 6 -> 4 49.0 / 50.9,
+    // 15 -> 4 70.1 / 74.0, 5 + 2 in three 73.2 / 71.8, 15 -> 1 65.8 / 63.5
+    const bool short_of_registers = ot == 4 && (beta == 1 || (beta == 3 && tw == 1));
+    const u32 nb = n == 1 ? 1 : (n % 3 == 0 && (n == 3 || !short_of_registers) ? 3 : 2);
     const u64* negp = c->d_moddown + 2 * c->k_pad + (size_t)c->k_pad * c->num_q + 2 * c->num_q;
     const dim3 grid((xw * E + 7) / 8 * 8, (c_out + ot - 1) / ot);
     // in: the digits with their own limbs, c0, the keys, nine masks, the weights, the sums so far; out: the sums

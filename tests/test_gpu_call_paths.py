@@ -64,7 +64,8 @@ def test_inner_products_and_sum_in_one_kernel(log_n, num_q, num_p, dnum, level, 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,width,c_in,c_out",
                          [(12, 5, 2, 3, 4, 2048, 2, 2), (13, 6, 2, 4, 5, 8, 19, 4), (13, 9, 3, 3, 6, 8, 33, 1), (14, 20, 5, 4, 17, 16, 9, 2),
-                          (15, 7, 2, 4, 6, 8, 16, 3), (16, 12, 8, 2, 11, 8, 9, 4), (16, 12, 12, 1, 11, 8, 17, 1)])
+                          (15, 7, 2, 4, 6, 8, 16, 3), (16, 12, 8, 2, 11, 8, 9, 4), (16, 12, 12, 1, 11, 8, 17, 1), (16, 6, 2, 3, 5, 8, 6, 4),
+                          (12, 3, 3, 1, 2, 8, 12, 4)])
 @pytest.mark.parametrize("low", [False, True])
 def test_inner_products_and_sum_equal_stored_copies(log_n, num_q, num_p, dnum, level, width, c_in, c_out, low):
     """Against the same layer with enough outputs for the stored copies, whose first outputs are the same: three taps without a rotation (rows as
