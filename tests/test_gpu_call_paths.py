@@ -137,11 +137,13 @@ def test_deferred_convolutions_stay_within_their_workspace(log_n, num_q, num_p, 
             assert np.array_equal(got[o], want[o]), f"output {o}"
 
 
-@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g", [(12, 4, 1, 4, 3, 16), (12, 24, 8, 3, 20, 16), (12, 14, 14, 1, 13, 2), (13, 10, 5, 2, 9, 5), (14, 9, 9, 1, 7, 3), (14, 8, 2, 4, 3, 16),
-                                                            (15, 20, 7, 3, 18, 4), (16, 12, 4, 4, 11, 2), (16, 3, 3, 1, 2, 9), (17, 3, 2, 2, 2, 3)])
-def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
-    """Products, rotations, sum and rescale one by one: one to three items per partial sum and sums of up to fifteen, one to twelve special
-    primes, one and two targets per workgroup with a ragged last group, every number of rows."""
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,g,shared", [(12, 4, 1, 4, 3, 16, False), (12, 24, 8, 3, 20, 16, True), (12, 14, 14, 1, 13, 2, True), (13, 10, 5, 2, 9, 5, True),
+                                                                   (14, 9, 9, 1, 7, 3, True), (14, 8, 2, 4, 3, 16, True), (15, 20, 7, 3, 18, 4, True), (16, 12, 4, 4, 11, 2, True),
+                                                                   (16, 3, 3, 1, 2, 9, True), (16, 6, 3, 2, 5, 9, True), (16, 8, 4, 2, 7, 16, True), (17, 3, 2, 2, 2, 3, True)])
+def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g, shared):
+    """Products, rotations, sum and rescale one by one, on both sides of the line from which the rotations share a division: one item per partial sum, two,
+    three and four with a ragged last one (the cases at 2^16 of 9 and 16 blocks), sums of up to fifteen, one to fourteen special primes, rings of two to 64 rows."""
+    assert ((level + 1 + num_p) << log_n >= 3 << 15) == shared  # sums_together
     p = make_params(log_n, num_q, num_p, dnum)
     ctx = hx.Context(p)
     residues, q = uniform(ctx, p, 31 * g + log_n)
@@ -157,6 +159,64 @@ def test_merge_equals_its_steps(log_n, num_q, num_p, dnum, level, g):
             t = hx.ckks_rotate_hoisted(ctx, t, level, [-i * sts], [keys[i]], False)[0]
         total = (total + t).remainder_(q[live].unsqueeze(-1))
     assert torch.equal(got, hx.ckks_rescale(ctx, total, level))
+
+
+def test_merge_in_a_smaller_workspace():
+    """Fifteen rotations that share a division, in the queried workspace (all at once) and in that of nine blocks (eight at a time): the second batch adds to
+    the sum of the first, in place."""
+    p = make_params(12, 24, 8, 3)
+    ctx, level, g = hx.Context(p), 20, 16
+    residues, _ = uniform(ctx, p, 77)
+    live, sts = list(range(level + 1)), ctx.N // 2 // g
+    cts, mask = [residues(2, limbs=live) for _ in range(g)], residues(limbs=live)
+    keys = [None] + [hx.ckks_key_load(ctx, residues(3, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, -i * sts)) for i in range(1, g)]
+    results = []
+    for blocks in (g, 9):
+        buf, ws = guarded(hx.he_accumulator_workspace_bytes(ctx, level, blocks))
+        results.append(hx.he_accumulator_merge(ctx, cts, level, sts, mask, keys, ws=ws))
+        assert untouched(buf)
+    assert hx.he_accumulator_workspace_bytes(ctx, level, 9) < hx.he_accumulator_workspace_bytes(ctx, level, g)
+    assert torch.equal(results[0], results[1])
+
+
+@pytest.mark.parametrize("log_n,num_q,num_p,dnum,c_in,c_out", [(12, 5, 2, 3, 18, 8), (15, 6, 2, 3, 3, 2)])
+def test_few_outputs_in_a_captured_graph(log_n, num_q, num_p, dnum, c_in, c_out):
+    """The one-kernel convolution captured and replayed between eager work, with other inputs at the last replay, against the eager call."""
+    p = make_params(log_n, num_q, num_p, dnum)
+    ctx, level = hx.Context(p), num_q - 1
+    residues, _ = uniform(ctx, p, c_in)
+    live, ext = list(range(level + 1)), list(range(num_q)) + list(range(num_q, ctx.M))
+    cts, masks = [residues(2, limbs=live) for _ in range(c_in)], residues(9, limbs=ext)
+    keys = [hx.ckks_key_load(ctx, residues(dnum, 2, limbs=list(range(ctx.M))), hx.ckks_galois_element(ctx, o)) if o else None for o in conv_tap_offsets(4)]
+    w = hx.from_host(w_residues(np.random.default_rng(c_in).integers(-2 ** 31, 2 ** 31, size=(c_out, c_in, 9)), [p.moduli[t] for t in ext], len(ext) - 1))
+    ws = hx.empty(hx.he_conv_workspace_bytes(ctx, c_in, c_out, 1, 4, 1, level, hx.HE_CONV_DEFERRED_MERGED) // 8 + 1)
+    outs = [hx.empty(2, level, ctx.N) for _ in range(c_out)]
+    st = torch.cuda.Stream()
+
+    def run(to, stream):
+        hx.he_conv_batched(ctx, 1, 4, 1, level, cts, keys, masks, w, c_out, outs=to, ws=ws, alignment=hx.HE_CONV_DEFERRED_MERGED, stream=stream)
+
+    def eager():
+        to = [hx.empty(2, level, ctx.N) for _ in range(c_out)]
+        run(to, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        return to
+
+    want = eager()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        run(outs, st.cuda_stream)
+    for replay in range(3):
+        if replay == 2:
+            for c in cts:
+                c.copy_(residues(2, limbs=live))
+            want = eager()
+        for o in outs:
+            o.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, v) for o, v in zip(outs, want)), replay
 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,lo,hi", [(13, 5, 13, 3, [0, 5], [0, 7, 9]), (15, 5, 2, 3, [1], list(range(3, 40, 2))), (16, 5, 4, 3, [0, 3], [0, 0, 4, 0]),
@@ -229,10 +289,10 @@ def test_activations_together_equal_single_ones(log_n, num_q, num_p, dnum, level
 
 
 @pytest.mark.parametrize("log_n,num_q,num_p,dnum,level,n", [(12, 4, 1, 4, 3, 3), (12, 13, 13, 1, 12, 2), (13, 8, 4, 2, 7, 17), (14, 7, 3, 3, 5, 9), (15, 4, 2, 2, 3, 2), (16, 3, 3, 1, 1, 1),
-                                                            (13, 15, 5, 3, 14, 16), (16, 4, 2, 2, 3, 8)])
+                                                            (13, 15, 5, 3, 14, 16), (16, 4, 2, 2, 3, 8), (12, 30, 8, 4, 29, 16)])
 def test_hoisted_rotations_of_every_row_count(log_n, num_q, num_p, dnum, level, n):
     """One set of digits read through each rotation, against the oracle: one to four digits, several batches, rings of two to 32
-    rows, and enough of them for the inner products to wait for the division."""
+    rows, and enough of them for the inner products to wait for the division (the last three; on 2^12 points that takes sixteen of 29 limbs and more)."""
     p = make_params(log_n, num_q, num_p, dnum)
     orc, ctx = Oracle(p), hx.Context(p)
     residues, _ = uniform(ctx, p, n)

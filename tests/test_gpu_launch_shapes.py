@@ -208,7 +208,8 @@ def test_whole_ring_kernels(bits, dnum, level):
 
 @pytest.mark.parametrize("num_p", [3, 6, 8, 10, 14])
 def test_whole_ring_divisions(num_p):
-    """N = 2^12: divisions of whole sums into 113 to 256 limb-polys are one launch each way.  Six hoisted rotations, the eight of a direct convolution
+    """N = 2^12: divisions of whole sums into 113 to 256 limb-polys are one launch each way.  Six hoisted rotations of six digits (with up to four, whose
+    inner products go on into the inverse transform, they take no such division: two digits), the eight of a direct convolution
     and the merged divisions of a deferred one, by three to fourteen special primes (four, eight and sixteen terms) and with the
     level's own limb (four, eight, nine and twelve of twelve, sixteen)."""
     p = make_params(12, 12, num_p, 2)
@@ -225,6 +226,12 @@ def test_whole_ring_divisions(num_p):
     outs = hx.ckks_rotate_hoisted(ctx, hx.from_host(ct), level, offs, [dkeys[o] for o in offs], True)
     for out, want in zip(outs, orc.rotate_many(ct, level, offs, [keys[o] for o in offs], True)):
         assert np.array_equal(hx.to_host(out), want), "rotations"
+    p6 = make_params(12, 12, num_p, 6)
+    orc6, ctx6 = Oracle(p6), hx.Context(p6)
+    keys6 = [np.stack([np.stack([rand_poly(rng, p6.moduli, n) for _ in range(2)]) for _ in range(6)]) for _ in offs]
+    outs = hx.ckks_rotate_hoisted(ctx6, hx.from_host(ct), level, offs, [hx.ckks_key_load(ctx6, hx.from_host(k), hx.ckks_galois_element(ctx6, o)) for k, o in zip(keys6, offs)], True)
+    for out, want in zip(outs, orc6.rotate_many(ct, level, offs, keys6, True)):
+        assert np.array_equal(hx.to_host(out), want), "rotations of six digits"
     w = rng.integers(-2 ** 31, 2 ** 31, size=(c_out, 1, 9))
     for al in (hx.HE_CONV_ALIGN_DIRECT, hx.HE_CONV_DEFERRED_MERGED):
         idx = orc.ext_moduli_idx(level) if al == hx.HE_CONV_DEFERRED_MERGED else list(range(level + 1))
