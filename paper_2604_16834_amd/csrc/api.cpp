@@ -1172,7 +1172,8 @@ uint32_t ckks_galois_element(const ckks_ctx* c, int32_t offset) {
 // Polynomials of a large batch that go through both passes before the next ones do.  The first pass writes what the second reads: 240 MB of
 // it stay in the 256 MB last-level cache in between, at the price of a drain and a fill of the chip per launch (about 8 us).  Forward and inverse
 // together in us, all at once / in parts of about 240 MB: N = 2^16, 30 limbs, 472 MB 666 / 655, 692 MB 1016 / 959, 991 MB 1468 / 1381; 2^15, 24 limbs,
-// 478 MB 664 / 657, 994 MB 1423 / 1365; 2^13 480 MB 668 / 632, 999 MB 1451 / 1317; parts of 170 MB of 346 MB 467 / 497, of 126 MB of 991 MB 1493, so a
+// 478 MB 664 / 657, 994 MB 1423 / 1365; 2^13 480 MB 668 / 632, 999 MB 1451 / 1317; the same calls over eight buffers in turn, which are not in any cache before: 2^16
+// 535 MB 784 / 744, 692 MB 1017 / 962, 1007 MB 1491 / 1369, 2^15 1007 MB 1442 / 1355, 2^13 944 MB 1386 / 1238; parts of 170 MB of 346 MB 467 / 497, of 126 MB of 991 MB 1493, so a
 // batch is cut from 444 MB on.  With 64-bit integer butterflies, which are bound by instruction issue: 994 MB 1868 / 1891, not cut.
 static u32 ntt_cached_batch(const ckks_ctx* c, u32 n_limbs, u32 batch) {
     if (!c->ntt_f64 || c->log_hi == 0 || ntt_one_pass(c)) return batch;
@@ -1402,8 +1403,9 @@ int ckks_rotate_hoisted(const ckks_ctx* c, const uint64_t* d_ct, uint32_t level,
             continue;
         }
         if (hoisted && fused_hoist) {
-            // same digits, one key per rotation: the rotations of a batch share one launch that reads the digits once and
-            // leaves P sigma_g(c0) + inner product on the extended basis (its ModDown is the rotation, c0 included)
+            // same digits, one key per rotation: the rotations of a batch share their launches, each reads the digits through its automorphism, and the
+            // sums P sigma_g(c0) + inner product make the division by P the rotation, c0 included (run_inner_divide; moduli above 2^50 and rings up to
+            // 2^11: rotated_inner, which reads the digits once for all)
             pend_key[nb] = keys[t];
             items[nb] = FinalItem{nullptr, nullptr, nullptr, out, g, 0};
             if (++nb == rb) {

@@ -2274,9 +2274,10 @@ u32 ntt_mid_modup(const ckks_ctx* c, u32 level, u32 n) {
     return mid_conv_per_of(c, nd, c->alpha_pad, c->ext_limbs(level) - nd, n * c->live_digits(level));
 }
 // Rings of 2^12 points: a division that starts from whole sums (lo_done: they have been through the inverse transform's first pass) takes
-// the whole-ring kernels where they give between half of the CUs and every CU a limb-poly of the result.  Hoisted rotations, pass by pass / whole ring
-// in us, by limb-polys: 84 36.0 / 37.6, 112 38.5 / 39.0, 168 46.2 / 43.9, 224 45.2 / 42.8, 336 53.9 / 58.2; direct convolution of five channels
-// of 14 + 4 limbs (224) 315 / 297
+// the whole-ring kernels where they give between half of the CUs and every CU a limb-poly of the result.  Pass by pass / whole ring in us, limb-polys of the largest
+// batch in brackets: direct convolutions of one channel of 16 + 6 limbs (256) 67.7 / 66.0, two of 7 + 4 (224) 63.7 / 62.3, five of 8 + 4 (240) 134 / 128, five of 7 + 4 (210)
+// 129 / 126; with four keys, one of 21 + 8 limbs 121 / 116, of 24 + 8 122 / 118; eight hoisted rotations of 14 + 2 limbs in seven digits (224) 91.7 / 90.9.  (Hoisted rotations
+// of up to four digits come with lo_done.)  At the window's ends, measured on hoisted rotations that came this way then: 84 36.0 / 37.6, 112 38.5 / 39.0, 336 53.9 / 58.2
 u32 ntt_mid_moddown(const ckks_ctx* c, u32 level, bool merged, u32 polys, bool lo_done) {
     const u32 n_out = merged ? level : level + 1;
     if (ntt_one_pass(c) && !lo_done && n_out * polys > 112 && n_out * polys <= 256) return 0;
